@@ -40,7 +40,7 @@ class tc_plan_info(C.Structure):
                  "num_decode_items", "num_merge_items", "num_partials", "split_tokens", "rows_per_prefill_item",
                  "grid_blocks", "block_threads")] + [("total_pages", C.c_int64), ("num_prefill_pieces", C.c_int32),
                                                       ("num_prefill_workgroups", C.c_int32), ("num_counters", C.c_int32),
-                                                      ("num_piece_partials", C.c_int32), ("decode_queue", C.c_int32), ("reserved_", C.c_int32), ("build_ns", C.c_int64), ("upload_ns", C.c_int64)]
+                                                      ("num_piece_partials", C.c_int32), ("decode_queue", C.c_int32), ("waves_per_item", C.c_int32), ("build_ns", C.c_int64), ("upload_ns", C.c_int64)]
 
 
 class TcError(RuntimeError):

@@ -19,9 +19,11 @@ constexpr int kBlock = 16;          // tokens per KV page
 constexpr int kMixedWaves = 8;
 constexpr int kDecodeWaves = 4;
 constexpr int kDecodeWgPerCu = 3;
+constexpr int kWideWaves = 4;       // waves that share one decode item in a batch of few decodes (two such workgroups per compute unit)
 constexpr int kPrefillRows = 32 * kMixedWaves;  // (position, head) rows per prefill workgroup, 32 per wave
 constexpr int kItemInts = 8;        // int32 fields per work item
 constexpr int kAppendInts = 4;      // int32 fields per append segment: first packed row, tokens, first token index, pool block
+constexpr int kCounterStride = 32;  // int32 between arrival counters: one per 128-byte line (see workgroup_arrives_last)
 constexpr int kMaxSplitPages = 64;  // a decode split's page ids fit one wavefront register
 constexpr int kPrefillTileTokens = 64;  // KV tokens per LDS tile of the prefill branch
 constexpr int kNumCu = 256;         // compute units the work list is balanced for
@@ -100,7 +102,9 @@ struct tc_plan {
     int64_t build_ns = 0, upload_ns = 0;  // host time of the latest work-list build and of enqueueing its upload
     tc::PlanScratch work;
 
-    int wg_waves() const { return n_pieces > 0 ? tc::kMixedWaves : tc::kDecodeWaves; }
+    int items_per_wg = tc::kDecodeWaves;  // decode items a workgroup runs side by side
+    int waves_per_item = 1;               // waves that share one of them: kWideWaves in a batch of few decodes, else 1
+    int launch_threads() const { return 64 * items_per_wg * waves_per_item; }
     int grid_blocks() const { return n_prefill_wg + n_decode_wg; }
     size_t workspace_bytes() const {
         // per decode partial: G heads x (D accumulators + running max + running sum), fp32; per piece region: kPrefillRows such rows

@@ -295,96 +295,94 @@ __device__ __forceinline__ void peer_store4(__amdgpu_buffer_rsrc_t win, uint32_t
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), win, (int)byte_off, 0, kCoherentAux);
 }
 
-// One output row (query head j of a decode sequence, or of one position of a cut prefill item) from its
-// ns partial results in workspace slots slot0 .. slot0 + ns - 1:
-//   out = sum_i 2^(m_i - m*) o_i / sum_i 2^(m_i - m*) l_i,   m* = max_i m_i,   partials in index order.
-// One wavefront per row; a lane owns D/64 adjacent head-dim elements, so each partial row is one coalesced
-// read.  Lane i first fetches (m_i, l_i) of partial i (at most 64 per pass; passes are chained by an online
-// rescale), the wave reduces the maximum, and the weighted sum runs over the partials in index order with
-// the weights broadcast from those registers.  The order is fixed, so the result does not depend on which
-// workgroup runs this or when.
-template <int D, class E, bool PEER>
-__device__ __forceinline__ void merge_row(const float *ws_o, const float *ws_ml, int64_t slot0, int ns, int G, int j,
-                                          uint16_t *dst_row, int lane) {
-    constexpr int NE = D / 64;  // elements per lane
-    float acc[NE];
-#pragma unroll
-    for (int e = 0; e < NE; e++) acc[e] = 0.f;
-    float m_star = -1e30f, den = 0.f;
-    for (int base = 0; base < ns; base += 64) {
-        const int n = min(64, ns - base);
-        const float *src = ws_o + ((int64_t)(slot0 + base) * G + j) * D + lane * NE;
-        // Partial rows are fetched kChunk at a time, all loads of a chunk in flight together; the
-        // first chunk is requested before the weights are known.
-        constexpr int kChunk = 8;
-        float row[kChunk][NE];
-        auto fetch = [&](int c0) {
-#pragma unroll
-            for (int u = 0; u < kChunk; u++)
-                if (c0 + u < n) {
-                    const float *r = src + (int64_t)(c0 + u) * G * D;
-                    if (NE == 2) {
-                        const float2 v = load2<PEER>(r);
-                        row[u][0] = v.x;
-                        row[u][NE - 1] = v.y;
-                    } else {
-                        row[u][0] = load1<PEER>(r);
-                    }
-                }
-        };
-        fetch(0);
-        const int64_t my_row = (int64_t)(slot0 + base + min(lane, n - 1)) * G + j;
-        const float2 ml = load2<PEER>(ws_ml + my_row * 2);  // lanes past n read the last partial's pair and ignore it
-        const float m_i = lane < n ? ml.x : -1e30f;
-        const float l_i = lane < n ? ml.y : 0.f;
-        float m_new = m_i;
-#pragma unroll
-        for (int sh = 1; sh < 64; sh *= 2) m_new = fmaxf(m_new, xor_lanes(m_new, sh));
-        m_new = fmaxf(m_new, m_star);
-        const float rescale = fast_exp2(m_star - m_new);
-        m_star = m_new;
-        const float w_i = fast_exp2(m_i - m_star);  // 0 for lanes past n
-        float wl = w_i * l_i;
-#pragma unroll
-        for (int sh = 1; sh < 64; sh *= 2) wl += xor_lanes(wl, sh);
-        den = den * rescale + wl;
-#pragma unroll
-        for (int e = 0; e < NE; e++) acc[e] *= rescale;
-        for (int c0 = 0; c0 < n; c0 += kChunk) {
-#pragma unroll
-            for (int u = 0; u < kChunk; u++)
-                if (c0 + u < n) {
-                    const float w = __shfl(w_i, c0 + u, 64);
-#pragma unroll
-                    for (int e = 0; e < NE; e++) acc[e] += w * row[u][e];
-                }
-            if (c0 + kChunk < n) fetch(c0 + kChunk);
-        }
+// Output rows of one split decode (sequence, KV head) pair, all G query heads, from its ns partial results in
+// workspace slots slot0 .. slot0 + ns - 1:
+//   out = sum_i 2^(m_i - m*) o_i / sum_i 2^(m_i - m*) l_i,   m* = max_i m_i.
+// Run by a whole workgroup of T threads.  What bounds it is the latency of the loads (a partial result comes from
+// another compute unit, past the caches), so as many of them as possible are in flight at once: a thread owns four
+// adjacent elements of a row (16-byte loads, a wave reads 1 KiB contiguous), where the rows do not need all
+// threads the partial results are dealt out to `slices` groups of threads, and a thread requests eight partial results
+// before it adds the first.  The slices meet in LDS (merge_lds_bytes) and are added in order, so the result depends
+// on T alone and not on which workgroup runs this or when.
+constexpr int kMergeBatch = 8;
+__host__ __device__ constexpr size_t merge_lds_bytes(int T) { return (size_t)T * 6 * sizeof(float); }
+struct RowSum {  // weighted sum relative to the reference m (log2 domain)
+    f32x4 o;
+    float m, l;
+    __device__ __forceinline__ void add(f32x4 oi, float mi, float li) {
+        const float m_new = fmaxf(m, mi);
+        const float a = fast_exp2(m - m_new), b = fast_exp2(mi - m_new);
+        m = m_new;
+        l = l * a + li * b;
+        o = o * a + oi * b;
     }
-    const float inv = 1.f / den;
-    uint16_t *dst = dst_row + lane * NE;
-    if (NE == 2) {
-        typename E::x2 w2;
-        w2[0] = (typename E::t)(acc[0] * inv);
-        w2[1] = (typename E::t)(acc[NE - 1] * inv);
-        *reinterpret_cast<typename E::x2 *>(dst) = w2;
-    } else {
-        const typename E::t w1 = (typename E::t)(acc[0] * inv);
-        *dst = __builtin_bit_cast(uint16_t, w1);
+};
+template <int D, class E, bool PEER>
+__device__ __forceinline__ void merge_pair(const float *ws_o, const float *ws_ml, int64_t slot0, int ns, int G, uint16_t *out_rows,
+                                           float *lds, int tid, int T) {
+    constexpr int VR = D / 4;  // vectors per row
+    const int n_vec = G * VR;
+    const int slices = max(1, T / n_vec);
+    f32x4 *const lds_o = reinterpret_cast<f32x4 *>(lds);
+    float *const lds_ml = lds + 4 * T;
+    for (int v0 = 0; v0 < n_vec; v0 += T) {  // one pass unless G * D / 4 > T
+        const int slice = n_vec <= T ? tid / n_vec : 0, v = n_vec <= T ? tid % n_vec : v0 + tid;
+        const bool active = slice < slices && v < n_vec;
+        RowSum acc = {f32x4{0.f, 0.f, 0.f, 0.f}, -1e30f, 0.f};
+        for (int base = 0; base < ns; base += kMergeBatch * slices) {
+            // a window of its own for every batch: a pair's partial results may span more than a buffer offset
+            const float *o_base = ws_o + (slot0 + base) * (int64_t)G * D;
+            const float *ml_base = ws_ml + (slot0 + base) * (int64_t)G * 2;
+            const __amdgpu_buffer_rsrc_t win = peer_window(o_base, (uint32_t)(kMergeBatch * slices * G * D * sizeof(float)));
+            f32x4 o[kMergeBatch];
+            float2 ml[kMergeBatch];
+#pragma unroll
+            for (int u = 0; u < kMergeBatch; u++) {
+                const int i = u * slices + slice;
+                if (active && base + i < ns) {
+                    o[u] = load4<PEER>(win, o_base, (uint32_t)(i * n_vec + v) * 16);
+                    ml[u] = load2<PEER>(ml_base + (i * G + v / VR) * 2);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kMergeBatch; u++)
+                if (active && base + u * slices + slice < ns) acc.add(o[u], ml[u].x, ml[u].y);
+        }
+        if (slices > 1) {
+            __syncthreads();  // the LDS is free (and read, on a second pass)
+            if (active) {
+                lds_o[tid] = acc.o;
+                lds_ml[2 * tid] = acc.m;
+                lds_ml[2 * tid + 1] = acc.l;
+            }
+            __syncthreads();
+            if (active && slice == 0)
+                for (int k = 1; k < slices; k++) acc.add(lds_o[tid + k * n_vec], lds_ml[2 * (tid + k * n_vec)], lds_ml[2 * (tid + k * n_vec) + 1]);
+        }
+        if (active && slice == 0) {
+            const float inv = 1.f / acc.l;
+            typename E::x4 w;
+#pragma unroll
+            for (int e = 0; e < 4; e++) w[e] = (typename E::t)(acc.o[e] * inv);
+            *reinterpret_cast<typename E::x4 *>(out_rows + (int64_t)v * 4) = w;  // the G rows of a pair are adjacent
+        }
     }
 }
 
-// Arrival of one of the n parts of a split pair, after the part has stored its partial result with
-// peer_store2 and the stores have completed: the pair's counter is incremented.  Returns true to the part
-// that arrives last; that part combines the partial results (reading them with PEER loads) and puts the
-// counter back to zero for the next launch.  Nobody waits for anybody.
-// `leader`: the one lane that does the counting; all lanes of the calling wave get its answer.
-__device__ __forceinline__ bool arrive_is_last(int32_t *counter, int n, bool leader) {
-    stores_done();
-    int old = 0;
-    if (leader) old = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    old = __builtin_amdgcn_readfirstlane(old);
-    return old == n - 1;
+// Arrival of one of the n workgroups that hold the parts of a split pair, after its waves have stored their share of the
+// partial result (peer stores) and waited for their completion: thread 0 increments the pair's counter.  Returns true to
+// all threads of the workgroup that arrives last; that one combines the partial results (reading them with PEER loads)
+// and puts the counter back to zero for the next launch.  Nobody waits for another workgroup.
+// `flag`: one int of LDS.  Every thread of the workgroup calls this.
+// Counters lie kCounterStride apart: arrivals are counted past the caches, about 20 ns each on one line, and the pairs of a
+// batch finish together (504 parts of 8 pairs over 16384 tokens: 25.2 us with adjacent counters, 21.7 apart).
+__device__ __forceinline__ bool workgroup_arrives_last(int32_t *counter, int n, int *flag, int tid) {
+    __syncthreads();  // every wave's stores have completed; the LDS is free
+    if (tid == 0) *flag = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const bool last = *flag == n - 1;
+    if (last && tid == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return last;
 }
 
 // Partial result of one piece of a cut prefill item: what the 512 lanes of the workgroup hold at the end of
@@ -934,7 +932,7 @@ __device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ it, 
         stores_done();
         __syncthreads();  // every wave has left the sweep: LDS is free
         int *const arrived = reinterpret_cast<int *>(lds);
-        int32_t *const counter = A.counters + pc[PP_COUNTER];
+        int32_t *const counter = A.counters + pc[PP_COUNTER] * kCounterStride;
         if (tid == 0) *arrived = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
         if (*arrived != p_k - 1) return;
@@ -958,6 +956,7 @@ __device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ it, 
 // a few units must carry the whole decode stream: there a wave keeps kMixedDecodeStages - 1 pages in flight.
 constexpr int kDecodeStages = 2;
 constexpr int kMixedDecodeStages = 4;
+constexpr int kWideStages = 3;  // 2 and 5 measured 4 % and 15-25 % slower on batches of 8 to 96 decodes
 
 template <int D>
 struct DecodePage {  // K and V of one page, in MFMA A-operand registers
@@ -974,19 +973,27 @@ struct DecodePage {  // K and V of one page, in MFMA A-operand registers
 // here, scattered through a launch that streams K/V at the HBM limit, cost 40-60 us on 512 sequences where the
 // append kernel needs 14, and so did storing them from workgroups at the front of the launch; from workgroups at its
 // back, which run while the grid drains and after nearly every page has been read, they cost less than the launch they replace.)
-template <int D>
-__device__ __forceinline__ void decode_take_new_token(const AttnArgs &A, int kvh, int qrow, int tn, int j, int g, DecodePage<D> &st) {
-    const uint16_t *kn = A.k_new + ((int64_t)qrow * A.Hkv + kvh) * D;
-    const uint16_t *vn = A.v_new + ((int64_t)qrow * A.Hkv + kvh) * D;
+// STORE: the wavefront also stores the token's row into the page `id` (a batch of few decodes, whose launch is bound by its
+// chain of latencies and not by HBM: there eight workgroups more for the rows share a compute unit with the heaviest
+// splits and cost 5 us of 13).
+template <int D, bool STORE>
+__device__ __forceinline__ void decode_take_new_token(const AttnArgs &A, int kvh, int qrow, int id, int tn, int j, int g, DecodePage<D> &st) {
+    const int64_t src = ((int64_t)qrow * A.Hkv + kvh) * D, tile = ((int64_t)id * A.Hkv + kvh) * (int64_t)(kBlock * D);
+    const uint16_t *kn = A.k_new + src, *vn = A.v_new + src;
     if (j == tn) {  // K: this lane holds the 8-element pieces 4 kk + g of token j
 #pragma unroll
-        for (int kk = 0; kk < D / 32; kk++) st.k[kk] = *reinterpret_cast<const u32x4 *>(kn + (4 * kk + g) * 8);
+        for (int kk = 0; kk < D / 32; kk++) {
+            st.k[kk] = *reinterpret_cast<const u32x4 *>(kn + (4 * kk + g) * 8);
+            if (STORE) *reinterpret_cast<u32x4 *>(A.k_pool + tile + ((4 * kk + g) * kBlock + tn) * 8) = st.k[kk];
+        }
     }
     if (g == (tn >> 2)) {  // V: this lane holds tokens 4 g .. 4 g + 3 of the elements 16 c + j
         const int e = tn & 3;
 #pragma unroll
         for (int c = 0; c < D / 16; c++) {
-            const uint32_t val = vn[16 * c + j];
+            const uint16_t elem = vn[16 * c + j];
+            if (STORE) A.v_pool[tile + (16 * c + j) * kBlock + v_slot(tn)] = elem;
+            const uint32_t val = elem;
             u32x2 w = st.v[c];
             const uint32_t keep = (e & 1) ? 0x0000FFFFu : 0xFFFF0000u, put = (e & 1) ? val << 16 : val;
             if (e >> 1) w[1] = (w[1] & keep) | put; else w[0] = (w[0] & keep) | put;
@@ -995,27 +1002,38 @@ __device__ __forceinline__ void decode_take_new_token(const AttnArgs &A, int kvh
     }
 }
 
-// The append of a batch of decodes, done by the last workgroups of the attention launch: thread = (sequence, KV head,
-// 8-element piece) copies the piece of the new token's K and scatters the piece of its V (token-minor pool), four per
-// thread.  `segments`: the plan's append segments, one per sequence here (one token each).
+// The append of decode rows: thread = (sequence, KV head, element), so that the lanes of a wave store adjacent rows of
+// the token-minor V block (four lanes per 128-byte line; with a thread per 8-element piece every lane of a store had a
+// line of its own and a workgroup took 5 us more).  kAppendPerThread elements per thread, all loads before the stores.
+// `segments`: the plan's append segments of these sequences, one each (one token).  Used by the last workgroups of the
+// attention launch of a batch of decodes and by the append kernel.
+constexpr int kAppendPerThread = 4;
 template <int D>
-__device__ __forceinline__ void append_decode_rows(const AttnArgs &A, const int32_t *__restrict__ segments, int n_rows, int wg) {
-    constexpr int CH = D / 8, kPerThread = 4;
-    const int total = n_rows * A.Hkv * CH;
+__device__ __forceinline__ void append_decode_rows(uint16_t *k_pool, uint16_t *v_pool, const uint16_t *__restrict__ k_new,
+                                                   const uint16_t *__restrict__ v_new, int Hkv, const int32_t *__restrict__ segments,
+                                                   int n_rows, int wg) {
+    const int n_pairs = n_rows * Hkv, per_pass = (int)blockDim.x / D, d = (int)threadIdx.x % D;
+    uint16_t k[kAppendPerThread], v[kAppendPerThread];
+    int64_t k_at[kAppendPerThread], v_at[kAppendPerThread];
 #pragma unroll
-    for (int i = 0; i < kPerThread; i++) {
-        const int x = (wg * kPerThread + i) * (int)blockDim.x + (int)threadIdx.x;
-        if (x < total) {
-            const int c = x % CH, h = (x / CH) % A.Hkv;
-            const int32_t *seg = segments + (int64_t)(x / (CH * A.Hkv)) * kAppendInts;
-            const int row = seg[0], tok = seg[2];
-            const int64_t tile = ((int64_t)seg[3] * A.Hkv + h) * (int64_t)(kBlock * D);
-            const int64_t src = ((int64_t)row * A.Hkv + h) * D + c * 8;
-            *reinterpret_cast<u32x4 *>(A.k_pool + tile + ((int64_t)c * kBlock + tok) * 8) = *reinterpret_cast<const u32x4 *>(A.k_new + src);
-            const u32x4 v = *reinterpret_cast<const u32x4 *>(A.v_new + src);
-            uint16_t *dst = A.v_pool + tile + (int64_t)(c * 8) * kBlock + v_slot(tok);
+    for (int i = 0; i < kAppendPerThread; i++) {
+        const int pair = (wg * kAppendPerThread + i) * per_pass + (int)threadIdx.x / D;
+        if (pair < n_pairs) {
+            const int h = pair % Hkv;
+            const int32_t *seg = segments + (int64_t)(pair / Hkv) * kAppendInts;
+            const int tok = seg[2];
+            const int64_t tile = ((int64_t)seg[3] * Hkv + h) * (int64_t)(kBlock * D), src = ((int64_t)seg[0] * Hkv + h) * D + d;
+            k[i] = k_new[src];
+            v[i] = v_new[src];
+            k_at[i] = tile + ((d >> 3) * kBlock + tok) * 8 + (d & 7);
+            v_at[i] = tile + d * kBlock + v_slot(tok);
+        }
+    }
 #pragma unroll
-            for (int e = 0; e < 8; e++) dst[e * kBlock] = (uint16_t)(v[e >> 1] >> ((e & 1) * 16));
+    for (int i = 0; i < kAppendPerThread; i++) {
+        if ((wg * kAppendPerThread + i) * per_pass + (int)threadIdx.x / D < n_pairs) {
+            k_pool[k_at[i]] = k[i];
+            v_pool[v_at[i]] = v[i];
         }
     }
 }
@@ -1100,18 +1118,101 @@ __device__ __forceinline__ void decode_consume(const AttnArgs &A, DecodePage<D> 
     for (int c = 0; c < MT; c++) o[c] = E::mfma16k16(__builtin_bit_cast(x4, st.v[c]), pb, o[c]);
 }
 
+// One wave's sweep over n_pg pages (the first of them page `first_page` of the sequence) that hold n_tok tokens: the
+// unnormalised accumulators, the reference maximum and this lane's column sum (complete over the lanes of the column).
+// takes_new: the last token is the sequence's newest and is taken from k_new / v_new (see decode_take_new_token).
+template <int D, class E, int NS, bool STORE>
+__device__ __forceinline__ void decode_sweep(const AttnArgs &A, int kvh, int qrow, const int32_t *__restrict__ pages, int n_pg, int n_tok,
+                                             bool takes_new, int lane, f32x4 (&o)[D / 16], float &m_run, float &l_run) {
+    using x8 = typename E::x8;
+    constexpr int KS = D / 32;  // k-steps of K Q^T
+    const int j = lane & 15, g = lane >> 4;
+    const int G = A.G;
+    const int my_page = pages[min(lane, n_pg - 1)];  // lane i holds the id of page i of the range
+
+    x8 qreg[KS];
+    const int64_t q_off = ((int64_t)qrow * A.Hq + kvh * G + min(j, G - 1)) * D;
+#pragma unroll
+    for (int kk = 0; kk < KS; kk++) {
+        u32x4 w = *reinterpret_cast<const u32x4 *>(A.q + q_off + (4 * kk + g) * 8);
+        if (j >= G) w = u32x4{0u, 0u, 0u, 0u};
+        qreg[kk] = __builtin_bit_cast(x8, w);
+    }
+
+    // A ring of NS register stages, one page each: while page i is consumed the loads of pages
+    // i+1 .. i+NS-1 are in flight.
+    DecodePage<D> st[NS];
+#pragma unroll
+    for (int u = 0; u < NS - 1; u++)
+        if (u < n_pg) decode_fetch<D>(A, kvh, __builtin_amdgcn_readlane(my_page, u), j, g, st[u]);
+    // Main part: every page consumed here is full and every fetch is of a page of the range, so the body
+    // has no branch around the loads and the compiler's wait before a stage's first use counts exactly
+    // the loads issued after it.  (With a conditional fetch the wait has to be right for the path
+    // without it, and then also waits for the page just requested: one page in flight instead of NS - 1.)
+    int pp = 0;
+    for (; pp + 2 * (NS - 1) < n_pg; pp += NS) {
+#pragma unroll
+        for (int u = 0; u < NS; u++) {
+            decode_fetch<D>(A, kvh, __builtin_amdgcn_readlane(my_page, pp + u + NS - 1), j, g, st[(u + NS - 1) % NS]);
+            decode_consume<D, E>(A, st[u], qreg, kBlock, g, o, m_run, l_run);
+        }
+    }
+    // The last pages (at most 2 NS - 2): fetch while there is a page left, the last one may be partial.
+    for (; pp < n_pg; pp += NS) {
+#pragma unroll
+        for (int u = 0; u < NS; u++) {
+            const int cur = pp + u;
+            if (cur < n_pg) {
+                const int nxt = cur + NS - 1;
+                if (nxt < n_pg) decode_fetch<D>(A, kvh, __builtin_amdgcn_readlane(my_page, nxt), j, g, st[(u + NS - 1) % NS]);
+                if (takes_new && cur == n_pg - 1)
+                    decode_take_new_token<D, STORE>(A, kvh, qrow, __builtin_amdgcn_readlane(my_page, cur), (n_tok - 1) & (kBlock - 1), j, g, st[u]);
+                decode_consume<D, E>(A, st[u], qreg, n_tok - cur * kBlock, g, o, m_run, l_run);
+            }
+        }
+    }
+    l_run += xor_lanes(l_run, 16);
+    l_run = half_swap_sum(l_run);
+}
+
+// Results of waves that meet in LDS: O^T of every wave [waves][G][D + 4] (the four floats of padding put the rows a
+// store instruction touches on different banks: at stride D all of them start on the same one), then (m, l)
+// [waves][G][2].
+template <int D>
+struct WaveResults {
+    static constexpr int kStride = D + 4;
+    float *o, *ml;
+    int G;
+    __device__ __forceinline__ WaveResults(float *lds, int waves, int G_) : o(lds), ml(lds + (size_t)waves * G_ * kStride), G(G_) {}
+    __device__ __forceinline__ void put(int wave, int lane, const f32x4 (&acc)[D / 16], float m, float l) const {
+        const int j = lane & 15, g = lane >> 4;
+        if (j >= G) return;
+        float *dst = o + (wave * G + j) * kStride + 4 * g;
+#pragma unroll
+        for (int c = 0; c < D / 16; c++) *reinterpret_cast<f32x4 *>(dst + 16 * c) = acc[c];
+        if (g == 0) {
+            ml[(wave * G + j) * 2] = m;
+            ml[(wave * G + j) * 2 + 1] = l;
+        }
+    }
+    // element vector at head-dim position d of row j of wave i
+    __device__ __forceinline__ f32x4 get(int i, int j, int d) const { return *reinterpret_cast<const f32x4 *>(o + (i * G + j) * kStride + d); }
+    __device__ __forceinline__ float2 get_ml(int i, int j) const { return float2{ml[(i * G + j) * 2], ml[(i * G + j) * 2 + 1]}; }
+};
+// Bytes of LDS a decode workgroup of `waves` waves needs: the waves' results, and (later) the slices of a merge.
+__host__ __device__ constexpr size_t decode_lds_bytes(int waves, int G, int D) {
+    const size_t results = (size_t)waves * G * (D + 4 + 2) * sizeof(float), merge = merge_lds_bytes(waves * 64);
+    return results > merge ? results : merge;
+}
+
 // The splits of one (sequence, KV head) that share a workgroup form a team (consecutive waves): the
 // members leave their (m, l, O) in LDS and the team's first wave combines them, in wave order, with its
-// own and writes the output rows, or one partial result if the (sequence, KV head) has more teams.
-// Bytes of LDS a decode workgroup of `waves` waves needs for that.
-__host__ __device__ constexpr size_t decode_team_lds_bytes(int waves, int G, int D) { return (size_t)waves * G * (D + 2) * sizeof(float); }
-
+// own and writes the output rows, or one partial result if the (sequence, KV head) has more teams (then
+// the team is the whole workgroup).
 template <int D, class E, int NS>
 __device__ void decode_item(const AttnArgs &A, const int32_t *__restrict__ it, float *team_lds, int wg_waves) {
-    using x8 = typename E::x8;
     using x4 = typename E::x4;
     using el = typename E::t;
-    constexpr int KS = D / 32;  // k-steps of K Q^T
     constexpr int MT = D / 16;  // 16-row tiles of O^T
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));  // may be called in a loop: derive the per-lane values afresh for every item (see prefill_item)
@@ -1130,85 +1231,27 @@ __device__ void decode_item(const AttnArgs &A, const int32_t *__restrict__ it, f
     for (int c = 0; c < MT; c++) o[c] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m_run = -1e30f, l_run = 0.f;
 
-    if (n_tok > 0) {
-        const int page0 = t0 / kBlock;
-        const int n_pg = (n_tok + kBlock - 1) / kBlock;  // 1..64
-        const int32_t *pages = A.pages + it[DC_PAGEOFF] + page0;
-        const int my_page = pages[min(lane, n_pg - 1)];  // lane i holds the id of page i of the split
+    if (n_tok > 0)
+        decode_sweep<D, E, NS, false>(A, kvh, qrow, A.pages + it[DC_PAGEOFF] + t0 / kBlock, (n_tok + kBlock - 1) / kBlock, n_tok, takes_new, lane, o,
+                               m_run, l_run);
 
-        x8 qreg[KS];
-        const int64_t q_off = ((int64_t)qrow * A.Hq + kvh * G + min(j, G - 1)) * D;
-#pragma unroll
-        for (int kk = 0; kk < KS; kk++) {
-            u32x4 w = *reinterpret_cast<const u32x4 *>(A.q + q_off + (4 * kk + g) * 8);
-            if (j >= G) w = u32x4{0u, 0u, 0u, 0u};
-            qreg[kk] = __builtin_bit_cast(x8, w);
-        }
-
-        // A ring of NS register stages, one page each: while page i is consumed the loads of pages
-        // i+1 .. i+NS-1 are in flight.
-        DecodePage<D> st[NS];
-#pragma unroll
-        for (int u = 0; u < NS - 1; u++)
-            if (u < n_pg) decode_fetch<D>(A, kvh, __builtin_amdgcn_readlane(my_page, u), j, g, st[u]);
-        // Main part: every page consumed here is full and every fetch is of a page of the split, so the body
-        // has no branch around the loads and the compiler's wait before a stage's first use counts exactly
-        // the loads issued after it.  (With a conditional fetch the wait has to be right for the path
-        // without it, and then also waits for the page just requested: one page in flight instead of NS - 1.)
-        int pp = 0;
-        for (; pp + 2 * (NS - 1) < n_pg; pp += NS) {
-#pragma unroll
-            for (int u = 0; u < NS; u++) {
-                decode_fetch<D>(A, kvh, __builtin_amdgcn_readlane(my_page, pp + u + NS - 1), j, g, st[(u + NS - 1) % NS]);
-                decode_consume<D, E>(A, st[u], qreg, kBlock, g, o, m_run, l_run);
-            }
-        }
-        // The last pages (at most 2 NS - 2): fetch while there is a page left, the last one may be partial.
-        for (; pp < n_pg; pp += NS) {
-#pragma unroll
-            for (int u = 0; u < NS; u++) {
-                const int cur = pp + u;
-                if (cur < n_pg) {
-                    const int nxt = cur + NS - 1;
-                    if (nxt < n_pg) decode_fetch<D>(A, kvh, __builtin_amdgcn_readlane(my_page, nxt), j, g, st[(u + NS - 1) % NS]);
-                    if (takes_new && cur == n_pg - 1)
-                        decode_take_new_token<D>(A, kvh, qrow, (n_tok - 1) & (kBlock - 1), j, g, st[u]);
-                    decode_consume<D, E>(A, st[u], qreg, n_tok - cur * kBlock, g, o, m_run, l_run);
-                }
-            }
-        }
-        l_run += xor_lanes(l_run, 16);
-        l_run = half_swap_sum(l_run);
-    }
-
-    // ---- team: members (positions 1 ..) hand their result to the first wave through LDS
-    // LDS: O^T of every wave [waves][G][D], then (m, l) [waves][G][2]; a lane reads back the elements it owns
-    float *const my_o = team_lds + (size_t)wave * G * D;
-    float *const my_ml = team_lds + (size_t)wg_waves * G * D + (size_t)wave * G * 2;
-    if (team_pos > 0 && j < G) {
-        float *dst = my_o + j * D + 4 * g;
-#pragma unroll
-        for (int c = 0; c < MT; c++) *reinterpret_cast<f32x4 *>(dst + 16 * c) = o[c];
-        if (g == 0) {
-            my_ml[2 * j] = m_run;
-            my_ml[2 * j + 1] = l_run;
-        }
-    }
+    // ---- team: members (positions 1 ..) hand their result to the first wave through LDS; a lane reads back
+    // the elements it owns
+    const WaveResults<D> res(team_lds, wg_waves, G);
+    if (team_pos > 0) res.put(wave, lane, o, m_run, l_run);
     __syncthreads();  // executed once by every wave of a decode workgroup, for every unit of items it runs
-    if (team_pos > 0 || n_tok == 0) return;
-    const int jc = min(j, G - 1);  // head columns past G are padding: they follow column G - 1 and store nothing
-    for (int i = 1; i < team_n; i++) {
-        const float m_i = my_ml[(i * G + jc) * 2], l_i = my_ml[(i * G + jc) * 2 + 1];
-        const float m_new = fmaxf(m_run, m_i);
-        const float a = fast_exp2(m_run - m_new), b = fast_exp2(m_i - m_new);
-        m_run = m_new;
-        l_run = l_run * a + l_i * b;
-        const float *src = my_o + (size_t)i * G * D + jc * D + 4 * g;
+    if (team_pos == 0 && n_tok > 0) {
+        const int jc = min(j, G - 1);  // head columns past G are padding: they follow column G - 1 and store nothing
+        for (int i = 1; i < team_n; i++) {
+            const float2 ml_i = res.get_ml(wave + i, jc);
+            const float m_new = fmaxf(m_run, ml_i.x);
+            const float a = fast_exp2(m_run - m_new), b = fast_exp2(ml_i.x - m_new);
+            m_run = m_new;
+            l_run = l_run * a + ml_i.y * b;
 #pragma unroll
-        for (int c = 0; c < MT; c++) o[c] = o[c] * a + *reinterpret_cast<const f32x4 *>(src + 16 * c) * b;
-    }
-    if (slot < 0) {
-        if (j < G) {
+            for (int c = 0; c < MT; c++) o[c] = o[c] * a + res.get(wave + i, jc, 16 * c + 4 * g) * b;
+        }
+        if (j < G && slot < 0) {
             const float inv = 1.f / l_run;
             uint16_t *dst = A.out + ((int64_t)qrow * A.Hq + kvh * G + j) * D + 4 * g;
 #pragma unroll
@@ -1218,38 +1261,106 @@ __device__ void decode_item(const AttnArgs &A, const int32_t *__restrict__ it, f
                 for (int e = 0; e < 4; e++) w[e] = (el)(o[c][e] * inv);
                 *reinterpret_cast<x4 *>(dst + 16 * c) = w;
             }
-        }
-        return;
-    }
-    if (j < G) {
-        float *dst = A.ws_o + ((int64_t)slot * G + j) * D + 4 * g;
-        float *ml = A.ws_ml + ((int64_t)slot * G + j) * 2;
-        if (A.fused) {
+        } else if (j < G) {
+            float *const row = A.ws_o + ((int64_t)slot * G + j) * D;
+            float *const ml = A.ws_ml + ((int64_t)slot * G + j) * 2;
+            if (A.fused) {
+                const __amdgpu_buffer_rsrc_t win = peer_window(A.ws_o + (int64_t)slot * G * D, (uint32_t)(G * D * sizeof(float)));
 #pragma unroll
-            for (int c = 0; c < MT; c++) {
-                peer_store2(dst + 16 * c, o[c][0], o[c][1]);
-                peer_store2(dst + 16 * c + 2, o[c][2], o[c][3]);
-            }
-            if (g == 0) peer_store2(ml, m_run, l_run);
-        } else {
-            // partial results are written once and read once: stream them past the caches (plain
-            // stores of these 2 KiB per split measured 3 % less bandwidth on a batch of decodes)
+                for (int c = 0; c < MT; c++) peer_store4(win, (uint32_t)((j * D + 16 * c + 4 * g) * sizeof(float)), o[c]);
+                if (g == 0) peer_store2(ml, m_run, l_run);
+            } else {
+                // partial results are written once and read once: stream them past the caches (plain
+                // stores of these 2 KiB per split measured 3 % less bandwidth on a batch of decodes)
 #pragma unroll
-            for (int c = 0; c < MT; c++) __builtin_nontemporal_store(o[c], reinterpret_cast<f32x4 *>(dst + 16 * c));
-            if (g == 0) {
-                ml[0] = m_run;
-                ml[1] = l_run;
+                for (int c = 0; c < MT; c++) __builtin_nontemporal_store(o[c], reinterpret_cast<f32x4 *>(row + 16 * c + 4 * g));
+                if (g == 0) {
+                    ml[0] = m_run;
+                    ml[1] = l_run;
+                }
             }
         }
+        if (slot >= 0) stores_done();
     }
-    if (!A.fused) return;
-    // the last team of the (sequence, KV head) to get here combines the partial results of all of them
+    if (slot < 0 || !A.fused) return;
+    // A partial result was left, so the team is the whole workgroup.  The last of the pair's workgroups to get here
+    // combines all of them.
     const int32_t *mg = A.merge + (int64_t)merge_item * kItemInts;
-    int32_t *const counter = A.counters + mg[MG_COUNTER];
-    if (!arrive_is_last(counter, mg[MG_NSPLIT], lane == 0)) return;
-    for (int h = 0; h < G; h++)
-        merge_row<D, E, true>(A.ws_o, A.ws_ml, mg[MG_SLOT0], mg[MG_NSPLIT], G, h, A.out + ((int64_t)qrow * A.Hq + kvh * G + h) * D, lane);
-    if (lane == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!workgroup_arrives_last(A.counters + mg[MG_COUNTER] * kCounterStride, mg[MG_NSPLIT], reinterpret_cast<int *>(team_lds), tid)) return;
+    merge_pair<D, E, true>(A.ws_o, A.ws_ml, mg[MG_SLOT0], mg[MG_NSPLIT], G, A.out + ((int64_t)qrow * A.Hq + kvh * G) * D, team_lds, tid,
+                           wg_waves * 64);
+}
+
+// A batch of few decodes: one split is run by a whole workgroup of R waves, which share its pages out (a contiguous
+// run each, so that a wave has at most 64 / R pages: most of them are in flight at once, and the workgroup needs about
+// one memory latency for its split where a single wave needs one per page).  All waves then meet in LDS and the
+// combination is spread over all threads: a thread owns four adjacent elements of a row.
+template <int D, class E, int NS, int R>
+__device__ void decode_item_wide(const AttnArgs &A, const int32_t *__restrict__ it, float *lds) {
+    using x4 = typename E::x4;
+    using el = typename E::t;
+    constexpr int MT = D / 16;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kvh = it[DC_KVH], t0 = it[DC_BEGIN], t1 = it[DC_END], qrow = it[DC_QROW], slot = it[DC_SLOT];
+    const int merge_item = (it[DC_TEAM] >> 8) - 1;
+    const int G = A.G;
+    const int n_pages = (t1 - t0 + kBlock - 1) / kBlock;
+    const int p0 = n_pages * wave / R, p1 = n_pages * (wave + 1) / R;  // this wave's pages of the split
+    f32x4 o[MT];
+#pragma unroll
+    for (int c = 0; c < MT; c++) o[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m_run = -1e30f, l_run = 0.f;
+    if (p1 > p0) {
+        const bool takes_new = p1 == n_pages && (it[DC_TEAM] & kTeamTailBit) && A.k_new != nullptr;
+        decode_sweep<D, E, NS, true>(A, kvh, qrow, A.pages + it[DC_PAGEOFF] + t0 / kBlock + p0, p1 - p0, min(t1 - t0, p1 * kBlock) - p0 * kBlock,
+                               takes_new, lane, o, m_run, l_run);
+    }
+    const WaveResults<D> res(lds, R, G);
+    res.put(wave, lane, o, m_run, l_run);
+    __syncthreads();
+    constexpr int VR = D / 4;
+    float *const part = slot < 0 ? nullptr : A.ws_o + (int64_t)slot * G * D;
+    float *const part_ml = slot < 0 ? nullptr : A.ws_ml + (int64_t)slot * G * 2;
+    for (int v = tid; v < G * VR; v += R * 64) {
+        const int j = v / VR, d = (v % VR) * 4;
+        float2 ml[R];
+        float m = -1e30f;
+#pragma unroll
+        for (int i = 0; i < R; i++) {
+            ml[i] = res.get_ml(i, j);
+            m = fmaxf(m, ml[i].x);
+        }
+        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+        float l = 0.f;
+#pragma unroll
+        for (int i = 0; i < R; i++) {
+            const float w = fast_exp2(ml[i].x - m);
+            l += w * ml[i].y;
+            acc += res.get(i, j, d) * w;
+        }
+        if (slot < 0) {
+            const float inv = 1.f / l;
+            x4 w4;
+#pragma unroll
+            for (int e = 0; e < 4; e++) w4[e] = (el)(acc[e] * inv);
+            *reinterpret_cast<x4 *>(A.out + ((int64_t)qrow * A.Hq + kvh * G) * D + (int64_t)v * 4) = w4;
+        } else if (A.fused) {
+            peer_store4(peer_window(part, (uint32_t)(G * D * sizeof(float))), (uint32_t)v * 16, acc);
+            if (d == 0) peer_store2(part_ml + 2 * j, m, l);
+        } else {
+            __builtin_nontemporal_store(acc, reinterpret_cast<f32x4 *>(part + v * 4));
+            if (d == 0) {
+                part_ml[2 * j] = m;
+                part_ml[2 * j + 1] = l;
+            }
+        }
+    }
+    if (slot < 0 || !A.fused) return;
+    stores_done();
+    const int32_t *mg = A.merge + (int64_t)merge_item * kItemInts;
+    if (!workgroup_arrives_last(A.counters + mg[MG_COUNTER] * kCounterStride, mg[MG_NSPLIT], reinterpret_cast<int *>(lds), tid)) return;
+    merge_pair<D, E, true>(A.ws_o, A.ws_ml, mg[MG_SLOT0], mg[MG_NSPLIT], G, A.out + ((int64_t)qrow * A.Hq + kvh * G) * D, lds, tid, R * 64);
 }
 
 #ifdef TC_WG_TRACE
@@ -1257,6 +1368,18 @@ __device__ void decode_item(const AttnArgs &A, const int32_t *__restrict__ it, f
 // it started, the time its prefill pieces were done and the time it ended (100 MHz counter), and where it ran.
 constexpr int kTraceWorkgroups = 16384;
 __device__ long long g_wg_trace[kTraceWorkgroups * 4];
+__device__ __forceinline__ void wg_trace(long long t_start, long long t_mid, bool is_decode) {
+    __syncthreads();
+    if (threadIdx.x != 0 || blockIdx.x >= kTraceWorkgroups) return;
+    unsigned hw, xcc;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_HW_ID)" : "=s"(hw));
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
+    long long *t = g_wg_trace + (long long)blockIdx.x * 4;
+    t[0] = t_start;
+    t[1] = __builtin_amdgcn_s_memrealtime();
+    t[2] = ((long long)xcc << 32) | hw;
+    t[3] = (is_decode ? 1 : 0) | ((t_mid - t_start) << 8);
+}
 #endif
 
 struct AttnScalars {
@@ -1299,7 +1422,7 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : kDecode
     if constexpr (WAVES == kDecodeWaves) {
         const int first_append_wg = (int)gridDim.x - sc.n_front;
         if ((int)blockIdx.x >= first_append_wg) {
-            append_decode_rows<D>(A, append, sc.n_append_rows, (int)blockIdx.x - first_append_wg);
+            append_decode_rows<D>(k_pool, v_pool, k_new, v_new, sc.Hkv, append, sc.n_append_rows, (int)blockIdx.x - first_append_wg);
             return;
         }
     }
@@ -1335,7 +1458,7 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : kDecode
         // splits of a pair combined by the last to arrive, measured slower than units with their teams.)
         // The workgroup that leaves last puts both counters back to zero for the next launch.
         int *const drawn = reinterpret_cast<int *>(lds + PrefillCfg<D>::kQueueSlot);
-        int32_t *const next_unit = A.counters + A.queue, *const gone = next_unit + 1;
+        int32_t *const next_unit = A.counters + A.queue * kCounterStride, *const gone = next_unit + kCounterStride;
         const int n_units = A.n_decode / WAVES;
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         for (;;) {
@@ -1353,32 +1476,48 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : kDecode
         }
     }
 #ifdef TC_WG_TRACE
-    __syncthreads();
-    if (threadIdx.x == 0 && blockIdx.x < kTraceWorkgroups) {
-        unsigned hw, xcc;
-        asm volatile("s_getreg_b32 %0, hwreg(HW_REG_HW_ID)" : "=s"(hw));
-        asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
-        long long *t = g_wg_trace + (long long)blockIdx.x * 4;
-        t[0] = t_start;
-        t[1] = __builtin_amdgcn_s_memrealtime();
-        t[2] = ((long long)xcc << 32) | hw;
-        t[3] = (((int)blockIdx.x < sc.n_prefill) ? 0 : 1) | ((t_mid - t_start) << 8);
-    }
+    wg_trace(t_start, t_mid, (int)blockIdx.x >= sc.n_prefill);
+#endif
+}
+
+// A batch of few decodes: one workgroup of kWideWaves waves per split (decode_item_wide), one per compute unit, with
+// registers for kWideStages - 1 pages in flight per wave; the wave that takes a sequence's new token from k_new / v_new also
+// stores its row.  Arguments as above; the prefill lists are empty.
+template <int D, class E>
+__global__ void __launch_bounds__(kWideWaves * 64, 2)
+    wide_decode_kernel(uint16_t *k_pool, uint16_t *v_pool, const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_new,
+                       const uint16_t *__restrict__ v_new, uint16_t *__restrict__ out, const int32_t *__restrict__ pages,
+                       const int32_t *__restrict__ decode, const int32_t *__restrict__ merge, int32_t *counters, float *ws,
+                       const AttnScalars sc) {
+    extern __shared__ __align__(16) char lds[];
+#ifdef TC_WG_TRACE
+    const long long t_start = __builtin_amdgcn_s_memrealtime();
+#endif
+    AttnArgs A = {};
+    A.k_pool = k_pool; A.v_pool = v_pool; A.q = q; A.k_new = k_new; A.v_new = v_new; A.out = out; A.pages = pages; A.decode = decode;
+    A.merge = merge; A.counters = counters;
+    A.ws_o = ws; A.ws_ml = ws + (int64_t)sc.n_partials * sc.G * D;
+    A.n_decode = sc.n_decode; A.Hq = sc.Hq; A.Hkv = sc.Hkv; A.G = sc.G; A.fused = sc.fused; A.scale_log2 = sc.scale_log2;
+    decode_item_wide<D, E, kWideStages, kWideWaves>(A, decode + (int64_t)blockIdx.x * kItemInts, reinterpret_cast<float *>(lds));
+#ifdef TC_WG_TRACE
+    wg_trace(t_start, t_start, true);
 #endif
 }
 
 // ------------------------------------------------------------------------------------
 // Split-KV merge as a launch of its own (the two-call form; the fused kernel does the same inside)
 // ------------------------------------------------------------------------------------
-// One workgroup per split decode (sequence, KV head) pair; one wavefront per query head.
+// One workgroup per split decode (sequence, KV head) pair, with as many threads as a workgroup of the attention launch
+// (the order of the sums depends on that number).
 template <int D, class E>
-__global__ void __launch_bounds__(256) split_merge_kernel(const int32_t *__restrict__ items, const float *__restrict__ ws_o,
+__global__ void __launch_bounds__(512) split_merge_kernel(const int32_t *__restrict__ items, const float *__restrict__ ws_o,
                                                           const float *__restrict__ ws_ml, uint16_t *__restrict__ out,
                                                           int Hq, int G) {
+    extern __shared__ __align__(16) char lds[];
     const int32_t *it = items + (int64_t)blockIdx.x * kItemInts;
     const int kvh = it[MG_KVH], qrow = it[MG_QROW], ns = it[MG_NSPLIT], slot0 = it[MG_SLOT0];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int j = wave; j < G; j += 4) merge_row<D, E, false>(ws_o, ws_ml, slot0, ns, G, j, out + ((int64_t)qrow * Hq + kvh * G + j) * D, lane);
+    merge_pair<D, E, false>(ws_o, ws_ml, slot0, ns, G, out + ((int64_t)qrow * Hq + kvh * G) * D, reinterpret_cast<float *>(lds),
+                            (int)threadIdx.x, (int)blockDim.x);
 }
 
 // One workgroup per cut prefill item, with the lane-to-row map of the prefill branch: the lanes read the pieces'
@@ -1549,22 +1688,27 @@ static int launch_attention_d(const tc_plan *p, const AttnArgs &A, int launches,
     // A batch of decodes whose rows this launch stores: workgroups at the back of the grid do it (four (row, KV head,
     // 8-element piece) units per thread).  A batch with a prefill chunk never gets here with k_new set (see launch_attention).
     int n_front = 0;
-    if (grid > 0 && A.k_new && p->n_pieces == 0) {
-        const int64_t units = (int64_t)p->n_append * p->Hkv * (D / 8);
-        n_front = (int)((units + kDecodeWaves * 64 * 4 - 1) / (kDecodeWaves * 64 * 4));
+    if (grid > 0 && A.k_new && p->n_pieces == 0 && p->waves_per_item == 1) {
+        const int64_t units = (int64_t)p->n_append * p->Hkv * D;  // a row's element of one KV head
+        const int per_wg = p->launch_threads() * kAppendPerThread;
+        n_front = (int)((units + per_wg - 1) / per_wg);
         grid += n_front;
     }
     const AttnScalars sc = {A.n_prefill, A.n_decode, A.Hq, A.Hkv, A.G, A.fused, A.queue, p->n_partials, n_front, p->n_append, A.scale_log2};
     const int32_t *append = p->dev + p->off_append;
     if (grid > 0 && p->n_pieces > 0) {
         const int lds = PrefillCfg<D>::kLdsBytes;  // the decode workgroups of the launch need less, for any G
-        static_assert(decode_team_lds_bytes(kMixedWaves, 16, D) <= (size_t)PrefillCfg<D>::kLdsBytes, "team buffers must fit the prefill tiles' LDS");
+        static_assert(decode_lds_bytes(kMixedWaves, 16, D) <= (size_t)PrefillCfg<D>::kLdsBytes, "team buffers must fit the prefill tiles' LDS");
         if (int err = allow_prefill_lds<D, E>(p->device)) return err;
         mixed_attention_kernel<D, E, kMixedWaves><<<grid, kMixedWaves * 64, lds, st>>>(
             A.k_pool, A.v_pool, A.q, A.k_new, A.v_new, A.out, A.pages, A.prefill, A.pieces, A.wg_first, A.decode, A.merge, append,
             A.counters, A.ws_o, sc);
+    } else if (grid > 0 && p->waves_per_item > 1) {
+        static_assert(decode_lds_bytes(kWideWaves, 16, D) <= 65536, "more than 64 KiB of dynamic LDS needs an opt-in");
+        wide_decode_kernel<D, E><<<grid, kWideWaves * 64, decode_lds_bytes(kWideWaves, p->G, D), st>>>(A.k_pool, A.v_pool, A.q, A.k_new, A.v_new, A.out, A.pages, A.decode, A.merge,
+                                                                     A.counters, A.ws_o, sc);
     } else if (grid > 0) {
-        mixed_attention_kernel<D, E, kDecodeWaves><<<grid, kDecodeWaves * 64, decode_team_lds_bytes(kDecodeWaves, p->G, D), st>>>(
+        mixed_attention_kernel<D, E, kDecodeWaves><<<grid, kDecodeWaves * 64, decode_lds_bytes(kDecodeWaves, p->G, D), st>>>(
             A.k_pool, A.v_pool, A.q, A.k_new, A.v_new, A.out, A.pages, A.prefill, A.pieces, A.wg_first, A.decode, A.merge, append,
             A.counters, A.ws_o, sc);
     }
@@ -1577,7 +1721,7 @@ static int launch_attention_d(const tc_plan *p, const AttnArgs &A, int launches,
         if (e != hipSuccess) return (int)e;
     }
     if ((launches & kLaunchMerge) && p->n_merge > p->n_merge_prefill)
-        split_merge_kernel<D, E><<<p->n_merge - p->n_merge_prefill, 256, 0, st>>>(p->dev + p->off_merge + (size_t)p->n_merge_prefill * kItemInts,
+        split_merge_kernel<D, E><<<p->n_merge - p->n_merge_prefill, p->launch_threads(), merge_lds_bytes(p->launch_threads()), st>>>(p->dev + p->off_merge + (size_t)p->n_merge_prefill * kItemInts,
                                                                                  A.ws_o, A.ws_ml, A.out, A.Hq, A.G);
     return (int)hipGetLastError();
 }

@@ -38,6 +38,37 @@ static int choose_split(int64_t decode_token_heads) {
     return 128;
 }
 
+// A batch of few decodes (no prefill chunk) whose single-wave splits would leave wave slots empty or keep a few waves
+// busy long after the others: every split is run by a whole workgroup instead (decode_item_wide), and a sequence of more than
+// 1024 tokens is cut into as many splits as it takes to have one workgroup per compute unit (two per unit once
+// they would hold more than 900 tokens each).  Returns the split length, or 0 when the single-wave form serves better.
+// Measured (32/8 heads, head_dim 128, attention launch with its append, us, single-wave form / this one):
+//   8 requests, lognormal lengths of mean 1024  29.6 / 11.5       1 request of 16000 tokens         22.8 / 18
+//   24 of lognormal mean 1500                   52.1 / 29.8       32 of 128-384 tokens              10.2 / 9.4
+//   96 of lognormal mean 1500 (1.15 M tokens x heads)   106.5 / 101.7     96 of 512-1536 tokens      68.2 / 74.6
+// The line: with 3072 splits of 256 tokens or more the single-wave form fills the chip and streams at the HBM rate,
+// which this form, whose workgroups all start and combine alike, misses by 5-8 %.  Below that the single-wave form
+// serves better where it has no partial results to combine (at most 4096 tokens), this one would have (over 1024), and
+// the longest sequence is not far above the mean load of a compute unit (24 requests of 512-1536 tokens: 21.8 / 24.6, 16 of
+// them 19.3 / 15.9).
+static int choose_wide_split(const tc_plan *p, int S, int64_t decode_tokens) {
+    const int64_t token_heads = decode_tokens * p->Hkv;
+    if (token_heads >= (int64_t)kNumCu * kDecodeWgPerCu * kDecodeWaves * 256) return 0;
+    int64_t longest = 0;
+    for (int s = 0; s < S; s++) longest = std::max<int64_t>(longest, (int64_t)p->ctx_len[s] + 1);
+    const int64_t max_split = (int64_t)kMaxSplitPages * kBlock;
+    if (longest > max_split && longest <= kDecodeWaves * max_split && 4 * longest * kNumCu < 7 * token_heads) return 0;
+    const int64_t target = token_heads > 900 * kNumCu ? 2 * kNumCu : kNumCu;
+    int lo = 128 / kBlock, hi = kMaxSplitPages;  // pages: the shortest split that needs no more workgroups than that
+    while (lo < hi) {
+        const int mid = (lo + hi) / 2;
+        int64_t n = 0;
+        for (int s = 0; s < S; s++) n += ((int64_t)p->ctx_len[s] + 1 + mid * kBlock - 1) / (mid * kBlock);
+        if (n * p->Hkv <= target) hi = mid; else lo = mid + 1;
+    }
+    return lo * kBlock;
+}
+
 // First token of split i of a decode sequence of kv tokens cut into ns splits: the sequence's pages are
 // dealt out evenly (the first splits get the odd pages), so the splits of a sequence take the same time
 // and the waves that run them side by side finish together.  split_begin(kv, ns, ns) >= kv.
@@ -251,8 +282,16 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     // (1, 2, 4 .. splits) go as one team into the first open workgroup with room (first fit over a
     // bounded window; the oldest is closed when none has room).  Runs are taken longest split first.
     // Wave slots left free hold padding items (no tokens).
-    const int W = w.blocks.empty() ? kDecodeWaves : kMixedWaves;
     p->split_tokens = choose_split(decode_tokens * Hkv);
+    p->items_per_wg = w.blocks.empty() ? kDecodeWaves : kMixedWaves;
+    p->waves_per_item = 1;
+    if (w.blocks.empty() && n_decode_seqs > 0)
+        if (const int split = choose_wide_split(p, S, decode_tokens)) {
+            p->split_tokens = split;
+            p->items_per_wg = 1;
+            p->waves_per_item = kWideWaves;
+        }
+    const int W = p->items_per_wg;
     w.runs.clear();
     for (int s = 0; s < S; s++) {
         if (p->q_start[s + 1] - p->q_start[s] != 1) continue;
@@ -319,8 +358,9 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     const size_t off_wg = off_pieces + (size_t)n_pieces * kItemInts;
     const size_t off_decode = off_wg + (size_t)n_prefill_wg;
     const size_t off_merge = off_decode + (size_t)n_decode * kItemInts;
-    const size_t off_counters = off_merge + (size_t)n_merge * kItemInts;
-    const size_t total = std::max<size_t>(off_counters + (size_t)(n_counters + n_queue_counters), 1);
+    const size_t off_counters = (off_merge + (size_t)n_merge * kItemInts + kCounterStride - 1) / kCounterStride * kCounterStride;  // each on a line of its own
+    const size_t n_counter_ints = (size_t)(n_counters + n_queue_counters) * kCounterStride;
+    const size_t total = std::max<size_t>(off_counters + n_counter_ints, 1);
     if (int err = begin_plan_host(p, total)) return fail(TC_ERR_DEVICE, std::string("host buffer of the plan: ") + hip_error_text(err));
     int32_t *H = p->host;
 
@@ -447,7 +487,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
             int32_t *dc = dc0 + ((int64_t)g * W + at) * kItemInts;
             dc[DC_SEQ] = -1; dc[DC_KVH] = 0; dc[DC_BEGIN] = dc[DC_END] = 0; dc[DC_QROW] = 0; dc[DC_SLOT] = -1; dc[DC_PAGEOFF] = 0; dc[DC_TEAM] = 1;
         }
-    std::memset(H + off_counters, 0, (size_t)(n_counters + n_queue_counters) * sizeof(int32_t));
+    std::memset(H + off_counters, 0, n_counter_ints * sizeof(int32_t));
 
     p->S = S; p->T = S ? p->q_start[S] : 0;
     p->n_prefill_seqs = n_prefill_seqs; p->n_decode_seqs = n_decode_seqs;
@@ -513,7 +553,8 @@ tc_status tc_plan_get_info(const tc_plan *p, tc_plan_info *info) {
     info->num_prefill_items = p->n_prefill; info->num_decode_items = p->n_decode;
     info->num_merge_items = p->n_merge; info->num_partials = p->n_partials; info->num_piece_partials = p->n_piece_partials;
     info->split_tokens = p->split_tokens; info->rows_per_prefill_item = tc::kPrefillRows;
-    info->grid_blocks = p->grid_blocks(); info->block_threads = p->wg_waves() * 64;
+    info->grid_blocks = p->grid_blocks(); info->block_threads = p->items_per_wg * 64;
+    info->waves_per_item = p->waves_per_item;
     info->total_pages = p->total_pages;
     info->num_prefill_pieces = p->n_pieces;
     info->num_prefill_workgroups = p->n_prefill_wg;

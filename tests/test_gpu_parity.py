@@ -374,6 +374,42 @@ def test_append_fused_into_attention_full_size_configs(H, idx):
     check_fused_step(H, W.make_batch(W.config_spec(idx)), f"config{idx}")
 
 
+# Batches of decodes only.  Few tokens: a split is run by a whole workgroup of four waves (three stages: edges of fewer
+# pages than waves, one to three pages per wave and one more, 64 pages and one more; merges of one batch of partial
+# results and of several, with one slice of threads and with several).  Many tokens (or sequences that one team covers
+# evenly): one wave per split, teams of four, merges.
+DECODE_FORMS = {
+    # name: (Hq, Hkv, D, contexts without the new token, dtype, waves per item)
+    "wide_page_edges": (8, 2, 128, [0, 14, 15, 16, 31, 47, 48, 63, 64, 65, 127, 128, 191, 192, 193, 255, 256], "bf16", 4),
+    "wide_split_edges": (8, 2, 128, [1022, 1023, 1024, 1025, 2047, 2048, 129 * 16], "bf16", 4),
+    "wide_merge_g16": (16, 1, 128, [30000, 4096, 77], "bf16", 4),
+    "wide_merge_g1_d64": (3, 3, 64, [33000, 2000], "fp16", 4),
+    "wide_merge_g5": (10, 2, 128, [9000, 20000], "fp16", 4),
+    "wide_many_short": (8, 2, 64, [(13 * i) % 300 for i in range(200)], "bf16", 4),
+    "waves_teams_and_merges": (32, 32, 64, [9000, 8192, 4097, 4096, 1025, 500, 31, 0], "bf16", 1),
+    "waves_merge_g16_d128": (256, 16, 128, [30000, 19000, 1000], "fp16", 1),
+    "waves_even_sequences": (8, 2, 128, [1400 + 5 * i for i in range(150)], "bf16", 1),
+}
+
+
+@pytest.mark.parametrize("name", list(DECODE_FORMS))
+def test_decode_forms_match_oracle_and_each_call(H, name):
+    import torch
+    Hq, Hkv, D, ctx, dtype, waves = DECODE_FORMS[name]
+    b = W.make_batch(W.custom_spec(name, Hq, Hkv, D, [1] * len(ctx), ctx, seed=zlib.crc32(name.encode()) % 10007, dtype=dtype))
+    (mx, rel), db = run_and_compare(H, b, name, gather=None)
+    assert db.plan.info.waves_per_item == waves
+    assert dtype != "fp16" or (mx <= FP16_MAX_ABS and rel <= FP16_REL_L2), (mx, rel)
+    single = H.to_host(db.out).copy()
+    db.out.fill_(0)
+    db.workspace.fill_(0xFF)
+    db.attention_partials()
+    db.split_merge()
+    torch.cuda.synchronize()
+    assert np.array_equal(H.to_host(db.out), single), "two-launch form"
+    check_fused_step(H, b, name)
+
+
 def test_append_fused_into_attention_half_precision(H):
     Hq, Hkv, D, q_len, ctx = SMALL["decode_long_ragged"]
     check_fused_step(H, W.make_batch(W.custom_spec("fused16", Hq, Hkv, D, q_len, ctx, seed=5, dtype="fp16")), "fp16")
