@@ -1295,12 +1295,14 @@ __device__ void decode_item(const AttnArgs &A, const int32_t *__restrict__ it, f
 // run each, so that a wave has at most 64 / R pages: most of them are in flight at once, and the workgroup needs about
 // one memory latency for its split where a single wave needs one per page).  All waves then meet in LDS and the
 // combination is spread over all threads: a thread owns four adjacent elements of a row.
-template <int D, class E, int NS, int R>
+template <int D, class E, int NS, int R, bool STORE>
 __device__ void decode_item_wide(const AttnArgs &A, const int32_t *__restrict__ it, float *lds) {
     using x4 = typename E::x4;
     using el = typename E::t;
     constexpr int MT = D / 16;
-    const int tid = threadIdx.x, lane = tid & 63;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));  // may be called in a loop (see prefill_item)
+    const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kvh = it[DC_KVH], t0 = it[DC_BEGIN], t1 = it[DC_END], qrow = it[DC_QROW], slot = it[DC_SLOT];
     const int merge_item = (it[DC_TEAM] >> 8) - 1;
@@ -1313,7 +1315,7 @@ __device__ void decode_item_wide(const AttnArgs &A, const int32_t *__restrict__ 
     float m_run = -1e30f, l_run = 0.f;
     if (p1 > p0) {
         const bool takes_new = p1 == n_pages && (it[DC_TEAM] & kTeamTailBit) && A.k_new != nullptr;
-        decode_sweep<D, E, NS, true>(A, kvh, qrow, A.pages + it[DC_PAGEOFF] + t0 / kBlock + p0, p1 - p0, min(t1 - t0, p1 * kBlock) - p0 * kBlock,
+        decode_sweep<D, E, NS, STORE>(A, kvh, qrow, A.pages + it[DC_PAGEOFF] + t0 / kBlock + p0, p1 - p0, min(t1 - t0, p1 * kBlock) - p0 * kBlock,
                                takes_new, lane, o, m_run, l_run);
     }
     const WaveResults<D> res(lds, R, G);
@@ -1397,8 +1399,9 @@ struct AttnScalars {
 // scalar loads.  WAVES = 8: batches with a prefill chunk (one workgroup per compute unit, up to 256
 // registers per wave); WAVES = 4: decode-only batches (three workgroups per compute unit).
 // Workgroups [0, n_prefill) run the prefill pieces the plan gave them, one after the other; the rest run
-// decode items, one per wave.
-template <int D, class E, int WAVES>
+// decode items, one per wave, or (WIDE; a form of its own, so that neither pays for the other's registers: both in one
+// kernel, chosen at run time, cost 1 us of 195 on a 2048-token chunk with 64 decodes) one per workgroup.
+template <int D, class E, int WAVES, bool WIDE>
 __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : kDecodeWgPerCu)
     mixed_attention_kernel(uint16_t *k_pool, uint16_t *v_pool, const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_new,
                            const uint16_t *__restrict__ v_new, uint16_t *__restrict__ out, const int32_t *__restrict__ pages,
@@ -1441,7 +1444,9 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : kDecode
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const int idx = (wg - A.n_prefill) * WAVES + wave;
         // the decode items fill whole workgroups (padding items at the end of some): every wave gets one
-        if (idx < A.n_decode) decode_item<D, E, NS>(A, decode + (int64_t)idx * kItemInts, reinterpret_cast<float *>(lds), WAVES);
+        if constexpr (WIDE)
+            decode_item_wide<D, E, NS, WAVES, false>(A, decode + (int64_t)(wg - A.n_prefill) * kItemInts, reinterpret_cast<float *>(lds));
+        else if (idx < A.n_decode) decode_item<D, E, NS>(A, decode + (int64_t)idx * kItemInts, reinterpret_cast<float *>(lds), WAVES);
     }
 #ifdef TC_WG_TRACE
     t_mid = __builtin_amdgcn_s_memrealtime();
@@ -1459,7 +1464,7 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : kDecode
         // The workgroup that leaves last puts both counters back to zero for the next launch.
         int *const drawn = reinterpret_cast<int *>(lds + PrefillCfg<D>::kQueueSlot);
         int32_t *const next_unit = A.counters + A.queue * kCounterStride, *const gone = next_unit + kCounterStride;
-        const int n_units = A.n_decode / WAVES;
+        const int n_units = WIDE ? A.n_decode : A.n_decode / WAVES;
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         for (;;) {
             __syncthreads();  // the unit before (or the last prefill piece) is done with the LDS
@@ -1467,7 +1472,8 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : kDecode
             __syncthreads();
             const int unit = *drawn;
             if (unit >= n_units) break;
-            decode_item<D, E, NS>(A, decode + ((int64_t)unit * WAVES + wave) * kItemInts, reinterpret_cast<float *>(lds), WAVES);
+            if constexpr (WIDE) decode_item_wide<D, E, NS, WAVES, false>(A, decode + (int64_t)unit * kItemInts, reinterpret_cast<float *>(lds));
+            else decode_item<D, E, NS>(A, decode + ((int64_t)unit * WAVES + wave) * kItemInts, reinterpret_cast<float *>(lds), WAVES);
         }
         if (threadIdx.x == 0 && __hip_atomic_fetch_add(gone, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1) {
             __hip_atomic_store(next_unit, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1498,7 +1504,7 @@ __global__ void __launch_bounds__(kWideWaves * 64, 2)
     A.merge = merge; A.counters = counters;
     A.ws_o = ws; A.ws_ml = ws + (int64_t)sc.n_partials * sc.G * D;
     A.n_decode = sc.n_decode; A.Hq = sc.Hq; A.Hkv = sc.Hkv; A.G = sc.G; A.fused = sc.fused; A.scale_log2 = sc.scale_log2;
-    decode_item_wide<D, E, kWideStages, kWideWaves>(A, decode + (int64_t)blockIdx.x * kItemInts, reinterpret_cast<float *>(lds));
+    decode_item_wide<D, E, kWideStages, kWideWaves, true>(A, decode + (int64_t)blockIdx.x * kItemInts, reinterpret_cast<float *>(lds));
 #ifdef TC_WG_TRACE
     wg_trace(t_start, t_start, true);
 #endif
@@ -1670,12 +1676,12 @@ int launch_kv_migrate(const tc_plan *p, bool import, int page0, int n_pages, int
 
 // More than 64 KiB of dynamic LDS needs an opt-in per kernel function and per device; remembered per
 // instantiation and device (setting it twice is harmless, so racing first calls need no lock).
-template <int D, class E>
+template <int D, class E, bool WIDE>
 static int allow_prefill_lds(int device) {
     static std::atomic<bool> done[kMaxDevices];
     const bool known = device >= 0 && device < kMaxDevices;
     if (known && done[device].load(std::memory_order_acquire)) return 0;
-    hipError_t e = hipFuncSetAttribute((const void *)mixed_attention_kernel<D, E, kMixedWaves>,
+    hipError_t e = hipFuncSetAttribute((const void *)mixed_attention_kernel<D, E, kMixedWaves, WIDE>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, PrefillCfg<D>::kLdsBytes);
     if (e != hipSuccess) return (int)e;
     if (known) done[device].store(true, std::memory_order_release);
@@ -1699,16 +1705,21 @@ static int launch_attention_d(const tc_plan *p, const AttnArgs &A, int launches,
     if (grid > 0 && p->n_pieces > 0) {
         const int lds = PrefillCfg<D>::kLdsBytes;  // the decode workgroups of the launch need less, for any G
         static_assert(decode_lds_bytes(kMixedWaves, 16, D) <= (size_t)PrefillCfg<D>::kLdsBytes, "team buffers must fit the prefill tiles' LDS");
-        if (int err = allow_prefill_lds<D, E>(p->device)) return err;
-        mixed_attention_kernel<D, E, kMixedWaves><<<grid, kMixedWaves * 64, lds, st>>>(
-            A.k_pool, A.v_pool, A.q, A.k_new, A.v_new, A.out, A.pages, A.prefill, A.pieces, A.wg_first, A.decode, A.merge, append,
-            A.counters, A.ws_o, sc);
+        auto launch = [&](auto wide) {
+            constexpr bool WIDE = decltype(wide)::value;
+            if (int err = allow_prefill_lds<D, E, WIDE>(p->device)) return err;
+            mixed_attention_kernel<D, E, kMixedWaves, WIDE><<<grid, kMixedWaves * 64, lds, st>>>(
+                A.k_pool, A.v_pool, A.q, A.k_new, A.v_new, A.out, A.pages, A.prefill, A.pieces, A.wg_first, A.decode, A.merge, append,
+                A.counters, A.ws_o, sc);
+            return 0;
+        };
+        if (int err = p->waves_per_item > 1 ? launch(std::true_type()) : launch(std::false_type())) return err;
     } else if (grid > 0 && p->waves_per_item > 1) {
         static_assert(decode_lds_bytes(kWideWaves, 16, D) <= 65536, "more than 64 KiB of dynamic LDS needs an opt-in");
         wide_decode_kernel<D, E><<<grid, kWideWaves * 64, decode_lds_bytes(kWideWaves, p->G, D), st>>>(A.k_pool, A.v_pool, A.q, A.k_new, A.v_new, A.out, A.pages, A.decode, A.merge,
                                                                      A.counters, A.ws_o, sc);
     } else if (grid > 0) {
-        mixed_attention_kernel<D, E, kDecodeWaves><<<grid, kDecodeWaves * 64, decode_lds_bytes(kDecodeWaves, p->G, D), st>>>(
+        mixed_attention_kernel<D, E, kDecodeWaves, false><<<grid, kDecodeWaves * 64, decode_lds_bytes(kDecodeWaves, p->G, D), st>>>(
             A.k_pool, A.v_pool, A.q, A.k_new, A.v_new, A.out, A.pages, A.prefill, A.pieces, A.wg_first, A.decode, A.merge, append,
             A.counters, A.ws_o, sc);
     }

@@ -29,6 +29,17 @@ tc_status check_pool_matches(const tc_plan *plan, const tc_kv_pool *pool, bool n
     return TC_OK;
 }
 
+// Measured rates the planner balances with (one MI355X): a prefill workgroup needs about kTileUs
+// microseconds per 64-token KV tile at head_dim 128 (half of that at 64), a piece costs about
+// kPieceOverheadTiles tiles on top of its sweep (loading Q, filling the copy pipeline, leaving or combining
+// partial results), the decode branch reads about 5 TB/s when it has the chip to itself and about
+// kDecodeCuGBs GB/s per compute unit when only a few units run it.
+constexpr double kTileUs = 1.8;
+constexpr double kPieceOverheadTiles = 3.0;
+constexpr double kDecodeCuGBs = 40.0;
+constexpr int kMinPieceTiles = 4;   // a levelled piece is never shorter than this
+constexpr int kMinBinTiles = 8;     // and a levelled workgroup never holds less than this
+
 // The KV range of a decode sequence is cut into the fewest splits of at most `split` tokens, equal up
 // to a page; the split is the largest of 1024..128 tokens that still yields enough items to fill the chip.
 static int choose_split(int64_t decode_token_heads) {
@@ -36,6 +47,19 @@ static int choose_split(int64_t decode_token_heads) {
     for (int split = kMaxSplitPages * kBlock; split > 128; split /= 2)
         if (decode_token_heads / split >= want_items) return split;
     return 128;
+}
+
+// The shortest split, from 128 to 1024 tokens, that cuts the decode sequences into no more than `target` (split, KV head) pairs.
+static int shortest_split(const tc_plan *p, int S, int64_t target) {
+    int lo = 128 / kBlock, hi = kMaxSplitPages;  // pages
+    while (lo < hi) {
+        const int mid = (lo + hi) / 2;
+        int64_t n = 0;
+        for (int s = 0; s < S; s++)
+            if (p->q_start[s + 1] - p->q_start[s] == 1) n += ((int64_t)p->ctx_len[s] + 1 + mid * kBlock - 1) / (mid * kBlock);
+        if (n * p->Hkv <= target) hi = mid; else lo = mid + 1;
+    }
+    return lo * kBlock;
 }
 
 // A batch of few decodes (no prefill chunk) whose single-wave splits would leave wave slots empty or keep a few waves
@@ -58,15 +82,27 @@ static int choose_wide_split(const tc_plan *p, int S, int64_t decode_tokens) {
     for (int s = 0; s < S; s++) longest = std::max<int64_t>(longest, (int64_t)p->ctx_len[s] + 1);
     const int64_t max_split = (int64_t)kMaxSplitPages * kBlock;
     if (longest > max_split && longest <= kDecodeWaves * max_split && 4 * longest * kNumCu < 7 * token_heads) return 0;
-    const int64_t target = token_heads > 900 * kNumCu ? 2 * kNumCu : kNumCu;
-    int lo = 128 / kBlock, hi = kMaxSplitPages;  // pages: the shortest split that needs no more workgroups than that
-    while (lo < hi) {
-        const int mid = (lo + hi) / 2;
-        int64_t n = 0;
-        for (int s = 0; s < S; s++) n += ((int64_t)p->ctx_len[s] + 1 + mid * kBlock - 1) / (mid * kBlock);
-        if (n * p->Hkv <= target) hi = mid; else lo = mid + 1;
-    }
-    return lo * kBlock;
+    return shortest_split(p, S, token_heads > 900 * kNumCu ? 2 * kNumCu : kNumCu);
+}
+
+// The same beside a prefill chunk, where a decode workgroup has eight waves and a compute unit to itself.  Eight
+// single-wave splits per sequence (up to 8192 tokens; none to combine across workgroups) stream best as long as the longest
+// of them is not what the launch waits for: a wave needs about 1.1 us per page then, so a sequence of 4000 tokens takes
+// 35 us however little else there is to do.  When that is more than 0.8 of what the rest of the batch needs (t_rest_us: the
+// longest sweep, or the sweeps spread over the chip and the decode bytes at 5 TB/s), the splits are run by whole workgroups, as short as the units that the chunk leaves free can take at once.
+// Measured (us per step, single-wave splits / whole workgroups): three first chunks of 1079 tokens with 16 decodes (lognormal
+// 1024) 64.9 / 40.5; a first chunk of 300 with 4 decodes 34.8 / 17.6; 128 at 2048 with 16 decodes of 512-4096 tokens
+// 50.8 / 39.3, with 64 of them 110.5 / 124.4; 512 at 2048 with 16 of them 55.9 / 57.5, 1024 at 2048 76.3 / 78.0.
+static int choose_wide_split_beside_chunk(const tc_plan *p, int S, double t_rest_us, int64_t n_prefill_wg) {
+    int64_t longest = 0;  // decode sequences that one workgroup covers
+    for (int s = 0; s < S; s++)
+        if (p->q_start[s + 1] - p->q_start[s] == 1) {
+            const int64_t kv = (int64_t)p->ctx_len[s] + 1;
+            if (kv <= (int64_t)kMixedWaves * kMaxSplitPages * kBlock) longest = std::max(longest, kv);
+        }
+    const double t_longest = 1.1 * (p->D / 128.0) * (double)longest / (kBlock * kMixedWaves);
+    if (t_longest <= 0.8 * std::max(t_rest_us, 8.0)) return 0;
+    return shortest_split(p, S, std::max<int64_t>(kNumCu - n_prefill_wg, kNumCu / 4));
 }
 
 // First token of split i of a decode sequence of kv tokens cut into ns splits: the sequence's pages are
@@ -90,17 +126,6 @@ static int num_splits(int64_t kv, int split, int W) {
     while (n < ns && n < W) n *= 2;
     return n;
 }
-
-// Measured rates the planner balances with (one MI355X): a prefill workgroup needs about kTileUs
-// microseconds per 64-token KV tile at head_dim 128 (half of that at 64), a piece costs about
-// kPieceOverheadTiles tiles on top of its sweep (loading Q, filling the copy pipeline, leaving or combining
-// partial results), the decode branch reads about 5 TB/s when it has the chip to itself and about
-// kDecodeCuGBs GB/s per compute unit when only a few units run it.
-constexpr double kTileUs = 1.8;
-constexpr double kPieceOverheadTiles = 3.0;
-constexpr double kDecodeCuGBs = 40.0;
-constexpr int kMinPieceTiles = 4;   // a levelled piece is never shorter than this
-constexpr int kMinBinTiles = 8;     // and a levelled workgroup never holds less than this
 
 // When a batch has few prefill row blocks (a small chunk, as on a decode-heavy instance), each of
 // them sweeps its whole KV range in one workgroup while most of the chip idles, and that sweep is the
@@ -291,6 +316,20 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
             p->items_per_wg = 1;
             p->waves_per_item = kWideWaves;
         }
+    if (!w.blocks.empty() && n_decode_seqs > 0) {
+        double longest_piece = 0, tiles = 0;
+        for (const PlanPiece &x : w.pieces) {
+            longest_piece = std::max<double>(longest_piece, x.t1 - x.t0);
+            tiles += (x.t1 - x.t0) * (double)Hkv;
+        }
+        const double tile_us = kTileUs * (D / 128.0);
+        const double t_rest = std::max(longest_piece * tile_us, tiles * tile_us / kNumCu + (double)decode_bytes / 5.0e6);
+        if (const int split = choose_wide_split_beside_chunk(p, S, t_rest, (int64_t)n_wg_head * Hkv)) {
+            p->split_tokens = split;
+            p->items_per_wg = 1;
+            p->waves_per_item = kMixedWaves;
+        }
+    }
     const int W = p->items_per_wg;
     w.runs.clear();
     for (int s = 0; s < S; s++) {

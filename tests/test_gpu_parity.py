@@ -410,6 +410,39 @@ def test_decode_forms_match_oracle_and_each_call(H, name):
     check_fused_step(H, b, name)
 
 
+# The same beside prefill chunks: few long decodes are run by whole workgroups of eight waves (drawn from the queue when the
+# row blocks take more than a quarter of the units, workgroups of their own otherwise), balanced ones by single waves.
+MIXED_DECODE_FORMS = {
+    # name: (Hq, Hkv, D, q_len, ctx, dtype, waves per item, queue)
+    "wide_own_workgroups": (32, 8, 128, [64] + [1] * 6, [0, 4000, 1024, 1023, 127, 16, 0], "bf16", 8, 0),
+    "wide_queue": (40, 8, 128, [701, 333, 45] + [1] * 5, [0, 0, 0, 5000, 2000, 900, 60, 3], "fp16", 8, 1),
+    "wide_long_and_merge_g16": (16, 1, 128, [20, 1, 1, 1], [10, 12000, 7000, 5], "bf16", 8, 0),
+    "wide_d64": (8, 8, 64, [150, 1, 1], [3, 8000, 33], "bf16", 8, 0),
+    "waves_balanced": (8, 2, 64, [600] + [1] * 60, [3000] + [500 + i for i in range(60)], "fp16", 1, 0),
+}
+
+
+@pytest.mark.parametrize("name", list(MIXED_DECODE_FORMS))
+def test_decode_forms_beside_a_chunk(H, name):
+    import torch
+    Hq, Hkv, D, q_len, ctx, dtype, waves, queue = MIXED_DECODE_FORMS[name]
+    b = W.make_batch(W.custom_spec(name, Hq, Hkv, D, q_len, ctx, seed=zlib.crc32(name.encode()) % 10007, dtype=dtype))
+    (mx, rel), db = run_and_compare(H, b, name, gather=None)
+    assert (db.plan.info.waves_per_item, db.plan.info.decode_queue) == (waves, queue)
+    assert dtype != "fp16" or (mx <= FP16_MAX_ABS and rel <= FP16_REL_L2), (mx, rel)
+    single = H.to_host(db.out).copy()
+    for _ in range(2):  # the counters of queue and merges are back at zero after every launch
+        db.out.fill_(0)
+        db.attention()
+        torch.cuda.synchronize()
+        assert np.array_equal(H.to_host(db.out), single)
+    db.out.fill_(0)
+    db.attention_partials()
+    db.split_merge()
+    torch.cuda.synchronize()
+    assert np.array_equal(H.to_host(db.out), single), "two-launch form"
+
+
 def test_append_fused_into_attention_half_precision(H):
     Hq, Hkv, D, q_len, ctx = SMALL["decode_long_ragged"]
     check_fused_step(H, W.make_batch(W.custom_spec("fused16", Hq, Hkv, D, q_len, ctx, seed=5, dtype="fp16")), "fp16")
