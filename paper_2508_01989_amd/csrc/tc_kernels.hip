@@ -951,12 +951,13 @@ __device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ it, 
 //   O^T[d][head]    += sum_token V^T[d][token] P^T[token][head]   16x16x16, contraction over the page's
 //                      16 tokens: lane feeds tokens 4g..4g+3
 // Pages resident in registers per wave (NS): one being consumed, the rest in flight.  Two keep the
-// decode-only kernel within 168 VGPRs (three waves per SIMD; a third stage spills there).  In a launch
-// with a prefill chunk the decode workgroups are one per compute unit and share the chip with the chunk, so
-// a few units must carry the whole decode stream: there a wave keeps kMixedDecodeStages - 1 pages in flight.
+// decode-only kernel within 168 VGPRs (three waves per SIMD; a third stage spills there), and serve best beside a
+// prefill chunk as well: what a compute unit streams is bound by its outstanding requests, not by the pages its waves ask
+// for, and more of them in flight only queue up behind each other (four stages against two: 128 tokens at 2048 with 16 decodes
+// 39.3 / 37.6 us, 1024 with 16 78.7 / 76.8, three first chunks with 16 41.7 / 40.3, prefill-heavy 197.9 / 197.8).
 constexpr int kDecodeStages = 2;
-constexpr int kMixedDecodeStages = 4;
-constexpr int kWideStages = 3;  // 2 and 5 measured 4 % and 15-25 % slower on batches of 8 to 96 decodes
+// A split run by a whole workgroup of the decode-only launch: 2 and 5 measured 4 % and 15-25 % slower on 8 to 96 decodes.
+constexpr int kWideStages = 3;
 
 template <int D>
 struct DecodePage {  // K and V of one page, in MFMA A-operand registers
@@ -1421,7 +1422,7 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : kDecode
     A.ws_o = ws; A.ws_ml = ws + (int64_t)sc.n_partials * sc.G * D; A.ws_pieces = A.ws_ml + (int64_t)sc.n_partials * sc.G * 2;
     A.n_prefill = sc.n_prefill; A.n_decode = sc.n_decode; A.Hq = sc.Hq; A.Hkv = sc.Hkv; A.G = sc.G; A.fused = sc.fused; A.queue = sc.queue;
     A.scale_log2 = sc.scale_log2;
-    constexpr int NS = WAVES == kMixedWaves ? kMixedDecodeStages : kDecodeStages;
+    constexpr int NS = kDecodeStages;
     if constexpr (WAVES == kDecodeWaves) {
         const int first_append_wg = (int)gridDim.x - sc.n_front;
         if ((int)blockIdx.x >= first_append_wg) {
