@@ -301,10 +301,14 @@ __device__ __forceinline__ void peer_store4(__amdgpu_buffer_rsrc_t win, uint32_t
 // Run by a whole workgroup of T threads.  What bounds it is the latency of the loads (a partial result comes from
 // another compute unit, past the caches), so as many of them as possible are in flight at once: a thread owns four
 // adjacent elements of a row (16-byte loads, a wave reads 1 KiB contiguous), where the rows do not need all
-// threads the partial results are dealt out to `slices` groups of threads, and a thread requests eight partial results
-// before it adds the first.  The slices meet in LDS (merge_lds_bytes) and are added in order, so the result depends
+// threads the partial results are dealt out to `slices` groups of threads, and a thread requests BATCH partial
+// results before it adds the first.  The slices meet in LDS (merge_lds_bytes) and are added in order, so the result depends
 // on T alone and not on which workgroup runs this or when.
-constexpr int kMergeBatch = 8;
+// Partial results a thread requests at once: what the kernel it runs in has registers for (sixteen in the four-wave kernel of
+// few decodes at head_dim 128: 4 decodes of 16-32 thousand tokens, 16 heads on one KV head 34.6 -> 32.4 us; thirty-two
+// spill; at head_dim 64 the rows leave more slices and sixteen measured 1.5 % slower).  The order of the
+// sums does not depend on it.
+constexpr int kMergeBatch = 8, kWideMergeBatch = 16;
 __host__ __device__ constexpr size_t merge_lds_bytes(int T) { return (size_t)T * 6 * sizeof(float); }
 struct RowSum {  // weighted sum relative to the reference m (log2 domain)
     f32x4 o;
@@ -317,7 +321,7 @@ struct RowSum {  // weighted sum relative to the reference m (log2 domain)
         o = o * a + oi * b;
     }
 };
-template <int D, class E, bool PEER>
+template <int D, class E, bool PEER, int BATCH>
 __device__ __forceinline__ void merge_pair(const float *ws_o, const float *ws_ml, int64_t slot0, int ns, int G, uint16_t *out_rows,
                                            float *lds, int tid, int T) {
     constexpr int VR = D / 4;  // vectors per row
@@ -329,15 +333,15 @@ __device__ __forceinline__ void merge_pair(const float *ws_o, const float *ws_ml
         const int slice = n_vec <= T ? tid / n_vec : 0, v = n_vec <= T ? tid % n_vec : v0 + tid;
         const bool active = slice < slices && v < n_vec;
         RowSum acc = {f32x4{0.f, 0.f, 0.f, 0.f}, -1e30f, 0.f};
-        for (int base = 0; base < ns; base += kMergeBatch * slices) {
+        for (int base = 0; base < ns; base += BATCH * slices) {
             // a window of its own for every batch: a pair's partial results may span more than a buffer offset
             const float *o_base = ws_o + (slot0 + base) * (int64_t)G * D;
             const float *ml_base = ws_ml + (slot0 + base) * (int64_t)G * 2;
-            const __amdgpu_buffer_rsrc_t win = peer_window(o_base, (uint32_t)(kMergeBatch * slices * G * D * sizeof(float)));
-            f32x4 o[kMergeBatch];
-            float2 ml[kMergeBatch];
+            const __amdgpu_buffer_rsrc_t win = peer_window(o_base, (uint32_t)(BATCH * slices * G * D * sizeof(float)));
+            f32x4 o[BATCH];
+            float2 ml[BATCH];
 #pragma unroll
-            for (int u = 0; u < kMergeBatch; u++) {
+            for (int u = 0; u < BATCH; u++) {
                 const int i = u * slices + slice;
                 if (active && base + i < ns) {
                     o[u] = load4<PEER>(win, o_base, (uint32_t)(i * n_vec + v) * 16);
@@ -345,7 +349,7 @@ __device__ __forceinline__ void merge_pair(const float *ws_o, const float *ws_ml
                 }
             }
 #pragma unroll
-            for (int u = 0; u < kMergeBatch; u++)
+            for (int u = 0; u < BATCH; u++)
                 if (active && base + u * slices + slice < ns) acc.add(o[u], ml[u].x, ml[u].y);
         }
         if (slices > 1) {
@@ -1288,7 +1292,7 @@ __device__ void decode_item(const AttnArgs &A, const int32_t *__restrict__ it, f
     // combines all of them.
     const int32_t *mg = A.merge + (int64_t)merge_item * kItemInts;
     if (!workgroup_arrives_last(A.counters + mg[MG_COUNTER] * kCounterStride, mg[MG_NSPLIT], reinterpret_cast<int *>(team_lds), tid)) return;
-    merge_pair<D, E, true>(A.ws_o, A.ws_ml, mg[MG_SLOT0], mg[MG_NSPLIT], G, A.out + ((int64_t)qrow * A.Hq + kvh * G) * D, team_lds, tid,
+    merge_pair<D, E, true, kMergeBatch>(A.ws_o, A.ws_ml, mg[MG_SLOT0], mg[MG_NSPLIT], G, A.out + ((int64_t)qrow * A.Hq + kvh * G) * D, team_lds, tid,
                            wg_waves * 64);
 }
 
@@ -1363,7 +1367,8 @@ __device__ void decode_item_wide(const AttnArgs &A, const int32_t *__restrict__ 
     stores_done();
     const int32_t *mg = A.merge + (int64_t)merge_item * kItemInts;
     if (!workgroup_arrives_last(A.counters + mg[MG_COUNTER] * kCounterStride, mg[MG_NSPLIT], reinterpret_cast<int *>(lds), tid)) return;
-    merge_pair<D, E, true>(A.ws_o, A.ws_ml, mg[MG_SLOT0], mg[MG_NSPLIT], G, A.out + ((int64_t)qrow * A.Hq + kvh * G) * D, lds, tid, R * 64);
+    merge_pair<D, E, true, STORE && D == 128 ? kWideMergeBatch : kMergeBatch>(A.ws_o, A.ws_ml, mg[MG_SLOT0], mg[MG_NSPLIT], G,
+                                                                             A.out + ((int64_t)qrow * A.Hq + kvh * G) * D, lds, tid, R * 64);
 }
 
 #ifdef TC_WG_TRACE
@@ -1523,7 +1528,7 @@ __global__ void __launch_bounds__(512) split_merge_kernel(const int32_t *__restr
     extern __shared__ __align__(16) char lds[];
     const int32_t *it = items + (int64_t)blockIdx.x * kItemInts;
     const int kvh = it[MG_KVH], qrow = it[MG_QROW], ns = it[MG_NSPLIT], slot0 = it[MG_SLOT0];
-    merge_pair<D, E, false>(ws_o, ws_ml, slot0, ns, G, out + ((int64_t)qrow * Hq + kvh * G) * D, reinterpret_cast<float *>(lds),
+    merge_pair<D, E, false, kMergeBatch>(ws_o, ws_ml, slot0, ns, G, out + ((int64_t)qrow * Hq + kvh * G) * D, reinterpret_cast<float *>(lds),
                             (int)threadIdx.x, (int)blockDim.x);
 }
 
