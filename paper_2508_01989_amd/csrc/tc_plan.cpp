@@ -88,12 +88,17 @@ static int choose_wide_split(const tc_plan *p, int S, int64_t decode_tokens) {
 // The same beside a prefill chunk, where a decode workgroup has eight waves and a compute unit to itself.  Eight
 // single-wave splits per sequence (up to 8192 tokens; none to combine across workgroups) stream best as long as the longest
 // of them is not what the launch waits for: a wave needs about 1.1 us per page then, so a sequence of 4000 tokens takes
-// 35 us however little else there is to do.  When that is more than 0.8 of what the rest of the batch needs (t_rest_us: the
-// longest sweep, or the sweeps spread over the chip and the decode bytes at 5 TB/s), the splits are run by whole workgroups, as short as the units that the chunk leaves free can take at once.
-// Measured (us per step, single-wave splits / whole workgroups): three first chunks of 1079 tokens with 16 decodes (lognormal
-// 1024) 64.9 / 40.5; a first chunk of 300 with 4 decodes 34.8 / 17.6; 128 at 2048 with 16 decodes of 512-4096 tokens
-// 50.8 / 39.3, with 64 of them 110.5 / 124.4; 512 at 2048 with 16 of them 55.9 / 57.5, 1024 at 2048 76.3 / 78.0.
-static int choose_wide_split_beside_chunk(const tc_plan *p, int S, double t_rest_us, int64_t n_prefill_wg) {
+// 35 us however little else there is to do.  When that is more than half of what the rest of the batch needs (t_rest_us: the
+// longest sweep, or the sweeps spread over the chip and the decode bytes at 5 TB/s), the splits are run by whole
+// workgroups, as short as the units that the chunk leaves free can take at once.  Where the pieces of a cut chunk hold most units
+// and there is no queue, so that decode workgroups beyond the free units wait for a piece to end, the line is at 0.8.
+// Measured (us per step, single-wave splits / whole workgroups; the share is what the longest sequence takes of the rest):
+//   three first chunks, 1079 tokens, 16 decodes (lognormal 1024)     64.9 / 40.5    first chunk of 300, 4 decodes          34.8 / 17.6
+//   2000 at 0, 32 decodes (lognormal 1500; share 0.7)                89.9 / 75.5    256 at 500, 64 of them (share 0.6)     97.1 / 81.5
+//   128 at 1000, 32 decodes of 512-4096, 40/8 heads, 16 layers (0.6)  971 / 922     128 at 2048, 40 of them (share 0.4)    73.6 / 78.2
+//   256 at 500, 128 decodes (lognormal 1500; share 0.35)            145.7 / 156.5   128 at 2048, 64 of 512-4096 (0.3)     109.6 / 121.4
+//   512 at 2048 in 192 pieces, 16 of 512-4096 (share 0.75)           55.6 / 56.8
+static int choose_wide_split_beside_chunk(const tc_plan *p, int S, double t_rest_us, int64_t n_prefill_wg, bool queue) {
     int64_t longest = 0;  // decode sequences that one workgroup covers
     for (int s = 0; s < S; s++)
         if (p->q_start[s + 1] - p->q_start[s] == 1) {
@@ -101,7 +106,8 @@ static int choose_wide_split_beside_chunk(const tc_plan *p, int S, double t_rest
             if (kv <= (int64_t)kMixedWaves * kMaxSplitPages * kBlock) longest = std::max(longest, kv);
         }
     const double t_longest = 1.1 * (p->D / 128.0) * (double)longest / (kBlock * kMixedWaves);
-    if (t_longest <= 0.8 * std::max(t_rest_us, 8.0)) return 0;
+    const double share = !queue && n_prefill_wg > kNumCu / 2 ? 0.8 : 0.5;
+    if (t_longest <= share * std::max(t_rest_us, 8.0)) return 0;
     return shortest_split(p, S, std::max<int64_t>(kNumCu - n_prefill_wg, kNumCu / 4));
 }
 
@@ -324,7 +330,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
         }
         const double tile_us = kTileUs * (D / 128.0);
         const double t_rest = std::max(longest_piece * tile_us, tiles * tile_us / kNumCu + (double)decode_bytes / 5.0e6);
-        if (const int split = choose_wide_split_beside_chunk(p, S, t_rest, (int64_t)n_wg_head * Hkv)) {
+        if (const int split = choose_wide_split_beside_chunk(p, S, t_rest, (int64_t)n_wg_head * Hkv, queue)) {
             p->split_tokens = split;
             p->items_per_wg = 1;
             p->waves_per_item = kMixedWaves;
