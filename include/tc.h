@@ -93,7 +93,7 @@ typedef struct {
     int32_t num_partials;               /* partial results of decode teams held in the workspace */
     int32_t split_tokens;               /* KV tokens a decode split holds at most, except that a sequence */
                                         /* one workgroup's waves can cover with splits of up to 1024 is cut into that many */
-    int32_t rows_per_prefill_item;      /* (position, head) rows per prefill workgroup       */
+    int32_t rows_per_prefill_item;      /* (position, head) rows per prefill workgroup: 256, or 128 for a small chunk */
     int32_t grid_blocks, block_threads; /* workgroups of the attention kernel; 64 threads per wave slot of a  */
                                         /* workgroup.  A workgroup has block_threads * waves_per_item threads  */
     int64_t total_pages;                /* table entries copied                              */

@@ -20,7 +20,7 @@ constexpr int kMixedWaves = 8;
 constexpr int kDecodeWaves = 4;
 constexpr int kDecodeWgPerCu = 3;
 constexpr int kWideWaves = 4;       // waves that share one decode item in a batch of few decodes (two such workgroups per compute unit)
-constexpr int kPrefillRows = 32 * kMixedWaves;  // (position, head) rows per prefill workgroup, 32 per wave
+constexpr int kPrefillRows = 32 * kMixedWaves;  // (position, head) rows a prefill workgroup has room for, 32 per wave
 constexpr int kItemInts = 8;        // int32 fields per work item
 constexpr int kAppendInts = 4;      // int32 fields per append segment: first packed row, tokens, first token index, pool block
 constexpr int kCounterStride = 32;  // int32 between arrival counters: one per 128-byte line (see workgroup_arrives_last)
@@ -103,6 +103,7 @@ struct tc_plan {
     tc::PlanScratch work;
 
     int items_per_wg = tc::kDecodeWaves;  // decode items a workgroup runs side by side
+    int rows_per_item = tc::kPrefillRows;  // (position, head) rows of a prefill item: 256, or 128 for a small chunk
     int waves_per_item = 1;               // waves that share one of them: kWideWaves in a batch of few decodes, else 1
     int launch_threads() const { return 64 * items_per_wg * waves_per_item; }
     int grid_blocks() const { return n_prefill_wg + n_decode_wg; }

@@ -803,17 +803,6 @@ __device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ it, 
     x8 vf[2][MT];  // V^T fragments of the half whose P V product comes next
     x8 pb[2];      // probabilities of that half (B operands, one per page)
     f32x16 sc, sn;
-    W::load_k((lds_cptr)(lds_k + k_lane_off), 0, kf);
-    W::qk(kf, qreg, sc);
-    W::load_k((lds_cptr)(lds_k + k_lane_off), 1, kf);
-    // the first phase has no earlier half to accumulate: give its P V product zero probabilities
-    W::load_v((lds_cptr)(lds_v + v_lane_off), 0, vf);
-#pragma unroll
-    for (int b = 0; b < 2; b++)
-#pragma unroll
-        for (int e = 0; e < 8; e++) pb[b][e] = (el)0.f;
-    if (t_begin * C::kTileTokens + 31 > wave_pmin) W::causal_mask(sc, t_begin * C::kTileTokens, hh, p_abs);
-    m_run = next_reference_max(m_run, W::row_max(sc) * c_log2);  // the first half-tile's true maxima
     float psum = 0.f;  // this lane's sum of the probabilities just computed
 
     // After the probabilities `pb` of a half-tile with scores `s_pb`, and after the product of the half
@@ -909,7 +898,21 @@ __device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ it, 
         }
         s0 = s1;
     };
-    {
+    if (!copier && wave * 32 >= n_rows) {
+        // No rows and no copies to make (an item of at most 128 rows): the SIMD is left to its other wave.
+        for (int j = 0; j < n_sweep; j++) __syncthreads();
+    } else {
+        W::load_k((lds_cptr)(lds_k + k_lane_off), 0, kf);
+        W::qk(kf, qreg, sc);
+        W::load_k((lds_cptr)(lds_k + k_lane_off), 1, kf);
+        // the first phase has no earlier half to accumulate: give its P V product zero probabilities
+        W::load_v((lds_cptr)(lds_v + v_lane_off), 0, vf);
+    #pragma unroll
+        for (int b = 0; b < 2; b++)
+    #pragma unroll
+            for (int e = 0; e < 8; e++) pb[b][e] = (el)0.f;
+        if (t_begin * C::kTileTokens + 31 > wave_pmin) W::causal_mask(sc, t_begin * C::kTileTokens, hh, p_abs);
+        m_run = next_reference_max(m_run, W::row_max(sc) * c_log2);  // the first half-tile's true maxima
         const std::true_type yes;
         const std::false_type no;
         // steps 0 .. n_plain - 1 prepare tiles that lie wholly at or before every row's position
@@ -919,9 +922,8 @@ __device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ it, 
         for (; j < n_plain; j++) step(j, no, yes);
         for (; j + 1 < n_sweep; j++) step(j, yes, yes);
         step(j, yes, no);
+        W::pv(vf, pb, o);  // the product of the last half
     }
-    // the product of the last half
-    W::pv(vf, pb, o);
 
     float l = half_swap_sum(l_run);
     if (p_slot >= 0) {

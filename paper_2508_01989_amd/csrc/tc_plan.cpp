@@ -139,13 +139,13 @@ static int num_splits(int64_t kv, int split, int W) {
 // separate workgroups; the last of them to finish combines their partial results.  k is the smallest count
 // that brings the sweep down to the time the decode branch needs anyway (both estimated from measured
 // rates), at most 8, at least 8 tiles per piece, and never more pieces than workgroup slots.
-static void choose_prefill_cuts(std::vector<PlanRowBlock> &blocks, int Hkv, int64_t decode_bytes) {
+static void choose_prefill_cuts(std::vector<PlanRowBlock> &blocks, int Hkv, int64_t decode_bytes, double tile_us) {
     const int64_t slots = kNumCu;  // one prefill workgroup per compute unit
     const int64_t items = (int64_t)blocks.size() * Hkv;
     const int k_cap = (int)std::min<int64_t>(8, slots / items);
     const double t_decode_us = std::max(16.0, (double)decode_bytes / 5.0e6);
     for (PlanRowBlock &b : blocks) {
-        const int want = (int)std::ceil(b.n_tiles * 2.0 / t_decode_us);
+        const int want = (int)std::ceil(b.n_tiles * tile_us / t_decode_us);
         b.k = std::max(1, std::min({want, k_cap, b.n_tiles / 8}));
     }
 }
@@ -186,6 +186,29 @@ static void level_prefill(std::vector<PlanRowBlock> &blocks, std::vector<PlanPie
             if (bin < bins - 1 && fill + o + kMinPieceTiles > target) { bin++; open_bin(blocks.size() - i - (t == b.n_tiles ? 1 : 0)); }
         }
     }
+}
+
+// Rows of a prefill item: 256, or 128 when the chunk is small.  An item of 128 rows keeps one wave per SIMD busy, and such a
+// wave sweeps a tile in about 0.55 of the time it takes beside a second one, so twice as many items finish in a little more than
+// half the time; spread over a full chip they would cost 10 % more.  So halves where they still fit the compute units: for
+// short sweeps (first chunks; at most 16 tiles, where cutting the KV range would cost more than it returns), and for the
+// few items whose KV range is cut (half the pieces per item, and so half the partial results to combine for the
+// same number of workgroups).  Not beside a decode branch that needs longer than the longest sweep: it needs the units.
+// Measured (us per step, 256 rows / 128; 32/8 heads, head_dim 128): 200 first tokens 15.0 / 12.1, 500 21.3 / 17.9, 1000
+// 36.8 / 27.6; 64 at 3000 34.0 / 30.0, 256 at 4000 43.1 / 38.7; three first chunks of 450 tokens with 4 decodes 21.3 / 18.5;
+// 1000 first tokens with 32 decodes (lognormal 1500) 53.6 / 58.4.
+static int choose_rows_per_item(const tc_plan *p, int S, int64_t decode_bytes) {
+    int64_t items = 0, longest = 0;
+    for (int s = 0; s < S; s++) {
+        const int q = p->q_start[s + 1] - p->q_start[s];
+        if (q <= 1) continue;
+        items += (int64_t)((q - 1) / (kPrefillRows / p->G) + 1) * p->Hkv;
+        longest = std::max<int64_t>(longest, (int64_t)p->ctx_len[s] + q);
+    }
+    const int64_t tiles = (longest + kPrefillTileTokens - 1) / kPrefillTileTokens;
+    if ((double)decode_bytes / 5.0e6 > tiles * kTileUs * (p->D / 128.0)) return kPrefillRows;
+    const bool half = (tiles <= 16 && items * 2 <= kNumCu) || items * 2 * 4 <= kNumCu;
+    return half ? kPrefillRows / 2 : kPrefillRows;
 }
 
 tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
@@ -246,7 +269,9 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     PlanScratch &w = p->work;
 
     // ---- prefill row blocks, heaviest (latest positions, longest KV range) first, and their pieces
-    const int pos_per_item = kPrefillRows / G;
+    const int64_t decode_bytes = decode_tokens * Hkv * D * 4;
+    p->rows_per_item = choose_rows_per_item(p, S, decode_bytes);
+    const int pos_per_item = p->rows_per_item / G;
     w.blocks.clear();
     for (int s = 0; s < S; s++) {
         const int q = p->q_start[s + 1] - p->q_start[s];
@@ -265,12 +290,11 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     //   more:                     one workgroup per item; the hardware hands them out heaviest first
     w.pieces.clear();
     const int64_t n_items = (int64_t)w.blocks.size() * Hkv, slots = kNumCu;
-    const int64_t decode_bytes = decode_tokens * Hkv * D * 4;
     int n_wg_per_head = 0;  // > 0: levelled; the prefill workgroups are numbered bin * Hkv + KV head
     // `queue`: the launch has no more workgroups than the chip has compute units and the decode items are drawn from a
     // queue, a workgroup's worth at a time, by whichever workgroup is free (see the kernel)
     bool queue = false;
-    if (n_items > 0 && n_items * 4 <= slots) choose_prefill_cuts(w.blocks, Hkv, decode_bytes);
+    if (n_items > 0 && n_items * 4 <= slots) choose_prefill_cuts(w.blocks, Hkv, decode_bytes, p->rows_per_item == kPrefillRows ? 2.0 : 1.1);
     if (n_items * 4 > slots && n_items <= 4 * slots) {
         queue = decode_tokens > 0 && n_items <= slots;
         // Row blocks that fill the chip (more than three quarters of the units) run uncut, one per workgroup: the
@@ -284,7 +308,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
         const double tile_us = kTileUs * (D / 128.0);
         const double t_sweep = w.blocks[0].n_tiles * tile_us;  // the heaviest block's
         const double t_decode_alone = decode_tokens ? std::max(16.0, (double)decode_bytes / 5.0e6) : 0.0;
-        if (n_items * 4 <= 3 * slots && t_decode_alone < 0.25 * t_sweep) {
+        if (n_items * 4 <= 3 * slots && t_decode_alone < 0.25 * t_sweep && p->rows_per_item == kPrefillRows) {
             const double t_prefill = tiles * Hkv * tile_us, t_decode = (double)decode_bytes / (kDecodeCuGBs * 1e3);
             const int cu_decode = decode_tokens ? std::max(1, (int)std::lround(slots * t_decode / (t_decode + t_prefill))) : 0;
             const int64_t by_units = std::max<int64_t>(1, (slots - std::min<int64_t>(cu_decode, slots / 2)) / Hkv);
@@ -597,7 +621,7 @@ tc_status tc_plan_get_info(const tc_plan *p, tc_plan_info *info) {
     info->num_prefill_seqs = p->n_prefill_seqs; info->num_decode_seqs = p->n_decode_seqs;
     info->num_prefill_items = p->n_prefill; info->num_decode_items = p->n_decode;
     info->num_merge_items = p->n_merge; info->num_partials = p->n_partials; info->num_piece_partials = p->n_piece_partials;
-    info->split_tokens = p->split_tokens; info->rows_per_prefill_item = tc::kPrefillRows;
+    info->split_tokens = p->split_tokens; info->rows_per_prefill_item = p->rows_per_item;
     info->grid_blocks = p->grid_blocks(); info->block_threads = p->items_per_wg * 64;
     info->waves_per_item = p->waves_per_item;
     info->total_pages = p->total_pages;

@@ -410,6 +410,41 @@ def test_decode_forms_match_oracle_and_each_call(H, name):
     check_fused_step(H, b, name)
 
 
+# Small chunks run items of 128 rows (four of a workgroup's eight waves), larger ones of 256: edges of an item's positions
+# (32, 25 and 8 per item for 4, 5 and 16 query heads per KV head), sweeps of one tile and more, items whose KV range is cut,
+# last items whose waves are partly or wholly without rows.
+ITEM_ROWS = {
+    # name: (Hq, Hkv, D, q_len, ctx, dtype, rows per item)
+    "half_position_edges_g4": (8, 2, 128, [31, 32, 33, 64, 65], [0, 1, 63, 64, 100], "bf16", 128),
+    "half_position_edges_g5": (10, 2, 128, [24, 25, 26, 51, 1], [0, 15, 16, 300, 700], "fp16", 128),
+    "half_position_edges_g16": (16, 1, 64, [7, 8, 9, 17], [0, 40, 64, 500], "bf16", 128),
+    "half_g1": (4, 4, 128, [127, 128, 129, 2], [0, 3, 200, 60], "bf16", 128),
+    "half_most_items": (32, 8, 128, [500, 24], [524, 0], "bf16", 128),
+    "half_cut": (32, 8, 128, [64], [3000], "bf16", 128),
+    "half_cut_ragged_d64": (8, 8, 64, [100, 1], [1500, 900], "fp16", 128),
+    "whole_cut": (8, 2, 128, [1300], [3000], "bf16", 256),
+    "whole_heavy_decodes": (32, 8, 128, [64] + [1] * 30, [10] + [1500] * 30, "bf16", 256),
+}
+
+
+@pytest.mark.parametrize("name", list(ITEM_ROWS))
+def test_rows_per_prefill_item(H, name):
+    import torch
+    Hq, Hkv, D, q_len, ctx, dtype, rows = ITEM_ROWS[name]
+    b = W.make_batch(W.custom_spec(name, Hq, Hkv, D, q_len, ctx, seed=zlib.crc32(name.encode()) % 10007, dtype=dtype))
+    (mx, rel), db = run_and_compare(H, b, name, gather=None)
+    assert db.plan.info.rows_per_prefill_item == rows
+    assert (db.plan.info.num_prefill_pieces > db.plan.info.num_prefill_items) == ("cut" in name)
+    assert dtype != "fp16" or (mx <= FP16_MAX_ABS and rel <= FP16_REL_L2), (mx, rel)
+    single = H.to_host(db.out).copy()
+    db.out.fill_(0)
+    db.workspace.fill_(0xFF)
+    db.attention_partials()
+    db.split_merge()
+    torch.cuda.synchronize()
+    assert np.array_equal(H.to_host(db.out), single), "two-launch form"
+
+
 # The same beside prefill chunks: few long decodes are run by whole workgroups of eight waves (drawn from the queue when the
 # row blocks take more than a quarter of the units, workgroups of their own otherwise), balanced ones by single waves.
 MIXED_DECODE_FORMS = {
