@@ -12,8 +12,9 @@
 //                                        that share a workgroup are combined in LDS),
 //                                        MFMA 16x16x32 and 16x16x16
 //       Two shapes: 8 waves per workgroup, one workgroup per compute unit, when the batch has a prefill
-//       chunk; 4 waves, three workgroups per compute unit, for a batch of decodes only.
-//       Instantiated for bf16 and IEEE half.
+//       chunk (with a form that runs a decode split by a whole workgroup); 4 waves, three workgroups per
+//       compute unit, for a batch of decodes only.  Instantiated for bf16 and IEEE half.
+//   wide_decode_kernel the same for a batch of few decodes: a split is run by a workgroup of four waves
 //   split_merge_kernel combine the partial results of split decode sequences and of cut prefill row blocks
 //
 // Both attention branches compute S^T = K Q^T and O^T = V^T P^T so that the
