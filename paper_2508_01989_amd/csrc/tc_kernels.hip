@@ -1685,14 +1685,17 @@ int launch_kv_migrate(const tc_plan *p, bool import, int page0, int n_pages, int
 
 // More than 64 KiB of dynamic LDS needs an opt-in per kernel function and per device; remembered per
 // instantiation and device (setting it twice is harmless, so racing first calls need no lock).
-template <int D, class E, bool WIDE>
+// Both forms of the mixed kernel at once, so that a caller who has run one batch of a shape may capture any other.
+template <int D, class E>
 static int allow_prefill_lds(int device) {
     static std::atomic<bool> done[kMaxDevices];
     const bool known = device >= 0 && device < kMaxDevices;
     if (known && done[device].load(std::memory_order_acquire)) return 0;
-    hipError_t e = hipFuncSetAttribute((const void *)mixed_attention_kernel<D, E, kMixedWaves, WIDE>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, PrefillCfg<D>::kLdsBytes);
-    if (e != hipSuccess) return (int)e;
+    const void *const forms[] = {(const void *)mixed_attention_kernel<D, E, kMixedWaves, false>, (const void *)mixed_attention_kernel<D, E, kMixedWaves, true>};
+    for (const void *f : forms) {
+        hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, PrefillCfg<D>::kLdsBytes);
+        if (e != hipSuccess) return (int)e;
+    }
     if (known) done[device].store(true, std::memory_order_release);
     return 0;
 }
@@ -1714,15 +1717,15 @@ static int launch_attention_d(const tc_plan *p, const AttnArgs &A, int launches,
     if (grid > 0 && p->n_pieces > 0) {
         const int lds = PrefillCfg<D>::kLdsBytes;  // the decode workgroups of the launch need less, for any G
         static_assert(decode_lds_bytes(kMixedWaves, 16, D) <= (size_t)PrefillCfg<D>::kLdsBytes, "team buffers must fit the prefill tiles' LDS");
+        if (int err = allow_prefill_lds<D, E>(p->device)) return err;
         auto launch = [&](auto wide) {
             constexpr bool WIDE = decltype(wide)::value;
-            if (int err = allow_prefill_lds<D, E, WIDE>(p->device)) return err;
             mixed_attention_kernel<D, E, kMixedWaves, WIDE><<<grid, kMixedWaves * 64, lds, st>>>(
                 A.k_pool, A.v_pool, A.q, A.k_new, A.v_new, A.out, A.pages, A.prefill, A.pieces, A.wg_first, A.decode, A.merge, append,
                 A.counters, A.ws_o, sc);
-            return 0;
         };
-        if (int err = p->waves_per_item > 1 ? launch(std::true_type()) : launch(std::false_type())) return err;
+        if (p->waves_per_item > 1) launch(std::true_type());
+        else launch(std::false_type());
     } else if (grid > 0 && p->waves_per_item > 1) {
         static_assert(decode_lds_bytes(kWideWaves, 16, D) <= 65536, "more than 64 KiB of dynamic LDS needs an opt-in");
         wide_decode_kernel<D, E><<<grid, kWideWaves * 64, decode_lds_bytes(kWideWaves, p->G, D), st>>>(A.k_pool, A.v_pool, A.q, A.k_new, A.v_new, A.out, A.pages, A.decode, A.merge,

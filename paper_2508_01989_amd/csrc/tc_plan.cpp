@@ -218,6 +218,9 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     p->n_prefill_seqs = p->n_decode_seqs = 0;
     p->n_prefill = p->n_decode = p->n_merge = p->n_partials = p->n_piece_partials = p->n_merge_prefill = p->n_pieces = p->n_prefill_wg = p->n_counters = p->n_append = p->n_append_prefill = p->n_decode_wg = 0;
     p->queue_counter = -1;
+    p->items_per_wg = kDecodeWaves;
+    p->waves_per_item = 1;
+    p->rows_per_item = kPrefillRows;
     p->total_pages = 0;
     p->host_n = 0;
     const int Hq = pool->num_q_heads, Hkv = pool->num_kv_heads, D = pool->head_dim;
@@ -339,7 +342,6 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     // Wave slots left free hold padding items (no tokens).
     p->split_tokens = choose_split(decode_tokens * Hkv);
     p->items_per_wg = w.blocks.empty() ? kDecodeWaves : kMixedWaves;
-    p->waves_per_item = 1;
     if (w.blocks.empty() && n_decode_seqs > 0)
         if (const int split = choose_wide_split(p, S, decode_tokens)) {
             p->split_tokens = split;
