@@ -98,6 +98,8 @@ static int choose_wide_split(const tc_plan *p, int S, int64_t decode_tokens) {
 //   128 at 1000, 32 decodes of 512-4096, 40/8 heads, 16 layers (0.6)  971 / 922     128 at 2048, 40 of them (share 0.4)    73.6 / 78.2
 //   256 at 500, 128 decodes (lognormal 1500; share 0.35)            145.7 / 156.5   128 at 2048, 64 of 512-4096 (0.3)     109.6 / 121.4
 //   512 at 2048 in 192 pieces, 16 of 512-4096 (share 0.75)           55.6 / 56.8
+// At head_dim 64 a split is half the bytes for the same start and combination, and the line is at 0.65: 128 at 1000 with 32
+// decodes of 512-4096 tokens (share 0.55) 38.0 / 40.2, 256 at 500 with 64 of lognormal 1500 (0.8) 50.6 / 46.4.
 static int choose_wide_split_beside_chunk(const tc_plan *p, int S, double t_rest_us, int64_t n_prefill_wg, bool queue) {
     int64_t longest = 0;  // decode sequences that one workgroup covers
     for (int s = 0; s < S; s++)
@@ -106,7 +108,7 @@ static int choose_wide_split_beside_chunk(const tc_plan *p, int S, double t_rest
             if (kv <= (int64_t)kMixedWaves * kMaxSplitPages * kBlock) longest = std::max(longest, kv);
         }
     const double t_longest = 1.1 * (p->D / 128.0) * (double)longest / (kBlock * kMixedWaves);
-    const double share = !queue && n_prefill_wg > kNumCu / 2 ? 0.8 : 0.5;
+    const double share = !queue && n_prefill_wg > kNumCu / 2 ? 0.8 : p->D == 64 ? 0.65 : 0.5;
     if (t_longest <= share * std::max(t_rest_us, 8.0)) return 0;
     return shortest_split(p, S, std::max<int64_t>(kNumCu - n_prefill_wg, kNumCu / 4));
 }

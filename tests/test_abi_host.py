@@ -357,3 +357,24 @@ def test_plan_update_gives_the_work_lists_of_fresh_plans(tc):
         reused.update(pool, np.array([0, 0], np.int32), np.zeros(1, np.int32), np.zeros((1, 1), np.int32))
     assert e.value.status == tc.TC_ERR_SPAN
     assert reused.info.num_seqs == 0 and reused.info.grid_blocks == 0 and reused.workspace_bytes == 0
+
+
+@pytest.mark.parametrize("name,Hq,Hkv,D,q_len,ctx,waves,rows", [
+    ("few decodes: a split per workgroup", 32, 8, 128, [1] * 8, [900, 64, 3000, 1023, 1024, 1025, 7, 0], 4, 256),
+    ("one decode over 200k tokens", 8, 2, 128, [1], [200000], 4, 256),
+    ("even decodes under 4096 tokens: a split per wave", 8, 2, 64, [1] * 200, [1400 + i for i in range(200)], 1, 256),
+    ("many decodes: a split per wave", 32, 8, 128, [1] * 120, [1000] * 120, 1, 256),
+    ("few long decodes beside a first chunk", 40, 8, 128, [300] + [1] * 4, [0, 6000, 2000, 12000, 30], 8, 256),  # 16 us of K/V, 9 of sweep
+    ("one long decode beside a first chunk", 40, 8, 128, [300, 1, 1], [0, 3000, 30], 8, 128),
+    ("few long decodes beside a chunk that fills the chip", 16, 4, 64, [4000] + [1] * 3, [0, 8000, 7000, 100], 1, 256),
+    ("short decodes beside a first chunk", 8, 8, 64, [64] + [1] * 4, [0, 36, 63, 99, 127], 1, 128),
+    ("small chunk over a long context: cut", 16, 1, 128, [20], [30000], 1, 128),
+    ("first chunk beside a heavy decode branch", 32, 8, 128, [64] + [1] * 40, [0] + [1500] * 40, 1, 256),
+])
+def test_work_lists_of_the_launch_forms(tc, name, Hq, Hkv, D, q_len, ctx, waves, rows):
+    """Every rule that chooses a launch form: the work list still covers the batch exactly, and the form is the one expected."""
+    sp = W.custom_spec(name, Hq, Hkv, D, q_len, ctx)
+    table, mb, nb = W.make_tables(sp, np.random.default_rng(6))
+    info = check_work_list(tc, sp, table, nb)
+    assert (info.waves_per_item, info.rows_per_prefill_item) == (waves, rows)
+    assert info.block_threads == 64 * (8 if info.num_prefill_items else 4) // (waves if waves > 1 else 1)
