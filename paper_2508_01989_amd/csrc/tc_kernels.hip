@@ -304,12 +304,14 @@ __device__ __forceinline__ void peer_store4(__amdgpu_buffer_rsrc_t win, uint32_t
 // adjacent elements of a row (16-byte loads, a wave reads 1 KiB contiguous), where the rows do not need all
 // threads the partial results are dealt out to `slices` groups of threads, and a thread requests BATCH partial
 // results before it adds the first.  The slices meet in LDS (merge_lds_bytes) and are added in order, so the result depends
-// on T alone and not on which workgroup runs this or when.
+// on T alone and not on which workgroup runs this or when.  The slices are added one after the other, about 60 ns each, so a slice
+// gets eight partial results, one request, before there is another slice: with all slices that T has room for (32 of them for
+// one query head at head_dim 64), 64 tokens beside a decode of 12000 took 15.7 us and take 14.5, beside 30000 and three more 48.6 / 47.3.
 // Partial results a thread requests at once: what the kernel it runs in has registers for (sixteen in the four-wave kernel of
 // few decodes at head_dim 128: 4 decodes of 16-32 thousand tokens, 16 heads on one KV head 34.6 -> 32.4 us; thirty-two
 // spill; at head_dim 64 the rows leave more slices and sixteen measured 1.5 % slower).  The order of the
 // sums does not depend on it.
-constexpr int kMergeBatch = 8, kWideMergeBatch = 16;
+constexpr int kMergeBatch = 8, kWideMergeBatch = 16, kMergePerSlice = 8;
 __host__ __device__ constexpr size_t merge_lds_bytes(int T) { return (size_t)T * 6 * sizeof(float); }
 struct RowSum {  // weighted sum relative to the reference m (log2 domain)
     f32x4 o;
@@ -327,7 +329,7 @@ __device__ __forceinline__ void merge_pair(const float *ws_o, const float *ws_ml
                                            float *lds, int tid, int T) {
     constexpr int VR = D / 4;  // vectors per row
     const int n_vec = G * VR;
-    const int slices = max(1, T / n_vec);
+    const int slices = max(1, min(T / n_vec, (ns + kMergePerSlice - 1) / kMergePerSlice));
     f32x4 *const lds_o = reinterpret_cast<f32x4 *>(lds);
     float *const lds_ml = lds + 4 * T;
     for (int v0 = 0; v0 < n_vec; v0 += T) {  // one pass unless G * D / 4 > T

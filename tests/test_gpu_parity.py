@@ -478,6 +478,34 @@ def test_decode_forms_beside_a_chunk(H, name):
     assert np.array_equal(H.to_host(db.out), single), "two-launch form"
 
 
+# Combinations of one to many partial results: a slice of threads takes eight of them before there is a second slice.  One and
+# several slices, the last of them with one partial result, and more partial results than all slices have room for at once.
+MERGE_SLICES = {
+    # name: (Hq, Hkv, D, q_len, ctx, dtype, partial results of the split pairs)
+    "alone_g1_d64": (1, 1, 64, [1] * 5, [1100, 2040, 2060, 3060, 17500], "bf16", [9, 16, 17, 24, 137]),
+    "alone_g5": (5, 1, 128, [1] * 4, [1100, 2040, 2060, 9000], "fp16", [9, 16, 17, 71]),
+    "alone_g16": (16, 1, 128, [1] * 3, [1100, 2060, 3060], "bf16", [9, 17, 24]),
+    "beside_chunk_g1_d64": (1, 1, 64, [16, 1, 1, 1], [5, 8500, 17000, 70], "bf16", [9, 17]),
+    "beside_chunk_g4": (4, 1, 128, [16, 1, 1], [5, 9000, 40000], "fp16", [9, 40]),
+}
+
+
+@pytest.mark.parametrize("name", list(MERGE_SLICES))
+def test_merge_slices(H, name):
+    import torch
+    Hq, Hkv, D, q_len, ctx, dtype, partials = MERGE_SLICES[name]
+    b = W.make_batch(W.custom_spec(name, Hq, Hkv, D, q_len, ctx, seed=zlib.crc32(name.encode()) % 10007, dtype=dtype))
+    (mx, rel), db = run_and_compare(H, b, name, gather=None)
+    assert sorted(db.plan.items(2)[:, 4].tolist()) == partials
+    assert dtype != "fp16" or (mx <= FP16_MAX_ABS and rel <= FP16_REL_L2), (mx, rel)
+    single = H.to_host(db.out).copy()
+    db.out.fill_(0)
+    db.attention_partials()
+    db.split_merge()
+    torch.cuda.synchronize()
+    assert np.array_equal(H.to_host(db.out), single), "two-launch form"
+
+
 def test_append_fused_into_attention_half_precision(H):
     Hq, Hkv, D, q_len, ctx = SMALL["decode_long_ragged"]
     check_fused_step(H, W.make_batch(W.custom_spec("fused16", Hq, Hkv, D, q_len, ctx, seed=5, dtype="fp16")), "fp16")
