@@ -141,15 +141,17 @@ static int num_splits(int64_t kv, int split, int W) {
 // separate workgroups; the last of them to finish combines their partial results.  k is the smallest count
 // that brings the sweep down to the time the decode branch needs anyway (both estimated from measured
 // rates), at most 8, at least 8 tiles per piece, and never more pieces than workgroup slots.
-static void choose_prefill_cuts(std::vector<PlanRowBlock> &blocks, int Hkv, int64_t decode_bytes, double tile_us) {
-    const int64_t slots = kNumCu;  // one prefill workgroup per compute unit
-    const int64_t items = (int64_t)blocks.size() * Hkv;
-    const int k_cap = (int)std::min<int64_t>(8, slots / items);
+// Tile times the cuts are chosen with: 256 rows, 128 rows.
+constexpr double kCutTileUs = 2.0, kCutHalfTileUs = 1.1;
+static int prefill_cuts(int n_tiles, int64_t items, int64_t decode_bytes, double tile_us) {
+    const int k_cap = (int)std::min<int64_t>(8, kNumCu / items);  // one prefill workgroup per compute unit
     const double t_decode_us = std::max(16.0, (double)decode_bytes / 5.0e6);
-    for (PlanRowBlock &b : blocks) {
-        const int want = (int)std::ceil(b.n_tiles * tile_us / t_decode_us);
-        b.k = std::max(1, std::min({want, k_cap, b.n_tiles / 8}));
-    }
+    const int want = (int)std::ceil(n_tiles * tile_us / t_decode_us);
+    return std::max(1, std::min({want, k_cap, n_tiles / 8}));
+}
+static void choose_prefill_cuts(std::vector<PlanRowBlock> &blocks, int Hkv, int64_t decode_bytes, double tile_us) {
+    const int64_t items = (int64_t)blocks.size() * Hkv;
+    for (PlanRowBlock &b : blocks) b.k = prefill_cuts(b.n_tiles, items, decode_bytes, tile_us);
 }
 
 // Pieces of a batch whose row blocks would leave a good part of the chip empty (between a quarter and three
@@ -191,26 +193,64 @@ static void level_prefill(std::vector<PlanRowBlock> &blocks, std::vector<PlanPie
 }
 
 // Rows of a prefill item: 256, or 128 when the chunk is small.  An item of 128 rows keeps one wave per SIMD busy, and such a
-// wave sweeps a tile in about 0.55 of the time it takes beside a second one, so twice as many items finish in a little more than
-// half the time; spread over a full chip they would cost 10 % more.  So halves where they still fit the compute units: for
-// short sweeps (first chunks; at most 16 tiles, where cutting the KV range would cost more than it returns), and for the
-// few items whose KV range is cut (half the pieces per item, and so half the partial results to combine for the
-// same number of workgroups).  Not beside a decode branch that needs longer than the longest sweep: it needs the units.
-// Measured (us per step, 256 rows / 128; 32/8 heads, head_dim 128): 200 first tokens 15.0 / 12.1, 500 21.3 / 17.9, 1000
-// 36.8 / 27.6; 64 at 3000 34.0 / 30.0, 256 at 4000 43.1 / 38.7; three first chunks of 450 tokens with 4 decodes 21.3 / 18.5;
-// 1000 first tokens with 32 decodes (lognormal 1500) 53.6 / 58.4.
+// wave sweeps a tile in about 0.6 of the time it takes beside a second one; but there are at least twice as many items,
+// by 128 / G against 256 / G positions more than twice where 256 / G is odd, three times for chunks of a few positions more than
+// an item of 128 rows holds twice, each starts and ends on its own, and K and V are read that much more often.  So the
+// items are counted as they will be made, and halves are taken:
+//   sweeps of at most 16 tiles (first chunks; cutting the KV range would cost more than it returns) whose 256-row items take
+//   half of the compute units at most: always without decodes (256 rows would be levelled over fewer units); beside decodes
+//   where the estimate is lower: the longest sweep, or the unit times of all items and of the decodes spread over the chip.
+//   longer sweeps whose 256-row items take an eighth of the units at most (their KV range is cut): where the estimate for the longest piece is
+//   lower.  On a full chip halves make longer pieces (they are cut less, and not at all when they are more than a quarter of
+//   the units), but fewer per item, which saves about 7 us of starting and combining at head_dim 128 (5.5 where decode
+//   workgroups wait for the pieces to end), and 5 more where halves are not cut at all.
+// Not beside a decode branch that needs longer than the longest sweep: it needs the units.
+// Measured (us per step, 256 rows / 128; 32/8 heads, head_dim 128, unless stated):
+//   first chunks   200 tokens 14.9 / 12.3, 500 20.6 / 17.3, 1000 35.4 / 25.9; 40/8 heads: 816 (264 items) 35.7 / 23.9, sixteen of 51
+//                  (384 items) 83.3 / 17.2
+//   with decodes   1000 with 32 (lognormal 1500) 53.6 / 58.4; 40/8 heads, decodes of 100-900 tokens: 801 with 16 of them 29.5 / 29.2, with
+//                  32 30.6 / 33.5; sixteen of 51 with 4 17.7 / 21.6; 400 and 405 with 4 23.2 / 23.1, with 16 24.6 / 28.3; 24/8 heads, the
+//                  same with 16 23.3 / 20.6, with 32 24.7 / 27.4
+//   cut            64 at 3000 33.2 / 29.1, at 60000 160.2 / 132.3 (cut in eight at most, 256 rows leave units empty); 256 at 3000
+//                  36.2 / 32.7, at 8000 54.3 / 52.8, at 20000 94.9 / 100.9, at 60000 227.3 / 269.9; 40/8 heads: 204 at 3000 (72 items,
+//                  uncut) 37.6 / 52.5, 102 at 20000 74.3 / 76.3; head_dim 64: 256 at 3000 24.2 / 22.6, at 8000 34.6 / 36.2
 static int choose_rows_per_item(const tc_plan *p, int S, int64_t decode_bytes) {
-    int64_t items = 0, longest = 0;
+    const int whole_pos = kPrefillRows / p->G, half_pos = kPrefillRows / 2 / p->G;
+    int64_t whole = 0, half = 0, longest = 0;   // items of 256 and of 128 rows, tokens of the longest sweep
+    double whole_tiles = 0, half_tiles = 0;     // tiles of all items' sweeps
     for (int s = 0; s < S; s++) {
         const int q = p->q_start[s + 1] - p->q_start[s];
         if (q <= 1) continue;
-        items += (int64_t)((q - 1) / (kPrefillRows / p->G) + 1) * p->Hkv;
+        const int64_t nw = (int64_t)((q - 1) / whole_pos + 1) * p->Hkv, nh = (int64_t)((q - 1) / half_pos + 1) * p->Hkv;
+        const double mean_tiles = ((double)p->ctx_len[s] + 0.5 * q) / kPrefillTileTokens + 0.5;
+        whole += nw;
+        half += nh;
+        whole_tiles += nw * mean_tiles;
+        half_tiles += nh * mean_tiles;
         longest = std::max<int64_t>(longest, (int64_t)p->ctx_len[s] + q);
     }
-    const int64_t tiles = (longest + kPrefillTileTokens - 1) / kPrefillTileTokens;
+    if (whole == 0) return kPrefillRows;
+    const int tiles = (int)((longest + kPrefillTileTokens - 1) / kPrefillTileTokens);
+    const bool d64 = p->D == 64;
     if ((double)decode_bytes / 5.0e6 > tiles * kTileUs * (p->D / 128.0)) return kPrefillRows;
-    const bool half = (tiles <= 16 && items * 2 <= kNumCu) || items * 2 * 4 <= kNumCu;
-    return half ? kPrefillRows / 2 : kPrefillRows;
+    const double half_us = d64 ? 0.62 : 1.1;  // time of a tile in an item of 128 rows
+    double t_whole, t_half;
+    if (tiles <= 16 && whole * 2 <= kNumCu) {
+        if (decode_bytes == 0) return kPrefillRows / 2;
+        const double whole_us = d64 ? 1.04 : 1.6, item_us = d64 ? 2.0 : 3.0;  // of a tile with 256 rows on a part of the chip; of an item's start and end
+        const double decode_us = (double)decode_bytes / (20.0e3 * kNumCu);    // 20 GB/s and unit
+        t_whole = std::max(tiles * whole_us, (whole_tiles * whole_us + whole * item_us) / kNumCu + decode_us);
+        t_half = std::max(tiles * half_us, (half_tiles * half_us + half * item_us) / kNumCu + decode_us);
+    } else if (whole * 8 <= kNumCu && half <= kNumCu) {
+        const int k_whole = prefill_cuts(tiles, whole, decode_bytes, kCutTileUs);
+        const int k_half = half * 4 <= kNumCu ? prefill_cuts(tiles, half, decode_bytes, kCutHalfTileUs) : 1;
+        const double whole_us = (p->D / 128.0) * (whole * k_whole > kNumCu / 2 ? kTileUs : 1.25);
+        t_whole = (double)tiles / k_whole * whole_us + (p->D / 128.0) * ((decode_bytes ? 5.5 : 7.0) + (k_half == 1 ? 5.0 : 0.0));
+        t_half = (double)tiles / k_half * half_us;
+    } else {
+        return kPrefillRows;
+    }
+    return t_half <= t_whole ? kPrefillRows / 2 : kPrefillRows;
 }
 
 tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
@@ -299,7 +339,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     // `queue`: the launch has no more workgroups than the chip has compute units and the decode items are drawn from a
     // queue, a workgroup's worth at a time, by whichever workgroup is free (see the kernel)
     bool queue = false;
-    if (n_items > 0 && n_items * 4 <= slots) choose_prefill_cuts(w.blocks, Hkv, decode_bytes, p->rows_per_item == kPrefillRows ? 2.0 : 1.1);
+    if (n_items > 0 && n_items * 4 <= slots) choose_prefill_cuts(w.blocks, Hkv, decode_bytes, p->rows_per_item == kPrefillRows ? kCutTileUs : kCutHalfTileUs);
     if (n_items * 4 > slots && n_items <= 4 * slots) {
         queue = decode_tokens > 0 && n_items <= slots;
         // Row blocks that fill the chip (more than three quarters of the units) run uncut, one per workgroup: the

@@ -378,3 +378,49 @@ def test_work_lists_of_the_launch_forms(tc, name, Hq, Hkv, D, q_len, ctx, waves,
     info = check_work_list(tc, sp, table, nb)
     assert (info.waves_per_item, info.rows_per_prefill_item) == (waves, rows)
     assert info.block_threads == 64 * (8 if info.num_prefill_items else 4) // (waves if waves > 1 else 1)
+
+
+def _longest_sweep(p):
+    """Tiles the busiest prefill workgroup sweeps."""
+    pc, wg = p.items(3), p.items(4)
+    tiles = pc[:, 2] - pc[:, 1]
+    return max(int(tiles[a:b].sum()) for a, b in zip(wg, list(wg[1:]) + [len(pc)]))
+
+
+@pytest.mark.parametrize("G", range(1, 17))
+@pytest.mark.parametrize("D,us,overhead", [(128, {256: 1.8, 128: 1.1}, 12.0), (64, {256: 0.9, 128: 0.62}, 6.0)])
+def test_small_items_never_make_the_longest_sweep_slower(tc, G, D, us, overhead):
+    """Items of 128 rows hold 128 // G positions, less than half of 256 // G where that is odd: however a chunk's length falls on
+    the two, the longest sweep, in microseconds at the rate of its item size, is not above that of 256-row items whose KV range is
+    cut to fill the chip, but for what starting and combining twice as many pieces per item costs."""
+    Hkv, whole, half = 8, 256 // G, 128 // G
+    lengths = sorted({n for m in (1, 2, 3, 4) for n in (m * whole - 1, m * whole, m * whole + 1, m * half, m * half + 1, m * (half * 2 + 1)) if n >= 2})
+    pool = tc.make_pool(G * Hkv, Hkv, D, 1 << 12)
+    for n in lengths:
+        for ctx in (2000, 8000, 30000):
+            tiles = (ctx + n + 63) // 64
+            items = -(-n // whole) * Hkv
+            if items * 4 > 256:
+                continue
+            p = tc.Plan(pool, np.array([0, n], np.int32), np.array([ctx], np.int32), np.zeros((1, (ctx + n + 15) // 16), np.int32), host_only=True)
+            k = max(1, min(8, 256 // items, tiles // 8))
+            bound = -(-tiles // k) * us[256] + overhead
+            got = _longest_sweep(p) * us[p.info.rows_per_prefill_item]
+            assert got <= bound, (n, ctx, p.info.rows_per_prefill_item, p.info.num_prefill_pieces, got, bound)
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,q_len,ctx,rows", [
+    (40, 8, 128, [204], [20000], 256),                          # 72 items of 128 rows could not be cut
+    (40, 8, 128, [102, 102], [20000, 15000], 256),
+    (24, 8, 128, [340], [24576], 256),
+    (32, 8, 128, [64], [20000], 128),                           # 256-row items cut in eight leave units empty
+    (32, 8, 128, [256], [20000], 256),                          # a full chip either way
+    (40, 8, 128, [801], [0], 128),                              # 264 short items
+    (40, 8, 128, [400, 405] + [1] * 16, [0, 0] + [500] * 16, 256),  # they leave no units for the decodes
+    (40, 8, 128, [51] * 16 + [1] * 4, [0] * 16 + [500] * 4, 256),   # 384 items of one tile
+    (32, 8, 128, [300] + [1] * 4, [0] + [500] * 4, 128),
+])
+def test_rows_per_item(tc, Hq, Hkv, D, q_len, ctx, rows):
+    sp = W.custom_spec("rows", Hq, Hkv, D, q_len, ctx)
+    table, mb, nb = W.make_tables(sp, np.random.default_rng(8))
+    assert check_work_list(tc, sp, table, nb).rows_per_prefill_item == rows
