@@ -341,7 +341,10 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     bool queue = false;
     if (n_items > 0 && n_items * 4 <= slots) choose_prefill_cuts(w.blocks, Hkv, decode_bytes, p->rows_per_item == kPrefillRows ? kCutTileUs : kCutHalfTileUs);
     if (n_items * 4 > slots && n_items <= 4 * slots) {
-        queue = decode_tokens > 0 && n_items <= slots;
+        // (Items of 128 rows take their unit for half as long: they have a queue from half of the units on.  On fewer units drawing
+        // from it costs more than it levels: 270 first tokens with 3 decodes of 100-300, 32/8 heads, in 72 items, without it /
+        // with it 15.3 / 16.8 us; at head_dim 64 with 46 of 30-300 12.0 / 13.7; 500 tokens, 128 items, with 16 of 100-900 19.0 / 20.8.)
+        queue = decode_tokens > 0 && n_items <= slots && (p->rows_per_item == kPrefillRows || n_items * 2 > slots);
         // Row blocks that fill the chip (more than three quarters of the units) run uncut, one per workgroup: the
         // queue lets the units of the lighter blocks carry the decode branch while the heavier ones still sweep, and
         // cutting measured slower there, with or without decodes (partial results and a second start per workgroup

@@ -424,3 +424,12 @@ def test_rows_per_item(tc, Hq, Hkv, D, q_len, ctx, rows):
     sp = W.custom_spec("rows", Hq, Hkv, D, q_len, ctx)
     table, mb, nb = W.make_tables(sp, np.random.default_rng(8))
     assert check_work_list(tc, sp, table, nb).rows_per_prefill_item == rows
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("n,items,queue", [(270, 72, 0), (400, 104, 0), (500, 128, 0), (516, 136, 1), (800, 200, 1)])
+def test_small_items_draw_decodes_from_a_queue_from_half_of_the_units_on(tc, D, n, items, queue):
+    sp = W.custom_spec("queue", 32, 8, D, [n] + [1] * 3, [0] + [200] * 3)
+    table, mb, nb = W.make_tables(sp, np.random.default_rng(9))
+    info = check_work_list(tc, sp, table, nb)
+    assert (info.rows_per_prefill_item, info.num_prefill_workgroups, info.decode_queue) == (128, items, queue)
