@@ -49,6 +49,28 @@ static int choose_split(int64_t decode_token_heads) {
     return 128;
 }
 
+// First token of split i of a decode sequence of kv tokens cut into ns splits: the sequence's pages are
+// dealt out evenly (the first splits get the odd pages), so the splits of a sequence take the same time
+// and the waves that run them side by side finish together.  split_begin(kv, ns, ns) >= kv.
+static int64_t split_begin(int64_t kv, int ns, int i) {
+    const int64_t pages = (kv + kBlock - 1) / kBlock;
+    return kBlock * (i * (pages / ns) + std::min<int64_t>(i, pages % ns));
+}
+
+// Splits of a decode sequence of kv tokens, to run in workgroups of W waves (W a power of two): pieces of
+// at most `split` tokens, their number rounded up to a power of two, so that the runs pack into
+// workgroups without gaps; a sequence that W pieces of up to kMaxSplitPages pages can cover is never cut
+// into more than W (all of them are then one team, which writes the output rows itself: no partial
+// result, no merge item); a longer one gets a multiple of W (whole workgroups).
+static int num_splits(int64_t kv, int split, int W) {
+    const int64_t ns = (kv + split - 1) / split;
+    const int64_t longest = (int64_t)kMaxSplitPages * kBlock;
+    if (kv > (int64_t)W * longest) return (int)((ns + W - 1) / W * W);
+    int n = 1;
+    while (n < ns && n < W) n *= 2;
+    return n;
+}
+
 // The shortest split, from 128 to 1024 tokens, that cuts the decode sequences into no more than `target` (split, KV head) pairs.
 static int shortest_split(const tc_plan *p, int S, int64_t target) {
     int lo = 128 / kBlock, hi = kMaxSplitPages;  // pages
@@ -75,11 +97,27 @@ static int shortest_split(const tc_plan *p, int S, int64_t target) {
 // serves better where it has no partial results to combine (at most 4096 tokens), this one would have (over 1024), and
 // the longest sequence is not far above the mean load of a compute unit (24 requests of 512-1536 tokens: 21.8 / 24.6, 16 of
 // them 19.3 / 15.9).
+// Every (sequence, KV head) pair is a workgroup here, however short its sequence, and two of them run on a unit at a time (at
+// head_dim 64, with half the registers for a page, they pass twice as fast): with more than three pairs per unit the starts
+// and combinations of many short sequences cost more than the shorter wait, unless a pair has 288 tokens on the mean, or single
+// waves would be busy for a dozen pages and more.  Measured (32/8 heads unless stated, in pairs):
+//   60-70 tokens, 512 pairs 8.3 / 7.5, 1024 11.6 / 14.0, 4096 37.2 / 46.3       1-16 tokens, 4096 pairs 19.0 / 31.7
+//   64-256 tokens, 512 pairs 12.3 / 11.5, 2048 38.4 / 41.2                      128-512 tokens, 1024 pairs 34.6 / 33.1, 2048 64.5 / 65.0
+//   head_dim 64: 60-70 tokens, 1024 pairs 7.3 / 7.4, 2048 11.7 / 13.5; 16-100, 4096 20.0 / 23.7; 128-512, 2048 33.9 / 33.5
+//   32/32 heads, one of 2157 tokens (34 pages a wave) among 29 short ones, 960 pairs 27.5 / 17.0
 static int choose_wide_split(const tc_plan *p, int S, int64_t decode_tokens) {
     const int64_t token_heads = decode_tokens * p->Hkv;
     if (token_heads >= (int64_t)kNumCu * kDecodeWgPerCu * kDecodeWaves * 256) return 0;
-    int64_t longest = 0;
-    for (int s = 0; s < S; s++) longest = std::max<int64_t>(longest, (int64_t)p->ctx_len[s] + 1);
+    const int split = choose_split(token_heads);  // of the single-wave form
+    int64_t longest = 0, longest_pages = 0;       // the longest sequence; the pages of the longest single-wave split
+    for (int s = 0; s < S; s++) {
+        const int64_t kv = (int64_t)p->ctx_len[s] + 1, pages = (kv + kBlock - 1) / kBlock, ns = num_splits(kv, split, kDecodeWaves);
+        longest = std::max(longest, kv);
+        longest_pages = std::max(longest_pages, (pages + ns - 1) / ns);
+    }
+    const int64_t pairs = (int64_t)S * p->Hkv;
+    const double chip_pairs = pairs * (p->D / 128.0);
+    if (chip_pairs > 3 * kNumCu && token_heads < 288 * pairs && longest_pages < 12 + chip_pairs / kNumCu) return 0;
     const int64_t max_split = (int64_t)kMaxSplitPages * kBlock;
     if (longest > max_split && longest <= kDecodeWaves * max_split && 4 * longest * kNumCu < 7 * token_heads) return 0;
     return shortest_split(p, S, token_heads > 900 * kNumCu ? 2 * kNumCu : kNumCu);
@@ -111,28 +149,6 @@ static int choose_wide_split_beside_chunk(const tc_plan *p, int S, double t_rest
     const double share = !queue && n_prefill_wg > kNumCu / 2 ? 0.8 : p->D == 64 ? 0.65 : 0.5;
     if (t_longest <= share * std::max(t_rest_us, 8.0)) return 0;
     return shortest_split(p, S, std::max<int64_t>(kNumCu - n_prefill_wg, kNumCu / 4));
-}
-
-// First token of split i of a decode sequence of kv tokens cut into ns splits: the sequence's pages are
-// dealt out evenly (the first splits get the odd pages), so the splits of a sequence take the same time
-// and the waves that run them side by side finish together.  split_begin(kv, ns, ns) >= kv.
-static int64_t split_begin(int64_t kv, int ns, int i) {
-    const int64_t pages = (kv + kBlock - 1) / kBlock;
-    return kBlock * (i * (pages / ns) + std::min<int64_t>(i, pages % ns));
-}
-
-// Splits of a decode sequence of kv tokens, to run in workgroups of W waves (W a power of two): pieces of
-// at most `split` tokens, their number rounded up to a power of two, so that the runs pack into
-// workgroups without gaps; a sequence that W pieces of up to kMaxSplitPages pages can cover is never cut
-// into more than W (all of them are then one team, which writes the output rows itself: no partial
-// result, no merge item); a longer one gets a multiple of W (whole workgroups).
-static int num_splits(int64_t kv, int split, int W) {
-    const int64_t ns = (kv + split - 1) / split;
-    const int64_t longest = (int64_t)kMaxSplitPages * kBlock;
-    if (kv > (int64_t)W * longest) return (int)((ns + W - 1) / W * W);
-    int n = 1;
-    while (n < ns && n < W) n *= 2;
-    return n;
 }
 
 // When a batch has few prefill row blocks (a small chunk, as on a decode-heavy instance), each of

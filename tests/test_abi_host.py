@@ -433,3 +433,23 @@ def test_small_items_draw_decodes_from_a_queue_from_half_of_the_units_on(tc, D, 
     table, mb, nb = W.make_tables(sp, np.random.default_rng(9))
     info = check_work_list(tc, sp, table, nb)
     assert (info.rows_per_prefill_item, info.num_prefill_workgroups, info.decode_queue) == (128, items, queue)
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,ctx,waves", [
+    (32, 8, 128, [65] * 64, 4),                     # 512 pairs: two workgroups per compute unit
+    (32, 8, 128, [65] * 96, 4),                     # 768, the line
+    (32, 8, 128, [65] * 97, 1),
+    (32, 32, 128, [65] * 25, 1),                    # the same with more KV heads
+    (32, 8, 64, [65] * 192, 4),                     # twice as many at head_dim 64
+    (32, 8, 64, [65] * 193, 1),
+    (32, 8, 128, [7] * 512, 1),
+    (8, 2, 64, [12] * 2000, 1),
+    (32, 8, 128, [286] * 200, 1),                   # 287 tokens with the new one
+    (32, 8, 128, [287] * 200, 4),
+    (32, 32, 128, [2100] + [30] * 29, 4),           # one sequence keeps single waves busy for 33 pages
+    (32, 8, 128, [900] + [30] * 120, 1),            # and for 15
+])
+def test_many_short_decodes_are_run_by_single_waves(tc, Hq, Hkv, D, ctx, waves):
+    sp = W.custom_spec("short", Hq, Hkv, D, [1] * len(ctx), ctx)
+    table, mb, nb = W.make_tables(sp, np.random.default_rng(10))
+    assert check_work_list(tc, sp, table, nb).waves_per_item == waves

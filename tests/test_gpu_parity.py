@@ -386,6 +386,7 @@ DECODE_FORMS = {
     "wide_merge_g1_d64": (3, 3, 64, [33000, 2000], "fp16", 4),
     "wide_merge_g5": (10, 2, 128, [9000, 20000], "fp16", 4),
     "wide_many_short": (8, 2, 64, [(13 * i) % 300 for i in range(200)], "bf16", 4),
+    "waves_many_short": (32, 8, 128, [(13 * i) % 100 for i in range(130)], "bf16", 1),
     "waves_teams_and_merges": (32, 32, 64, [9000, 8192, 4097, 4096, 1025, 500, 31, 0], "bf16", 1),
     "waves_merge_g16_d128": (256, 16, 128, [30000, 19000, 1000], "fp16", 1),
     "waves_even_sequences": (8, 2, 128, [1400 + 5 * i for i in range(150)], "bf16", 1),
