@@ -96,7 +96,8 @@ static int shortest_split(const tc_plan *p, int S, int64_t target) {
 // which this form, whose workgroups all start and combine alike, misses by 5-8 %.  Below that the single-wave form
 // serves better where it has no partial results to combine (at most 4096 tokens), this one would have (over 1024), and
 // the longest sequence is not far above the mean load of a compute unit (24 requests of 512-1536 tokens: 21.8 / 24.6, 16 of
-// them 19.3 / 15.9).
+// them 19.3 / 15.9): the line is at 7/4 of that load, and at 9/4 where this form would give a few units a second workgroup and
+// wait for those (head_dim 128, 8/8 heads, 25 requests of 260-1431 tokens, 288 workgroups, factor 2: 20.9 / 24.7).
 // Every (sequence, KV head) pair is a workgroup here, however short its sequence, and two of them run on a unit at a time (at
 // head_dim 64, with half the registers for a page, they pass twice as fast): with more than three pairs per unit the starts
 // and combinations of many short sequences cost more than the shorter wait, unless a pair has 288 tokens on the mean, or single
@@ -118,9 +119,13 @@ static int choose_wide_split(const tc_plan *p, int S, int64_t decode_tokens) {
     const int64_t pairs = (int64_t)S * p->Hkv;
     const double chip_pairs = pairs * (p->D / 128.0);
     if (chip_pairs > 3 * kNumCu && token_heads < 288 * pairs && longest_pages < 12 + chip_pairs / kNumCu) return 0;
+    const int wide = shortest_split(p, S, token_heads > 900 * kNumCu ? 2 * kNumCu : kNumCu);
+    int64_t items = 0;
+    for (int s = 0; s < S; s++) items += (int64_t)num_splits((int64_t)p->ctx_len[s] + 1, wide, 1) * p->Hkv;
+    const bool few_doubled = p->D == 128 && items > kNumCu && 2 * items < 3 * kNumCu;  // a few units get a second workgroup
     const int64_t max_split = (int64_t)kMaxSplitPages * kBlock;
-    if (longest > max_split && longest <= kDecodeWaves * max_split && 4 * longest * kNumCu < 7 * token_heads) return 0;
-    return shortest_split(p, S, token_heads > 900 * kNumCu ? 2 * kNumCu : kNumCu);
+    if (longest > max_split && longest <= kDecodeWaves * max_split && 4 * longest * kNumCu < (few_doubled ? 9 : 7) * token_heads) return 0;
+    return wide;
 }
 
 // The same beside a prefill chunk, where a decode workgroup has eight waves and a compute unit to itself.  Eight

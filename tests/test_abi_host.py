@@ -453,3 +453,14 @@ def test_many_short_decodes_are_run_by_single_waves(tc, Hq, Hkv, D, ctx, waves):
     sp = W.custom_spec("short", Hq, Hkv, D, [1] * len(ctx), ctx)
     table, mb, nb = W.make_tables(sp, np.random.default_rng(10))
     assert check_work_list(tc, sp, table, nb).waves_per_item == waves
+
+
+@pytest.mark.parametrize("Hkv,D,ctx,waves", [
+    (8, 128, [260, 310, 429, 539, 576, 595, 617, 665, 784, 851, 870, 922, 928, 943, 1046, 1127, 1149, 1162, 1173, 1240, 1259, 1306, 1353, 1365, 1431], 1),
+    (8, 64, [260, 310, 429, 539, 576, 595, 617, 665, 784, 851, 870, 922, 928, 943, 1046, 1127, 1149, 1162, 1173, 1240, 1259, 1306, 1353, 1365, 1431], 4),
+    (8, 128, [260, 310, 429, 539, 576, 595, 617, 665, 784, 851, 870, 922, 928, 943, 1046, 1127], 4),  # a unit each
+])
+def test_decodes_that_would_double_a_few_units_are_run_by_single_waves(tc, Hkv, D, ctx, waves):
+    sp = W.custom_spec("doubled", Hkv, Hkv, D, [1] * len(ctx), ctx)
+    table, mb, nb = W.make_tables(sp, np.random.default_rng(11))
+    assert check_work_list(tc, sp, table, nb).waves_per_item == waves
