@@ -221,10 +221,10 @@ static void level_prefill(std::vector<PlanRowBlock> &blocks, std::vector<PlanPie
 //   sweeps of at most 16 tiles (first chunks; cutting the KV range would cost more than it returns) whose 256-row items take
 //   half of the compute units at most: always without decodes (256 rows would be levelled over fewer units); beside decodes
 //   where the estimate is lower: the longest sweep, or the unit times of all items and of the decodes spread over the chip.
-//   longer sweeps whose 256-row items take an eighth of the units at most (their KV range is cut): where the estimate for the longest piece is
-//   lower.  On a full chip halves make longer pieces (they are cut less, and not at all when they are more than a quarter of
-//   the units), but fewer per item, which saves about 7 us of starting and combining at head_dim 128 (5.5 where decode
-//   workgroups wait for the pieces to end), and 5 more where halves are not cut at all.
+//   longer sweeps whose 256-row items take an eighth of the units at most (their KV range is cut): where the estimate is lower, for the longest
+//   piece and, beside decodes, for all the work spread over the chip.  On a full chip halves make longer pieces (they are cut less,
+//   and not at all when they are more than a quarter of the units), but fewer per item, which saves about 7 us of starting and
+//   combining at head_dim 128, and 5 more where halves are not cut at all.
 // Not beside a decode branch that needs longer than the longest sweep: it needs the units.
 // Measured (us per step, 256 rows / 128; 32/8 heads, head_dim 128, unless stated):
 //   first chunks   200 tokens 14.9 / 12.3, 500 20.6 / 17.3, 1000 35.4 / 25.9; 40/8 heads: 816 (264 items) 35.7 / 23.9, sixteen of 51
@@ -235,6 +235,7 @@ static void level_prefill(std::vector<PlanRowBlock> &blocks, std::vector<PlanPie
 //   cut            64 at 3000 33.2 / 29.1, at 60000 160.2 / 132.3 (cut in eight at most, 256 rows leave units empty); 256 at 3000
 //                  36.2 / 32.7, at 8000 54.3 / 52.8, at 20000 94.9 / 100.9, at 60000 227.3 / 269.9; 40/8 heads: 204 at 3000 (72 items,
 //                  uncut) 37.6 / 52.5, 102 at 20000 74.3 / 76.3; head_dim 64: 256 at 3000 24.2 / 22.6, at 8000 34.6 / 36.2
+//   with decodes   head_dim 64, 8/8 heads, 455 at 9062 with 37 (mean 1400) 39.5 / 50.2; 32/8 heads, 128 at 8000 with 8 (mean 500) 31.6 / 29.4
 static int choose_rows_per_item(const tc_plan *p, int S, int64_t decode_bytes) {
     const int whole_pos = kPrefillRows / p->G, half_pos = kPrefillRows / 2 / p->G;
     int64_t whole = 0, half = 0, longest = 0;   // items of 256 and of 128 rows, tokens of the longest sweep
@@ -252,24 +253,27 @@ static int choose_rows_per_item(const tc_plan *p, int S, int64_t decode_bytes) {
     }
     if (whole == 0) return kPrefillRows;
     const int tiles = (int)((longest + kPrefillTileTokens - 1) / kPrefillTileTokens);
-    const bool d64 = p->D == 64;
     if ((double)decode_bytes / 5.0e6 > tiles * kTileUs * (p->D / 128.0)) return kPrefillRows;
-    const double half_us = d64 ? 0.62 : 1.1;  // time of a tile in an item of 128 rows
-    double t_whole, t_half;
-    if (tiles <= 16 && whole * 2 <= kNumCu) {
+    int k_whole = 1, k_half = 1;
+    double add_whole = 0;  // what starting and combining the longest pieces takes longer with 256 rows
+    const bool d64 = p->D == 64, cut = tiles > 16;
+    if (!cut) {
+        if (whole * 2 > kNumCu) return kPrefillRows;
         if (decode_bytes == 0) return kPrefillRows / 2;
-        const double whole_us = d64 ? 1.04 : 1.6, item_us = d64 ? 2.0 : 3.0;  // of a tile with 256 rows on a part of the chip; of an item's start and end
-        const double decode_us = (double)decode_bytes / (20.0e3 * kNumCu);    // 20 GB/s and unit
-        t_whole = std::max(tiles * whole_us, (whole_tiles * whole_us + whole * item_us) / kNumCu + decode_us);
-        t_half = std::max(tiles * half_us, (half_tiles * half_us + half * item_us) / kNumCu + decode_us);
-    } else if (whole * 8 <= kNumCu && half <= kNumCu) {
-        const int k_whole = prefill_cuts(tiles, whole, decode_bytes, kCutTileUs);
-        const int k_half = half * 4 <= kNumCu ? prefill_cuts(tiles, half, decode_bytes, kCutHalfTileUs) : 1;
-        const double whole_us = (p->D / 128.0) * (whole * k_whole > kNumCu / 2 ? kTileUs : 1.25);
-        t_whole = (double)tiles / k_whole * whole_us + (p->D / 128.0) * ((decode_bytes ? 5.5 : 7.0) + (k_half == 1 ? 5.0 : 0.0));
-        t_half = (double)tiles / k_half * half_us;
     } else {
-        return kPrefillRows;
+        if (whole * 8 > kNumCu || half > kNumCu) return kPrefillRows;
+        k_whole = prefill_cuts(tiles, whole, decode_bytes, kCutTileUs);
+        if (half * 4 <= kNumCu) k_half = prefill_cuts(tiles, half, decode_bytes, kCutHalfTileUs);
+        add_whole = (p->D / 128.0) * (k_half == 1 ? 12.0 : 7.0);
+    }
+    // time of a tile: alone on a unit's SIMD, beside a second wave on a part of the chip, and on a full chip
+    const double half_us = d64 ? (cut ? 0.67 : 0.62) : 1.1;
+    const double whole_us = !cut ? (d64 ? 1.04 : 1.6) : whole * k_whole > kNumCu / 2 ? kTileUs * (p->D / 128.0) : (d64 ? 0.75 : 1.25);
+    double t_whole = tiles * whole_us / k_whole + add_whole, t_half = tiles * half_us / k_half;
+    if (decode_bytes > 0) {  // the unit times of all pieces (3 us each, at head_dim 64 two, and their tiles) and of the decodes
+        const double piece_us = d64 ? 2.0 : 3.0, decode_us = (double)decode_bytes / ((cut ? 35.0e3 : 20.0e3) * kNumCu);
+        t_whole = std::max(t_whole, (whole_tiles * (d64 ? 1.04 : 1.6) + whole * k_whole * piece_us) / kNumCu + decode_us);
+        t_half = std::max(t_half, (half_tiles * half_us + half * k_half * piece_us) / kNumCu + decode_us);
     }
     return t_half <= t_whole ? kPrefillRows / 2 : kPrefillRows;
 }
