@@ -424,7 +424,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
             longest_piece = std::max<double>(longest_piece, x.t1 - x.t0);
             tiles += (x.t1 - x.t0) * (double)Hkv;
         }
-        const double tile_us = kTileUs * (D / 128.0);
+        const double tile_us = kTileUs * (D / 128.0) * (p->rows_per_item == kPrefillRows ? 1.0 : 0.6);  // see choose_rows_per_item
         const double t_rest = std::max(longest_piece * tile_us, tiles * tile_us / kNumCu + (double)decode_bytes / 5.0e6);
         if (const int split = choose_wide_split_beside_chunk(p, S, t_rest, (int64_t)n_wg_head * Hkv, queue)) {
             p->split_tokens = split;

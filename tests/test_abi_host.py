@@ -466,3 +466,16 @@ def test_decodes_that_would_double_a_few_units_are_run_by_single_waves(tc, Hkv, 
     sp = W.custom_spec("doubled", Hkv, Hkv, D, [1] * len(ctx), ctx)
     table, mb, nb = W.make_tables(sp, np.random.default_rng(11))
     assert check_work_list(tc, sp, table, nb).waves_per_item == waves
+
+
+@pytest.mark.parametrize("Hq,rows,n,decodes,waves", [
+    (40, 128, 320, [157, 205, 214, 351, 267, 260, 184, 234, 368, 460, 231, 438, 149, 475], 8),
+    (64, 128, 438, [252, 24, 190, 374, 399, 465, 245, 341, 197, 199, 86, 380, 159], 8),
+    (32, 256, 2200, [465] * 10, 1),   # sweeps of 35 tiles at 256 rows
+])
+def test_sweeps_of_small_items_are_taken_at_their_own_rate(tc, Hq, rows, n, decodes, waves):
+    """Whether few long decodes are run by whole workgroups depends on what else the launch waits for."""
+    sp = W.custom_spec("rate", Hq, 8, 128, [n] + [1] * len(decodes), [0] + decodes)
+    table, mb, nb = W.make_tables(sp, np.random.default_rng(12))
+    info = check_work_list(tc, sp, table, nb)
+    assert (info.rows_per_prefill_item, info.waves_per_item) == (rows, waves)
