@@ -141,6 +141,10 @@ static int choose_wide_split(const tc_plan *p, int S, int64_t decode_tokens) {
 //   128 at 1000, 32 decodes of 512-4096, 40/8 heads, 16 layers (0.6)  971 / 922     128 at 2048, 40 of them (share 0.4)    73.6 / 78.2
 //   256 at 500, 128 decodes (lognormal 1500; share 0.35)            145.7 / 156.5   128 at 2048, 64 of 512-4096 (0.3)     109.6 / 121.4
 //   512 at 2048 in 192 pieces, 16 of 512-4096 (share 0.75)           55.6 / 56.8
+// Each (sequence, KV head) pair is a workgroup then, or a unit of the queue, however short its sequence, and each 256 of them beyond
+// the first take 2 us (3 where they are drawn) for starting and combining on top: one long sequence must not take hundreds of short
+// ones along.  128 at 0, 32/32 heads, four decodes of 8000 and 128 of 40-80 tokens (5120 workgroups) 137.6 / 154.5, one of 6000 and 64
+// (2240) 74.1 / 52.1; 701, 333 and 45 at 0, 32/8 heads, head_dim 64, one of 6000 and 400 (3248) 46.5 / 56.5, and 128 39.4 / 27.8.
 // At head_dim 64 a split is half the bytes for the same start and combination, and the line is at 0.65: 128 at 1000 with 32
 // decodes of 512-4096 tokens (share 0.55) 38.0 / 40.2, 256 at 500 with 64 of lognormal 1500 (0.8) 50.6 / 46.4.
 static int choose_wide_split_beside_chunk(const tc_plan *p, int S, double t_rest_us, int64_t n_prefill_wg, bool queue) {
@@ -152,8 +156,14 @@ static int choose_wide_split_beside_chunk(const tc_plan *p, int S, double t_rest
         }
     const double t_longest = 1.1 * (p->D / 128.0) * (double)longest / (kBlock * kMixedWaves);
     const double share = !queue && n_prefill_wg > kNumCu / 2 ? 0.8 : p->D == 64 ? 0.65 : 0.5;
-    if (t_longest <= share * std::max(t_rest_us, 8.0)) return 0;
-    return shortest_split(p, S, std::max<int64_t>(kNumCu - n_prefill_wg, kNumCu / 4));
+    const double t_rest = std::max(t_rest_us, 8.0);
+    if (t_longest <= share * t_rest) return 0;
+    const int split = shortest_split(p, S, std::max<int64_t>(kNumCu - n_prefill_wg, kNumCu / 4));
+    int64_t items = 0;  // workgroups of the decode branch
+    for (int s = 0; s < S; s++)
+        if (p->q_start[s + 1] - p->q_start[s] == 1) items += (int64_t)num_splits((int64_t)p->ctx_len[s] + 1, split, 1) * p->Hkv;
+    const double t_starts = (queue ? 3.0 : 2.0) * std::max<int64_t>(0, items - kNumCu) / kNumCu;
+    return t_longest <= share * (t_rest + t_starts) ? 0 : split;
 }
 
 // When a batch has few prefill row blocks (a small chunk, as on a decode-heavy instance), each of

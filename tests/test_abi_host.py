@@ -479,3 +479,16 @@ def test_sweeps_of_small_items_are_taken_at_their_own_rate(tc, Hq, rows, n, deco
     table, mb, nb = W.make_tables(sp, np.random.default_rng(12))
     info = check_work_list(tc, sp, table, nb)
     assert (info.rows_per_prefill_item, info.waves_per_item) == (rows, waves)
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,chunks,long,n_short,waves", [
+    (32, 32, 128, [128], [8000] * 4, 128, 1),     # 5120 workgroups
+    (32, 32, 128, [128], [6000], 64, 8),          # 2240, and nothing else to wait for
+    (32, 8, 64, [701, 333, 45], [6000], 400, 1),  # 3248 units of the queue
+    (32, 8, 64, [701, 333, 45], [6000], 128, 8),
+    (32, 8, 128, [128], [6000], 400, 8),          # 3248, half as long as the long one
+])
+def test_one_long_decode_beside_a_chunk_does_not_take_many_short_ones_along(tc, Hq, Hkv, D, chunks, long, n_short, waves):
+    sp = W.custom_spec("along", Hq, Hkv, D, chunks + [1] * (len(long) + n_short), [0] * len(chunks) + long + [40 + i % 41 for i in range(n_short)])
+    table, mb, nb = W.make_tables(sp, np.random.default_rng(13))
+    assert check_work_list(tc, sp, table, nb).waves_per_item == waves
