@@ -314,7 +314,7 @@ def bench_workload(name, steps, warmup, stream, ceilings, cpu_target_s, event_ev
                         "head_dim": spec.head_dim, "block_size": spec.block_size, "num_seqs": spec.num_seqs,
                         "tokens": T, "prefill_chunk": int(spec.q_len.max()) if (spec.q_len > 1).any() else 0,
                         "sum_kv_len": work["sum_kv_len"], "seed": spec.seed},
-             "launch": {"grid_blocks": info.grid_blocks, "block_threads": info.block_threads * info.waves_per_item,
+             "launch": {"grid_blocks": info.grid_blocks, "block_threads": info.block_threads,
                         "prefill_workgroups": info.num_prefill_workgroups, "prefill_pieces": info.num_prefill_pieces,
                         "decode_items": info.num_decode_items, "decode_queue": bool(info.decode_queue),
                         "workspace_bytes": db.plan.workspace_bytes},

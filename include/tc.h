@@ -91,11 +91,11 @@ typedef struct {
                                         /* padding included (whole workgroups)               */
     int32_t num_merge_items;            /* (query row, KV head) pairs that need the merge    */
     int32_t num_partials;               /* partial results of decode teams held in the workspace */
-    int32_t split_tokens;               /* KV tokens a decode split holds at most, except that a sequence */
-                                        /* one workgroup's waves can cover with splits of up to 1024 is cut into that many */
+    int32_t split_tokens;               /* KV tokens a decode split holds at most, except that a sequence which one   */
+                                        /* workgroup's wave slots can cover with splits of up to 1024 is cut into no  */
+                                        /* more splits than it has slots (one, where waves_per_item > 1)              */
     int32_t rows_per_prefill_item;      /* (position, head) rows per prefill workgroup: 256, or 128 for a small chunk */
-    int32_t grid_blocks, block_threads; /* workgroups of the attention kernel; 64 threads per wave slot of a  */
-                                        /* workgroup.  A workgroup has block_threads * waves_per_item threads  */
+    int32_t grid_blocks, block_threads; /* launch shape of the fused attention kernel        */
     int64_t total_pages;                /* table entries copied                              */
     int32_t num_prefill_pieces;         /* an item whose KV range is cut is several pieces, else one */
     int32_t num_prefill_workgroups;     /* each runs one or more pieces, one after the other */
@@ -104,7 +104,8 @@ typedef struct {
     int32_t decode_queue;               /* 1: the decode items are drawn from a queue, in units of one workgroup's   */
                                         /* worth, by grid_blocks - num_prefill_workgroups decode workgroups and by   */
                                         /* the prefill workgroups once their pieces are done (levelled chunks)       */
-    int32_t waves_per_item;             /* waves that share one decode item: 4 in a batch of few decodes, else 1 */
+    int32_t waves_per_item;             /* waves that share one decode item: 1, or all of a workgroup's (4 in a batch */
+                                        /* of few decodes, 8 for few long decodes beside a chunk)                     */
     int64_t build_ns;                   /* host time of the latest work-list build ...       */
     int64_t upload_ns;                  /* ... and of enqueueing its copy to the device      */
 } tc_plan_info;
@@ -150,11 +151,11 @@ tc_status tc_plan_get_info(const tc_plan *plan, tc_plan_info *info);
  * and cut into runs of equal cost, one workgroup each, which leaves compute units to the decode branch.
  * Piece c of a cut item leaves its partial result in piece region (first region of the item) + c.  A prefill
  * workgroup runs the pieces [first piece of the workgroup, .. the one marked last].
- * Decode items come in workgroups of W = block_threads / 64 wave slots.  A sequence is cut into 1, 2,
- * 4 .. W splits, or a multiple of W when W splits of 1024 tokens cannot cover it; its splits hold the
- * same number of pages up to one.  In a batch of few decodes (and no chunk) W is 1 and the one item of a workgroup is
- * run by waves_per_item waves, which share its pages out; a sequence of at most 1024 tokens is then one split, a
- * longer one any number of them.  Consecutive splits of one (sequence, KV head) in one workgroup are a
+ * Decode items come in workgroups of W = block_threads / (64 * waves_per_item) wave slots.  A sequence is cut
+ * into 1, 2, 4 .. W splits, or a multiple of W when W splits of 1024 tokens cannot cover it; its splits hold the
+ * same number of pages up to one.  Where waves_per_item > 1, W is 1 and the one item of a workgroup is run by all
+ * of its waves, which share its pages out; a sequence of at most 1024 tokens is then one split, a longer one any
+ * number of them.  Consecutive splits of one (sequence, KV head) in one workgroup are a
  * team (consecutive items, positions 0..members-1, all carrying the team's partial_slot): the workgroup
  * combines their results, and the team writes the output rows (-1) or one partial result.  An item
  * with kv_begin = kv_end (seq = -1) is padding. */

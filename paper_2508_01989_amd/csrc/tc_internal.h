@@ -104,7 +104,7 @@ struct tc_plan {
 
     int items_per_wg = tc::kDecodeWaves;  // decode items a workgroup runs side by side
     int rows_per_item = tc::kPrefillRows;  // (position, head) rows of a prefill item: 256, or 128 for a small chunk
-    int waves_per_item = 1;               // waves that share one of them: kWideWaves in a batch of few decodes, else 1
+    int waves_per_item = 1;               // waves that share one of them: a whole workgroup's (kWideWaves, beside a chunk kMixedWaves) or 1
     int launch_threads() const { return 64 * items_per_wg * waves_per_item; }
     int grid_blocks() const { return n_prefill_wg + n_decode_wg; }
     size_t workspace_bytes() const {

@@ -704,7 +704,7 @@ tc_status tc_plan_get_info(const tc_plan *p, tc_plan_info *info) {
     info->num_prefill_items = p->n_prefill; info->num_decode_items = p->n_decode;
     info->num_merge_items = p->n_merge; info->num_partials = p->n_partials; info->num_piece_partials = p->n_piece_partials;
     info->split_tokens = p->split_tokens; info->rows_per_prefill_item = p->rows_per_item;
-    info->grid_blocks = p->grid_blocks(); info->block_threads = p->items_per_wg * 64;
+    info->grid_blocks = p->grid_blocks(); info->block_threads = p->launch_threads();
     info->waves_per_item = p->waves_per_item;
     info->total_pages = p->total_pages;
     info->num_prefill_pieces = p->n_pieces;

@@ -51,7 +51,7 @@ def main():
     start, end = (t[:, 0] - t0) / 100.0, (t[:, 1] - t0) / 100.0  # microseconds
     kind = t[:, 3] & 255
     mid = start + (t[:, 3] >> 8) / 100.0
-    print(f"workload {args.workload}: grid {info.grid_blocks} workgroups of {info.block_threads * info.waves_per_item} threads, {info.num_prefill_workgroups} prefill workgroups "
+    print(f"workload {args.workload}: grid {info.grid_blocks} workgroups of {info.block_threads} threads, {info.num_prefill_workgroups} prefill workgroups "
           f"({info.num_prefill_pieces} pieces of {info.num_prefill_items} items), {info.num_decode_items} decode items, decode queue {bool(info.decode_queue)}")
     print(f"launch length {end.max():.1f} us ({'tc_attention_partials' if args.two_launch else 'tc_mixed_attention'})")
     pct = [0, 10, 50, 90, 100]

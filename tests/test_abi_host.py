@@ -203,7 +203,7 @@ def check_work_list(tc, sp, table, nb):
             assert np.all(per_head == per_head[:, :1])
             assert per_head[:, 0].max() <= per_head[:, 0].mean() * 1.15 + 8
     # decode: the items fill whole workgroups of W waves; padding items hold no tokens
-    W_ = info.block_threads // 64
+    W_ = info.block_threads // (64 * info.waves_per_item)
     assert len(dc) % W_ == 0 and len(dc) == info.num_decode_items
     real = dc[dc[:, 3] > dc[:, 2]]
     pad = dc[dc[:, 3] == dc[:, 2]]
@@ -266,7 +266,7 @@ def check_work_list(tc, sp, table, nb):
     # arrival counters: one per split pair, dense
     assert info.num_counters == len(counters) and sorted(counters) == list(range(len(counters)))
     assert p.workspace_bytes == (info.num_partials * G + info.num_piece_partials * 256) * (sp.head_dim + 2) * 4
-    units = -(-info.num_decode_items // (info.block_threads // 64))
+    units = -(-info.num_decode_items // W_)
     if info.decode_queue:   # no more workgroups than compute units; the decode items are drawn from a queue
         assert 0 < info.num_prefill_workgroups <= 256 and units > 0
         assert info.grid_blocks == info.num_prefill_workgroups + min(units, 256 - info.num_prefill_workgroups) <= 256
@@ -377,7 +377,7 @@ def test_work_lists_of_the_launch_forms(tc, name, Hq, Hkv, D, q_len, ctx, waves,
     table, mb, nb = W.make_tables(sp, np.random.default_rng(6))
     info = check_work_list(tc, sp, table, nb)
     assert (info.waves_per_item, info.rows_per_prefill_item) == (waves, rows)
-    assert info.block_threads == 64 * (8 if info.num_prefill_items else 4) // (waves if waves > 1 else 1)
+    assert info.block_threads == (512 if info.num_prefill_items else 256)   # the launch's, whatever the decode items are
 
 
 def _longest_sweep(p):
