@@ -23,7 +23,9 @@ constexpr int kWideWaves = 4;       // waves that share one decode item in a bat
 constexpr int kPrefillRows = 32 * kMixedWaves;  // (position, head) rows a prefill workgroup has room for, 32 per wave
 constexpr int kItemInts = 8;        // int32 fields per work item
 constexpr int kAppendInts = 4;      // int32 fields per append segment: first packed row, tokens, first token index, pool block
-constexpr int kCounterStride = 32;  // int32 between arrival counters: one per 128-byte line (see workgroup_arrives_last)
+// Arrival counters lie on a 128-byte line each (see workgroup_arrives_last) while all of them take no more than kCounterInts
+// int32 that way, closer together beyond: they are part of the image that every plan update clears and uploads.
+constexpr int kCounterLine = 32, kCounterInts = 8192;
 constexpr int kMaxSplitPages = 64;  // a decode split's page ids fit one wavefront register
 constexpr int kPrefillTileTokens = 64;  // KV tokens per LDS tile of the prefill branch
 constexpr int kNumCu = 256;         // compute units the work list is balanced for
@@ -81,7 +83,8 @@ struct tc_plan {
     int n_prefill_wg = 0;  // prefill workgroups: each runs one or more pieces
     int n_counters = 0;    // arrival counters: one per cut prefill item, one per (sequence, KV head) with several decode teams
     int n_decode_wg = 0;   // workgroups launched for the decode branch (fewer than the decode units when those are drawn from a queue)
-    int queue_counter = -1;  // index of the decode queue's two counters behind the arrival counters, or -1: no queue
+    int counter_stride = tc::kCounterLine;  // int32 between arrival counters
+    int queue_counter = -1;  // int32 from the first arrival counter to the decode queue's two (a line each, behind them), or -1: no queue
     int split_tokens = 0;
     int64_t total_pages = 0;
     std::vector<int32_t> q_start, ctx_len, page_off;  // host copies

@@ -501,7 +501,6 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     // blocks fill the chip): they draw decode items from the start, the prefill workgroups when their pieces are done.
     const int64_t n_decode_units = (int64_t)w.wg_fill.size();  // workgroups' worth of decode items
     const int64_t n_decode_wg = !queue ? n_decode_units : std::min<int64_t>(n_decode_units, std::max<int64_t>(slots - n_prefill_wg, 0));
-    const int64_t n_queue_counters = queue ? 2 : 0;
     const size_t off_append = 0, off_pages = (size_t)n_append * kAppendInts;
     const size_t off_valid = off_pages + (size_t)pages;
     const size_t off_prefill = off_valid + (size_t)pages;
@@ -509,8 +508,11 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     const size_t off_wg = off_pieces + (size_t)n_pieces * kItemInts;
     const size_t off_decode = off_wg + (size_t)n_prefill_wg;
     const size_t off_merge = off_decode + (size_t)n_decode * kItemInts;
-    const size_t off_counters = (off_merge + (size_t)n_merge * kItemInts + kCounterStride - 1) / kCounterStride * kCounterStride;  // each on a line of its own
-    const size_t n_counter_ints = (size_t)(n_counters + n_queue_counters) * kCounterStride;
+    const size_t off_counters = (off_merge + (size_t)n_merge * kItemInts + kCounterLine - 1) / kCounterLine * kCounterLine;
+    int counter_stride = kCounterLine;
+    while (counter_stride > 1 && n_counters * counter_stride > kCounterInts) counter_stride /= 2;
+    const size_t off_queue = ((size_t)n_counters * counter_stride + kCounterLine - 1) / kCounterLine * kCounterLine;  // from off_counters
+    const size_t n_counter_ints = queue ? off_queue + 2 * kCounterLine : (size_t)n_counters * counter_stride;
     const size_t total = std::max<size_t>(off_counters + n_counter_ints, 1);
     if (int err = begin_plan_host(p, total)) return fail(TC_ERR_DEVICE, std::string("host buffer of the plan: ") + hip_error_text(err));
     int32_t *H = p->host;
@@ -646,7 +648,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     p->n_prefill = (int)n_prefill; p->n_pieces = (int)n_pieces; p->n_prefill_wg = (int)n_prefill_wg; p->n_decode = (int)n_decode;
     p->n_merge = (int)n_merge; p->n_partials = (int)n_partials; p->n_counters = (int)n_counters; p->n_append = (int)n_append;
     p->n_piece_partials = (int)n_piece_partials; p->n_merge_prefill = (int)n_merge_prefill;
-    p->n_decode_wg = (int)n_decode_wg; p->queue_counter = queue ? (int)n_counters : -1;
+    p->n_decode_wg = (int)n_decode_wg; p->counter_stride = counter_stride; p->queue_counter = queue ? (int)off_queue : -1;
     p->off_append = off_append; p->off_pages = off_pages; p->off_valid = off_valid; p->off_prefill = off_prefill; p->off_pieces = off_pieces;
     p->off_wg = off_wg; p->off_decode = off_decode; p->off_merge = off_merge; p->off_counters = off_counters;
     p->host_n = total;

@@ -492,3 +492,34 @@ def test_one_long_decode_beside_a_chunk_does_not_take_many_short_ones_along(tc, 
     sp = W.custom_spec("along", Hq, Hkv, D, chunks + [1] * (len(long) + n_short), [0] * len(chunks) + long + [40 + i % 41 for i in range(n_short)])
     table, mb, nb = W.make_tables(sp, np.random.default_rng(13))
     assert check_work_list(tc, sp, table, nb).waves_per_item == waves
+
+
+COUNTER_IMAGE = """
+#include <cstdio>
+#include <cstdlib>
+#include "tc_internal.h"
+int main(int argc, char **argv) {
+    const int seqs = atoi(argv[1]), ctx = atoi(argv[2]), heads = atoi(argv[3]);
+    tc_kv_pool pool = {};
+    pool.num_q_heads = pool.num_kv_heads = heads; pool.head_dim = 64; pool.block_size = 16; pool.dtype = TC_BF16; pool.num_blocks = 1;
+    std::vector<int32_t> q_start(seqs + 1), ctx_len(seqs, ctx), table((size_t)seqs * (ctx / 16 + 1), 0);
+    for (int s = 0; s <= seqs; s++) q_start[s] = s;
+    tc_batch b = {seqs, q_start.data(), ctx_len.data(), table.data(), ctx / 16 + 1};
+    tc_plan *p = nullptr;
+    if (tc_plan_create_host(&pool, &b, &p)) return 1;
+    printf("%d %d %zu\\n", p->n_counters, p->counter_stride, (p->host_n - p->off_counters) * sizeof(int32_t));
+    tc_plan_destroy(p);
+}
+"""
+
+
+def test_arrival_counters_take_a_bounded_share_of_the_uploaded_image(tc, tmp_path):
+    """A line each for the pairs of few long decodes; closer together when there are many, so that clearing and uploading
+    them stays a small part of a plan update (32 KiB, or 4 bytes each beyond 8192 pairs)."""
+    src, exe, lib_dir = tmp_path / "t.cpp", tmp_path / "t", os.path.dirname(tc.LIB_PATH)
+    src.write_text(COUNTER_IMAGE)
+    cmd = f"g++ -std=c++17 -I {ROOT}/include -I {lib_dir}/csrc {src} {tc.LIB_PATH} -Wl,-rpath,{lib_dir} -Wl,-rpath-link,/opt/rocm/lib -o {exe}"
+    assert os.system(cmd) == 0
+    for seqs, pairs, stride, size in [(1, 8, 32, 1024), (32, 256, 32, 32768), (33, 264, 16, 16896), (512, 4096, 2, 32768), (2000, 16000, 1, 64000)]:
+        out = os.popen(f"LD_LIBRARY_PATH=/opt/rocm/lib {exe} {seqs} 20000 8").read().split()
+        assert [int(x) for x in out] == [pairs, stride, size], seqs
