@@ -44,7 +44,6 @@ struct Bf16 {
     typedef __bf16 t;
     typedef __bf16 x8 __attribute__((ext_vector_type(8)));
     typedef __bf16 x4 __attribute__((ext_vector_type(4)));
-    typedef __bf16 x2 __attribute__((ext_vector_type(2)));
     static __device__ __forceinline__ f32x16_t mfma32(x8 a, x8 b, f32x16_t c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
     static __device__ __forceinline__ f32x4_t mfma16(x8 a, x8 b, f32x4_t c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
     // 16x16x16: contraction over the 16 tokens of one page
@@ -57,7 +56,6 @@ struct Fp16 {
     typedef _Float16 t;
     typedef _Float16 x8 __attribute__((ext_vector_type(8)));
     typedef _Float16 x4 __attribute__((ext_vector_type(4)));
-    typedef _Float16 x2 __attribute__((ext_vector_type(2)));
     static __device__ __forceinline__ f32x16_t mfma32(x8 a, x8 b, f32x16_t c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
     static __device__ __forceinline__ f32x4_t mfma16(x8 a, x8 b, f32x4_t c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
     static __device__ __forceinline__ f32x4_t mfma16k16(x4 a, x4 b, f32x4_t c) { return __builtin_amdgcn_mfma_f32_16x16x16f16(a, b, c, 0, 0, 0); }
@@ -271,11 +269,6 @@ __device__ __forceinline__ float2 load2(const float *p) {
     if (!PEER) return *reinterpret_cast<const float2 *>(p);
     const uint64_t bits = __hip_atomic_load(reinterpret_cast<const uint64_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return float2{__uint_as_float((uint32_t)bits), __uint_as_float((uint32_t)(bits >> 32))};
-}
-template <bool PEER>
-__device__ __forceinline__ float load1(const float *p) {
-    if (!PEER) return *p;
-    return __uint_as_float(__hip_atomic_load(reinterpret_cast<const uint32_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
@@ -964,7 +957,9 @@ __device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ it, 
 // decode-only kernel within 168 VGPRs (three waves per SIMD; a third stage spills there), and serve best beside a
 // prefill chunk as well: what a compute unit streams is bound by its outstanding requests, not by the pages its waves ask
 // for, and more of them in flight only queue up behind each other (four stages against two: 128 tokens at 2048 with 16 decodes
-// 39.3 / 37.6 us, 1024 with 16 78.7 / 76.8, three first chunks with 16 41.7 / 40.3, prefill-heavy 197.9 / 197.8).
+// 39.3 / 37.6 us, 1024 with 16 78.7 / 76.8, three first chunks with 16 41.7 / 40.3, prefill-heavy 197.9 / 197.8; over 58 batches
+// of 32-256 decodes, run by single waves beside 64 to 512 tokens, four stages are 0.7 % slower on the mean, from 1 % faster to 1.6 %
+// slower).
 constexpr int kDecodeStages = 2;
 // A split run by a whole workgroup of the decode-only launch: 2 and 5 measured 4 % and 15-25 % slower on 8 to 96 decodes.
 constexpr int kWideStages = 3;
@@ -1017,7 +1012,7 @@ __device__ __forceinline__ void decode_take_new_token(const AttnArgs &A, int kvh
 // the token-minor V block (four lanes per 128-byte line; with a thread per 8-element piece every lane of a store had a
 // line of its own and a workgroup took 5 us more).  kAppendPerThread elements per thread, all loads before the stores.
 // `segments`: the plan's append segments of these sequences, one each (one token).  Used by the last workgroups of the
-// attention launch of a batch of decodes and by the append kernel.
+// attention launch of a batch of decodes whose splits are run by single waves.
 constexpr int kAppendPerThread = 4;
 template <int D>
 __device__ __forceinline__ void append_decode_rows(uint16_t *k_pool, uint16_t *v_pool, const uint16_t *__restrict__ k_new,
@@ -1499,7 +1494,7 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : kDecode
 #endif
 }
 
-// A batch of few decodes: one workgroup of kWideWaves waves per split (decode_item_wide), one per compute unit, with
+// A batch of few decodes: one workgroup of kWideWaves waves per split (decode_item_wide), one or two per compute unit, with
 // registers for kWideStages - 1 pages in flight per wave; the wave that takes a sequence's new token from k_new / v_new also
 // stores its row.  Arguments as above; the prefill lists are empty.
 template <int D, class E>
@@ -1708,8 +1703,8 @@ static int allow_prefill_lds(int device) {
 template <int D, class E>
 static int launch_attention_d(const tc_plan *p, const AttnArgs &A, int launches, hipStream_t st) {
     int grid = (launches & (kLaunchAttention | kLaunchFused)) ? p->grid_blocks() : 0;
-    // A batch of decodes whose rows this launch stores: workgroups at the back of the grid do it (four (row, KV head,
-    // 8-element piece) units per thread).  A batch with a prefill chunk never gets here with k_new set (see launch_attention).
+    // A batch of decodes whose rows this launch stores: workgroups at the back of the grid do it (kAppendPerThread
+    // elements per thread).  Where a split is run by a whole workgroup its wave with the new token does it.  A batch with a prefill chunk never gets here with k_new set (see launch_attention).
     int n_front = 0;
     if (grid > 0 && A.k_new && p->n_pieces == 0 && p->waves_per_item == 1) {
         const int64_t units = (int64_t)p->n_append * p->Hkv * D;  // a row's element of one KV head
