@@ -245,7 +245,8 @@ static void level_prefill(std::vector<PlanRowBlock> &blocks, std::vector<PlanPie
 //   cut            64 at 3000 33.2 / 29.1, at 60000 160.2 / 132.3 (cut in eight at most, 256 rows leave units empty); 256 at 3000
 //                  36.2 / 32.7, at 8000 54.3 / 52.8, at 20000 94.9 / 100.9, at 60000 227.3 / 269.9; 40/8 heads: 204 at 3000 (72 items,
 //                  uncut) 37.6 / 52.5, 102 at 20000 74.3 / 76.3; head_dim 64: 256 at 3000 24.2 / 22.6, at 8000 34.6 / 36.2
-//   with decodes   head_dim 64, 8/8 heads, 455 at 9062 with 37 (mean 1400) 39.5 / 50.2; 32/8 heads, 128 at 8000 with 8 (mean 500) 31.6 / 29.4
+//   with decodes   head_dim 64, 8/8 heads, 455 at 9062 with 37 (mean 1400) 39.5 / 50.2; 32/8 heads, 128 at 8000 with 8 (mean 500) 31.6 / 29.4;
+//                  head_dim 128, 256 at 2048 with 32 of 512-4096 64.1 / 59.9, 128 53.4 / 52.1 with 24 of them
 static int choose_rows_per_item(const tc_plan *p, int S, int64_t decode_bytes) {
     const int whole_pos = kPrefillRows / p->G, half_pos = kPrefillRows / 2 / p->G;
     int64_t whole = 0, half = 0, longest = 0;   // items of 256 and of 128 rows, tokens of the longest sweep
@@ -276,14 +277,15 @@ static int choose_rows_per_item(const tc_plan *p, int S, int64_t decode_bytes) {
         if (half * 4 <= kNumCu) k_half = prefill_cuts(tiles, half, decode_bytes, kCutHalfTileUs);
         add_whole = (p->D / 128.0) * (k_half == 1 ? 12.0 : 7.0);
     }
-    // time of a tile: alone on a unit's SIMD, beside a second wave on a part of the chip, and on a full chip
-    const double half_us = d64 ? (cut ? 0.67 : 0.62) : 1.1;
-    const double whole_us = !cut ? (d64 ? 1.04 : 1.6) : whole * k_whole > kNumCu / 2 ? kTileUs * (p->D / 128.0) : (d64 ? 0.75 : 1.25);
+    // time of a tile in an item of either size, by how full the chip is with them
+    const bool half_full = half * k_half > kNumCu / 2, whole_full = whole * k_whole > kNumCu / 2;
+    const double half_us = !cut ? (d64 ? 0.62 : 1.1) : (half_full ? 1.08 : 0.95) * (d64 ? 0.61 : 1.0);
+    const double whole_us = !cut ? (d64 ? 1.04 : 1.6) : whole_full ? kTileUs * (p->D / 128.0) : (d64 ? 0.75 : 1.25);
     double t_whole = tiles * whole_us / k_whole + add_whole, t_half = tiles * half_us / k_half;
-    if (decode_bytes > 0) {  // the unit times of all pieces (3 us each, at head_dim 64 two, and their tiles) and of the decodes
-        const double piece_us = d64 ? 2.0 : 3.0, decode_us = (double)decode_bytes / ((cut ? 35.0e3 : 20.0e3) * kNumCu);
-        t_whole = std::max(t_whole, (whole_tiles * (d64 ? 1.04 : 1.6) + whole * k_whole * piece_us) / kNumCu + decode_us);
-        t_half = std::max(t_half, (half_tiles * half_us + half * k_half * piece_us) / kNumCu + decode_us);
+    if (decode_bytes > 0) {  // unit times: a piece takes 3 us beside its tiles, 6 if it leaves a partial result (two thirds at head_dim 64)
+        const double s = d64 ? 0.65 : 1.0, decode_us = (double)decode_bytes / ((cut ? 30.0e3 : 20.0e3) * kNumCu);
+        t_whole = std::max(t_whole, s * (whole_tiles * (cut ? 1.85 : 1.6) + whole * k_whole * (k_whole > 1 ? 6.0 : 3.0)) / kNumCu + decode_us);
+        t_half = std::max(t_half, (half_tiles * half_us + s * half * k_half * (k_half > 1 ? 6.0 : 3.0)) / kNumCu + decode_us);
     }
     return t_half <= t_whole ? kPrefillRows / 2 : kPrefillRows;
 }

@@ -421,6 +421,7 @@ def test_small_items_never_make_the_longest_sweep_slower(tc, G, D, us, overhead)
     (32, 8, 128, [300] + [1] * 4, [0] + [500] * 4, 128),
     (8, 8, 64, [455] + [1] * 37, [9062] + [1400] * 37, 256),    # pieces of both sizes are as long, halves take all units
     (32, 8, 64, [128] + [1] * 8, [8000] + [500] * 8, 128),
+    (32, 8, 128, [256] + [1] * 32, [2048] + [2270] * 32, 128),  # neither size is worth cutting more than once under the decodes
 ])
 def test_rows_per_item(tc, Hq, Hkv, D, q_len, ctx, rows):
     sp = W.custom_spec("rows", Hq, Hkv, D, q_len, ctx)
