@@ -83,7 +83,7 @@ struct tc_plan {
     int n_prefill_wg = 0;  // prefill workgroups: each runs one or more pieces
     int n_counters = 0;    // arrival counters: one per cut prefill item, one per (sequence, KV head) with several decode teams
     int n_decode_wg = 0;   // workgroups launched for the decode branch (fewer than the decode units when those are drawn from a queue)
-    int counter_stride = tc::kCounterLine;  // int32 between arrival counters
+    int counter_stride = tc::kCounterLine;  // int32 between arrival counters; the items of the image hold a counter's index times this
     int queue_counter = -1;  // int32 from the first arrival counter to the decode queue's two (a line each, behind them), or -1: no queue
     int split_tokens = 0;
     int64_t total_pages = 0;

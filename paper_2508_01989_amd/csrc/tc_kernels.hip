@@ -83,7 +83,6 @@ struct AttnArgs {
     int n_prefill, n_decode; // prefill workgroups, decode wave slots
     int Hq, Hkv, G;
     int fused;               // 1: the last piece or team of a split pair to finish combines its partial results
-    int counter_stride;      // int32 from one arrival counter to the next
     int queue;               // where the decode queue's two counters (next unit, workgroups that have left; a line each) lie, or -1
     float scale_log2;        // softmax scale times log2(e)
 };
@@ -935,7 +934,7 @@ __device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ it, 
         stores_done();
         __syncthreads();  // every wave has left the sweep: LDS is free
         int *const arrived = reinterpret_cast<int *>(lds);
-        int32_t *const counter = A.counters + pc[PP_COUNTER] * A.counter_stride;
+        int32_t *const counter = A.counters + pc[PP_COUNTER];
         if (tid == 0) *arrived = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
         if (*arrived != p_k - 1) return;
@@ -1292,7 +1291,7 @@ __device__ void decode_item(const AttnArgs &A, const int32_t *__restrict__ it, f
     // A partial result was left, so the team is the whole workgroup.  The last of the pair's workgroups to get here
     // combines all of them.
     const int32_t *mg = A.merge + (int64_t)merge_item * kItemInts;
-    if (!workgroup_arrives_last(A.counters + mg[MG_COUNTER] * A.counter_stride, mg[MG_NSPLIT], reinterpret_cast<int *>(team_lds), tid)) return;
+    if (!workgroup_arrives_last(A.counters + mg[MG_COUNTER], mg[MG_NSPLIT], reinterpret_cast<int *>(team_lds), tid)) return;
     merge_pair<D, E, true, kMergeBatch>(A.ws_o, A.ws_ml, mg[MG_SLOT0], mg[MG_NSPLIT], G, A.out + ((int64_t)qrow * A.Hq + kvh * G) * D, team_lds, tid,
                            wg_waves * 64);
 }
@@ -1367,7 +1366,7 @@ __device__ void decode_item_wide(const AttnArgs &A, const int32_t *__restrict__ 
     if (slot < 0 || !A.fused) return;
     stores_done();
     const int32_t *mg = A.merge + (int64_t)merge_item * kItemInts;
-    if (!workgroup_arrives_last(A.counters + mg[MG_COUNTER] * A.counter_stride, mg[MG_NSPLIT], reinterpret_cast<int *>(lds), tid)) return;
+    if (!workgroup_arrives_last(A.counters + mg[MG_COUNTER], mg[MG_NSPLIT], reinterpret_cast<int *>(lds), tid)) return;
     merge_pair<D, E, true, STORE && D == 128 ? kWideMergeBatch : kMergeBatch>(A.ws_o, A.ws_ml, mg[MG_SLOT0], mg[MG_NSPLIT], G,
                                                                              A.out + ((int64_t)qrow * A.Hq + kvh * G) * D, lds, tid, R * 64);
 }
@@ -1395,7 +1394,6 @@ struct AttnScalars {
     int n_prefill, n_decode;
     int Hq, Hkv, G;
     int fused;
-    int counter_stride;
     int queue;
     int n_partials;
     int n_front, n_append_rows;  // a batch of decodes whose rows this launch stores: the workgroups (the last of the grid) that do it, rows
@@ -1428,7 +1426,7 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : kDecode
     // workspace: decode partials [n_partials][G][D], their (max, sum) pairs [n_partials][G][2], then the piece regions
     A.ws_o = ws; A.ws_ml = ws + (int64_t)sc.n_partials * sc.G * D; A.ws_pieces = A.ws_ml + (int64_t)sc.n_partials * sc.G * 2;
     A.n_prefill = sc.n_prefill; A.n_decode = sc.n_decode; A.Hq = sc.Hq; A.Hkv = sc.Hkv; A.G = sc.G; A.fused = sc.fused; A.queue = sc.queue;
-    A.counter_stride = sc.counter_stride; A.scale_log2 = sc.scale_log2;
+    A.scale_log2 = sc.scale_log2;
     constexpr int NS = kDecodeStages;
     if constexpr (WAVES == kDecodeWaves) {
         const int first_append_wg = (int)gridDim.x - sc.n_front;
@@ -1511,8 +1509,7 @@ __global__ void __launch_bounds__(kWideWaves * 64, 2)
     A.k_pool = k_pool; A.v_pool = v_pool; A.q = q; A.k_new = k_new; A.v_new = v_new; A.out = out; A.pages = pages; A.decode = decode;
     A.merge = merge; A.counters = counters;
     A.ws_o = ws; A.ws_ml = ws + (int64_t)sc.n_partials * sc.G * D;
-    A.n_decode = sc.n_decode; A.Hq = sc.Hq; A.Hkv = sc.Hkv; A.G = sc.G; A.fused = sc.fused; A.counter_stride = sc.counter_stride;
-    A.scale_log2 = sc.scale_log2;
+    A.n_decode = sc.n_decode; A.Hq = sc.Hq; A.Hkv = sc.Hkv; A.G = sc.G; A.fused = sc.fused; A.scale_log2 = sc.scale_log2;
     decode_item_wide<D, E, kWideStages, kWideWaves, true>(A, decode + (int64_t)blockIdx.x * kItemInts, reinterpret_cast<float *>(lds));
 #ifdef TC_WG_TRACE
     wg_trace(t_start, t_start, true);
@@ -1712,7 +1709,7 @@ static int launch_attention_d(const tc_plan *p, const AttnArgs &A, int launches,
         n_front = (int)((units + per_wg - 1) / per_wg);
         grid += n_front;
     }
-    const AttnScalars sc = {A.n_prefill, A.n_decode, A.Hq, A.Hkv, A.G, A.fused, A.counter_stride, A.queue, p->n_partials, n_front, p->n_append, A.scale_log2};
+    const AttnScalars sc = {A.n_prefill, A.n_decode, A.Hq, A.Hkv, A.G, A.fused, A.queue, p->n_partials, n_front, p->n_append, A.scale_log2};
     const int32_t *append = p->dev + p->off_append;
     if (grid > 0 && p->n_pieces > 0) {
         const int lds = PrefillCfg<D>::kLdsBytes;  // the decode workgroups of the launch need less, for any G
@@ -1775,7 +1772,6 @@ int launch_attention(const tc_plan *p, const tc_kv_pool *pool, const void *q, co
     A.Hkv = p->Hkv;
     A.G = p->G;
     A.fused = (launches & kLaunchFused) ? 1 : 0;
-    A.counter_stride = p->counter_stride;
     A.queue = p->queue_counter;
     A.scale_log2 = scale * 1.4426950408889634f;
     hipStream_t st = (hipStream_t)stream;

@@ -567,7 +567,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
                 pf[PF_PAGEOFF] = p->page_off[x.seq]; pf[PF_NPAGES] = p->page_off[x.seq + 1] - p->page_off[x.seq];
                 if (x.k == 1) continue;
                 mg[MG_SEQ] = x.seq; mg[MG_KVH] = h; mg[MG_QROW] = p->q_start[x.seq] + x.pos0;
-                mg[MG_SLOT0] = next_region; mg[MG_NSPLIT] = x.k; mg[MG_COUNTER] = next_counter++; mg[MG_NPOS] = x.npos; mg[MG_ITEM] = item;
+                mg[MG_SLOT0] = next_region; mg[MG_NSPLIT] = x.k; mg[MG_COUNTER] = counter_stride * next_counter++; mg[MG_NPOS] = x.npos; mg[MG_ITEM] = item;
                 mg += kItemInts;
                 next_region += x.k;
             }
@@ -596,7 +596,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
                     q[PP_ITEM] = x.block * Hkv + h; q[PP_T0] = x.t0; q[PP_T1] = x.t1;
                     q[PP_SLOT] = blk.k > 1 ? blk.slot0 + h * blk.k : -1;
                     q[PP_K] = blk.k; q[PP_C] = x.c;
-                    q[PP_COUNTER] = blk.k > 1 ? first_counter[x.block] + h : -1;
+                    q[PP_COUNTER] = blk.k > 1 ? counter_stride * (first_counter[x.block] + h) : -1;
                     q[PP_LAST] = u + 1 == j;
                 }
             }
@@ -614,7 +614,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
             w.slot0[(size_t)s * Hkv + h] = next_slot;
             w.merge_of[(size_t)s * Hkv + h] = (int32_t)((mg - (H + off_merge)) / kItemInts);
             mg[MG_SEQ] = s; mg[MG_KVH] = h; mg[MG_QROW] = p->q_start[s]; mg[MG_SLOT0] = next_slot; mg[MG_NSPLIT] = nt;
-            mg[MG_COUNTER] = next_counter++; mg[MG_NPOS] = 1; mg[MG_ITEM] = -1;
+            mg[MG_COUNTER] = counter_stride * next_counter++; mg[MG_NPOS] = 1; mg[MG_ITEM] = -1;
             mg += kItemInts;
             next_slot += nt;
         }
@@ -735,6 +735,11 @@ tc_status tc_plan_copy_items(const tc_plan *p, int32_t kind, int32_t *dst, size_
     else { tc::set_error("kind must be 0, 1, 2, 3 or 4"); return TC_ERR_ARG; }
     n = std::min(n, cap_items);
     if (n) std::memcpy(dst, p->host + off, n * tc::kItemInts * sizeof(int32_t));
+    if (kind == 2 || kind == 3)  // the image says where a counter lies, the item which one it is
+        for (size_t i = 0; i < n; i++) {
+            int32_t &c = dst[i * tc::kItemInts + (kind == 2 ? tc::MG_COUNTER : tc::PP_COUNTER)];
+            if (c > 0) c /= p->counter_stride;
+        }
     return TC_OK;
 }
 
