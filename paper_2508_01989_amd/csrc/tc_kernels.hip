@@ -71,10 +71,8 @@ struct AttnArgs {
     const uint16_t *k_new, *v_new;  // this iteration's K/V rows, or null when tc_kv_append has stored them already
     uint16_t *out;
     const int32_t *pages;    // page ids of all sequences, CSR by sequence
-    const int32_t *prefill;  // work items
-    const int32_t *pieces;   // KV tile ranges of prefill items, stored workgroup by workgroup
-    const int32_t *wg_first; // first piece of every prefill workgroup
-    const int32_t *decode;
+    const int32_t *records;  // pieces of prefill items
+    const int32_t *decode;   // work items
     const int32_t *merge;    // merge items: where the partial results of a split pair lie
     int32_t *counters;       // arrival counters of split pairs; zero before and after every launch
     float *ws_o;             // [n_partials][G][D]
@@ -464,20 +462,26 @@ struct PiecePartial {
     }
 };
 
-// Output rows of a prefill item from a lane's accumulators and its row's sum: o / l, rounded to the element type.
+// Output rows of a prefill item from a lane's accumulators and its row's sum: o / l, rounded to the element type.  The two lanes of a
+// row hold alternate groups of four elements; they exchange every other one, so that a lane stores eight adjacent elements (16 bytes).
 template <int D, class E>
-__device__ __forceinline__ void prefill_write_rows(uint16_t *row, const f32x16 (&o)[D / 32], float l, int hh) {
+__device__ __forceinline__ void prefill_write_rows(uint16_t *row, bool valid, const f32x16 (&o)[D / 32], float l, int hh) {
     typedef typename E::x4 x4;
     typedef typename E::t el;
     const float inv = 1.f / l;
 #pragma unroll
     for (int c = 0; c < D / 32; c++)
 #pragma unroll
-        for (int q4 = 0; q4 < 4; q4++) {
-            x4 w;
+        for (int p = 0; p < 2; p++) {
+            x4 even, odd;
 #pragma unroll
-            for (int e = 0; e < 4; e++) w[e] = (el)(o[c][4 * q4 + e] * inv);
-            *reinterpret_cast<x4 *>(row + 32 * c + 8 * q4 + 4 * hh) = w;
+            for (int e = 0; e < 4; e++) {
+                even[e] = (el)(o[c][8 * p + e] * inv);
+                odd[e] = (el)(o[c][8 * p + 4 + e] * inv);
+            }
+            const u32x2 a = __builtin_bit_cast(u32x2, even), b = __builtin_bit_cast(u32x2, odd);
+            const auto s0 = __builtin_amdgcn_permlane32_swap(a[0], b[0], false, false), s1 = __builtin_amdgcn_permlane32_swap(a[1], b[1], false, false);
+            if (valid) *reinterpret_cast<u32x4 *>(row + 32 * c + 16 * p + 8 * hh) = u32x4{s0[0], s1[0], s0[1], s1[1]};
         }
 }
 
@@ -517,13 +521,6 @@ __device__ __forceinline__ void lds_load_runs(const __attribute__((address_space
     if constexpr (N > 1) __builtin_amdgcn_global_load_lds(src, dst, 16, 1024, 0);
     if constexpr (N > 2) __builtin_amdgcn_global_load_lds(src, dst, 16, 2048, 0);
     if constexpr (N > 3) __builtin_amdgcn_global_load_lds(src, dst, 16, 3072, 0);
-}
-
-// Page id of page `page_in_tile` of KV tile `tile` (a scalar load; past the end of the sequence the
-// last page is named, whose copy is never used).
-template <int D>
-__device__ __forceinline__ int prefill_page_id(const int32_t *__restrict__ pages, int n_pages, int tile, int page_in_tile) {
-    return pages[min(tile * PrefillCfg<D>::kTilePages + page_in_tile, n_pages - 1)];
 }
 
 // Tile copies.  The 8 waves of a workgroup share every tile.  A copier moves one page of a tile (copier
@@ -697,6 +694,13 @@ __device__ __forceinline__ float next_reference_max(float m_run, float row_max_l
     return row_max_log2 > m_run + kMaxSlack ? row_max_log2 : m_run;
 }
 
+// A piece costs its start and its end on top of the sweep, and both are chains of accesses to memory (about 0.9 us each past the
+// caches, which a kernel finds cold): everything a workgroup has to know lies in one record whose place follows from its index, the
+// page ids of the first tiles among it, and the sweep begins when K(0), V(0) and Q have landed.  (With the piece, its item, the
+// page ids and five tiles one after the other the start took 4.0 us at head_dim 128 and 2.4 at 64; with the outputs in 8-byte stores the end
+// 2.4.  First chunks, 32/8 heads, attention and append: 2048 tokens 57.1 -> 54.4 us, at head_dim 64 39.0 -> 36.8, 1500 40.5 -> 37.6; 16/2 heads, 1207
+// 34.7 -> 30.9; 1024 at 4096 87.8 -> 84.7.)
+//
 // The KV sweep is software-pipelined inside every wave, in units of half a tile (32 tokens), three
 // halves deep: in one phase the matrix cores compute the scores of half h + 1 and accumulate P V of
 // half h - 1 while the vector ALU turns the scores of half h into probabilities.  (MFMA and VALU
@@ -712,7 +716,7 @@ __device__ __forceinline__ float next_reference_max(float m_run, float row_max_l
 // which set the pace, are spared them (1 % on a long sweep; copies by waves 4-7 alone measured 0.2 %
 // slower than one tensor per wave group).
 template <int D, class E>
-__device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ it, const int32_t *__restrict__ pc, char *lds) {
+__device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ rec, int kvh, char *lds) {
     using C = PrefillCfg<D>;
     using W = PrefillWave<D, E>;
     using x8 = typename E::x8;
@@ -727,9 +731,9 @@ __device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ it, 
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, hh = lane >> 5;
-    const int kvh = it[PF_KVH], pos0 = it[PF_POS0], npos = it[PF_NPOS], qrow0 = it[PF_QROW0], ctx = it[PF_CTX];
-    const int n_pages = it[PF_NPAGES];
-    const int32_t *pages = A.pages + it[PF_PAGEOFF];
+    const int pos0 = rec[RC_POS0], npos = rec[RC_NPOS], qrow0 = rec[RC_QROW0], ctx = rec[RC_CTX];
+    const int n_pages = rec[RC_NPAGES];
+    const int32_t *pages = A.pages + rec[RC_PAGEOFF];
     const int G = A.G;
     const int n_rows = npos * G;
     // this lane's row of the workgroup's 256: position pos0 + R / G, head kvh * G + R % G
@@ -741,8 +745,8 @@ __device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ it, 
     // first position of the rows this wave owns (wave-uniform): tiles that end at or before it need no mask
     const int wave_pmin = ctx + pos0 + min(wave * 32, n_rows - 1) / G;
     const int kv_len = ctx + pos0 + npos;  // tokens this workgroup may read (all appended already)
-    // KV tiles [t_begin, t_end) of the item; p_slot < 0: the whole range, results go to `out`
-    const int t_begin = pc[PP_T0], t_end = pc[PP_T1], p_slot = pc[PP_SLOT], p_k = pc[PP_K];
+    // KV tiles [t_begin, t_end) of the item; region < 0: the whole range, results go to `out`
+    const int t_begin = rec[RC_T0], t_end = rec[RC_T1], region = rec[RC_REGION], p_k = rec[RC_K];
     const int n_sweep = t_end - t_begin;
     const float c_log2 = A.scale_log2;
     char *const lds_k = lds, *const lds_v = lds + C::kStages * C::kTileBytes;
@@ -772,27 +776,26 @@ __device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ it, 
     const int pg = cpk.page_in_tile;
     int idk_cur = 0, idv_cur = 0;  // pages this wave copies in step 0
     // The page ids for the copies of step j are fetched in step j - (NS - 2) into slot j mod (NS - 2) of this
-    // wave (K ids, then V ids); those of steps 1 .. NS - 3 are fetched here.
+    // wave (K ids, then V ids).
     char *const idk_slots = lds + 2 * NS * C::kTileBytes + (2 * wave) * (C::kIdSlots * kIdSlotBytes);
     char *const idv_slots = idk_slots + C::kIdSlots * kIdSlotBytes;
     if (copier) {
+        // In the order in which the sweep needs them.  The ids of all these pages lie in the record, so that only two accesses to
+        // memory follow one after the other before the first product: the record, and the tiles (and Q).
+        const int32_t *ids = rec + RC_IDS + pg;
+        auto id = [&](int t) { return ids[t * C::kTilePages]; };
+        static_assert(NS + 1 == (kRecordInts - RC_IDS) / C::kTilePages, "the record holds the ids of the tiles copied here and in step 0");
+        cpk.copy(id(0), 0);
+        cpv.copy(id(0), 0);
 #pragma unroll
-        for (int t = 0; t < NS - 1; t++) {
-            cpk.copy(prefill_page_id<D>(pages, n_pages, t_begin + t, pg), t);
-            cpv.copy(prefill_page_id<D>(pages, n_pages, t_begin + t, pg), t);
+        for (int t = 1; t < NS; t++) {
+            cpk.copy(id(t), t);
+            if (t < NS - 1) cpv.copy(id(t), t);
         }
-        cpk.copy(prefill_page_id<D>(pages, n_pages, t_begin + NS - 1, pg), NS - 1);
-        idk_cur = prefill_page_id<D>(pages, n_pages, t_begin + NS, pg);
-        idv_cur = prefill_page_id<D>(pages, n_pages, t_begin + NS - 1, pg);
-#pragma unroll
-        for (int t = 1; t < C::kIdSlots; t++) {
-            page_id_fetch(pages + min((t_begin + t + NS) * C::kTilePages + pg, n_pages - 1), idk_slots + t * kIdSlotBytes);
-            page_id_fetch(pages + min((t_begin + t + NS - 1) * C::kTilePages + pg, n_pages - 1), idv_slots + t * kIdSlotBytes);
-        }
-        wait_all_loads();
-#pragma unroll
-        for (int t = 0; t < NS - 1; t++)
-            if ((t_begin + t + 1) * C::kTileTokens > kv_len) prefill_fix_tail<D>(lds_v + t * C::kTileBytes, t_begin + t, pg, lane, kv_len);
+        idk_cur = id(NS);
+        idv_cur = id(NS - 1);
+        wait_loads_but<(2 * NS - 3) * C::kRuns>();  // all but K(0) and V(0)
+        if ((t_begin + 1) * C::kTileTokens > kv_len) prefill_fix_tail<D>(lds_v, t_begin, pg, lane, kv_len);
     }
     __syncthreads();
     x8 kf[KS];     // K fragments of the half whose scores are computed next
@@ -914,34 +917,36 @@ __device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ it, 
         // steps 0 .. n_plain - 1 prepare tiles that lie wholly at or before every row's position
         // and before the last token: tile t needs no mask if (t + 1) * 64 - 1 <= wave_pmin
         const int n_plain = max(0, min(n_sweep - 1, (wave_pmin + 1) / C::kTileTokens - t_begin - 1));
+        if (copier) wait_loads_but<(2 * NS - 4) * C::kRuns>();  // K(1), for step 0; the others are waited for in its end
         int j = 0;
         for (; j < n_plain; j++) step(j, no, yes);
         for (; j + 1 < n_sweep; j++) step(j, yes, yes);
         step(j, yes, no);
         W::pv(vf, pb, o);  // the product of the last half
+        if (copier) wait_all_loads();  // copies past the end of the range, before the LDS is used for anything else
     }
 
     float l = half_swap_sum(l_run);
-    if (p_slot >= 0) {
+    if (region >= 0) {
         // A piece of a cut item: every lane leaves its unnormalised accumulators, and the rows' running maximum
         // (log2 domain) and sum, in the piece's region of the workspace as they lie in registers; rows that see no
         // key of this piece carry (m, l, o) = (-1e30, 0, 0) and get weight 0 in the combination.
-        float *const region = A.ws_pieces + (int64_t)(p_slot + pc[PP_C]) * PiecePartial<D>::kFloats;
-        PiecePartial<D>::store(region, wave, lane, o, m_run, l, A.fused != 0);
+        const int first = region + kvh * p_k;  // region of the item's piece 0 for this KV head
+        PiecePartial<D>::store(A.ws_pieces + (int64_t)(first + rec[RC_C]) * PiecePartial<D>::kFloats, wave, lane, o, m_run, l, A.fused != 0);
         if (!A.fused) return;
         // The last of the item's pieces to get here combines them all (the others leave; nobody waits).  Every
         // wave waits for its own stores to complete, the workgroup meets, one thread counts the arrival.
         stores_done();
         __syncthreads();  // every wave has left the sweep: LDS is free
         int *const arrived = reinterpret_cast<int *>(lds);
-        int32_t *const counter = A.counters + pc[PP_COUNTER];
+        int32_t *const counter = A.counters + rec[RC_COUNTER] + kvh * rec[RC_CSTRIDE];
         if (tid == 0) *arrived = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
         if (*arrived != p_k - 1) return;
         if (tid == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
-        PiecePartial<D>::template combine<true>(A.ws_pieces + (int64_t)p_slot * PiecePartial<D>::kFloats, p_k, wave, lane, o, l);
+        PiecePartial<D>::template combine<true>(A.ws_pieces + (int64_t)first * PiecePartial<D>::kFloats, p_k, wave, lane, o, l);
     }
-    if (row_valid) prefill_write_rows<D, E>(A.out + row_off, o, l, hh);
+    prefill_write_rows<D, E>(A.out + row_off, row_valid, o, l, hh);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1411,9 +1416,7 @@ template <int D, class E, int WAVES, bool WIDE>
 __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : kDecodeWgPerCu)
     mixed_attention_kernel(uint16_t *k_pool, uint16_t *v_pool, const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_new,
                            const uint16_t *__restrict__ v_new, uint16_t *__restrict__ out, const int32_t *__restrict__ pages,
-                           const int32_t *__restrict__ prefill, const int32_t *__restrict__ pieces,
-                           const int32_t *__restrict__ wg_first, const int32_t *__restrict__ decode,
-                           const int32_t *__restrict__ merge, const int32_t *__restrict__ append, int32_t *counters, float *ws,
+                           const int32_t *__restrict__ records, const int32_t *__restrict__ decode, const int32_t *__restrict__ merge, const int32_t *__restrict__ append, int32_t *counters, float *ws,
                            const AttnScalars sc) {
     extern __shared__ __align__(16) char lds[];
 #ifdef TC_WG_TRACE
@@ -1421,8 +1424,8 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : kDecode
     long long t_mid = t_start;
 #endif
     AttnArgs A;
-    A.k_pool = k_pool; A.v_pool = v_pool; A.q = q; A.k_new = k_new; A.v_new = v_new; A.out = out; A.pages = pages; A.prefill = prefill;
-    A.pieces = pieces; A.wg_first = wg_first; A.decode = decode; A.merge = merge; A.counters = counters;
+    A.k_pool = k_pool; A.v_pool = v_pool; A.q = q; A.k_new = k_new; A.v_new = v_new; A.out = out; A.pages = pages;
+    A.records = records; A.decode = decode; A.merge = merge; A.counters = counters;
     // workspace: decode partials [n_partials][G][D], their (max, sum) pairs [n_partials][G][2], then the piece regions
     A.ws_o = ws; A.ws_ml = ws + (int64_t)sc.n_partials * sc.G * D; A.ws_pieces = A.ws_ml + (int64_t)sc.n_partials * sc.G * 2;
     A.n_prefill = sc.n_prefill; A.n_decode = sc.n_decode; A.Hq = sc.Hq; A.Hkv = sc.Hkv; A.G = sc.G; A.fused = sc.fused; A.queue = sc.queue;
@@ -1438,11 +1441,13 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : kDecode
     const int wg = (int)blockIdx.x;
     if (WAVES == kMixedWaves && (int)blockIdx.x < A.n_prefill) {
         if constexpr (WAVES == kMixedWaves) {
-            const int32_t *pc = pieces + (int64_t)wg_first[blockIdx.x] * kItemInts;
+            const int kvh = wg % A.Hkv;
+            const int32_t *rec = records + (int64_t)(wg / A.Hkv) * kRecordInts;
             for (;;) {
-                prefill_item<D, E>(A, prefill + (int64_t)pc[PP_ITEM] * kItemInts, pc, lds);
-                if (pc[PP_LAST]) break;
-                pc += kItemInts;
+                const int next = rec[RC_NEXT];
+                prefill_item<D, E>(A, rec, kvh, lds);
+                if (next < 0) break;
+                rec = records + (int64_t)next * kRecordInts;
                 __syncthreads();  // the next piece's tile copies reuse the LDS
             }
         }
@@ -1546,7 +1551,7 @@ __global__ void __launch_bounds__(kMixedWaves * 64) prefill_merge_kernel(const i
     f32x16 o[D / 32];
     float l;
     PiecePartial<D>::template combine<false>(ws_pieces + (int64_t)mg[MG_SLOT0] * PiecePartial<D>::kFloats, mg[MG_NSPLIT], wave, lane, o, l);
-    if (R < npos * G) prefill_write_rows<D, E>(out + ((int64_t)(qrow0 + pos0 + R / G) * Hq + kvh * G + R % G) * D, o, l, hh);
+    prefill_write_rows<D, E>(out + ((int64_t)(qrow0 + pos0 + R / G) * Hq + kvh * G + R % G) * D, R < npos * G, o, l, hh);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1587,7 +1592,7 @@ int upload_plan(tc_plan *p, void *stream) {
     if (e != hipSuccess) return (int)e;
     if (p->device >= 0 && p->device != device) return (int)hipErrorInvalidDevice;
     p->device = device;
-    if (p->host_n > p->dev_cap) {
+    if (p->upload_n > p->dev_cap) {
         if (p->dev) (void)hipFree(p->dev);
         p->dev = nullptr;
         p->dev_cap = 0;
@@ -1601,7 +1606,7 @@ int upload_plan(tc_plan *p, void *stream) {
         if (e != hipSuccess) return (int)e;
         p->upload_event = ev;
     }
-    e = hipMemcpyAsync(p->dev, p->host, p->host_n * sizeof(int32_t), hipMemcpyHostToDevice, (hipStream_t)stream);
+    e = hipMemcpyAsync(p->dev, p->host, p->upload_n * sizeof(int32_t), hipMemcpyHostToDevice, (hipStream_t)stream);
     if (e != hipSuccess) return (int)e;
     return (int)hipEventRecord((hipEvent_t)p->upload_event, (hipStream_t)stream);
 }
@@ -1619,7 +1624,7 @@ void free_plan_buffers(tc_plan *p) {
         if (p->host_pinned) (void)hipHostFree(p->host); else std::free(p->host);
     }
     p->host = nullptr;
-    p->host_cap = p->host_n = 0;
+    p->host_cap = p->host_n = p->upload_n = 0;
 }
 
 // ------------------------------------------------------------------------------------
@@ -1718,7 +1723,7 @@ static int launch_attention_d(const tc_plan *p, const AttnArgs &A, int launches,
         auto launch = [&](auto wide) {
             constexpr bool WIDE = decltype(wide)::value;
             mixed_attention_kernel<D, E, kMixedWaves, WIDE><<<grid, kMixedWaves * 64, lds, st>>>(
-                A.k_pool, A.v_pool, A.q, A.k_new, A.v_new, A.out, A.pages, A.prefill, A.pieces, A.wg_first, A.decode, A.merge, append,
+                A.k_pool, A.v_pool, A.q, A.k_new, A.v_new, A.out, A.pages, A.records, A.decode, A.merge, append,
                 A.counters, A.ws_o, sc);
         };
         if (p->waves_per_item > 1) launch(std::true_type());
@@ -1729,7 +1734,7 @@ static int launch_attention_d(const tc_plan *p, const AttnArgs &A, int launches,
                                                                      A.counters, A.ws_o, sc);
     } else if (grid > 0) {
         mixed_attention_kernel<D, E, kDecodeWaves, false><<<grid, kDecodeWaves * 64, decode_lds_bytes(kDecodeWaves, p->G, D), st>>>(
-            A.k_pool, A.v_pool, A.q, A.k_new, A.v_new, A.out, A.pages, A.prefill, A.pieces, A.wg_first, A.decode, A.merge, append,
+            A.k_pool, A.v_pool, A.q, A.k_new, A.v_new, A.out, A.pages, A.records, A.decode, A.merge, append,
             A.counters, A.ws_o, sc);
     }
     hipError_t e = hipGetLastError();
@@ -1757,9 +1762,7 @@ int launch_attention(const tc_plan *p, const tc_kv_pool *pool, const void *q, co
     A.v_new = p->n_pieces == 0 ? (const uint16_t *)v_new : nullptr;
     A.out = (uint16_t *)out;
     A.pages = p->dev + p->off_pages;
-    A.prefill = p->dev + p->off_prefill;
-    A.pieces = p->dev + p->off_pieces;
-    A.wg_first = p->dev + p->off_wg;
+    A.records = p->dev + p->off_records;
     A.decode = p->dev + p->off_decode;
     A.merge = p->dev + p->off_merge;
     A.counters = p->dev + p->off_counters;

@@ -301,7 +301,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     p->waves_per_item = 1;
     p->rows_per_item = kPrefillRows;
     p->total_pages = 0;
-    p->host_n = 0;
+    p->host_n = p->upload_n = 0;
     const int Hq = pool->num_q_heads, Hkv = pool->num_kv_heads, D = pool->head_dim;
     if (pool->dtype != TC_BF16 && pool->dtype != TC_FP16) return fail(TC_ERR_SHAPE, "dtype must be TC_BF16 or TC_FP16");
     if (pool->block_size != kBlock) return fail(TC_ERR_SHAPE, "block_size must be 16");
@@ -503,19 +503,21 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     // blocks fill the chip): they draw decode items from the start, the prefill workgroups when their pieces are done.
     const int64_t n_decode_units = (int64_t)w.wg_fill.size();  // workgroups' worth of decode items
     const int64_t n_decode_wg = !queue ? n_decode_units : std::min<int64_t>(n_decode_units, std::max<int64_t>(slots - n_prefill_wg, 0));
-    const size_t off_append = 0, off_pages = (size_t)n_append * kAppendInts;
+    const size_t off_records = 0;  // first: a record is a 128-byte line
+    const size_t off_append = w.pieces.size() * kRecordInts, off_pages = off_append + (size_t)n_append * kAppendInts;
     const size_t off_valid = off_pages + (size_t)pages;
     const size_t off_prefill = off_valid + (size_t)pages;
-    const size_t off_pieces = off_prefill + (size_t)n_prefill * kItemInts;
-    const size_t off_wg = off_pieces + (size_t)n_pieces * kItemInts;
-    const size_t off_decode = off_wg + (size_t)n_prefill_wg;
+    const size_t off_decode = off_prefill + (size_t)n_prefill * kItemInts;
     const size_t off_merge = off_decode + (size_t)n_decode * kItemInts;
     const size_t off_counters = (off_merge + (size_t)n_merge * kItemInts + kCounterLine - 1) / kCounterLine * kCounterLine;
     int counter_stride = kCounterLine;
     while (counter_stride > 1 && n_counters * counter_stride > kCounterInts) counter_stride /= 2;
     const size_t off_queue = ((size_t)n_counters * counter_stride + kCounterLine - 1) / kCounterLine * kCounterLine;  // from off_counters
     const size_t n_counter_ints = queue ? off_queue + 2 * kCounterLine : (size_t)n_counters * counter_stride;
-    const size_t total = std::max<size_t>(off_counters + n_counter_ints, 1);
+    const size_t upload = std::max<size_t>(off_counters + n_counter_ints, 1);
+    const size_t off_pieces = upload;  // from here on for tc_plan_copy_items only
+    const size_t off_wg = off_pieces + (size_t)n_pieces * kItemInts;
+    const size_t total = off_wg + (size_t)n_prefill_wg;
     if (int err = begin_plan_host(p, total)) return fail(TC_ERR_DEVICE, std::string("host buffer of the plan: ") + hip_error_text(err));
     int32_t *H = p->host;
 
@@ -580,6 +582,32 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
             int32_t c = 0;
             for (size_t i = 0; i < w.blocks.size(); i++)
                 if (w.blocks[i].k > 1) { first_counter[i] = c; c += Hkv; }
+        }
+        // Records: that of a workgroup's first piece has the workgroup's index, those of its other pieces lie behind all of these.
+        {
+            int32_t next_record = n_wg_head;
+            int32_t *before = nullptr;  // the record of the piece before, of the same workgroup
+            for (size_t u = 0; u < w.pieces.size(); u++) {
+                const PlanPiece &x = w.pieces[u];
+                const PlanRowBlock &blk = w.blocks[x.block];
+                const bool first = u == 0 || w.pieces[u - 1].wg != x.wg;
+                const int32_t index = first ? x.wg : next_record++;
+                if (!first) before[RC_NEXT] = index;
+                int32_t *r = H + off_records + (size_t)index * kRecordInts;
+                r[RC_T0] = x.t0; r[RC_T1] = x.t1; r[RC_K] = blk.k; r[RC_C] = x.c;
+                r[RC_REGION] = blk.k > 1 ? blk.slot0 : -1;
+                r[RC_COUNTER] = blk.k > 1 ? counter_stride * first_counter[x.block] : 0; r[RC_CSTRIDE] = counter_stride;
+                r[RC_NEXT] = -1;
+                r[RC_POS0] = blk.pos0; r[RC_NPOS] = blk.npos; r[RC_QROW0] = p->q_start[blk.seq]; r[RC_CTX] = p->ctx_len[blk.seq];
+                r[RC_PAGEOFF] = p->page_off[blk.seq];
+                const int np = p->page_off[blk.seq + 1] - p->page_off[blk.seq];
+                r[RC_NPAGES] = np;
+                r[RC_NPAGES + 1] = r[RC_NPAGES + 2] = 0;
+                const int32_t *ids = H + off_pages + p->page_off[blk.seq];
+                constexpr int kTilePages = kPrefillTileTokens / kBlock;
+                for (int i = 0; i < kRecordInts - RC_IDS; i++) r[RC_IDS + i] = ids[std::min(x.t0 * kTilePages + i, np - 1)];  // past the end: the last page, never used
+                before = r;
+            }
         }
         // `pieces` lists each workgroup's pieces once, for all KV heads alike: workgroup (w, KV head h) has the
         // index w * Hkv + h and its pieces are stored next to each other.
@@ -651,9 +679,10 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     p->n_merge = (int)n_merge; p->n_partials = (int)n_partials; p->n_counters = (int)n_counters; p->n_append = (int)n_append;
     p->n_piece_partials = (int)n_piece_partials; p->n_merge_prefill = (int)n_merge_prefill;
     p->n_decode_wg = (int)n_decode_wg; p->counter_stride = counter_stride; p->queue_counter = queue ? (int)off_queue : -1;
-    p->off_append = off_append; p->off_pages = off_pages; p->off_valid = off_valid; p->off_prefill = off_prefill; p->off_pieces = off_pieces;
+    p->off_records = off_records; p->off_append = off_append; p->off_pages = off_pages; p->off_valid = off_valid; p->off_prefill = off_prefill; p->off_pieces = off_pieces;
     p->off_wg = off_wg; p->off_decode = off_decode; p->off_merge = off_merge; p->off_counters = off_counters;
     p->host_n = total;
+    p->upload_n = upload;
     return TC_OK;
 }
 
