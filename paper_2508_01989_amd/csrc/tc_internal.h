@@ -21,6 +21,8 @@ constexpr int kDecodeWaves = 4;
 constexpr int kDecodeWgPerCu = 3;
 constexpr int kWideWaves = 4;       // waves that share one decode item in a batch of few decodes (two such workgroups per compute unit)
 constexpr int kPrefillRows = 32 * kMixedWaves;  // (position, head) rows a prefill workgroup has room for, 32 per wave
+constexpr int kSmallWaves = 4;      // waves of a workgroup of the form for small prefill items (128 rows)
+constexpr int small_wg_per_cu(int head_dim) { return head_dim == 128 ? 2 : 3; }  // such workgroups on a compute unit: registers and LDS
 constexpr int kItemInts = 8;        // int32 fields per work item
 constexpr int kAppendInts = 4;      // int32 fields per append segment: first packed row, tokens, first token index, pool block
 // Arrival counters lie on a 128-byte line each (see workgroup_arrives_last) while all of them take no more than kCounterInts
@@ -71,6 +73,7 @@ struct PlanScratch {
     std::vector<PlanTeam> teams;
     std::vector<int> wg_fill, open;
     std::vector<int32_t> n_teams, slot0, merge_of;
+    std::vector<double> units;
 };
 
 }  // namespace tc
@@ -113,12 +116,13 @@ struct tc_plan {
     tc::PlanScratch work;
 
     int items_per_wg = tc::kDecodeWaves;  // decode items a workgroup runs side by side
-    int rows_per_item = tc::kPrefillRows;  // (position, head) rows of a prefill item: 256, or 128 for a small chunk
+    int prefill_waves = tc::kMixedWaves;   // waves of a workgroup beside a prefill chunk: 8, or 4 (prefill items of 128 rows)
+    int rows_per_item = tc::kPrefillRows;  // (position, head) rows of a prefill item: 256 or 128
     int waves_per_item = 1;               // waves that share one of them: a whole workgroup's (kWideWaves, beside a chunk kMixedWaves) or 1
     int launch_threads() const { return 64 * items_per_wg * waves_per_item; }
     int grid_blocks() const { return n_prefill_wg + n_decode_wg; }
     size_t workspace_bytes() const {
-        // per decode partial: G heads x (D accumulators + running max + running sum), fp32; per piece region: kPrefillRows such rows
+        // per decode partial: G heads x (D accumulators + running max + running sum), fp32; per piece region: kPrefillRows such rows at most
         return ((size_t)n_partials * (size_t)G + (size_t)n_piece_partials * tc::kPrefillRows) * (size_t)(D + 2) * sizeof(float);
     }
 };

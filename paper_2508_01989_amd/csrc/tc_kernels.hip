@@ -5,14 +5,15 @@
 //   kv_migrate_kernel  pool <-> contiguous transfer buffer, all layers (paper Sec. 3.5)   (HBM-bound)
 //   mixed_attention_kernel  ONE launch per layer for the whole mixed batch
 //       (paper Sec. 2.2: a prompt chunk plus piggybacked decodes share an iteration):
-//         workgroups [0, n_prefill)      causal chunked-prefill pieces: 8 waves = 256 (position, head) rows
+//         workgroups [0, n_prefill)      causal chunked-prefill pieces: 8 (4) waves = 256 (128) (position, head) rows
 //                                        of one KV head over a range of 64-token KV tiles, MFMA 32x32x16,
 //                                        software-pipelined so that the softmax runs under the MFMAs
 //         remaining workgroups           one decode KV split per wavefront (splits of one sequence and KV head
 //                                        that share a workgroup are combined in LDS),
 //                                        MFMA 16x16x32 and 16x16x16
-//       Two shapes: 8 waves per workgroup, one workgroup per compute unit, when the batch has a prefill
-//       chunk (with a form that runs a decode split by a whole workgroup); 4 waves, three workgroups per
+//       Three shapes: 8 waves per workgroup, one workgroup per compute unit, when the batch has a prefill
+//       chunk, or 4 waves, two or three workgroups per compute unit, for chunks of uneven sweeps (each with a form
+//       that runs a decode split by a whole workgroup); 4 waves, three workgroups per
 //       compute unit, for a batch of decodes only.  Instantiated for bf16 and IEEE half.
 //   wide_decode_kernel the same for a batch of few decodes: a split is run by a workgroup of four waves
 //   split_merge_kernel combine the partial results of split decode sequences and of cut prefill row blocks
@@ -304,6 +305,11 @@ __device__ __forceinline__ void peer_store4(__amdgpu_buffer_rsrc_t win, uint32_t
 // sums does not depend on it.
 constexpr int kMergeBatch = 8, kWideMergeBatch = 16, kMergePerSlice = 8;
 __host__ __device__ constexpr size_t merge_lds_bytes(int T) { return (size_t)T * 6 * sizeof(float); }
+// Bytes of LDS a decode workgroup of `waves` waves needs: the waves' results, and (later) the slices of a merge.
+__host__ __device__ constexpr size_t decode_lds_bytes(int waves, int G, int D) {
+    const size_t results = (size_t)waves * G * (D + 4 + 2) * sizeof(float), merge = merge_lds_bytes(waves * 64);
+    return results > merge ? results : merge;
+}
 struct RowSum {  // weighted sum relative to the reference m (log2 domain)
     f32x4 o;
     float m, l;
@@ -502,14 +508,19 @@ struct PrefillCfg {
     static constexpr int kPageBytes = kBlock * D * 2;               // one (page, KV head) tile of K or of V
     static constexpr int kTileBytes = kTilePages * kPageBytes;      // K part or V part of one LDS stage
     static constexpr int kRuns = kPageBytes / 1024;                 // 1 KiB wave-wide loads per page and tensor
-    // kStages LDS stages of K and of V: a tile is copied kStages - 1 steps before its first use.
-    // 96 KiB at D = 128.  (A fourth stage, 128 KiB, measured no faster; the pipeline below is written in
-    // terms of kStages, but three is the only depth that is built and tested.)
-    static constexpr int kStages = 3;
-    static_assert(kStages == 3, "three stages is the only depth that is built and tested");
-    static constexpr int kIdSlots = kStages - 2;  // page ids in flight per copying wave and tensor
-    static constexpr int kQueueSlot = 2 * kStages * kTileBytes + kMixedWaves * kIdSlots * 64 * 4;  // where a workgroup keeps the decode unit it drew
-    static constexpr int kLdsBytes = kQueueSlot + 16;
+};
+
+// LDS of a workgroup of NW waves.  K has three stages (a tile is copied two steps before its first use; a fourth measured no
+// faster), V three, or two (copied one step before) where a second workgroup has to fit the compute unit at head_dim 128.
+template <int D, int NW>
+struct PrefillLds {
+    using C = PrefillCfg<D>;
+    static constexpr int kStages = 3, kStagesV = NW == kSmallWaves && D == 128 ? 2 : 3;
+    static constexpr int kV = kStages * C::kTileBytes;                 // where the V stages begin
+    static constexpr int kIds = kV + kStagesV * C::kTileBytes;         // eight waves: slots for the page ids of the next copies
+    static constexpr int kBytes = kIds + (NW == kMixedWaves ? NW * 64 * 4 : 0);
+    static_assert(decode_lds_bytes(NW, 16, D) <= (size_t)kIds, "team buffers lie in the LDS of the prefill tiles");
+    static_assert(NW == kMixedWaves || small_wg_per_cu(D) * kBytes <= 160 * 1024, "all workgroups of a compute unit fit its LDS");
 };
 
 // N direct-to-LDS loads of 1 KiB each (16 bytes per lane) at immediate offsets 0, 1024, ...
@@ -523,7 +534,7 @@ __device__ __forceinline__ void lds_load_runs(const __attribute__((address_space
     if constexpr (N > 3) __builtin_amdgcn_global_load_lds(src, dst, 16, 3072, 0);
 }
 
-// Tile copies.  The 8 waves of a workgroup share every tile.  A copier moves one page of a tile (copier
+// Tile copies.  The waves of a workgroup share every tile.  A copier moves one page of a tile (copier
 // index 0-3: the four K pages, 4-7: the four V^T pages) with direct-to-LDS loads: lane L deposits its 16 bytes at
 // (wave-uniform base) + 16 L, so each load copies a 1 KiB run; the runs of a page are contiguous both
 // in the pool and in LDS, so they share one address register and one LDS base and differ only in the
@@ -543,7 +554,7 @@ struct TileCopier {
     bool is_v;
     int page_in_tile;
     __device__ __forceinline__ TileCopier(const AttnArgs &A, int kvh, char *lds_k, char *lds_v, int wave, int lane) {  // wave = copier index
-        static_assert(2 * C::kTilePages == kMixedWaves, "the waves 0 .. kTilePages - 1 are the older wave of each SIMD");
+        static_assert(C::kTilePages == kSmallWaves && 2 * C::kTilePages == kMixedWaves, "waves 0 .. kTilePages - 1: all of a small workgroup, or the older wave of each SIMD");
         static_assert(C::kTileTokens == kPrefillTileTokens, "the planner cuts KV ranges in units of this tile");
         is_v = wave >= C::kTilePages;
         page_in_tile = wave & (C::kTilePages - 1);
@@ -715,9 +726,10 @@ __device__ __forceinline__ float next_reference_max(float m_run, float row_max_l
 // a step's phases early and would wait at the barrier, so the copies cost them nothing, while waves 4-7,
 // which set the pace, are spared them (1 % on a long sweep; copies by waves 4-7 alone measured 0.2 %
 // slower than one tensor per wave group).
-template <int D, class E>
+template <int D, class E, int NW>
 __device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ rec, int kvh, char *lds) {
     using C = PrefillCfg<D>;
+    using L = PrefillLds<D, NW>;
     using W = PrefillWave<D, E>;
     using x8 = typename E::x8;
     using el = typename E::t;
@@ -736,7 +748,7 @@ __device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ rec,
     const int32_t *pages = A.pages + rec[RC_PAGEOFF];
     const int G = A.G;
     const int n_rows = npos * G;
-    // this lane's row of the workgroup's 256: position pos0 + R / G, head kvh * G + R % G
+    // this lane's row of the workgroup's 32 * NW: position pos0 + R / G, head kvh * G + R % G
     const int R = wave * 32 + n;
     const bool row_valid = R < n_rows;
     const int Rc = row_valid ? R : n_rows - 1;
@@ -749,7 +761,7 @@ __device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ rec,
     const int t_begin = rec[RC_T0], t_end = rec[RC_T1], region = rec[RC_REGION], p_k = rec[RC_K];
     const int n_sweep = t_end - t_begin;
     const float c_log2 = A.scale_log2;
-    char *const lds_k = lds, *const lds_v = lds + C::kStages * C::kTileBytes;
+    char *const lds_k = lds, *const lds_v = lds + L::kV;
     // per-lane byte offsets of the MFMA A operands inside a stage
     const int k_lane_off = (n >> 4) * C::kPageBytes + (n & 15) * 16 + hh * (kBlock * 16);
     const int v_lane_off = n * 32 + ((hh ^ ((n >> 3) & 1)) * 16);
@@ -766,35 +778,39 @@ __device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ rec,
     float m_run = -1e30f;  // running row maximum (log2 domain)
     float l_run = 0.f;     // running sum of this lane's half of the row
 
-    // ---- prologue: tile j of the sweep lives in stage j mod NS of its tensor.  K(0..NS-1) and V(0..NS-2)
-    // are copied here; step j then copies K(j+NS) and V(j+NS-1).
-    constexpr int NS = C::kStages;
+    // ---- prologue: tile j of the sweep lives in stage j mod NS (K) and j mod VS (V).  K(0..NS-1) and V(0..VS-2)
+    // are copied here; step j then copies K(j+NS) and V(j+VS-1).
+    constexpr int NS = L::kStages, VS = L::kStagesV;
     // Waves 0-3 copy both tensors: wave w page w of the K tile and of the V tile.  Waves 4-7 issue no loads.
-    const bool copier = wave < C::kTilePages;
+    const bool copier = NW == C::kTilePages || wave < C::kTilePages;
     const TileCopier<D> cpk(A, kvh, lds_k, lds_v, wave & (C::kTilePages - 1), lane);
     const TileCopier<D> cpv(A, kvh, lds_k, lds_v, (wave & (C::kTilePages - 1)) + C::kTilePages, lane);
     const int pg = cpk.page_in_tile;
-    int idk_cur = 0, idv_cur = 0;  // pages this wave copies in step 0
-    // The page ids for the copies of step j are fetched in step j - (NS - 2) into slot j mod (NS - 2) of this
-    // wave (K ids, then V ids).
-    char *const idk_slots = lds + 2 * NS * C::kTileBytes + (2 * wave) * (C::kIdSlots * kIdSlotBytes);
-    char *const idv_slots = idk_slots + C::kIdSlots * kIdSlotBytes;
+    // Page ids of the copies.  Eight waves: those of step j + 1 are fetched in step j, into a slot of this wave's own (K id, V id).
+    // Four waves, whose LDS is full: lane t of `window` holds the id for tile t mod 64 of the sweep, taken over when its turn
+    // comes; waiting for the next window, once in 64 steps, costs about a microsecond.
+    int id_next[3] = {0, 0, 0};  // pages this wave copies of tiles j + 1 .. j + 3
+    int window = 0;
+    char *const idk_slot = lds + L::kIds + (2 * wave) * kIdSlotBytes, *const idv_slot = idk_slot + kIdSlotBytes;
+    auto page_index = [&](int tile) { return min(tile * C::kTilePages + pg, n_pages - 1); };  // past the end: the last page, whose copy is never used
     if (copier) {
         // In the order in which the sweep needs them.  The ids of all these pages lie in the record, so that only two accesses to
         // memory follow one after the other before the first product: the record, and the tiles (and Q).
         const int32_t *ids = rec + RC_IDS + pg;
         auto id = [&](int t) { return ids[t * C::kTilePages]; };
-        static_assert(NS + 1 == (kRecordInts - RC_IDS) / C::kTilePages, "the record holds the ids of the tiles copied here and in step 0");
+        static_assert(NS == 3 && NS + 1 == (kRecordInts - RC_IDS) / C::kTilePages, "the record holds the ids of the tiles copied here and in step 0");
+        if (NW == kSmallWaves) window = pages[page_index(t_begin + lane)];
         cpk.copy(id(0), 0);
         cpv.copy(id(0), 0);
 #pragma unroll
         for (int t = 1; t < NS; t++) {
             cpk.copy(id(t), t);
-            if (t < NS - 1) cpv.copy(id(t), t);
+            if (t < VS - 1) cpv.copy(id(t), t);
         }
-        idk_cur = id(NS);
-        idv_cur = id(NS - 1);
-        wait_loads_but<(2 * NS - 3) * C::kRuns>();  // all but K(0) and V(0)
+#pragma unroll
+        for (int t = 0; t < NS; t++) id_next[t] = id(t + 1);
+        wait_loads_but<(NS + VS - 3) * C::kRuns>();  // all but K(0) and V(0)
+        if (NW == kSmallWaves) asm volatile("" : "+v"(window));  // has landed: no wait in the loop
         if ((t_begin + 1) * C::kTileTokens > kv_len) prefill_fix_tail<D>(lds_v, t_begin, pg, lane, kv_len);
     }
     __syncthreads();
@@ -861,54 +877,82 @@ __device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ rec,
         }
         settle(cur);
     };
-    // One step for tile t_begin + j, which lives in stage s0 = j mod NS: `sc` holds the scores of its first
-    // half, `kf` the K fragments of its second half.  NEXT: tile j + 1 exists.
-    int s0 = 0, id_slot = 0;  // stage of the step's tile; slot that receives the page id fetched in the step (j mod (NS - 2))
+    // One step for tile t_begin + j, which lives in stages s0 = j mod NS and v0 = j mod VS: `sc` holds the scores of its
+    // first half, `kf` the K fragments of its second half.  NEXT: tile j + 1 exists.
+    int s0 = 0, v0 = 0;
+    auto copies = [&](int j) {  // K(j+NS) replaces K(j), V(j+VS-1) replaces V(j-1)
+        const int vm1 = v0 == 0 ? VS - 1 : v0 - 1;
+        if constexpr (NW == kMixedWaves) {
+            // First the page ids for the next step's copies.  They are counted by vmcnt like the copies.
+            page_id_fetch(pages + page_index(t_begin + j + 1 + NS), idk_slot);
+            page_id_fetch(pages + page_index(t_begin + j + 1 + VS - 1), idv_slot);
+            cpk.copy(id_next[2], s0);
+            cpv.copy(id_next[VS - 2], vm1);
+        } else {
+            cpv.copy(id_next[VS - 2], vm1);
+            cpk.copy(id_next[2], s0);
+        }
+    };
+    auto copies_landed = [&](int j) {  // those of the step before (two stages of V: this step's V too), and the page ids
+        wait_loads_but<VS == 3 ? 2 * C::kRuns : C::kRuns>();
+        if constexpr (NW == kMixedWaves) {
+            id_next[2] = page_id_read(idk_slot, lane);
+            id_next[VS - 2] = page_id_read(idv_slot, lane);
+        } else {
+            const int t = j + 1 + NS;
+            if ((t & 63) == 0) {
+                window = pages[page_index(t_begin + t + lane)];
+                asm volatile("" : "+v"(window));
+            }
+            id_next[0] = id_next[1];
+            id_next[1] = id_next[2];
+            id_next[2] = __builtin_amdgcn_readlane(window, t & 63);
+        }
+    };
     auto step = [&](int j, auto mask_tag, auto next_tag) {
         constexpr bool NEXT = decltype(next_tag)::value;
         const int tile = t_begin + j;
-        const int s1 = s0 == NS - 1 ? 0 : s0 + 1, sm1 = s0 == 0 ? NS - 1 : s0 - 1;
+        const int s1 = s0 == NS - 1 ? 0 : s0 + 1, v1 = v0 == VS - 1 ? 0 : v0 + 1;
         lds_cptr k_nxt = (lds_cptr)(lds_k + s1 * C::kTileBytes + k_lane_off);
-        lds_cptr v_cur = (lds_cptr)(lds_v + s0 * C::kTileBytes + v_lane_off);
+        lds_cptr v_cur = (lds_cptr)(lds_v + v0 * C::kTileBytes + v_lane_off);
         // have both operand addresses in registers here, outside the scheduled regions below
         asm volatile("" : "+v"(k_nxt), "+v"(v_cur));
-        __syncthreads();  // every wave is done with step j - 1; the copies issued in step j - (NS - 1) are visible
-        if (NEXT && copier) {
-            // first the page ids for the copies of step j + NS - 2, then this step's copies: K(j+NS) replaces K(j),
-            // V(j+NS-1) replaces V(j-1).  Past the end of the range the page index is clamped and the copy
-            // is never read.
-            page_id_fetch(pages + min((tile + NS - 2 + NS) * C::kTilePages + pg, n_pages - 1), idk_slots + id_slot * kIdSlotBytes);
-            page_id_fetch(pages + min((tile + NS - 2 + NS - 1) * C::kTilePages + pg, n_pages - 1), idv_slots + id_slot * kIdSlotBytes);
-            cpk.copy(idk_cur, s0);
-            cpv.copy(idv_cur, sm1);
-        }
+        __syncthreads();  // every wave is done with step j - 1; the copies waited for at its end are visible
+        if (NEXT && copier) copies(j);  // past the end of the range the copies are never read
         const std::true_type yes;
         phase(v_cur, 0, k_nxt, 0, sc, sn, tile * C::kTileTokens + 32, mask_tag, yes, next_tag);
         phase(v_cur, 1, k_nxt, 1, sn, sc, (tile + 1) * C::kTileTokens, mask_tag, next_tag, next_tag);
         if (NEXT && copier) {
-            // loads return in order: all but the copies of the last NS - 2 steps and the page ids fetched
-            // after those for step j + 1 have landed, i.e. those page ids and the copies of step j - (NS - 2)
-            wait_loads_but<(NS - 2) * (2 * C::kRuns + 2) - 2>();
-            id_slot = id_slot == C::kIdSlots - 1 ? 0 : id_slot + 1;  // slot of step j + 1
-            idk_cur = page_id_read(idk_slots + id_slot * kIdSlotBytes, lane);
-            idv_cur = page_id_read(idv_slots + id_slot * kIdSlotBytes, lane);
+            copies_landed(j);
             if (decltype(mask_tag)::value && (tile + 2) * C::kTileTokens > kv_len)
-                prefill_fix_tail<D>(lds_v + s1 * C::kTileBytes, tile + 1, pg, lane, kv_len);
+                prefill_fix_tail<D>(lds_v + v1 * C::kTileBytes, tile + 1, pg, lane, kv_len);
         }
         s0 = s1;
+        v0 = v1;
     };
-    if (!copier && wave * 32 >= n_rows) {
-        // No rows and no copies to make (an item of at most 128 rows): the SIMD is left to its other wave.
-        for (int j = 0; j < n_sweep; j++) __syncthreads();
+    if (wave * 32 >= n_rows) {
+        // No rows (the last block of a chunk): the wave copies its pages, if it has any to copy, and leaves the SIMD to the others.
+        if (copier) wait_loads_but<(NS + VS - 4) * C::kRuns>();
+        for (int j = 0; j < n_sweep; j++) {
+            __syncthreads();
+            if (copier && j + 1 < n_sweep) {
+                copies(j);
+                copies_landed(j);
+                s0 = s0 == NS - 1 ? 0 : s0 + 1;
+                v0 = v0 == VS - 1 ? 0 : v0 + 1;
+                if ((t_begin + j + 2) * C::kTileTokens > kv_len)
+                    prefill_fix_tail<D>(lds_v + v0 * C::kTileBytes, t_begin + j + 1, pg, lane, kv_len);
+            }
+        }
     } else {
         W::load_k((lds_cptr)(lds_k + k_lane_off), 0, kf);
         W::qk(kf, qreg, sc);
         W::load_k((lds_cptr)(lds_k + k_lane_off), 1, kf);
         // the first phase has no earlier half to accumulate: give its P V product zero probabilities
         W::load_v((lds_cptr)(lds_v + v_lane_off), 0, vf);
-    #pragma unroll
+#pragma unroll
         for (int b = 0; b < 2; b++)
-    #pragma unroll
+#pragma unroll
             for (int e = 0; e < 8; e++) pb[b][e] = (el)0.f;
         if (t_begin * C::kTileTokens + 31 > wave_pmin) W::causal_mask(sc, t_begin * C::kTileTokens, hh, p_abs);
         m_run = next_reference_max(m_run, W::row_max(sc) * c_log2);  // the first half-tile's true maxima
@@ -917,17 +961,17 @@ __device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ rec,
         // steps 0 .. n_plain - 1 prepare tiles that lie wholly at or before every row's position
         // and before the last token: tile t needs no mask if (t + 1) * 64 - 1 <= wave_pmin
         const int n_plain = max(0, min(n_sweep - 1, (wave_pmin + 1) / C::kTileTokens - t_begin - 1));
-        if (copier) wait_loads_but<(2 * NS - 4) * C::kRuns>();  // K(1), for step 0; the others are waited for in its end
+        if (copier) wait_loads_but<(NS + VS - 4) * C::kRuns>();  // K(1), for step 0; the others are waited for in its end
         int j = 0;
         for (; j < n_plain; j++) step(j, no, yes);
         for (; j + 1 < n_sweep; j++) step(j, yes, yes);
         step(j, yes, no);
         W::pv(vf, pb, o);  // the product of the last half
-        if (copier) wait_all_loads();  // copies past the end of the range, before the LDS is used for anything else
     }
+    if (copier) wait_all_loads();  // copies past the end of the range, before the LDS is used for anything else
 
     float l = half_swap_sum(l_run);
-    if (region >= 0) {
+    if (NW == kMixedWaves && region >= 0) {  // (small workgroups run whole items only)
         // A piece of a cut item: every lane leaves its unnormalised accumulators, and the rows' running maximum
         // (log2 domain) and sum, in the piece's region of the workspace as they lie in registers; rows that see no
         // key of this piece carry (m, l, o) = (-1e30, 0, 0) and get weight 0 in the combination.
@@ -1209,12 +1253,6 @@ struct WaveResults {
     __device__ __forceinline__ f32x4 get(int i, int j, int d) const { return *reinterpret_cast<const f32x4 *>(o + (i * G + j) * kStride + d); }
     __device__ __forceinline__ float2 get_ml(int i, int j) const { return float2{ml[(i * G + j) * 2], ml[(i * G + j) * 2 + 1]}; }
 };
-// Bytes of LDS a decode workgroup of `waves` waves needs: the waves' results, and (later) the slices of a merge.
-__host__ __device__ constexpr size_t decode_lds_bytes(int waves, int G, int D) {
-    const size_t results = (size_t)waves * G * (D + 4 + 2) * sizeof(float), merge = merge_lds_bytes(waves * 64);
-    return results > merge ? results : merge;
-}
-
 // The splits of one (sequence, KV head) that share a workgroup form a team (consecutive waves): the
 // members leave their (m, l, O) in LDS and the team's first wave combines them, in wave order, with its
 // own and writes the output rows, or one partial result if the (sequence, KV head) has more teams (then
@@ -1407,13 +1445,14 @@ struct AttnScalars {
 
 // The work lists and the page table are separate const __restrict__ kernel arguments (not struct
 // members) so that the compiler knows they are never written and can fetch them with
-// scalar loads.  WAVES = 8: batches with a prefill chunk (one workgroup per compute unit, up to 256
-// registers per wave); WAVES = 4: decode-only batches (three workgroups per compute unit).
+// scalar loads.  CHUNK: batches with a prefill chunk; WAVES = 8: one workgroup per compute unit, up to 256 registers per
+// wave; WAVES = 4: two of them (three at head_dim 64, 168 registers), chosen by estimate_chunk.  Without CHUNK: decode-only
+// batches (WAVES = 4, three workgroups per compute unit).
 // Workgroups [0, n_prefill) run the prefill pieces the plan gave them, one after the other; the rest run
 // decode items, one per wave, or (WIDE; a form of its own, so that neither pays for the other's registers: both in one
 // kernel, chosen at run time, cost 1 us of 195 on a 2048-token chunk with 64 decodes) one per workgroup.
-template <int D, class E, int WAVES, bool WIDE>
-__global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : kDecodeWgPerCu)
+template <int D, class E, int WAVES, bool CHUNK, bool WIDE>
+__global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : CHUNK ? small_wg_per_cu(D) : kDecodeWgPerCu)
     mixed_attention_kernel(uint16_t *k_pool, uint16_t *v_pool, const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_new,
                            const uint16_t *__restrict__ v_new, uint16_t *__restrict__ out, const int32_t *__restrict__ pages,
                            const int32_t *__restrict__ records, const int32_t *__restrict__ decode, const int32_t *__restrict__ merge, const int32_t *__restrict__ append, int32_t *counters, float *ws,
@@ -1431,7 +1470,7 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : kDecode
     A.n_prefill = sc.n_prefill; A.n_decode = sc.n_decode; A.Hq = sc.Hq; A.Hkv = sc.Hkv; A.G = sc.G; A.fused = sc.fused; A.queue = sc.queue;
     A.scale_log2 = sc.scale_log2;
     constexpr int NS = kDecodeStages;
-    if constexpr (WAVES == kDecodeWaves) {
+    if constexpr (!CHUNK) {
         const int first_append_wg = (int)gridDim.x - sc.n_front;
         if ((int)blockIdx.x >= first_append_wg) {
             append_decode_rows<D>(k_pool, v_pool, k_new, v_new, sc.Hkv, append, sc.n_append_rows, (int)blockIdx.x - first_append_wg);
@@ -1439,14 +1478,14 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : kDecode
         }
     }
     const int wg = (int)blockIdx.x;
-    if (WAVES == kMixedWaves && (int)blockIdx.x < A.n_prefill) {
-        if constexpr (WAVES == kMixedWaves) {
+    if (CHUNK && wg < A.n_prefill) {
+        if constexpr (CHUNK) {
             const int kvh = wg % A.Hkv;
             const int32_t *rec = records + (int64_t)(wg / A.Hkv) * kRecordInts;
             for (;;) {
                 const int next = rec[RC_NEXT];
-                prefill_item<D, E>(A, rec, kvh, lds);
-                if (next < 0) break;
+                prefill_item<D, E, WAVES>(A, rec, kvh, lds);
+                if (WAVES == kSmallWaves || next < 0) break;  // (several pieces: levelled chunks)
                 rec = records + (int64_t)next * kRecordInts;
                 __syncthreads();  // the next piece's tile copies reuse the LDS
             }
@@ -1473,7 +1512,7 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : kDecode
         // round had freed until the prefill workgroups ended.  Handing out single items to single waves, with the
         // splits of a pair combined by the last to arrive, measured slower than units with their teams.)
         // The workgroup that leaves last puts both counters back to zero for the next launch.
-        int *const drawn = reinterpret_cast<int *>(lds + PrefillCfg<D>::kQueueSlot);
+        int *const drawn = reinterpret_cast<int *>(lds + PrefillLds<D, WAVES>::kIds);  // the slots of the page ids: free when no sweep runs
         int32_t *const next_unit = A.counters + A.queue, *const gone = next_unit + kCounterLine;
         const int n_units = WIDE ? A.n_decode : A.n_decode / WAVES;
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1687,17 +1726,21 @@ int launch_kv_migrate(const tc_plan *p, bool import, int page0, int n_pages, int
 
 // More than 64 KiB of dynamic LDS needs an opt-in per kernel function and per device; remembered per
 // instantiation and device (setting it twice is harmless, so racing first calls need no lock).
-// Both forms of the mixed kernel at once, so that a caller who has run one batch of a shape may capture any other.
+// All forms of the kernel at once, so that a caller who has run one batch of a shape may capture any other.
 template <int D, class E>
 static int allow_prefill_lds(int device) {
     static std::atomic<bool> done[kMaxDevices];
     const bool known = device >= 0 && device < kMaxDevices;
     if (known && done[device].load(std::memory_order_acquire)) return 0;
-    const void *const forms[] = {(const void *)mixed_attention_kernel<D, E, kMixedWaves, false>, (const void *)mixed_attention_kernel<D, E, kMixedWaves, true>};
-    for (const void *f : forms) {
-        hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, PrefillCfg<D>::kLdsBytes);
+    auto allow = [](auto waves, auto wide) {
+        constexpr int NW = decltype(waves)::value;
+        return hipFuncSetAttribute((const void *)mixed_attention_kernel<D, E, NW, true, decltype(wide)::value>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   PrefillLds<D, NW>::kBytes);
+    };
+    const std::integral_constant<int, kMixedWaves> large;
+    const std::integral_constant<int, kSmallWaves> small;
+    for (hipError_t e : {allow(large, std::false_type()), allow(large, std::true_type()), allow(small, std::false_type()), allow(small, std::true_type())})
         if (e != hipSuccess) return (int)e;
-    }
     if (known) done[device].store(true, std::memory_order_release);
     return 0;
 }
@@ -1717,23 +1760,23 @@ static int launch_attention_d(const tc_plan *p, const AttnArgs &A, int launches,
     const AttnScalars sc = {A.n_prefill, A.n_decode, A.Hq, A.Hkv, A.G, A.fused, A.queue, p->n_partials, n_front, p->n_append, A.scale_log2};
     const int32_t *append = p->dev + p->off_append;
     if (grid > 0 && p->n_pieces > 0) {
-        const int lds = PrefillCfg<D>::kLdsBytes;  // the decode workgroups of the launch need less, for any G
-        static_assert(decode_lds_bytes(kMixedWaves, 16, D) <= (size_t)PrefillCfg<D>::kLdsBytes, "team buffers must fit the prefill tiles' LDS");
         if (int err = allow_prefill_lds<D, E>(p->device)) return err;
-        auto launch = [&](auto wide) {
-            constexpr bool WIDE = decltype(wide)::value;
-            mixed_attention_kernel<D, E, kMixedWaves, WIDE><<<grid, kMixedWaves * 64, lds, st>>>(
-                A.k_pool, A.v_pool, A.q, A.k_new, A.v_new, A.out, A.pages, A.records, A.decode, A.merge, append,
-                A.counters, A.ws_o, sc);
+        auto launch = [&](auto waves, auto wide) {
+            constexpr int NW = decltype(waves)::value;
+            mixed_attention_kernel<D, E, NW, true, decltype(wide)::value><<<grid, NW * 64, PrefillLds<D, NW>::kBytes, st>>>(
+                A.k_pool, A.v_pool, A.q, A.k_new, A.v_new, A.out, A.pages, A.records, A.decode, A.merge, append, A.counters, A.ws_o, sc);
         };
-        if (p->waves_per_item > 1) launch(std::true_type());
-        else launch(std::false_type());
+        const std::integral_constant<int, kMixedWaves> large;
+        const std::integral_constant<int, kSmallWaves> small;
+        const bool wide = p->waves_per_item > 1;
+        if (p->prefill_waves == kMixedWaves) wide ? launch(large, std::true_type()) : launch(large, std::false_type());
+        else wide ? launch(small, std::true_type()) : launch(small, std::false_type());
     } else if (grid > 0 && p->waves_per_item > 1) {
         static_assert(decode_lds_bytes(kWideWaves, 16, D) <= 65536, "more than 64 KiB of dynamic LDS needs an opt-in");
         wide_decode_kernel<D, E><<<grid, kWideWaves * 64, decode_lds_bytes(kWideWaves, p->G, D), st>>>(A.k_pool, A.v_pool, A.q, A.k_new, A.v_new, A.out, A.pages, A.decode, A.merge,
                                                                      A.counters, A.ws_o, sc);
     } else if (grid > 0) {
-        mixed_attention_kernel<D, E, kDecodeWaves, false><<<grid, kDecodeWaves * 64, decode_lds_bytes(kDecodeWaves, p->G, D), st>>>(
+        mixed_attention_kernel<D, E, kDecodeWaves, false, false><<<grid, kDecodeWaves * 64, decode_lds_bytes(kDecodeWaves, p->G, D), st>>>(
             A.k_pool, A.v_pool, A.q, A.k_new, A.v_new, A.out, A.pages, A.records, A.decode, A.merge, append,
             A.counters, A.ws_o, sc);
     }

@@ -5,6 +5,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <new>
 
 #include "tc_internal.h"
@@ -39,6 +40,9 @@ constexpr double kPieceOverheadTiles = 3.0;
 constexpr double kDecodeCuGBs = 40.0;
 constexpr int kMinPieceTiles = 4;   // a levelled piece is never shorter than this
 constexpr int kMinBinTiles = 8;     // and a levelled workgroup never holds less than this
+
+// Workgroups of a launch with a prefill chunk that the chip holds at a time.
+static int64_t wg_slots(const tc_plan *p) { return p->prefill_waves == kMixedWaves ? kNumCu : (int64_t)kNumCu * small_wg_per_cu(p->D); }
 
 // The KV range of a decode sequence is cut into the fewest splits of at most `split` tokens, equal up
 // to a page; the split is the largest of 1024..128 tokens that still yields enough items to fill the chip.
@@ -148,21 +152,23 @@ static int choose_wide_split(const tc_plan *p, int S, int64_t decode_tokens) {
 // At head_dim 64 a split is half the bytes for the same start and combination, and the line is at 0.65: 128 at 1000 with 32
 // decodes of 512-4096 tokens (share 0.55) 38.0 / 40.2, 256 at 500 with 64 of lognormal 1500 (0.8) 50.6 / 46.4.
 static int choose_wide_split_beside_chunk(const tc_plan *p, int S, double t_rest_us, int64_t n_prefill_wg, bool queue) {
+    const int W = p->prefill_waves;
+    const int64_t slots = wg_slots(p);
     int64_t longest = 0;  // decode sequences that one workgroup covers
     for (int s = 0; s < S; s++)
         if (p->q_start[s + 1] - p->q_start[s] == 1) {
             const int64_t kv = (int64_t)p->ctx_len[s] + 1;
-            if (kv <= (int64_t)kMixedWaves * kMaxSplitPages * kBlock) longest = std::max(longest, kv);
+            if (kv <= (int64_t)W * kMaxSplitPages * kBlock) longest = std::max(longest, kv);
         }
-    const double t_longest = 1.1 * (p->D / 128.0) * (double)longest / (kBlock * kMixedWaves);
-    const double share = !queue && n_prefill_wg > kNumCu / 2 ? 0.8 : p->D == 64 ? 0.65 : 0.5;
+    const double t_longest = 1.1 * (p->D / 128.0) * (double)longest / (kBlock * W);
+    const double share = !queue && n_prefill_wg > slots / 2 ? 0.8 : p->D == 64 ? 0.65 : 0.5;
     const double t_rest = std::max(t_rest_us, 8.0);
     if (t_longest <= share * t_rest) return 0;
-    const int split = shortest_split(p, S, std::max<int64_t>(kNumCu - n_prefill_wg, kNumCu / 4));
+    const int split = shortest_split(p, S, std::max<int64_t>(slots - n_prefill_wg, slots / 4));
     int64_t items = 0;  // workgroups of the decode branch
     for (int s = 0; s < S; s++)
         if (p->q_start[s + 1] - p->q_start[s] == 1) items += (int64_t)num_splits((int64_t)p->ctx_len[s] + 1, split, 1) * p->Hkv;
-    const double t_starts = (queue ? 3.0 : 2.0) * std::max<int64_t>(0, items - kNumCu) / kNumCu;
+    const double t_starts = (queue ? 3.0 : 2.0) * std::max<int64_t>(0, items - slots) / slots;
     return t_longest <= share * (t_rest + t_starts) ? 0 : split;
 }
 
@@ -290,6 +296,71 @@ static int choose_rows_per_item(const tc_plan *p, int S, int64_t decode_bytes) {
     return t_half <= t_whole ? kPrefillRows / 2 : kPrefillRows;
 }
 
+// Row blocks of `rows` (position, head) rows, heaviest (latest positions, longest KV range) first.
+static void make_row_blocks(const tc_plan *p, int S, int rows, std::vector<PlanRowBlock> &blocks) {
+    const int pos_per_item = rows / p->G;
+    blocks.clear();
+    for (int s = 0; s < S; s++) {
+        const int q = p->q_start[s + 1] - p->q_start[s];
+        if (q <= 1) continue;
+        for (int pos0 = 0; pos0 < q; pos0 += pos_per_item) {
+            const int npos = std::min(pos_per_item, q - pos0);
+            const int64_t cost = (int64_t)p->ctx_len[s] + pos0 + npos;
+            blocks.push_back({s, pos0, npos, cost, (int)((cost - 1) / kPrefillTileTokens) + 1, 1, 0});
+        }
+    }
+    std::stable_sort(blocks.begin(), blocks.end(), [](const PlanRowBlock &x, const PlanRowBlock &y) { return x.cost > y.cost; });
+}
+
+// What a chunk of more than a quarter of the compute units' worth of items takes in each of its forms, estimated, us:
+//   whole     items of 256 rows, one workgroup each.  On a unit of its own the longest sweep is what counts; its tiles take 1.25 us while most
+//             of the chip is idle and 1.6-1.7 when all of it sweeps (the clock falls); beyond 256 items, list scheduling.
+//   levelled  the sweeps cut into runs of equal length, one per unit: pieces leave partial results and start twice.
+//   small     items of 128 rows, workgroups of four waves, two or three to a unit.  A unit's workgroups copy their tiles each for itself and
+//             get through 15-20 % less together than one of eight waves does, but a long sweep has a short one beside it and is
+//             swept at 1.07-1.2 us a tile while the other is at work or gone.
+// Measured (us per step, whole / levelled / small, head_dim 128 unless stated):
+//   uneven sweeps, first chunks   32/8 heads, 2048 at 0 52.4 / 51.4 / 46.6, head_dim 64 36.0 / 32.2 / 29.6, 1500 38.9 / 35.4 / 34.5; 16/2 heads, 1207
+//                                 33.2 / 31.3 / 26.8; 8/8 heads, 7760 176.6 / 151.8 / 159.3, 6000 122.1 / 96.9 / 107.8; 64/8 heads, 1280 39.8 / 42.1 / 38.4
+//   an offset                     32/8 heads, 2048 at 1000 79.1 / 83.8 / 74.1, at 4096 159.3 / 161.4 / 159.1; 1200 at 2000 69.4 / 62.4 / 68.2; 1024 at 4096
+//                                 102.5 / 82.1 / 87.9; 1000 at 0 and 900 at 6000 134.3 / 121.7 / 117.5
+//   more items than units         32/8 heads, 4096 at 0 131.3 / 151.9 / 143.9; 32/32 heads, 2568 84.0 / 97.2 / 80.8; 64/8 heads, head_dim 64, 1055 at 13870 (264
+//                                 items) 407.0 / 249.5 / 322.0
+//   decodes                       16/2 heads, 1270 at 18176 with 126 of lognormal 7720 357.8 / 266.7 / 346.5; 32/8 heads, 2048 at 0 with 32 of 500-1500
+//                                 60.2 / 62.9 / 58.3, 2200 with 10 of 465 57.8 / 65.8 / 54.2
+struct ChunkForms {
+    double whole, levelled, small;
+};
+static ChunkForms estimate_chunk(const tc_plan *p, const std::vector<PlanRowBlock> &blocks, std::vector<double> &units) {
+    const bool d64 = p->D == 64;
+    const int Hkv = p->Hkv;
+    const int64_t items = (int64_t)blocks.size() * Hkv;
+    double tiles = 0;
+    for (const PlanRowBlock &b : blocks) tiles += b.n_tiles;
+    const double load = tiles * Hkv / kNumCu, longest = blocks[0].n_tiles, fill = std::min(1.0, load / longest);
+    const double o = d64 ? 3.5 : 5.5;  // start and end of a workgroup
+    ChunkForms t;
+    if (items <= kNumCu) t.whole = longest * (d64 ? std::max(0.92, 0.85 + 0.2 * fill) : std::max(1.25, 1.05 + 0.65 * fill)) + o;
+    else {  // heaviest first, to the unit that is free first
+        const double tile_us = d64 ? 1.03 : 1.6;
+        units.assign(kNumCu, 0.0);
+        for (const PlanRowBlock &b : blocks)
+            for (int h = 0; h < Hkv; h++) {
+                std::pop_heap(units.begin(), units.end(), std::greater<double>());
+                units.back() += b.n_tiles * tile_us + o;
+                std::push_heap(units.begin(), units.end(), std::greater<double>());
+            }
+        t.whole = *std::max_element(units.begin(), units.end());
+    }
+    const double full = std::max(0.0, (double)(items - 160) / 96);  // the more items, the more of them are cut
+    t.levelled = std::max(load, (double)kMinBinTiles) * (d64 ? 1.03 : 1.7) + (d64 ? 14.0 : 15.0 + 6.0 * full);
+    const double small_items = 2.0 * items, slots = (double)kNumCu * small_wg_per_cu(p->D);
+    const double alone_us = d64 ? std::min(0.8, std::max(0.66, 0.65 + 0.25 * fill)) : std::min(1.2, std::max(1.07, 1.0 + 0.3 * fill));
+    const double shared_us = d64 ? (small_items > slots ? 0.62 : 0.59) : (small_items > slots ? 1.06 : 0.98);
+    t.small = std::max(longest * alone_us, 2.0 * load * shared_us) + o;
+    return t;
+}
+
 tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     if (!p || !pool || !b) return fail(TC_ERR_NULL, "plan, pool or batch is NULL");
     // an error below leaves the plan describing an empty batch
@@ -300,6 +371,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     p->items_per_wg = kDecodeWaves;
     p->waves_per_item = 1;
     p->rows_per_item = kPrefillRows;
+    p->prefill_waves = kMixedWaves;
     p->total_pages = 0;
     p->host_n = p->upload_n = 0;
     const int Hq = pool->num_q_heads, Hkv = pool->num_kv_heads, D = pool->head_dim;
@@ -353,55 +425,61 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     // ---- prefill row blocks, heaviest (latest positions, longest KV range) first, and their pieces
     const int64_t decode_bytes = decode_tokens * Hkv * D * 4;
     p->rows_per_item = choose_rows_per_item(p, S, decode_bytes);
-    const int pos_per_item = p->rows_per_item / G;
-    w.blocks.clear();
-    for (int s = 0; s < S; s++) {
-        const int q = p->q_start[s + 1] - p->q_start[s];
-        if (q <= 1) continue;
-        for (int pos0 = 0; pos0 < q; pos0 += pos_per_item) {
-            const int npos = std::min(pos_per_item, q - pos0);
-            const int64_t cost = (int64_t)p->ctx_len[s] + pos0 + npos;
-            w.blocks.push_back({s, pos0, npos, cost, (int)((cost - 1) / kPrefillTileTokens) + 1, 1, 0});
-        }
-    }
-    std::stable_sort(w.blocks.begin(), w.blocks.end(), [](const PlanRowBlock &x, const PlanRowBlock &y) { return x.cost > y.cost; });
+    make_row_blocks(p, S, p->rows_per_item, w.blocks);
     // Regimes by the number of prefill items (row blocks x KV heads) against the compute units:
-    //   at most a quarter:        cut each item's KV range so that more units work on the chunk
-    //   up to three quarters:     level the sweeps over a fixed number of workgroups, leaving units to the decode branch
-    //   up to as many:            one workgroup per item, the decode items drawn from a queue by the units that finish early
-    //   more:                     one workgroup per item; the hardware hands them out heaviest first
-    w.pieces.clear();
-    const int64_t n_items = (int64_t)w.blocks.size() * Hkv, slots = kNumCu;
-    int n_wg_per_head = 0;  // > 0: levelled; the prefill workgroups are numbered bin * Hkv + KV head
+    //   at most a quarter:  cut each item's KV range so that more units work on the chunk
+    //   up to four times:   whole items, levelled runs or small workgroups, whichever is estimated to take least (estimate_chunk)
+    //   more:               whole items; the hardware hands them out heaviest first
     // `queue`: the launch has no more workgroups than the chip has compute units and the decode items are drawn from a
-    // queue, a workgroup's worth at a time, by whichever workgroup is free (see the kernel)
+    // queue, a workgroup's worth at a time, by whichever workgroup is free (see the kernel).
+    w.pieces.clear();
+    int n_wg_per_head = 0;  // > 0: levelled; the prefill workgroups are numbered bin * Hkv + KV head
     bool queue = false;
-    if (n_items > 0 && n_items * 4 <= slots) choose_prefill_cuts(w.blocks, Hkv, decode_bytes, p->rows_per_item == kPrefillRows ? kCutTileUs : kCutHalfTileUs);
-    if (n_items * 4 > slots && n_items <= 4 * slots) {
-        // (Items of 128 rows take their unit for half as long: they have a queue from half of the units on.  On fewer units drawing
-        // from it costs more than it levels: 270 first tokens with 3 decodes of 100-300, 32/8 heads, in 72 items, without it /
-        // with it 15.3 / 16.8 us; at head_dim 64 with 46 of 30-300 12.0 / 13.7; 500 tokens, 128 items, with 16 of 100-900 19.0 / 20.8.)
-        queue = decode_tokens > 0 && n_items <= slots && (p->rows_per_item == kPrefillRows || n_items * 2 > slots);
-        // Row blocks that fill the chip (more than three quarters of the units) run uncut, one per workgroup: the
-        // queue lets the units of the lighter blocks carry the decode branch while the heavier ones still sweep, and
-        // cutting measured slower there, with or without decodes (partial results and a second start per workgroup
-        // cost more than the uneven sweeps).  Fewer row blocks leave units empty: with a decode branch of some
-        // weight those units carry it from the start (decode workgroups and the queue) and the blocks again run
-        // uncut; with little or no decode work the sweeps are levelled over the whole chip instead.
-        double tiles = 0;
-        for (const PlanRowBlock &x : w.blocks) tiles += x.n_tiles;
-        const double tile_us = kTileUs * (D / 128.0);
-        const double t_sweep = w.blocks[0].n_tiles * tile_us;  // the heaviest block's
-        const double t_decode_alone = decode_tokens ? std::max(16.0, (double)decode_bytes / 5.0e6) : 0.0;
-        if (n_items * 4 <= 3 * slots && t_decode_alone < 0.25 * t_sweep && p->rows_per_item == kPrefillRows) {
-            const double t_prefill = tiles * Hkv * tile_us, t_decode = (double)decode_bytes / (kDecodeCuGBs * 1e3);
-            const int cu_decode = decode_tokens ? std::max(1, (int)std::lround(slots * t_decode / (t_decode + t_prefill))) : 0;
-            const int64_t by_units = std::max<int64_t>(1, (slots - std::min<int64_t>(cu_decode, slots / 2)) / Hkv);
-            n_wg_per_head = (int)std::max<int64_t>(1, std::min<int64_t>(by_units, (int64_t)tiles / kMinBinTiles));
-            level_prefill(w.blocks, w.pieces, n_wg_per_head);
-            queue = decode_tokens > 0;
+    if (!w.blocks.empty()) {
+        const int64_t items = (int64_t)w.blocks.size() * Hkv;
+        if (p->rows_per_item != kPrefillRows) {
+            if (items * 4 <= kNumCu) choose_prefill_cuts(w.blocks, Hkv, decode_bytes, kCutHalfTileUs);
+            // Four waves to a workgroup where several of them share a unit (us, eight waves / four): 40/8 heads, 1000 at 0 (320 items) 32.0 / 26.9,
+            // sixteen of 51 (384) 15.2 / 12.8; head_dim 64, 32/8 heads, 1000 at 0 (256) 18.0 / 17.1, 816 (208) 15.3 / 15.1.  Not where every item has a
+            // unit to itself at head_dim 128 (32/8 heads, 1000 at 0 24.3 / 25.0, 816 21.4 / 22.0), nor beside decodes, of which eight
+            // waves carry more at a time (972 at 0 with 2 25.2 / 26.4; 19 at 737 with 15 17.9 / 18.6).
+            if (decode_tokens == 0 && items > (D == 64 ? kNumCu / 2 : kNumCu)) p->prefill_waves = kSmallWaves;
+            // (Items of 128 rows take their unit for half as long: they have a queue from half of the units on.  On fewer units drawing
+            // from it costs more than it levels: 270 first tokens with 3 decodes of 100-300, 32/8 heads, in 72 items, without it /
+            // with it 15.3 / 16.8 us; at head_dim 64 with 46 of 30-300 12.0 / 13.7; 500 tokens, 128 items, with 16 of 100-900 19.0 / 20.8.)
+            queue = decode_tokens > 0 && items <= kNumCu && items * 2 > kNumCu;
+        } else if (items * 4 <= kNumCu) {
+            choose_prefill_cuts(w.blocks, Hkv, decode_bytes, kCutTileUs);
+        } else if (items <= 4 * kNumCu) {
+            const ChunkForms t = estimate_chunk(p, w.blocks, w.units);
+            const double t_decode = (double)decode_bytes / 5.0e6;                                 // alone on the chip
+            const double unit_decode = (double)decode_bytes / (kDecodeCuGBs * 1e3) / kNumCu;  // what it takes of every unit beside sweeps
+            const double t_whole = std::max(t.whole, t_decode), t_levelled = t.levelled + unit_decode;
+            // Levelled: not beside a decode branch that needs about as long (512 at 2048, 16 of 512-4096; 1024 at 2048, 64 decodes, 600 MB of K/V, whole /
+            // levelled 143 / 155), and where the items nearly fill the chip beside decodes at all, whose queue levels too, only when the sweeps
+            // are very uneven (1700 at 3000 with 32 of lognormal 1024 116.2 / 118.1; 8, 800 at 0 and 746 at 7226 with 21 of 1200 156.0 / 129.2).
+            const double level_below = decode_tokens > 0 && items * 4 > 3 * kNumCu ? 0.7 : 0.95;
+            if (t_levelled < level_below * t_whole && t_levelled < t.small && t_decode < 0.75 * t_levelled) {
+                double tiles = 0;
+                for (const PlanRowBlock &x : w.blocks) tiles += x.n_tiles;
+                const double unit_prefill = tiles * Hkv * kTileUs * (D / 128.0) / kNumCu;
+                const int cu_decode = decode_tokens ? std::max(1, (int)std::lround(kNumCu * unit_decode / (unit_decode + unit_prefill))) : 0;
+                const int64_t by_units = std::max<int64_t>(1, (kNumCu - std::min<int64_t>(cu_decode, kNumCu / 2)) / Hkv);
+                n_wg_per_head = (int)std::max<int64_t>(1, std::min<int64_t>(by_units, (int64_t)tiles / kMinBinTiles));
+                level_prefill(w.blocks, w.pieces, n_wg_per_head);
+                queue = decode_tokens > 0;
+            // Small workgroups: beside more decodes the queue fills the units whose sweeps end early; long sweeps run at a lower clock in either
+            // form than the estimates say (6562 at 16848, 8/8 heads, 526 / 543).
+            } else if (t.small < (w.blocks[0].n_tiles <= 64 ? 0.97 : 0.9) * t_whole && t_decode < 0.05 * t.small) {
+                p->prefill_waves = kSmallWaves;
+                p->rows_per_item = kPrefillRows / 2;
+                make_row_blocks(p, S, p->rows_per_item, w.blocks);
+            } else {
+                queue = decode_tokens > 0 && items <= kNumCu;
+            }
         }
     }
+    const int64_t n_items = (int64_t)w.blocks.size() * Hkv, slots = wg_slots(p);
     if (n_wg_per_head <= 0) {
         // one workgroup per piece; within a block the pieces share the tiles out evenly
         for (size_t i = 0; i < w.blocks.size(); i++) {
@@ -423,7 +501,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     // bounded window; the oldest is closed when none has room).  Runs are taken longest split first.
     // Wave slots left free hold padding items (no tokens).
     p->split_tokens = choose_split(decode_tokens * Hkv);
-    p->items_per_wg = w.blocks.empty() ? kDecodeWaves : kMixedWaves;
+    p->items_per_wg = w.blocks.empty() ? kDecodeWaves : p->prefill_waves;
     if (w.blocks.empty() && n_decode_seqs > 0)
         if (const int split = choose_wide_split(p, S, decode_tokens)) {
             p->split_tokens = split;
@@ -441,7 +519,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
         if (const int split = choose_wide_split_beside_chunk(p, S, t_rest, (int64_t)n_wg_head * Hkv, queue)) {
             p->split_tokens = split;
             p->items_per_wg = 1;
-            p->waves_per_item = kMixedWaves;
+            p->waves_per_item = p->prefill_waves;
         }
     }
     const int W = p->items_per_wg;
@@ -584,14 +662,22 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
                 if (w.blocks[i].k > 1) { first_counter[i] = c; c += Hkv; }
         }
         // Records: that of a workgroup's first piece has the workgroup's index, those of its other pieces lie behind all of these.
+        // Small workgroups that are all on the chip from the start, the first kNumCu one on each unit and the next ones beside them in
+        // the same order: every other row of them is turned round, so that the longest sweep has the shortest beside it.
         {
+            const bool turn = p->prefill_waves == kSmallWaves && (int64_t)n_wg_head * Hkv <= slots;
+            const int row = std::max(1, kNumCu / Hkv);
+            auto place = [&](int wg) {
+                const int first = wg / row * row;
+                return turn && (wg / row & 1) ? first + std::min(row, n_wg_head - first) - 1 - (wg - first) : wg;
+            };
             int32_t next_record = n_wg_head;
             int32_t *before = nullptr;  // the record of the piece before, of the same workgroup
             for (size_t u = 0; u < w.pieces.size(); u++) {
                 const PlanPiece &x = w.pieces[u];
                 const PlanRowBlock &blk = w.blocks[x.block];
                 const bool first = u == 0 || w.pieces[u - 1].wg != x.wg;
-                const int32_t index = first ? x.wg : next_record++;
+                const int32_t index = first ? place(x.wg) : next_record++;
                 if (!first) before[RC_NEXT] = index;
                 int32_t *r = H + off_records + (size_t)index * kRecordInts;
                 r[RC_T0] = x.t0; r[RC_T1] = x.t1; r[RC_K] = blk.k; r[RC_C] = x.c;

@@ -446,6 +446,40 @@ def test_rows_per_prefill_item(H, name):
     assert np.array_equal(H.to_host(db.out), single), "two-launch form"
 
 
+# Chunks of uneven sweeps run workgroups of four waves (128 rows), two or three on a compute unit: the edges of an item's
+# positions and of tiles, one and several items on a unit, waves without rows, sweeps of one tile up to more than the 64
+# tiles a wave holds page ids for, new tokens stored by the append before, a decode beside them.
+SMALL_WORKGROUPS = {
+    # name: (Hq, Hkv, D, q_len, ctx, dtype, every how many rows are compared)
+    "g8": (64, 8, 128, [600], [0], "bf16", 1),
+    "g5_half": (40, 8, 128, [900, 2], [0, 61], "fp16", 3),
+    "g4_with_a_decode": (32, 8, 128, [1250, 1], [0, 300], "bf16", 5),
+    "g3_unaligned_offset": (48, 16, 128, [701], [99], "bf16", 3),
+    "g4_d64_ragged_chunks": (32, 8, 64, [700, 333, 45, 2], [0, 64, 100, 0], "bf16", 3),
+    "g1_d64": (32, 32, 64, [900, 300], [5, 0], "fp16", 5),
+    "g16_d64": (16, 1, 64, [1100], [3], "bf16", 1),
+    "window_of_page_ids": (32, 8, 128, [1200, 1200], [3400, 0], "bf16", 37),
+    "window_of_page_ids_d64": (32, 8, 64, [1500, 900], [3400, 0], "fp16", 37),
+}
+
+
+@pytest.mark.parametrize("name", list(SMALL_WORKGROUPS))
+def test_small_workgroups(H, name):
+    import torch
+    Hq, Hkv, D, q_len, ctx, dtype, every = SMALL_WORKGROUPS[name]
+    b = W.make_batch(W.custom_spec(name, Hq, Hkv, D, q_len, ctx, seed=zlib.crc32(name.encode()) % 10007, dtype=dtype))
+    # the last row of every sequence among them: it sees the last tile to its end
+    rows = None if every == 1 else np.unique(np.concatenate([np.arange(0, b.total_q, every), b.q_start[1:] - 1]))
+    (mx, rel), db = run_and_compare(H, b, name, rows=rows, gather=None)
+    assert (db.plan.info.rows_per_prefill_item, db.plan.info.block_threads) == (128, 256)
+    assert dtype != "fp16" or (mx <= FP16_MAX_ABS and rel <= FP16_REL_L2), (mx, rel)
+    single = H.to_host(db.out).copy()
+    db.out.fill_(0)
+    db.attention()
+    torch.cuda.synchronize()
+    assert np.array_equal(H.to_host(db.out), single)
+
+
 # The same beside prefill chunks: few long decodes are run by whole workgroups of eight waves (drawn from the queue when the
 # row blocks take more than a quarter of the units, workgroups of their own otherwise), balanced ones by single waves.
 MIXED_DECODE_FORMS = {
