@@ -457,8 +457,9 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
             const double t_whole = std::max(t.whole, t_decode), t_levelled = t.levelled + unit_decode;
             // Levelled: not beside a decode branch that needs about as long (512 at 2048, 16 of 512-4096; 1024 at 2048, 64 decodes, 600 MB of K/V, whole /
             // levelled 143 / 155), and where the items nearly fill the chip beside decodes at all, whose queue levels too, only when the sweeps
-            // are very uneven (1700 at 3000 with 32 of lognormal 1024 116.2 / 118.1; 8, 800 at 0 and 746 at 7226 with 21 of 1200 156.0 / 129.2).
-            const double level_below = decode_tokens > 0 && items * 4 > 3 * kNumCu ? 0.7 : 0.95;
+            // are very uneven (1700 at 3000 with 32 of lognormal 1024 116.2 / 118.1; 8, 800 at 0 and 746 at 7226 with 21 of 1200 156.0 / 129.2);
+            // without decodes not for a few per cent either (1500 at 20000, 40/8 heads, head_dim 64, 326 / 341).
+            const double level_below = items * 4 <= 3 * kNumCu ? 0.95 : decode_tokens > 0 ? 0.7 : 0.9;
             if (t_levelled < level_below * t_whole && t_levelled < t.small && t_decode < 0.75 * t_levelled) {
                 double tiles = 0;
                 for (const PlanRowBlock &x : w.blocks) tiles += x.n_tiles;
