@@ -1341,55 +1341,32 @@ __device__ void decode_item(const AttnArgs &A, const int32_t *__restrict__ it, f
                            wg_waves * 64);
 }
 
-// A batch of few decodes: one split is run by a whole workgroup of R waves, which share its pages out (a contiguous
-// run each, so that a wave has at most 64 / R pages: most of them are in flight at once, and the workgroup needs about
-// one memory latency for its split where a single wave needs one per page).  All waves then meet in LDS and the
-// combination is spread over all threads: a thread owns four adjacent elements of a row.
-template <int D, class E, int NS, int R, bool STORE>
-__device__ void decode_item_wide(const AttnArgs &A, const int32_t *__restrict__ it, float *lds) {
+// What `N` waves found for one split, from first_wave on, combined from LDS by `threads` threads (t of them this one; a thread owns four adjacent
+// elements of a row): the output rows, or a partial result if the (sequence, KV head) has more workgroups.
+template <int D, class E, int N>
+__device__ __forceinline__ void wide_combine(const AttnArgs &A, const WaveResults<D> &res, int first_wave, int t, int threads, int kvh, int qrow, int slot) {
     using x4 = typename E::x4;
     using el = typename E::t;
-    constexpr int MT = D / 16;
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));  // may be called in a loop (see prefill_item)
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kvh = it[DC_KVH], t0 = it[DC_BEGIN], t1 = it[DC_END], qrow = it[DC_QROW], slot = it[DC_SLOT];
-    const int merge_item = (it[DC_TEAM] >> 8) - 1;
     const int G = A.G;
-    const int n_pages = (t1 - t0 + kBlock - 1) / kBlock;
-    const int p0 = n_pages * wave / R, p1 = n_pages * (wave + 1) / R;  // this wave's pages of the split
-    f32x4 o[MT];
-#pragma unroll
-    for (int c = 0; c < MT; c++) o[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m_run = -1e30f, l_run = 0.f;
-    if (p1 > p0) {
-        const bool takes_new = p1 == n_pages && (it[DC_TEAM] & kTeamTailBit) && A.k_new != nullptr;
-        decode_sweep<D, E, NS, STORE>(A, kvh, qrow, A.pages + it[DC_PAGEOFF] + t0 / kBlock + p0, p1 - p0, min(t1 - t0, p1 * kBlock) - p0 * kBlock,
-                               takes_new, lane, o, m_run, l_run);
-    }
-    const WaveResults<D> res(lds, R, G);
-    res.put(wave, lane, o, m_run, l_run);
-    __syncthreads();
     constexpr int VR = D / 4;
     float *const part = slot < 0 ? nullptr : A.ws_o + (int64_t)slot * G * D;
     float *const part_ml = slot < 0 ? nullptr : A.ws_ml + (int64_t)slot * G * 2;
-    for (int v = tid; v < G * VR; v += R * 64) {
+    for (int v = t; v < G * VR; v += threads) {
         const int j = v / VR, d = (v % VR) * 4;
-        float2 ml[R];
+        float2 ml[N];
         float m = -1e30f;
 #pragma unroll
-        for (int i = 0; i < R; i++) {
-            ml[i] = res.get_ml(i, j);
+        for (int i = 0; i < N; i++) {
+            ml[i] = res.get_ml(first_wave + i, j);
             m = fmaxf(m, ml[i].x);
         }
         f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
         float l = 0.f;
 #pragma unroll
-        for (int i = 0; i < R; i++) {
+        for (int i = 0; i < N; i++) {
             const float w = fast_exp2(ml[i].x - m);
             l += w * ml[i].y;
-            acc += res.get(i, j, d) * w;
+            acc += res.get(first_wave + i, j, d) * w;
         }
         if (slot < 0) {
             const float inv = 1.f / l;
@@ -1408,7 +1385,42 @@ __device__ void decode_item_wide(const AttnArgs &A, const int32_t *__restrict__ 
             }
         }
     }
-    if (slot < 0 || !A.fused) return;
+}
+
+// A batch of few decodes: one split is run by a whole workgroup of R waves, which share its pages out (a contiguous
+// run each, so that a wave has at most 64 / R pages: most of them are in flight at once, and the workgroup needs about
+// one memory latency for its split where a single wave needs one per page).  All waves then meet in LDS and the
+// combination is spread over all threads.
+// W = 2: two splits (items it[0], it[1]) to a workgroup, R / 2 waves each: the two halves of up to 2048 tokens of one (sequence, KV head),
+// a team with one result, or splits of two pairs that are not cut (or one and a padding item).
+template <int D, class E, int NS, int R, int W, bool STORE>
+__device__ void decode_item_wide(const AttnArgs &A, const int32_t *__restrict__ items, float *lds) {
+    constexpr int MT = D / 16, RI = R / W;  // RI: waves of a split
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));  // may be called in a loop (see prefill_item)
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int32_t *it = items + (W > 1 ? wave / RI * kItemInts : 0);
+    const int kvh = it[DC_KVH], t0 = it[DC_BEGIN], t1 = it[DC_END], qrow = it[DC_QROW], slot = it[DC_SLOT];
+    const int team = it[DC_TEAM], merge_item = (team >> 8) - 1;
+    const int G = A.G;
+    const int n_pages = (t1 - t0 + kBlock - 1) / kBlock;
+    const int p0 = n_pages * (wave % RI) / RI, p1 = n_pages * (wave % RI + 1) / RI;  // this wave's pages of the split
+    f32x4 o[MT];
+#pragma unroll
+    for (int c = 0; c < MT; c++) o[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m_run = -1e30f, l_run = 0.f;
+    if (p1 > p0) {
+        const bool takes_new = p1 == n_pages && (team & kTeamTailBit) && A.k_new != nullptr;
+        decode_sweep<D, E, NS, STORE>(A, kvh, qrow, A.pages + it[DC_PAGEOFF] + t0 / kBlock + p0, p1 - p0, min(t1 - t0, p1 * kBlock) - p0 * kBlock,
+                               takes_new, lane, o, m_run, l_run);
+    }
+    const WaveResults<D> res(lds, R, G);
+    res.put(wave, lane, o, m_run, l_run);
+    __syncthreads();
+    if (W == 1 || (team & 15) == W) wide_combine<D, E, R>(A, res, 0, tid, R * 64, kvh, qrow, slot);
+    else if (n_pages > 0) wide_combine<D, E, RI>(A, res, wave / RI * RI, tid % (RI * 64), RI * 64, kvh, qrow, slot);
+    if (slot < 0 || !A.fused) return;  // (a partial result: the whole workgroup's)
     stores_done();
     const int32_t *mg = A.merge + (int64_t)merge_item * kItemInts;
     if (!workgroup_arrives_last(A.counters + mg[MG_COUNTER], mg[MG_NSPLIT], reinterpret_cast<int *>(lds), tid)) return;
@@ -1451,9 +1463,9 @@ struct AttnScalars {
 // wave; WAVES = 4: two of them (three at head_dim 64, 168 registers), chosen by estimate_chunk.  Without CHUNK: decode-only
 // batches (WAVES = 4, three workgroups per compute unit).
 // Workgroups [0, n_prefill) run the prefill pieces the plan gave them, one after the other; the rest run
-// decode items, one per wave, or (WIDE; a form of its own, so that neither pays for the other's registers: both in one
-// kernel, chosen at run time, cost 1 us of 195 on a 2048-token chunk with 64 decodes) one per workgroup.
-template <int D, class E, int WAVES, bool CHUNK, bool WIDE>
+// decode items, one per wave, or (WIDE = 1 or 2; forms of their own, so that neither pays for the other's registers: both in one
+// kernel, chosen at run time, cost 1 us of 195 on a 2048-token chunk with 64 decodes) one or two per workgroup.
+template <int D, class E, int WAVES, bool CHUNK, int WIDE>
 __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : CHUNK ? small_wg_per_cu(D) : kDecodeWgPerCu)
     mixed_attention_kernel(uint16_t *k_pool, uint16_t *v_pool, const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_new,
                            const uint16_t *__restrict__ v_new, uint16_t *__restrict__ out, const int32_t *__restrict__ pages,
@@ -1492,18 +1504,18 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : CHUNK ?
                 __syncthreads();  // the next piece's tile copies reuse the LDS
             }
         }
-    } else if (WAVES != kMixedWaves || A.queue < 0) {
+    } else if (WAVES != kMixedWaves || WIDE == 2 || A.queue < 0) {
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const int idx = (wg - A.n_prefill) * WAVES + wave;
         // the decode items fill whole workgroups (padding items at the end of some): every wave gets one
-        if constexpr (WIDE)
-            decode_item_wide<D, E, NS, WAVES, false>(A, decode + (int64_t)(wg - A.n_prefill) * kItemInts, reinterpret_cast<float *>(lds));
+        if constexpr (WIDE > 0)
+            decode_item_wide<D, E, NS, WAVES, WIDE, false>(A, decode + (int64_t)(wg - A.n_prefill) * WIDE * kItemInts, reinterpret_cast<float *>(lds));
         else if (idx < A.n_decode) decode_item<D, E, NS>(A, decode + (int64_t)idx * kItemInts, reinterpret_cast<float *>(lds), WAVES);
     }
 #ifdef TC_WG_TRACE
     t_mid = __builtin_amdgcn_s_memrealtime();
 #endif
-    if constexpr (WAVES == kMixedWaves) {
+    if constexpr (WAVES == kMixedWaves && WIDE < 2) {
         if (A.queue >= 0) {
         // Decode queue (the launch has no more workgroups than the chip has compute units, all resident from the
         // start).  The decode items are handed out in units of one workgroup's worth (WAVES items, teams included)
@@ -1524,7 +1536,7 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : CHUNK ?
             __syncthreads();
             const int unit = *drawn;
             if (unit >= n_units) break;
-            if constexpr (WIDE) decode_item_wide<D, E, NS, WAVES, false>(A, decode + (int64_t)unit * kItemInts, reinterpret_cast<float *>(lds));
+            if constexpr (WIDE > 0) decode_item_wide<D, E, NS, WAVES, 1, false>(A, decode + (int64_t)unit * kItemInts, reinterpret_cast<float *>(lds));
             else decode_item<D, E, NS>(A, decode + ((int64_t)unit * WAVES + wave) * kItemInts, reinterpret_cast<float *>(lds), WAVES);
         }
         if (threadIdx.x == 0 && __hip_atomic_fetch_add(gone, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1) {
@@ -1538,10 +1550,10 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : CHUNK ?
 #endif
 }
 
-// A batch of few decodes: one workgroup of kWideWaves waves per split (decode_item_wide), one or two per compute unit, with
+// A batch of few decodes: one workgroup of kWideWaves waves per split, or per two (decode_item_wide), one or two per compute unit, with
 // registers for kWideStages - 1 pages in flight per wave; the wave that takes a sequence's new token from k_new / v_new also
 // stores its row.  Arguments as above; the prefill lists are empty.
-template <int D, class E>
+template <int D, class E, int W>
 __global__ void __launch_bounds__(kWideWaves * 64, 2)
     wide_decode_kernel(uint16_t *k_pool, uint16_t *v_pool, const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_new,
                        const uint16_t *__restrict__ v_new, uint16_t *__restrict__ out, const int32_t *__restrict__ pages,
@@ -1556,7 +1568,7 @@ __global__ void __launch_bounds__(kWideWaves * 64, 2)
     A.merge = merge; A.counters = counters;
     A.ws_o = ws; A.ws_ml = ws + (int64_t)sc.n_partials * sc.G * D;
     A.n_decode = sc.n_decode; A.Hq = sc.Hq; A.Hkv = sc.Hkv; A.G = sc.G; A.fused = sc.fused; A.scale_log2 = sc.scale_log2;
-    decode_item_wide<D, E, kWideStages, kWideWaves, true>(A, decode + (int64_t)blockIdx.x * kItemInts, reinterpret_cast<float *>(lds));
+    decode_item_wide<D, E, kWideStages, kWideWaves, W, true>(A, decode + (int64_t)blockIdx.x * W * kItemInts, reinterpret_cast<float *>(lds));
 #ifdef TC_WG_TRACE
     wg_trace(t_start, t_start, true);
 #endif
@@ -1729,6 +1741,7 @@ int launch_kv_migrate(const tc_plan *p, bool import, int page0, int n_pages, int
 // More than 64 KiB of dynamic LDS needs an opt-in per kernel function and per device; remembered per
 // instantiation and device (setting it twice is harmless, so racing first calls need no lock).
 // All forms of the kernel at once, so that a caller who has run one batch of a shape may capture any other.
+template <int N> using Int = std::integral_constant<int, N>;
 template <int D, class E>
 static int allow_prefill_lds(int device) {
     static std::atomic<bool> done[kMaxDevices];
@@ -1739,9 +1752,9 @@ static int allow_prefill_lds(int device) {
         return hipFuncSetAttribute((const void *)mixed_attention_kernel<D, E, NW, true, decltype(wide)::value>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                    PrefillLds<D, NW>::kBytes);
     };
-    const std::integral_constant<int, kMixedWaves> large;
-    const std::integral_constant<int, kSmallWaves> small;
-    for (hipError_t e : {allow(large, std::false_type()), allow(large, std::true_type()), allow(small, std::false_type()), allow(small, std::true_type())})
+    const Int<kMixedWaves> large;
+    const Int<kSmallWaves> small;
+    for (hipError_t e : {allow(large, Int<0>()), allow(large, Int<1>()), allow(large, Int<2>()), allow(small, Int<0>()), allow(small, Int<1>())})
         if (e != hipSuccess) return (int)e;
     if (known) done[device].store(true, std::memory_order_release);
     return 0;
@@ -1768,17 +1781,20 @@ static int launch_attention_d(const tc_plan *p, const AttnArgs &A, int launches,
             mixed_attention_kernel<D, E, NW, true, decltype(wide)::value><<<grid, NW * 64, PrefillLds<D, NW>::kBytes, st>>>(
                 A.k_pool, A.v_pool, A.q, A.k_new, A.v_new, A.out, A.pages, A.records, A.decode, A.merge, append, A.counters, A.ws_o, sc);
         };
-        const std::integral_constant<int, kMixedWaves> large;
-        const std::integral_constant<int, kSmallWaves> small;
-        const bool wide = p->waves_per_item > 1;
-        if (p->prefill_waves == kMixedWaves) wide ? launch(large, std::true_type()) : launch(large, std::false_type());
-        else wide ? launch(small, std::true_type()) : launch(small, std::false_type());
+        const Int<kMixedWaves> large;
+        const Int<kSmallWaves> small;
+        const int wide = p->waves_per_item > 1 ? p->items_per_wg : 0;
+        if (p->prefill_waves == kMixedWaves) wide == 2 ? launch(large, Int<2>()) : wide == 1 ? launch(large, Int<1>()) : launch(large, Int<0>());
+        else wide ? launch(small, Int<1>()) : launch(small, Int<0>());
     } else if (grid > 0 && p->waves_per_item > 1) {
         static_assert(decode_lds_bytes(kWideWaves, 16, D) <= 65536, "more than 64 KiB of dynamic LDS needs an opt-in");
-        wide_decode_kernel<D, E><<<grid, kWideWaves * 64, decode_lds_bytes(kWideWaves, p->G, D), st>>>(A.k_pool, A.v_pool, A.q, A.k_new, A.v_new, A.out, A.pages, A.decode, A.merge,
-                                                                     A.counters, A.ws_o, sc);
+        auto launch = [&](auto per_wg) {
+            wide_decode_kernel<D, E, decltype(per_wg)::value><<<grid, kWideWaves * 64, decode_lds_bytes(kWideWaves, p->G, D), st>>>(
+                A.k_pool, A.v_pool, A.q, A.k_new, A.v_new, A.out, A.pages, A.decode, A.merge, A.counters, A.ws_o, sc);
+        };
+        p->items_per_wg == 2 ? launch(Int<2>()) : launch(Int<1>());
     } else if (grid > 0) {
-        mixed_attention_kernel<D, E, kDecodeWaves, false, false><<<grid, kDecodeWaves * 64, decode_lds_bytes(kDecodeWaves, p->G, D), st>>>(
+        mixed_attention_kernel<D, E, kDecodeWaves, false, 0><<<grid, kDecodeWaves * 64, decode_lds_bytes(kDecodeWaves, p->G, D), st>>>(
             A.k_pool, A.v_pool, A.q, A.k_new, A.v_new, A.out, A.pages, A.records, A.decode, A.merge, append,
             A.counters, A.ws_o, sc);
     }

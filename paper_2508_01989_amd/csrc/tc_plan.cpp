@@ -88,6 +88,43 @@ static int shortest_split(const tc_plan *p, int S, int64_t target) {
     return lo * kBlock;
 }
 
+// Workgroups of the decode branch when a split of at most `split` tokens is run by a whole one (W = 1), or two of them by one (W = 2;
+// sequences that are a single split then share a workgroup with another, but are counted as if they did not).
+static int64_t wide_workgroups(const tc_plan *p, int S, int split, int W, int64_t *single = nullptr) {
+    int64_t full = 0, one = 0;
+    for (int s = 0; s < S; s++)
+        if (p->q_start[s + 1] - p->q_start[s] == 1) {
+            const int n = num_splits((int64_t)p->ctx_len[s] + 1, split, W);
+            if (n >= W) full += n / W; else one++;
+        }
+    if (single) *single = one * p->Hkv;
+    return (full + one) * p->Hkv;
+}
+
+// Splits of up to 1024 tokens run by whole workgroups that fill the last of two to four rounds only in part leave units idle
+// in it, and each split costs its start and its combination.  Where two splits to a workgroup (half of its waves each; the halves of up
+// to 2048 tokens of a sequence have one result) save the round: the shortest splits that do, else 0.  Not for many sequences
+// that are a single split, whose pages then have half as many waves: beside a chunk up to a quarter of the workgroups, without one no
+// sequence of up to 2048 tokens.
+// Measured (us per step, one split to a workgroup / two; 32/8 heads, head_dim 128, unless stated):
+//   beside 128 at 1000   24 of 512-4096 48.4 / 43.6, 40 of lognormal 1500 51.6 / 47.5, 12 of lognormal 6000 58.2 / 52.7, 40/8 heads, head_dim 64
+//                        36.6 / 31.9, 28 of lognormal 2500 35.8 / 31.2
+//   decodes only         12 of lognormal 6000 52.6 / 48.7, 40/8 heads, head_dim 64 29.9 / 27.5; 10 of 4000-12000 54.2 / 50.2, 6 of 8000-20000
+//                        59.2 / 56.9; with shorter sequences, 31 of 489-3912, 52.4 / 52.9, 8/8 heads 50.3 / 52.1, 40 of lognormal 1500 45.9 / 46.7
+//   single splits        16/2 heads, 176 short decodes beside 564 first tokens 20.1 / 24.8
+static int two_split_workgroups(const tc_plan *p, int S, int split, int64_t at_once, bool decodes_only) {
+    const int64_t rounds = (wide_workgroups(p, S, split, 1) + at_once - 1) / at_once;
+    if (split < kMaxSplitPages * kBlock || rounds < 2 || rounds > 4) return 0;
+    if (decodes_only && *std::min_element(p->ctx_len.begin(), p->ctx_len.begin() + S) < 2 * kMaxSplitPages * kBlock) return 0;
+    const int max_pages = decodes_only ? 40 : kMaxSplitPages;  // two waves for a split: no more than 20 pages each
+    for (int pages = kMaxSplitPages / 2; pages <= max_pages; pages++) {
+        int64_t single = 0;
+        const int64_t n = wide_workgroups(p, S, pages * kBlock, 2, &single);
+        if (n <= (rounds - 1) * at_once) return single * 4 > n ? 0 : pages * kBlock;
+    }
+    return 0;
+}
+
 // A batch of few decodes (no prefill chunk) whose single-wave splits would leave wave slots empty or keep a few waves
 // busy long after the others: every split is run by a whole workgroup instead (decode_item_wide), and a sequence of more than
 // 1024 tokens is cut into as many splits as it takes to have one workgroup per compute unit (two per unit once
@@ -124,8 +161,7 @@ static int choose_wide_split(const tc_plan *p, int S, int64_t decode_tokens) {
     const double chip_pairs = pairs * (p->D / 128.0);
     if (chip_pairs > 3 * kNumCu && token_heads < 288 * pairs && longest_pages < 12 + chip_pairs / kNumCu) return 0;
     const int wide = shortest_split(p, S, token_heads > 900 * kNumCu ? 2 * kNumCu : kNumCu);
-    int64_t items = 0;
-    for (int s = 0; s < S; s++) items += (int64_t)num_splits((int64_t)p->ctx_len[s] + 1, wide, 1) * p->Hkv;
+    const int64_t items = wide_workgroups(p, S, wide, 1);
     const bool few_doubled = p->D == 128 && items > kNumCu && 2 * items < 3 * kNumCu;  // a few units get a second workgroup
     const int64_t max_split = (int64_t)kMaxSplitPages * kBlock;
     if (longest > max_split && longest <= kDecodeWaves * max_split && 4 * longest * kNumCu < (few_doubled ? 9 : 7) * token_heads) return 0;
@@ -165,9 +201,7 @@ static int choose_wide_split_beside_chunk(const tc_plan *p, int S, double t_rest
     const double t_rest = std::max(t_rest_us, 8.0);
     if (t_longest <= share * t_rest) return 0;
     const int split = shortest_split(p, S, std::max<int64_t>(slots - n_prefill_wg, slots / 4));
-    int64_t items = 0;  // workgroups of the decode branch
-    for (int s = 0; s < S; s++)
-        if (p->q_start[s + 1] - p->q_start[s] == 1) items += (int64_t)num_splits((int64_t)p->ctx_len[s] + 1, split, 1) * p->Hkv;
+    const int64_t items = wide_workgroups(p, S, split, 1);
     const double t_starts = (queue ? 3.0 : 2.0) * std::max<int64_t>(0, items - slots) / slots;
     return t_longest <= share * (t_rest + t_starts) ? 0 : split;
 }
@@ -457,7 +491,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
             const double t_whole = std::max(t.whole, t_decode), t_levelled = t.levelled + unit_decode;
             // Levelled: not beside a decode branch that needs about as long (512 at 2048, 16 of 512-4096; 1024 at 2048, 64 decodes, 600 MB of K/V, whole /
             // levelled 143 / 155), and where the items nearly fill the chip beside decodes at all, whose queue levels too, only when the sweeps
-            // are very uneven (1700 at 3000 with 32 of lognormal 1024 116.2 / 118.1; 8, 800 at 0 and 746 at 7226 with 21 of 1200 156.0 / 129.2);
+            // are very uneven (1700 at 3000 with 32 of lognormal 1024 116.2 / 118.1; 8, 800 at 0 and 746 at 7226 with 21 of 1200 156.0 / 129.2),
             // without decodes not for a few per cent either (1500 at 20000, 40/8 heads, head_dim 64, 326 / 341).
             const double level_below = items * 4 <= 3 * kNumCu ? 0.95 : decode_tokens > 0 ? 0.7 : 0.9;
             if (t_levelled < level_below * t_whole && t_levelled < t.small && t_decode < 0.75 * t_levelled) {
@@ -508,6 +542,11 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
             p->split_tokens = split;
             p->items_per_wg = 1;
             p->waves_per_item = kWideWaves;
+            if (const int two = two_split_workgroups(p, S, split, 2 * kNumCu, true)) {
+                p->split_tokens = two;
+                p->items_per_wg = 2;
+                p->waves_per_item = kWideWaves / 2;
+            }
         }
     if (!w.blocks.empty() && n_decode_seqs > 0) {
         double longest_piece = 0, tiles = 0;
@@ -521,6 +560,13 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
             p->split_tokens = split;
             p->items_per_wg = 1;
             p->waves_per_item = p->prefill_waves;
+            const int64_t free_units = kNumCu - (int64_t)n_wg_head * Hkv;
+            if (!queue && p->prefill_waves == kMixedWaves && free_units >= kNumCu / 4)
+                if (const int two = two_split_workgroups(p, S, split, free_units, false)) {
+                    p->split_tokens = two;
+                    p->items_per_wg = 2;
+                    p->waves_per_item = kMixedWaves / 2;
+                }
         }
     }
     const int W = p->items_per_wg;

@@ -480,6 +480,45 @@ def test_small_workgroups(H, name):
     assert np.array_equal(H.to_host(db.out), single)
 
 
+# Two splits to a workgroup, half of its waves each: sequences of one split beside another of theirs or a padding item, of two (one
+# result) and of up to 28 (partial results), whole pages and ragged ends, new tokens from the pool and (fused) from k_new / v_new.
+TWO_SPLITS = {
+    # name: (Hq, Hkv, D, q_len, ctx, dtype, threads); the decodes follow one chunk, or there is none
+    "beside_a_chunk": (35, 7, 128, [21] + [1] * 16, [100, 5000, 3000, 2047, 1023, 2049, 1024, 100, 0, 2900, 3100, 3500, 2500, 1700, 4099, 700, 5200], "fp16", 512),
+    "beside_a_chunk_padding": (21, 7, 128, [21] + [1] * 17, [100, 5000, 3000, 2047, 1023, 2049, 1024, 100, 0, 2900, 3100, 3500, 2500, 1700, 4099, 700, 1500, 500], "bf16", 512),
+    "beside_a_chunk_g16_d64_padding": (112, 7, 64, [30] + [1] * 14, [3, 2048, 5000, 3000, 2047, 6143, 2049, 2100, 2900, 3100, 3500, 2500, 1700, 5100, 300], "bf16", 512),
+    "beside_a_chunk_g1_d64": (32, 32, 64, [40] + [1] * 7, [100, 5000, 3000, 2047, 1023, 2049, 1024, 100], "bf16", 512),
+    "alone_g1": (8, 8, 128, [1] * 10, [7000, 8000, 2048, 2049, 5119, 10239, 10240, 7500, 9100, 8111], "bf16", 256),
+    "alone_g5": (40, 8, 128, [1] * 9, [7000, 8000, 2048, 5119, 10239, 10240, 7500, 9100, 8111], "fp16", 256),
+    "alone_g16_d64": (128, 8, 64, [1] * 5, [7000, 18000, 2048, 12239, 30240], "bf16", 256),
+}
+
+
+@pytest.mark.parametrize("name", list(TWO_SPLITS))
+def test_two_splits_to_a_workgroup(H, name):
+    import torch
+    Hq, Hkv, D, q_len, ctx, dtype, threads = TWO_SPLITS[name]
+    b = W.make_batch(W.custom_spec(name, Hq, Hkv, D, q_len, ctx, seed=zlib.crc32(name.encode()) % 10007, dtype=dtype))
+    (mx, rel), db = run_and_compare(H, b, name, gather=None)
+    info = db.plan.info
+    assert (info.block_threads, info.block_threads // 64 // info.waves_per_item, info.decode_queue) == (threads, 2, 0)
+    assert dtype != "fp16" or (mx <= FP16_MAX_ABS and rel <= FP16_REL_L2), (mx, rel)
+    items = db.plan.items(1)
+    assert ("padding" in name) == bool(np.any(items[:, 3] == items[:, 2]))  # a padding item has no tokens
+    single = H.to_host(db.out).copy()
+    for _ in range(2):  # the counters of the merges are back at zero after every launch
+        db.out.fill_(0)
+        db.attention()
+        torch.cuda.synchronize()
+        assert np.array_equal(H.to_host(db.out), single)
+    db.out.fill_(0)
+    db.attention_partials()
+    db.split_merge()
+    torch.cuda.synchronize()
+    assert np.array_equal(H.to_host(db.out), single), "two-launch form"
+    check_fused_step(H, b, name)
+
+
 # The same beside prefill chunks: few long decodes are run by whole workgroups of eight waves (drawn from the queue when the
 # row blocks take more than a quarter of the units, workgroups of their own otherwise), balanced ones by single waves.
 MIXED_DECODE_FORMS = {
