@@ -198,12 +198,20 @@ static int choose_wide_split_beside_chunk(const tc_plan *p, int S, double t_rest
         }
     const double t_longest = 1.1 * (p->D / 128.0) * (double)longest / (kBlock * W);
     const double share = !queue && n_prefill_wg > slots / 2 ? 0.8 : p->D == 64 ? 0.65 : 0.5;
-    const double t_rest = std::max(t_rest_us, 8.0);
-    if (t_longest <= share * t_rest) return 0;
+    // More sweeps than the chip takes at once: the decode workgroups start when the last of them have, so what their longest wave needs comes
+    // on top.  The line is at about 1900 tokens, 4700 at head_dim 64 (single-wave splits / whole workgroups): 32/8 heads, 2300 at 0 with 16 of
+    // lognormal 1024 88.2 / 65.5, 12 of 512-4096 74.4 / 69.7; 3500 at 0 with 3 of 4000-12000 153.2 / 120.5; 40/8 heads, 1800 at 0 with 32 of lognormal
+    // 1024 91.3 / 71.8, with 64 of 500-1500 90.3 / 92.9; head_dim 64, 64/8 heads, 2000 at 2000 with 16 of lognormal 1024 131.0 / 119.8, 1300 at 0 with
+    // 32 52.4 / 43.5; 12 of 512-4096 beside 2300 at 1000, 40/8 heads, 70.7 / 75.5, beside 2200 at 0, 32/32 heads, 74.5 / 82.1.
+    // With more than four times as many sweeps the last ones are short beside the whole (8192 at 24576, 64/8 heads, 32 decodes: whole workgroups
+    // are 0.8 % slower).
+    const bool late = !queue && n_prefill_wg > slots && n_prefill_wg <= 4 * slots;
+    const double t_rest = std::max(t_rest_us, 8.0), line = late ? std::min(share * t_rest, p->D == 64 ? 20.0 : 16.0) : share * t_rest;
+    if (t_longest <= line) return 0;
     const int split = shortest_split(p, S, std::max<int64_t>(slots - n_prefill_wg, slots / 4));
     const int64_t items = wide_workgroups(p, S, split, 1);
     const double t_starts = (queue ? 3.0 : 2.0) * std::max<int64_t>(0, items - slots) / slots;
-    return t_longest <= share * (t_rest + t_starts) ? 0 : split;
+    return t_longest <= (late ? line + t_starts : share * (t_rest + t_starts)) ? 0 : split;
 }
 
 // When a batch has few prefill row blocks (a small chunk, as on a decode-heavy instance), each of

@@ -480,6 +480,26 @@ def test_small_workgroups(H, name):
     assert np.array_equal(H.to_host(db.out), single)
 
 
+# More sweeps than the chip takes at once, and decodes behind them: by whole workgroups when one of them is long, else by single waves.
+LATE_DECODES = {
+    # name: (Hq, Hkv, D, q_len, ctx, dtype, waves per item)
+    "long_d64": (128, 8, 64, [600] + [1] * 3, [2000, 5000, 300, 8191], "bf16", 8),
+    "long_g16": (128, 8, 128, [570] + [1] * 5, [1203, 2200, 1700, 1700, 900, 17], "fp16", 8),
+    "short_g16": (128, 8, 128, [570] + [1] * 5, [1203, 1700, 1700, 1600, 900, 17], "bf16", 1),
+}
+
+
+@pytest.mark.parametrize("name", list(LATE_DECODES))
+def test_decodes_behind_more_sweeps_than_units(H, name):
+    Hq, Hkv, D, q_len, ctx, dtype, waves = LATE_DECODES[name]
+    b = W.make_batch(W.custom_spec(name, Hq, Hkv, D, q_len, ctx, seed=zlib.crc32(name.encode()) % 10007, dtype=dtype))
+    rows = np.unique(np.concatenate([np.arange(0, b.total_q, 7), b.q_start[1:] - 1]))
+    (mx, rel), db = run_and_compare(H, b, name, rows=rows, gather=None)
+    info = db.plan.info
+    assert info.num_prefill_workgroups > 256 and (info.block_threads, info.waves_per_item, info.decode_queue) == (512, waves, 0)
+    assert dtype != "fp16" or (mx <= FP16_MAX_ABS and rel <= FP16_REL_L2), (mx, rel)
+
+
 # Two splits to a workgroup, half of its waves each: sequences of one split beside another of theirs or a padding item, of two (one
 # result) and of up to 28 (partial results), whole pages and ragged ends, new tokens from the pool and (fused) from k_new / v_new.
 TWO_SPLITS = {
