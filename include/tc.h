@@ -104,8 +104,8 @@ typedef struct {
     int32_t decode_queue;               /* 1: the decode items are drawn from a queue, in units of one workgroup's   */
                                         /* worth, by grid_blocks - num_prefill_workgroups decode workgroups and by   */
                                         /* the prefill workgroups once their pieces are done (levelled chunks)       */
-    int32_t waves_per_item;             /* waves that share one decode item: 1, or all of a workgroup's (4 in a batch */
-                                        /* of few decodes, 8 for few long decodes beside a chunk)                     */
+    int32_t waves_per_item;             /* waves that share one decode item: 1, all of a workgroup's (few, long       */
+                                        /* decodes) or half of them                                                   */
     int64_t build_ns;                   /* host time of the latest work-list build ...       */
     int64_t upload_ns;                  /* ... and of enqueueing its copy to the device      */
 } tc_plan_info;
@@ -153,9 +153,8 @@ tc_status tc_plan_get_info(const tc_plan *plan, tc_plan_info *info);
  * workgroup runs the pieces [first piece of the workgroup, .. the one marked last].
  * Decode items come in workgroups of W = block_threads / (64 * waves_per_item) wave slots.  A sequence is cut
  * into 1, 2, 4 .. W splits, or a multiple of W when W splits of 1024 tokens cannot cover it; its splits hold the
- * same number of pages up to one.  Where waves_per_item > 1, W is 1 and the one item of a workgroup is run by all
- * of its waves, which share its pages out; a sequence of at most 1024 tokens is then one split, a longer one any
- * number of them.  Consecutive splits of one (sequence, KV head) in one workgroup are a
+ * same number of pages up to one.  Where waves_per_item > 1, the waves of an item share its pages out.  W is then 1 (a
+ * sequence of at most 1024 tokens is one split, a longer one any number of them) or 2 (half of the waves each).  Consecutive splits of one (sequence, KV head) in one workgroup are a
  * team (consecutive items, positions 0..members-1, all carrying the team's partial_slot): the workgroup
  * combines their results, and the team writes the output rows (-1) or one partial result.  An item
  * with kv_begin = kv_end (seq = -1) is padding. */
