@@ -33,6 +33,7 @@ constexpr int kPrefillTileTokens = 64;  // KV tokens per LDS tile of the prefill
 constexpr int kNumCu = 256;         // compute units the work list is balanced for
 constexpr int kMigrateLayers = 64;  // layers one migration launch covers (their pool pointers travel as kernel arguments)
 constexpr int kMaxLayers = 4096;
+constexpr size_t kStaticScratchBytes = (size_t)64 << 20;  // what tc_mixed_attention_static has for partial results
 constexpr int kMaxDevices = 64;     // per-device state (function attributes, the static scratch) is kept for this many GPUs
 
 // Field indices of work items (see tc_plan_copy_items in tc.h).

@@ -1849,7 +1849,6 @@ int launch_attention(const tc_plan *p, const tc_kv_pool *pool, const void *q, co
 // Partial results of split KV ranges for tc_mixed_attention_static.  Every GPU the library runs on holds
 // its own copy of the array, at its own address, until the process ends.  Host code never uses the
 // array's name as an address: the device address is asked for once per device and kept.
-constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 int static_scratch(int device, void **ptr, size_t *bytes) {

@@ -271,6 +271,22 @@ static void level_prefill(std::vector<PlanRowBlock> &blocks, std::vector<PlanPie
     }
 }
 
+// tc_mixed_attention_static takes every batch whose partial results fit its array.  Items that run whole leave none, so runs must not be
+// what takes a batch out of that array: piece regions that fit it beside the decodes' partial results.  Those are at most one per 1024 tokens
+// of a sequence longer than that, in teams or in splits, or as many as there are units to fill with shorter splits.
+static int64_t fitting_regions(const tc_plan *p, int S) {
+    int64_t partials = 0;
+    bool decodes = false;
+    for (int s = 0; s < S; s++)
+        if (p->q_start[s + 1] - p->q_start[s] == 1) {
+            decodes = true;
+            if (p->ctx_len[s] >= kMaxSplitPages * kBlock) partials += p->ctx_len[s] / (kMaxSplitPages * kBlock) + 1;
+        }
+    if (decodes) partials = std::max<int64_t>(partials * p->Hkv, kNumCu);
+    const int64_t row_bytes = (int64_t)(p->D + 2) * sizeof(float);
+    return std::max<int64_t>(0, (int64_t)kStaticScratchBytes - partials * p->G * row_bytes) / (kPrefillRows * row_bytes);
+}
+
 // Rows of a prefill item: 256, or 128 when the chunk is small.  An item of 128 rows keeps one wave per SIMD busy, and such a
 // wave sweeps a tile in about 0.6 of the time it takes beside a second one; but there are at least twice as many items,
 // by 128 / G against 256 / G positions more than twice where 256 / G is odd, three times for chunks of a few positions more than
@@ -468,6 +484,23 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     const int64_t decode_bytes = decode_tokens * Hkv * D * 4;
     p->rows_per_item = choose_rows_per_item(p, S, decode_bytes);
     make_row_blocks(p, S, p->rows_per_item, w.blocks);
+    // The sweeps in runs, at most `bins` per KV head: the number made, or 0 (the blocks as they were) where runs whose regions
+    // fit the static scratch would be far fewer.  A cut between two runs makes at most two regions.
+    auto level = [&](int bins, bool any_scratch) {
+        const int wanted = bins;
+        const int64_t fit = any_scratch ? INT64_MAX : fitting_regions(p, S) / Hkv;
+        while (bins * 16 >= wanted * 15) {
+            w.pieces.clear();
+            level_prefill(w.blocks, w.pieces, bins);
+            int64_t regions = 0;
+            for (const PlanRowBlock &x : w.blocks) regions += x.k > 1 ? x.k : 0;
+            if (regions <= fit) return bins;
+            bins -= (int)((regions - fit + 1) / 2);
+        }
+        w.pieces.clear();
+        for (PlanRowBlock &x : w.blocks) x.k = 1;
+        return 0;
+    };
     // Regimes by the number of prefill items (row blocks x KV heads) against the compute units:
     //   at most a quarter:  cut each item's KV range so that more units work on the chunk
     //   up to four times:   whole items, levelled runs or small workgroups, whichever is estimated to take least (estimate_chunk)
@@ -502,14 +535,19 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
             // are very uneven (1700 at 3000 with 32 of lognormal 1024 116.2 / 118.1; 8, 800 at 0 and 746 at 7226 with 21 of 1200 156.0 / 129.2),
             // without decodes not for a few per cent either (1500 at 20000, 40/8 heads, head_dim 64, 326 / 341).
             const double level_below = items * 4 <= 3 * kNumCu ? 0.95 : decode_tokens > 0 ? 0.7 : 0.9;
+            int runs = 0;
             if (t_levelled < level_below * t_whole && t_levelled < t.small && t_decode < 0.75 * t_levelled) {
                 double tiles = 0;
                 for (const PlanRowBlock &x : w.blocks) tiles += x.n_tiles;
                 const double unit_prefill = tiles * Hkv * kTileUs * (D / 128.0) / kNumCu;
                 const int cu_decode = decode_tokens ? std::max(1, (int)std::lround(kNumCu * unit_decode / (unit_decode + unit_prefill))) : 0;
                 const int64_t by_units = std::max<int64_t>(1, (kNumCu - std::min<int64_t>(cu_decode, kNumCu / 2)) / Hkv);
-                n_wg_per_head = (int)std::max<int64_t>(1, std::min<int64_t>(by_units, (int64_t)tiles / kMinBinTiles));
-                level_prefill(w.blocks, w.pieces, n_wg_per_head);
+                // (Chunks of up to three quarters of the units beside few decodes run like this whatever scratch they need.)
+                const bool any_scratch = items * 4 <= 3 * kNumCu && t_decode < 0.25 * w.blocks[0].n_tiles * kTileUs * (D / 128.0);
+                runs = level((int)std::max<int64_t>(1, std::min<int64_t>(by_units, (int64_t)tiles / kMinBinTiles)), any_scratch);
+            }
+            if (runs > 0) {
+                n_wg_per_head = runs;
                 queue = decode_tokens > 0;
             // Small workgroups: beside more decodes the queue fills the units whose sweeps end early; long sweeps run at a lower clock in either
             // form than the estimates say (6562 at 16848, 8/8 heads, 526 / 543).

@@ -495,6 +495,31 @@ def test_one_long_decode_beside_a_chunk_does_not_take_many_short_ones_along(tc, 
     assert check_work_list(tc, sp, table, nb).waves_per_item == waves
 
 
+STATIC_SCRATCH = 64 << 20  # what tc_mixed_attention_static has
+
+
+@pytest.mark.parametrize("Hq,Hkv,q_len,ctx,levelled", [
+    (16, 2, [8709], [20000], True),                             # runs whose cuts all leave two regions: 508 of 133 KB
+    (16, 1, [4116], [20000], True),
+    (4, 1, [20608], [40000], True),
+    (8, 2, [8410] * 3, [13417, 56851, 0], True),
+    (128, 8, [556] + [1] * 6, [20000] + [15000] * 6, True),     # beside the decodes' own partial results
+    (128, 8, [520] + [1] * 8, [30000] + [9000] * 8, True),
+    (32, 2, [2143] + [1] * 5, [51899] + [57495] * 5, True),
+    (128, 8, [639] + [1] * 15, [79919] + [9701] * 15, False),   # too few runs would fit
+])
+def test_chunks_cut_into_runs_fit_the_static_scratch(tc, Hq, Hkv, q_len, ctx, levelled):
+    """Whole items need no workspace: a chunk of more items than three quarters of the compute units (which ran whole at first)
+    must not be refused by tc_mixed_attention_static for the sake of a level load."""
+    sp = W.custom_spec("static", Hq, Hkv, 128, q_len, ctx)
+    mb = int((sp.kv_len.max() + 15) // 16)
+    qs = np.concatenate([[0], np.cumsum(q_len)]).astype(np.int32)
+    p = tc.Plan(tc.make_pool(Hq, Hkv, 128, 16), qs, sp.ctx_len, np.zeros((len(q_len), mb), np.int32), host_only=True)
+    assert 4 * p.info.num_prefill_items > 3 * 256
+    assert (p.info.num_prefill_workgroups < p.info.num_prefill_pieces) == levelled
+    assert p.workspace_bytes <= STATIC_SCRATCH
+
+
 COUNTER_IMAGE = """
 #include <cstdio>
 #include <cstdlib>
