@@ -535,23 +535,29 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
             // are very uneven (1700 at 3000 with 32 of lognormal 1024 116.2 / 118.1; 8, 800 at 0 and 746 at 7226 with 21 of 1200 156.0 / 129.2),
             // without decodes not for a few per cent either (1500 at 20000, 40/8 heads, head_dim 64, 326 / 341).
             const double level_below = items * 4 <= 3 * kNumCu ? 0.95 : decode_tokens > 0 ? 0.7 : 0.9;
+            // Small workgroups: beside more decodes the queue fills the units whose sweeps end early; long sweeps run at a lower clock in either
+            // form than the estimates say (6562 at 16848, 8/8 heads, 526 / 543).
+            const bool small = t.small < (w.blocks[0].n_tiles <= 64 ? 0.97 : 0.9) * t_whole && t_decode < 0.05 * t.small;
+            double tiles = 0;
+            for (const PlanRowBlock &x : w.blocks) tiles += x.n_tiles;
+            const double unit_prefill = tiles * Hkv * kTileUs * (D / 128.0) / kNumCu;
+            const int cu_decode = decode_tokens ? std::max(1, (int)std::lround(kNumCu * unit_decode / (unit_decode + unit_prefill))) : 0;
+            const int64_t by_units = std::max<int64_t>(1, (kNumCu - std::min<int64_t>(cu_decode, kNumCu / 2)) / Hkv);
+            const int bins = (int)std::max<int64_t>(1, std::min<int64_t>(by_units, (int64_t)tiles / kMinBinTiles));
+            // Where small workgroups are estimated to be faster still, but do not serve beside so many decodes: runs all the same (whole / levelled:
+            // 32/8 heads, 1408 at 0 with 3 of 579-4632 41.3 / 39.1; 64/8, 360 at 0 and 335 at 1064 with 2 of 981-7850 39.0 / 34.3; 16/2, head_dim 64,
+            // 1424 at 0 with 8 of 462-3698 27.5 / 21.2), if a KV head has eight of them: with fewer, of whole units for every head, too many units have
+            // none (32/32 heads, 1136 at 174 with one of 1000 40.9 / 47.2, 776 at 1489 with 2 of 442-3540 58.5 / 63.1).
             int runs = 0;
-            if (t_levelled < level_below * t_whole && t_levelled < t.small && t_decode < 0.75 * t_levelled) {
-                double tiles = 0;
-                for (const PlanRowBlock &x : w.blocks) tiles += x.n_tiles;
-                const double unit_prefill = tiles * Hkv * kTileUs * (D / 128.0) / kNumCu;
-                const int cu_decode = decode_tokens ? std::max(1, (int)std::lround(kNumCu * unit_decode / (unit_decode + unit_prefill))) : 0;
-                const int64_t by_units = std::max<int64_t>(1, (kNumCu - std::min<int64_t>(cu_decode, kNumCu / 2)) / Hkv);
+            if (t_levelled < level_below * t_whole && (t_levelled < t.small || (!small && bins >= 8)) && t_decode < 0.75 * t_levelled) {
                 // (Chunks of up to three quarters of the units beside few decodes run like this whatever scratch they need.)
                 const bool any_scratch = items * 4 <= 3 * kNumCu && t_decode < 0.25 * w.blocks[0].n_tiles * kTileUs * (D / 128.0);
-                runs = level((int)std::max<int64_t>(1, std::min<int64_t>(by_units, (int64_t)tiles / kMinBinTiles)), any_scratch);
+                runs = level(bins, any_scratch);
             }
             if (runs > 0) {
                 n_wg_per_head = runs;
                 queue = decode_tokens > 0;
-            // Small workgroups: beside more decodes the queue fills the units whose sweeps end early; long sweeps run at a lower clock in either
-            // form than the estimates say (6562 at 16848, 8/8 heads, 526 / 543).
-            } else if (t.small < (w.blocks[0].n_tiles <= 64 ? 0.97 : 0.9) * t_whole && t_decode < 0.05 * t.small) {
+            } else if (small) {
                 p->prefill_waves = kSmallWaves;
                 p->rows_per_item = kPrefillRows / 2;
                 make_row_blocks(p, S, p->rows_per_item, w.blocks);

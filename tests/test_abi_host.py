@@ -520,6 +520,23 @@ def test_chunks_cut_into_runs_fit_the_static_scratch(tc, Hq, Hkv, q_len, ctx, le
     assert p.workspace_bytes <= STATIC_SCRATCH
 
 
+@pytest.mark.parametrize("Hq,Hkv,D,q_len,ctx,levelled", [
+    (40, 8, 128, [1115] + [1] * 4, [2091] + [1200] * 4, True),
+    (64, 8, 64, [609] + [1] * 69, [4975] + [495] * 69, True),
+    (32, 8, 128, [1408] + [1] * 3, [0] + [2000] * 3, True),
+    (16, 2, 64, [1424] + [1] * 8, [0] + [2000] * 8, True),
+    (32, 8, 128, [1408], [0], False),                         # small workgroups, without decodes
+    (32, 32, 128, [1136, 1], [174, 1000], False),             # seven runs per KV head: whole items
+])
+def test_runs_where_small_workgroups_are_out_of_the_question(tc, Hq, Hkv, D, q_len, ctx, levelled):
+    """Beside decodes that small workgroups do not serve, the choice is between whole items and runs, whatever small ones would take."""
+    sp = W.custom_spec("runs", Hq, Hkv, D, q_len, ctx)
+    table, mb, nb = W.make_tables(sp, np.random.default_rng(14))
+    info = check_work_list(tc, sp, table, nb)
+    assert (info.num_prefill_workgroups < info.num_prefill_pieces) == levelled
+    assert info.block_threads == (512 if 1 in q_len else 256)
+
+
 COUNTER_IMAGE = """
 #include <cstdio>
 #include <cstdlib>
