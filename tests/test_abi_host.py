@@ -525,7 +525,7 @@ def test_chunks_cut_into_runs_fit_the_static_scratch(tc, Hq, Hkv, q_len, ctx, le
     (64, 8, 64, [609] + [1] * 69, [4975] + [495] * 69, True),
     (32, 8, 128, [1408] + [1] * 3, [0] + [2000] * 3, True),
     (16, 2, 64, [1424] + [1] * 8, [0] + [2000] * 8, True),
-    (32, 8, 128, [1408], [0], False),                         # small workgroups, without decodes
+    (32, 8, 128, [2048], [0], False),                         # small workgroups, without decodes
     (32, 32, 128, [1136, 1], [174, 1000], False),             # seven runs per KV head: whole items
 ])
 def test_runs_where_small_workgroups_are_out_of_the_question(tc, Hq, Hkv, D, q_len, ctx, levelled):
