@@ -187,7 +187,7 @@ static int choose_wide_split(const tc_plan *p, int S, int64_t decode_tokens) {
 // (2240) 74.1 / 52.1; 701, 333 and 45 at 0, 32/8 heads, head_dim 64, one of 6000 and 400 (3248) 46.5 / 56.5, and 128 39.4 / 27.8.
 // At head_dim 64 a split is half the bytes for the same start and combination, and the line is at 0.65: 128 at 1000 with 32
 // decodes of 512-4096 tokens (share 0.55) 38.0 / 40.2, 256 at 500 with 64 of lognormal 1500 (0.8) 50.6 / 46.4.
-static int choose_wide_split_beside_chunk(const tc_plan *p, int S, double t_rest_us, int64_t n_prefill_wg, bool queue) {
+static int choose_wide_split_beside_chunk(const tc_plan *p, int S, double t_rest_us, double t_decode_us, int64_t n_prefill_wg, bool queue) {
     const int W = p->prefill_waves;
     const int64_t slots = wg_slots(p);
     int64_t longest = 0;  // decode sequences that one workgroup covers
@@ -199,14 +199,17 @@ static int choose_wide_split_beside_chunk(const tc_plan *p, int S, double t_rest
     const double t_longest = 1.1 * (p->D / 128.0) * (double)longest / (kBlock * W);
     const double share = !queue && n_prefill_wg > slots / 2 ? 0.8 : p->D == 64 ? 0.65 : 0.5;
     // More sweeps than the chip takes at once: the decode workgroups start when the last of them have, so what their longest wave needs comes
-    // on top.  The line is at about 1900 tokens, 4700 at head_dim 64 (single-wave splits / whole workgroups): 32/8 heads, 2300 at 0 with 16 of
+    // on top, unless the decodes themselves keep the chip busy for twice as long.  Alone it counts from 16 us on, 20 at head_dim 64: 1900 and 4700 tokens
+    // beside workgroups of eight waves, half as many beside those of four.  (Single-wave splits / whole workgroups): 32/8 heads, 2300 at 0 with 16 of
     // lognormal 1024 88.2 / 65.5, 12 of 512-4096 74.4 / 69.7; 3500 at 0 with 3 of 4000-12000 153.2 / 120.5; 40/8 heads, 1800 at 0 with 32 of lognormal
     // 1024 91.3 / 71.8, with 64 of 500-1500 90.3 / 92.9; head_dim 64, 64/8 heads, 2000 at 2000 with 16 of lognormal 1024 131.0 / 119.8, 1300 at 0 with
     // 32 52.4 / 43.5; 12 of 512-4096 beside 2300 at 1000, 40/8 heads, 70.7 / 75.5, beside 2200 at 0, 32/32 heads, 74.5 / 82.1.
-    // With more than four times as many sweeps the last ones are short beside the whole (8192 at 24576, 64/8 heads, 32 decodes: whole workgroups
-    // are 0.8 % slower).
-    const bool late = !queue && n_prefill_wg > slots && n_prefill_wg <= 4 * slots;
-    const double t_rest = std::max(t_rest_us, 8.0), line = late ? std::min(share * t_rest, p->D == 64 ? 20.0 : 16.0) : share * t_rest;
+    // Many times as many sweeps: 1240 (128/8 heads, 2480 at 0 with one of 8200) 232.1 / 219.3, 1376 (8700 at 0, 6 of 1700-6900) 738.4 / 694.8, 4176 (128/8,
+    // 8344 at 65, 2 of 2400-9500) 2013 / 1969.  Long decode streams: 40/8 heads, 2664 at 0 with 29 of 2600-10400 (160 us of K/V) 216.7 / 226.1, 3136
+    // at 0 with 31 of 3800-15400 315.9 / 327.2; 32/8, 10816 at 4394 with 34 of 3600-14400 1590 / 1613.
+    const bool late = !queue && n_prefill_wg > slots;
+    const double t_rest = std::max(t_rest_us, 8.0);
+    const double line = late ? std::max(std::min(share * t_rest, p->D == 64 ? 20.0 : 16.0), 0.5 * t_decode_us) : share * t_rest;
     if (t_longest <= line) return 0;
     const int split = shortest_split(p, S, std::max<int64_t>(slots - n_prefill_wg, slots / 4));
     const int64_t items = wide_workgroups(p, S, split, 1);
@@ -607,8 +610,8 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
             tiles += (x.t1 - x.t0) * (double)Hkv;
         }
         const double tile_us = kTileUs * (D / 128.0) * (p->rows_per_item == kPrefillRows ? 1.0 : 0.6);  // see choose_rows_per_item
-        const double t_rest = std::max(longest_piece * tile_us, tiles * tile_us / kNumCu + (double)decode_bytes / 5.0e6);
-        if (const int split = choose_wide_split_beside_chunk(p, S, t_rest, (int64_t)n_wg_head * Hkv, queue)) {
+        const double t_decode = (double)decode_bytes / 5.0e6, t_rest = std::max(longest_piece * tile_us, tiles * tile_us / kNumCu + t_decode);
+        if (const int split = choose_wide_split_beside_chunk(p, S, t_rest, t_decode, (int64_t)n_wg_head * Hkv, queue)) {
             p->split_tokens = split;
             p->items_per_wg = 1;
             p->waves_per_item = p->prefill_waves;

@@ -537,6 +537,26 @@ def test_runs_where_small_workgroups_are_out_of_the_question(tc, Hq, Hkv, D, q_l
     assert info.block_threads == (512 if 1 in q_len else 256)
 
 
+@pytest.mark.parametrize("Hq,Hkv,D,chunk,offset,decodes,waves", [
+    (40, 8, 128, 2664, 0, [3000 + 250 * i for i in range(29)], 1),    # 155 us of K/V: the longest sequences are a part of that
+    (32, 8, 64, 3300, 0, [1500 + 180 * i for i in range(36)], 1),
+    (32, 8, 128, 3648, 0, [2264 + 25 * i for i in range(62)], 1),
+    (40, 8, 128, 2664, 0, [3000, 5000, 7000], 8),
+    (32, 8, 128, 8190, 0, [3000] * 8, 8),                             # 1024 sweeps, four for every unit
+    (32, 8, 128, 8224, 0, [3000] * 8, 8),                             # and 1032
+    (128, 8, 128, 2480, 0, [2546], 8),
+    (64, 8, 128, 8192, 24576, [16000] * 32, 1),
+])
+def test_decodes_behind_many_sweeps(tc, Hq, Hkv, D, chunk, offset, decodes, waves):
+    """Whole workgroups for decodes that start when the last sweeps have: however many sweeps there are, where the longest sequence
+    takes more than half of the time of the decodes' stream."""
+    sp = W.custom_spec("late", Hq, Hkv, D, [chunk] + [1] * len(decodes), [offset] + decodes)
+    table, mb, nb = W.make_tables(sp, np.random.default_rng(15))
+    info = check_work_list(tc, sp, table, nb)
+    assert info.num_prefill_workgroups > 256 and info.decode_queue == 0
+    assert (info.block_threads, info.waves_per_item) == (512, waves)
+
+
 COUNTER_IMAGE = """
 #include <cstdio>
 #include <cstdlib>
