@@ -67,6 +67,7 @@ struct PlanRowBlock { int seq, pos0, npos; int64_t cost; int n_tiles, k, slot0; 
 struct PlanPiece { int block, t0, t1, c, wg; };
 struct PlanRun { int seq, h, ns, len; };
 struct PlanTeam { int seq, h, first, n, idx, wg, at; };
+struct PlanUnits { double free_us; int n; };  // n compute units that are free from then on
 struct PlanScratch {
     std::vector<PlanRowBlock> blocks;
     std::vector<PlanPiece> pieces;
@@ -74,7 +75,7 @@ struct PlanScratch {
     std::vector<PlanTeam> teams;
     std::vector<int> wg_fill, open;
     std::vector<int32_t> n_teams, slot0, merge_of;
-    std::vector<double> units;
+    std::vector<PlanUnits> units;
 };
 
 }  // namespace tc

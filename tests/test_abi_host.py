@@ -557,6 +557,26 @@ def test_decodes_behind_many_sweeps(tc, Hq, Hkv, D, chunk, offset, decodes, wave
     assert (info.block_threads, info.waves_per_item) == (512, waves)
 
 
+def _build_ratio(tc, Hq, Hkv, first, second):
+    """Host time of building one work list over that of another: the least of many, in turn, which other load does not reach."""
+    pool, batches = tc.make_pool(Hq, Hkv, 128, 16), []
+    for q_len, ctx in (first, second):
+        sp = W.custom_spec("time", Hq, Hkv, 128, q_len, ctx)
+        qs = np.concatenate([[0], np.cumsum(q_len)]).astype(np.int32)
+        table = np.zeros((len(q_len), int((sp.kv_len.max() + 15) // 16)), np.int32)
+        batches.append((tc.Plan(pool, qs, sp.ctx_len, table, host_only=True), qs, sp.ctx_len, table, []))
+    for _ in range(300):
+        for p, qs, ctx_len, table, ns in batches:
+            p.update(pool, qs, ctx_len, table)
+            ns.append(p.info.build_ns)
+    return min(batches[0][4]) / min(batches[1][4])
+
+
+def test_estimating_the_forms_of_a_chunk_is_a_small_part_of_planning(tc):
+    """A plan is made every iteration.  1000 items, whose forms are estimated, against 1032, which run whole without a look at it."""
+    assert _build_ratio(tc, 32, 8, ([8000], [0]), ([8256], [0])) < 1.4
+
+
 COUNTER_IMAGE = """
 #include <cstdio>
 #include <cstdlib>
