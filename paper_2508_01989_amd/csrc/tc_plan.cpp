@@ -116,12 +116,17 @@ static int two_split_workgroups(const tc_plan *p, int S, int split, int64_t at_o
     if (split < kMaxSplitPages * kBlock || rounds < 2 || rounds > 4) return 0;
     if (decodes_only && *std::min_element(p->ctx_len.begin(), p->ctx_len.begin() + S) < 2 * kMaxSplitPages * kBlock) return 0;
     const int max_pages = decodes_only ? 40 : kMaxSplitPages;  // two waves for a split: no more than 20 pages each
-    for (int pages = kMaxSplitPages / 2; pages <= max_pages; pages++) {
-        int64_t single = 0;
-        const int64_t n = wide_workgroups(p, S, pages * kBlock, 2, &single);
-        if (n <= (rounds - 1) * at_once) return single * 4 > n ? 0 : pages * kBlock;
+    // Longer splits are never more workgroups: the shortest are found by halving the range (six counts of the sequences, not 33).
+    const int64_t most = (rounds - 1) * at_once;
+    int pages = kMaxSplitPages / 2, last = max_pages;
+    int64_t single = 0;
+    if (wide_workgroups(p, S, last * kBlock, 2) > most) return 0;
+    while (pages < last) {
+        const int mid = (pages + last) / 2;
+        if (wide_workgroups(p, S, mid * kBlock, 2) <= most) last = mid; else pages = mid + 1;
     }
-    return 0;
+    const int64_t n = wide_workgroups(p, S, pages * kBlock, 2, &single);
+    return single * 4 > n ? 0 : pages * kBlock;
 }
 
 // A batch of few decodes (no prefill chunk) whose single-wave splits would leave wave slots empty or keep a few waves

@@ -577,6 +577,12 @@ def test_estimating_the_forms_of_a_chunk_is_a_small_part_of_planning(tc):
     assert _build_ratio(tc, 32, 8, ([8000], [0]), ([8256], [0])) < 1.4
 
 
+def test_looking_for_two_splits_to_a_workgroup_is_a_small_part_of_planning(tc):
+    """499 short decodes and a long one, where the length of two splits is looked for, against 1099 and one, where it is not."""
+    batch = lambda n: ([128] + [1] * n, [1000, 8000] + [100] * (n - 1))
+    assert _build_ratio(tc, 8, 1, batch(500), batch(1100)) < 0.7
+
+
 COUNTER_IMAGE = """
 #include <cstdio>
 #include <cstdlib>
