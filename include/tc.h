@@ -133,7 +133,8 @@ tc_status tc_plan_get_info(const tc_plan *plan, tc_plan_info *info);
 
 /* Copy work items to HOST memory for inspection: kind 0 = prefill items, 1 = decode, 2 = merge,
  * 3 = prefill pieces; 8 int32 per item, at most cap_items items.  Kind 4 = index of the first piece of
- * every prefill workgroup, one int32 each.  Fields:
+ * every prefill workgroup, one int32 each.  Pieces and workgroups are read from what the kernel reads, in the
+ * order of the launch.  Fields:
  *   prefill {seq, kv_head, first_local_pos, num_pos, q_row0, ctx, page_off, num_pages}
  *   decode  {seq, kv_head, kv_begin, kv_end, q_row, partial_slot (-1 = writes out), page_off,
  *            team members | position in team << 4 | (split ends with the newest token) << 7 |

@@ -56,8 +56,9 @@ enum { PP_ITEM, PP_T0, PP_T1, PP_SLOT, PP_K, PP_C, PP_COUNTER, PP_LAST };
 // What the kernel reads of a piece: one 128-byte record, the same for all KV heads (workgroup w * Hkv + h runs the pieces of
 // record w and those chained to it for KV head h).  REGION / COUNTER: piece region of the item's piece 0 and arrival counter
 // (int32 from the first one) for KV head 0; head h's lie h * K regions and h * CSTRIDE int32 behind.  REGION = -1: the piece is the
-// whole item.  NEXT: record of the workgroup's next piece, or -1.  From RC_IDS on: the page ids of the first four KV tiles.
-enum { RC_T0, RC_T1, RC_K, RC_C, RC_REGION, RC_COUNTER, RC_CSTRIDE, RC_NEXT, RC_POS0, RC_NPOS, RC_QROW0, RC_CTX, RC_PAGEOFF, RC_NPAGES, RC_IDS = 16 };
+// whole item.  NEXT: record of the workgroup's next piece, or -1.  BLOCK: the prefill items are BLOCK * Hkv + h (for tc_plan_copy_items).  From
+// RC_IDS on: the page ids of the first four KV tiles.
+enum { RC_T0, RC_T1, RC_K, RC_C, RC_REGION, RC_COUNTER, RC_CSTRIDE, RC_NEXT, RC_POS0, RC_NPOS, RC_QROW0, RC_CTX, RC_PAGEOFF, RC_NPAGES, RC_BLOCK, RC_IDS = 16 };
 constexpr int kRecordInts = 32;
 
 void set_error(const std::string &msg);
@@ -103,10 +104,9 @@ struct tc_plan {
     // plans with a device copy (the upload is then a true asynchronous copy), plain memory otherwise.
     int32_t *host = nullptr;
     size_t host_n = 0, host_cap = 0;
-    size_t upload_n = 0;  // the first int32 of the image, which the device copy holds (the lists behind them are for tc_plan_copy_items)
     bool host_pinned = false;
-    size_t off_records = 0, off_append = 0, off_pages = 0, off_valid = 0, off_prefill = 0, off_pieces = 0, off_wg = 0, off_decode = 0,
-           off_merge = 0, off_counters = 0;  // off_valid: tokens (1..16) each page holds
+    size_t off_records = 0, off_append = 0, off_pages = 0, off_valid = 0, off_prefill = 0, off_decode = 0, off_merge = 0,
+           off_counters = 0;  // off_valid: tokens (1..16) each page holds
     int n_append = 0;  // (sequence, page) segments written by the append
     int n_append_prefill = 0;  // the first of them are those of the prefill chunks
     bool on_device = false;  // the plan keeps a device copy (tc_plan_create); false for tc_plan_create_host

@@ -1645,7 +1645,7 @@ int upload_plan(tc_plan *p, void *stream) {
     if (e != hipSuccess) return (int)e;
     if (p->device >= 0 && p->device != device) return (int)hipErrorInvalidDevice;
     p->device = device;
-    if (p->upload_n > p->dev_cap) {
+    if (p->host_n > p->dev_cap) {
         if (p->dev) (void)hipFree(p->dev);
         p->dev = nullptr;
         p->dev_cap = 0;
@@ -1659,7 +1659,7 @@ int upload_plan(tc_plan *p, void *stream) {
         if (e != hipSuccess) return (int)e;
         p->upload_event = ev;
     }
-    e = hipMemcpyAsync(p->dev, p->host, p->upload_n * sizeof(int32_t), hipMemcpyHostToDevice, (hipStream_t)stream);
+    e = hipMemcpyAsync(p->dev, p->host, p->host_n * sizeof(int32_t), hipMemcpyHostToDevice, (hipStream_t)stream);
     if (e != hipSuccess) return (int)e;
     return (int)hipEventRecord((hipEvent_t)p->upload_event, (hipStream_t)stream);
 }
@@ -1677,7 +1677,7 @@ void free_plan_buffers(tc_plan *p) {
         if (p->host_pinned) (void)hipHostFree(p->host); else std::free(p->host);
     }
     p->host = nullptr;
-    p->host_cap = p->host_n = p->upload_n = 0;
+    p->host_cap = p->host_n = 0;
 }
 
 // ------------------------------------------------------------------------------------

@@ -448,7 +448,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     p->rows_per_item = kPrefillRows;
     p->prefill_waves = kMixedWaves;
     p->total_pages = 0;
-    p->host_n = p->upload_n = 0;
+    p->host_n = 0;
     const int Hq = pool->num_q_heads, Hkv = pool->num_kv_heads, D = pool->head_dim;
     if (pool->dtype != TC_BF16 && pool->dtype != TC_FP16) return fail(TC_ERR_SHAPE, "dtype must be TC_BF16 or TC_FP16");
     if (pool->block_size != kBlock) return fail(TC_ERR_SHAPE, "block_size must be 16");
@@ -708,10 +708,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     while (counter_stride > 1 && n_counters * counter_stride > kCounterInts) counter_stride /= 2;
     const size_t off_queue = ((size_t)n_counters * counter_stride + kCounterLine - 1) / kCounterLine * kCounterLine;  // from off_counters
     const size_t n_counter_ints = queue ? off_queue + 2 * kCounterLine : (size_t)n_counters * counter_stride;
-    const size_t upload = std::max<size_t>(off_counters + n_counter_ints, 1);
-    const size_t off_pieces = upload;  // from here on for tc_plan_copy_items only
-    const size_t off_wg = off_pieces + (size_t)n_pieces * kItemInts;
-    const size_t total = off_wg + (size_t)n_prefill_wg;
+    const size_t total = std::max<size_t>(off_counters + n_counter_ints, 1);
     if (int err = begin_plan_host(p, total)) return fail(TC_ERR_DEVICE, std::string("host buffer of the plan: ") + hip_error_text(err));
     int32_t *H = p->host;
 
@@ -769,7 +766,6 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
             }
         }
         // the counters of cut blocks were handed out block by block, head by head
-        int32_t *pc = H + off_pieces, *wgf = H + off_wg;
         std::vector<int32_t> &first_counter = w.slot0;  // (borrowed) per block
         first_counter.assign(w.blocks.size(), -1);
         {
@@ -803,34 +799,12 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
                 r[RC_POS0] = blk.pos0; r[RC_NPOS] = blk.npos; r[RC_QROW0] = p->q_start[blk.seq]; r[RC_CTX] = p->ctx_len[blk.seq];
                 r[RC_PAGEOFF] = p->page_off[blk.seq];
                 const int np = p->page_off[blk.seq + 1] - p->page_off[blk.seq];
-                r[RC_NPAGES] = np;
-                r[RC_NPAGES + 1] = r[RC_NPAGES + 2] = 0;
+                r[RC_NPAGES] = np; r[RC_BLOCK] = x.block; r[RC_BLOCK + 1] = 0;
                 const int32_t *ids = H + off_pages + p->page_off[blk.seq];
                 constexpr int kTilePages = kPrefillTileTokens / kBlock;
                 for (int i = 0; i < kRecordInts - RC_IDS; i++) r[RC_IDS + i] = ids[std::min(x.t0 * kTilePages + i, np - 1)];  // past the end: the last page, never used
                 before = r;
             }
-        }
-        // `pieces` lists each workgroup's pieces once, for all KV heads alike: workgroup (w, KV head h) has the
-        // index w * Hkv + h and its pieces are stored next to each other.
-        size_t i = 0, out = 0;
-        while (i < w.pieces.size()) {
-            size_t j = i;
-            while (j < w.pieces.size() && w.pieces[j].wg == w.pieces[i].wg) j++;
-            for (int h = 0; h < Hkv; h++) {
-                wgf[(size_t)w.pieces[i].wg * Hkv + h] = (int32_t)out;
-                for (size_t u = i; u < j; u++, out++) {
-                    const PlanPiece &x = w.pieces[u];
-                    const PlanRowBlock &blk = w.blocks[x.block];
-                    int32_t *q = pc + out * kItemInts;
-                    q[PP_ITEM] = x.block * Hkv + h; q[PP_T0] = x.t0; q[PP_T1] = x.t1;
-                    q[PP_SLOT] = blk.k > 1 ? blk.slot0 + h * blk.k : -1;
-                    q[PP_K] = blk.k; q[PP_C] = x.c;
-                    q[PP_COUNTER] = blk.k > 1 ? counter_stride * (first_counter[x.block] + h) : -1;
-                    q[PP_LAST] = u + 1 == j;
-                }
-            }
-            i = j;
         }
     }
 
@@ -881,10 +855,9 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     p->n_merge = (int)n_merge; p->n_partials = (int)n_partials; p->n_counters = (int)n_counters; p->n_append = (int)n_append;
     p->n_piece_partials = (int)n_piece_partials; p->n_merge_prefill = (int)n_merge_prefill;
     p->n_decode_wg = (int)n_decode_wg; p->counter_stride = counter_stride; p->queue_counter = queue ? (int)off_queue : -1;
-    p->off_records = off_records; p->off_append = off_append; p->off_pages = off_pages; p->off_valid = off_valid; p->off_prefill = off_prefill; p->off_pieces = off_pieces;
-    p->off_wg = off_wg; p->off_decode = off_decode; p->off_merge = off_merge; p->off_counters = off_counters;
+    p->off_records = off_records; p->off_append = off_append; p->off_pages = off_pages; p->off_valid = off_valid; p->off_prefill = off_prefill;
+    p->off_decode = off_decode; p->off_merge = off_merge; p->off_counters = off_counters;
     p->host_n = total;
-    p->upload_n = upload;
     return TC_OK;
 }
 
@@ -951,26 +924,40 @@ tc_status tc_plan_get_info(const tc_plan *p, tc_plan_info *info) {
     return TC_OK;
 }
 
+// The pieces and workgroups of the launch, from the records that it reads: workgroup w * Hkv + h runs record w and those behind it for KV head h.
+static void copy_pieces(const tc_plan *p, int32_t *pieces, size_t cap_pieces, int32_t *first, size_t cap_first) {
+    size_t n = 0;
+    for (int wg = 0; wg < p->n_prefill_wg; wg++) {
+        const int h = wg % p->Hkv;
+        if ((size_t)wg < cap_first) first[wg] = (int32_t)n;
+        for (int i = wg / p->Hkv; i >= 0; n++) {
+            const int32_t *r = p->host + p->off_records + (size_t)i * tc::kRecordInts;
+            i = r[tc::RC_NEXT];
+            if (n >= cap_pieces) continue;
+            const bool cut = r[tc::RC_REGION] >= 0;
+            int32_t *q = pieces + n * tc::kItemInts;
+            q[tc::PP_ITEM] = r[tc::RC_BLOCK] * p->Hkv + h; q[tc::PP_T0] = r[tc::RC_T0]; q[tc::PP_T1] = r[tc::RC_T1];
+            q[tc::PP_SLOT] = cut ? r[tc::RC_REGION] + h * r[tc::RC_K] : -1;
+            q[tc::PP_K] = r[tc::RC_K]; q[tc::PP_C] = r[tc::RC_C];
+            q[tc::PP_COUNTER] = cut ? (r[tc::RC_COUNTER] + h * r[tc::RC_CSTRIDE]) / p->counter_stride : -1;
+            q[tc::PP_LAST] = i < 0;
+        }
+    }
+}
+
 tc_status tc_plan_copy_items(const tc_plan *p, int32_t kind, int32_t *dst, size_t cap_items) {
     if (!p || !dst) { tc::set_error("plan or dst is NULL"); return TC_ERR_NULL; }
     size_t off, n;
     if (kind == 0) { off = p->off_prefill; n = p->n_prefill; }
     else if (kind == 1) { off = p->off_decode; n = p->n_decode; }
     else if (kind == 2) { off = p->off_merge; n = p->n_merge; }
-    else if (kind == 3) { off = p->off_pieces; n = p->n_pieces; }
-    else if (kind == 4) {  // first piece of every prefill workgroup: plain int32, not 8-int items
-        n = std::min((size_t)p->n_prefill_wg, cap_items);
-        if (n) std::memcpy(dst, p->host + p->off_wg, n * sizeof(int32_t));
-        return TC_OK;
-    }
+    else if (kind == 3) { copy_pieces(p, dst, cap_items, nullptr, 0); return TC_OK; }
+    else if (kind == 4) { copy_pieces(p, nullptr, 0, dst, cap_items); return TC_OK; }  // plain int32, not 8-int items
     else { tc::set_error("kind must be 0, 1, 2, 3 or 4"); return TC_ERR_ARG; }
     n = std::min(n, cap_items);
     if (n) std::memcpy(dst, p->host + off, n * tc::kItemInts * sizeof(int32_t));
-    if (kind == 2 || kind == 3)  // the image says where a counter lies, the item which one it is
-        for (size_t i = 0; i < n; i++) {
-            int32_t &c = dst[i * tc::kItemInts + (kind == 2 ? tc::MG_COUNTER : tc::PP_COUNTER)];
-            if (c > 0) c /= p->counter_stride;
-        }
+    if (kind == 2)  // the image says where a counter lies, the item which one it is
+        for (size_t i = 0; i < n; i++) dst[i * tc::kItemInts + tc::MG_COUNTER] /= p->counter_stride;
     return TC_OK;
 }
 

@@ -193,10 +193,14 @@ def check_work_list(tc, sp, table, nb):
         if 256 % Hkv == 0:
             assert np.all(heads == wg_of_piece % Hkv)
         tiles_of_wg = np.bincount(wg_of_piece, weights=(pc[:, 2] - pc[:, 1]), minlength=n_wg)
-        levelled = 256 < 4 * len(pf) <= 3 * 256 and len(pc) > len(pf)   # (a mid-sized chunk beside a heavy decode branch runs uncut)
+        levelled = 256 < 4 * len(pf) and len(pc) > len(pf)   # (up to a quarter of the compute units items are cut evenly)
         if not levelled:      # one piece per workgroup, most tiles first (uncut items, or few items whose KV ranges are cut)
-            assert n_wg == len(pc) and np.all(np.diff(tiles_of_wg[::Hkv]) <= 0)
-        else:                 # items for a quarter to three quarters of the compute units: every KV head has the same runs, of nearly equal cost (tiles + 3 per piece)
+            tiles_of_record = tiles_of_wg[::Hkv].copy()
+            if len(pf) == len(pc) and info.block_threads == 256 and n_wg <= 256 * (2 if sp.head_dim == 128 else 3):
+                for first in range(256 // Hkv, n_wg // Hkv, 2 * (256 // Hkv)):  # workgroups of four waves that all run at once: every other row of 256 turned round
+                    tiles_of_record[first:first + 256 // Hkv] = tiles_of_record[first:first + 256 // Hkv][::-1].copy()
+            assert n_wg == len(pc) and np.all(np.diff(tiles_of_record) <= 0)
+        else:                 # every KV head has the same runs, of nearly equal cost (tiles + 3 per piece)
             assert n_wg % Hkv == 0 and n_wg <= 256
             cost_of_wg = tiles_of_wg + 3 * np.bincount(wg_of_piece, minlength=n_wg)
             per_head = cost_of_wg.reshape(-1, Hkv)
@@ -581,6 +585,114 @@ def test_looking_for_two_splits_to_a_workgroup_is_a_small_part_of_planning(tc):
     """499 short decodes and a long one, where the length of two splits is looked for, against 1099 and one, where it is not."""
     batch = lambda n: ([128] + [1] * n, [1000, 8000] + [100] * (n - 1))
     assert _build_ratio(tc, 8, 1, batch(500), batch(1100)) < 0.7
+
+
+RECORDS = """
+#include <cstdio>
+#include <vector>
+#include "tc_internal.h"
+int main(int, char **argv) {  // {heads, KV heads, head_dim, blocks, sequences, table columns, q_start, ctx_len, table} -> {records, the image's counters, stride}
+    FILE *in = fopen(argv[1], "rb"), *out = fopen(argv[2], "wb");
+    int32_t h[6];
+    if (!in || !out || fread(h, 4, 6, in) != 6) return 1;
+    std::vector<int32_t> a((size_t)(h[4] + 1) + h[4] + (size_t)h[4] * h[5]);
+    if (fread(a.data(), 4, a.size(), in) != a.size()) return 1;
+    tc_kv_pool pool = {};
+    pool.num_q_heads = h[0]; pool.num_kv_heads = h[1]; pool.head_dim = h[2]; pool.block_size = 16; pool.dtype = TC_BF16; pool.num_blocks = h[3];
+    tc_batch b = {h[4], a.data(), a.data() + h[4] + 1, a.data() + 2 * h[4] + 1, h[5]};
+    tc_plan *p = nullptr;
+    if (tc_plan_create_host(&pool, &b, &p)) return 1;
+    if (p->off_records % tc::kRecordInts) return 1;
+    const int32_t n[2] = {p->n_counters, p->counter_stride};
+    fwrite(n, 4, 2, out);
+    fwrite(p->host + p->off_records, 4, (size_t)p->n_pieces / h[1] * tc::kRecordInts, out);
+    tc_plan_destroy(p);
+    return fclose(out);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def records_of(tc, tmp_path_factory):
+    """The records of a plan as the kernels read them (the image that is uploaded), [record][32]."""
+    d = tmp_path_factory.mktemp("records")
+    src, exe, lib_dir = d / "t.cpp", d / "t", os.path.dirname(tc.LIB_PATH)
+    src.write_text(RECORDS)
+    assert os.system(f"g++ -std=c++17 -I {ROOT}/include -I {lib_dir}/csrc {src} {tc.LIB_PATH} -Wl,-rpath,{lib_dir} -Wl,-rpath-link,/opt/rocm/lib -o {exe}") == 0
+
+    def run(sp, table, nb):
+        qs = np.concatenate([[0], np.cumsum(sp.q_len)])
+        head = [sp.num_q_heads, sp.num_kv_heads, sp.head_dim, nb, sp.num_seqs, table.shape[1]]
+        np.concatenate([head, qs, sp.ctx_len, table.ravel()]).astype(np.int32).tofile(d / "in")
+        assert os.system(f"LD_LIBRARY_PATH=/opt/rocm/lib {exe} {d}/in {d}/out") == 0
+        out = np.fromfile(d / "out", np.int32)
+        return out[:2], out[2:].reshape(-1, 32)
+    return run
+
+
+CHUNK_FORMS = [
+    # Hq, Hkv, D, q_len, ctx, (block_threads, rows per item, waves per decode item, queue, several pieces to a workgroup)
+    (32, 8, 128, [1024], [4096], (512, 256, 1, 0, True)),                                    # 128 items
+    (8, 8, 128, [7760], [0], (512, 256, 1, 0, True)),                                        # 248
+    (64, 8, 64, [1055], [13870], (512, 256, 1, 0, True)),                                    # 264
+    (16, 1, 128, [4116], [20000], (512, 256, 1, 0, True)),                                   # 258, as many runs as fit the static scratch
+    (16, 2, 64, [1270] + [1] * 3, [18176] + [7000, 2000, 300], (512, 256, 1, 1, True)),
+    (32, 2, 128, [2143] + [1] * 5, [51899] + [57495] * 5, (512, 256, 1, 1, True)),           # 268, with partial results of the decodes
+    (16, 2, 64, [1424] + [1] * 8, [0] + [2000] * 8, (512, 256, 8, 1, True)),
+    (32, 8, 128, [2048], [0], (256, 128, 1, 0, False)),                                      # small workgroups: two full rows of 256
+    (40, 8, 128, [1000], [0], (256, 128, 1, 0, False)),                                      # one and a part
+    (32, 8, 64, [2048, 300], [0, 5], (256, 128, 1, 0, False)),                               # two and a part
+    (48, 3, 128, [904], [0], (256, 128, 1, 0, False)),                                       # rows of 85 workgroups per KV head
+    (64, 8, 64, [2544], [0], (256, 128, 1, 0, False)),                                       # more than the chip takes at once: not turned
+    (32, 8, 128, [2048, 1], [0, 2500], (256, 128, 4, 0, False)),                             # decodes by whole workgroups of four waves
+    (15, 3, 128, [1092, 1, 1], [0, 597, 1329], (256, 128, 4, 0, False)),                     # with partial results
+    (105, 7, 64, [387, 1, 1], [0, 24, 1038], (256, 128, 4, 0, False)),
+    (30, 2, 128, [841, 1, 1], [213, 17, 4613], (256, 128, 1, 0, False)),                     # by single waves, five teams and one
+    (32, 8, 128, [256], [3000], (512, 128, 1, 0, False)),                                    # few items: cut evenly
+    (12, 4, 128, [837, 1], [830, 29], (512, 256, 1, 0, False)),
+]
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,q_len,ctx,form", CHUNK_FORMS)
+def test_records_that_the_kernels_read(tc, records_of, Hq, Hkv, D, q_len, ctx, form):
+    """Every form of a chunk: the work list covers the batch, and the records name its items, pieces, regions, counters and pages."""
+    sp = W.custom_spec("records", Hq, Hkv, D, q_len, ctx)
+    table, mb, nb = W.make_tables(sp, np.random.default_rng(16))
+    info = check_work_list(tc, sp, table, nb)
+    levelled = info.num_prefill_workgroups < info.num_prefill_pieces
+    assert (info.block_threads, info.rows_per_prefill_item, info.waves_per_item, info.decode_queue, levelled) == form
+    qs = np.concatenate([[0], np.cumsum(q_len)]).astype(np.int32)
+    p = tc.Plan(tc.make_pool(Hq, Hkv, D, nb), qs, sp.ctx_len, table, host_only=True)
+    items, pieces, first = p.items(0), p.items(3), p.items(4)
+    (n_counters, stride), rec = records_of(sp, table, nb)
+    assert n_counters == info.num_counters and len(rec) * Hkv == info.num_prefill_pieces
+    t0, t1, k, c, region, counter, cstride, nxt, pos0, npos, qrow0, ctx_, pageoff, n_pages, block = rec[:, :15].T
+    # chains: from the record of every workgroup to the one marked last, each record once
+    n_wg, seen = info.num_prefill_workgroups // Hkv, []
+    chains = []
+    for i in range(n_wg):
+        chain = []
+        while i >= 0:
+            assert i < len(rec) and len(chain) <= len(rec)
+            chain.append(i)
+            i = int(nxt[i])
+        chains.append(chain)
+    assert sorted(sum(chains, [])) == list(range(len(rec)))
+    # what tc_plan_copy_items says is in these chains, in the order of the launch
+    assert first.tolist() == list(np.cumsum([0] + [len(chains[w // Hkv]) for w in range(n_wg * Hkv)])[:-1])
+    order = np.array([i * Hkv + h for chain in chains for h in range(Hkv) for i in chain])
+    i, h = order // Hkv, order % Hkv
+    assert np.array_equal(pieces[:, 0], block[i] * Hkv + h) and np.array_equal(pieces[:, 1:3], np.stack([t0[i], t1[i]], 1))
+    cut = k > 1
+    assert np.array_equal(pieces[:, 3], np.where(cut[i], region[i] + h * k[i], -1)) and np.array_equal(pieces[:, 4:6], np.stack([k[i], c[i]], 1))
+    assert np.all((region >= 0) == cut) and np.all(cstride == stride) and np.all(counter % stride == 0)
+    assert np.array_equal(pieces[:, 6], np.where(cut[i], counter[i] // stride + h, -1))
+    # the item's own fields, and the page ids of the first four tiles (past the end: the last page)
+    mine = items[block * Hkv]
+    assert np.array_equal(np.stack([pos0, npos, qrow0, ctx_, pageoff, n_pages], 1), mine[:, 2:8])
+    for r in range(len(rec)):
+        row = table[mine[r, 0]]
+        assert np.array_equal(rec[r, 16:], row[np.minimum(t0[r] * 4 + np.arange(16), n_pages[r] - 1)]), r
 
 
 COUNTER_IMAGE = """
