@@ -480,6 +480,81 @@ def test_small_workgroups(H, name):
     assert np.array_equal(H.to_host(db.out), single)
 
 
+# Decodes beside workgroups of four waves: run by whole ones, sequences of one and of many splits, or by single waves, in teams of up to
+# four and with partial results of several teams.
+SMALL_WITH_DECODES = {
+    # name: (Hq, Hkv, D, q_len, ctx, dtype, waves per decode item, every how many rows are compared)
+    "whole_merge_g5": (15, 3, 128, [1092, 1, 1], [0, 597, 1329], "fp16", 4, 3),
+    "whole_merge_g15_d64": (105, 7, 64, [387, 1, 1], [0, 24, 1038], "bf16", 4, 5),
+    "whole_merge_g4": (32, 8, 128, [2048, 1], [0, 2500], "bf16", 4, 61),
+    "waves_merge_g15": (30, 2, 128, [841, 1, 1], [213, 17, 4613], "bf16", 1, 3),
+    "waves_merge_g8_d64": (16, 2, 64, [1091, 1], [0, 5523], "fp16", 1, 3),
+    "waves_teams_g8_d64": (64, 8, 64, [709, 1, 1, 1], [867, 410, 27, 140], "bf16", 1, 5),
+}
+
+
+@pytest.mark.parametrize("name", list(SMALL_WITH_DECODES))
+def test_small_workgroups_with_decodes(H, name):
+    import torch
+    Hq, Hkv, D, q_len, ctx, dtype, waves, every = SMALL_WITH_DECODES[name]
+    b = W.make_batch(W.custom_spec(name, Hq, Hkv, D, q_len, ctx, seed=zlib.crc32(name.encode()) % 10007, dtype=dtype))
+    rows = np.unique(np.concatenate([np.arange(0, b.total_q, every), b.q_start[1:] - 1]))
+    (mx, rel), db = run_and_compare(H, b, name, rows=rows, gather=None)
+    info = db.plan.info
+    assert (info.rows_per_prefill_item, info.block_threads, info.waves_per_item) == (128, 256, waves)
+    assert (info.num_partials > 0) == ("merge" in name)
+    assert dtype != "fp16" or (mx <= FP16_MAX_ABS and rel <= FP16_REL_L2), (mx, rel)
+    single = H.to_host(db.out).copy()
+    for _ in range(2):  # the counters of the merges are back at zero after every launch
+        db.out.fill_(0)
+        db.attention()
+        torch.cuda.synchronize()
+        assert np.array_equal(H.to_host(db.out), single)
+    db.out.fill_(0)
+    db.attention_partials()
+    db.split_merge()
+    torch.cuda.synchronize()
+    assert np.array_equal(H.to_host(db.out), single), "two-launch form"
+
+
+# More items than three quarters of the compute units, more than all of them: cut into level runs, several pieces to a workgroup, alone and
+# with decodes drawn from the queue; the static scratch holds the partial results of all of them
+# (63 of its 64 MiB for the last).
+LEVEL_RUNS = {
+    # name: (Hq, Hkv, D, q_len, ctx, dtype, items, every how many rows are compared)
+    "d64_196_items_queue": (16, 1, 64, [3131, 1, 1], [0, 9000, 11], "fp16", 196, 7),
+    "d64_257_items_queue": (16, 1, 64, [4097, 1], [2, 56], "bf16", 257, 11),
+    "d64_264_items": (64, 8, 64, [1055], [13870], "bf16", 264, 97),
+    "d128_195_items_two_chunks_queue": (16, 1, 128, [2427, 680, 1], [0, 2529, 100], "bf16", 195, 11),
+    "d128_193_items_g8": (8, 1, 128, [6155], [2], "fp16", 193, 23),
+    "d128_258_items_g16": (16, 1, 128, [4116], [20000], "bf16", 258, 211),
+}
+
+
+@pytest.mark.parametrize("name", list(LEVEL_RUNS))
+def test_level_runs(H, name):
+    import torch
+    Hq, Hkv, D, q_len, ctx, dtype, items, every = LEVEL_RUNS[name]
+    b = W.make_batch(W.custom_spec(name, Hq, Hkv, D, q_len, ctx, seed=zlib.crc32(name.encode()) % 10007, dtype=dtype))
+    rows = np.unique(np.concatenate([np.arange(0, b.total_q, every), b.q_start[1:] - 1]))
+    (mx, rel), db = run_and_compare(H, b, name, rows=rows, gather=None)
+    info = db.plan.info
+    assert info.num_prefill_items == items and info.num_prefill_workgroups < info.num_prefill_pieces and 0 < info.num_piece_partials
+    assert info.decode_queue == ("queue" in name)
+    assert dtype != "fp16" or (mx <= FP16_MAX_ABS and rel <= FP16_REL_L2), (mx, rel)
+    single = H.to_host(db.out).copy()
+    for form in (db.attention, db.attention_static, db.attention):  # the counters are back at zero after every launch
+        db.out.fill_(0)
+        form()
+        torch.cuda.synchronize()
+        assert np.array_equal(H.to_host(db.out), single), form.__name__
+    db.out.fill_(0)
+    db.attention_partials()
+    db.split_merge()
+    torch.cuda.synchronize()
+    assert np.array_equal(H.to_host(db.out), single), "two-launch form"
+
+
 # More sweeps than the chip takes at once, and decodes behind them: by whole workgroups when one of them is long, else by single waves.
 LATE_DECODES = {
     # name: (Hq, Hkv, D, q_len, ctx, dtype, waves per item)
