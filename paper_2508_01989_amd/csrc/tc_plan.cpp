@@ -111,6 +111,29 @@ static int64_t wide_workgroups(const tc_plan *p, int S, int split, int W, int64_
 //   decodes only         12 of lognormal 6000 52.6 / 48.7, 40/8 heads, head_dim 64 29.9 / 27.5; 10 of 4000-12000 54.2 / 50.2, 6 of 8000-20000
 //                        59.2 / 56.9; with shorter sequences, 31 of 489-3912, 52.4 / 52.9, 8/8 heads 50.3 / 52.1, 40 of lognormal 1500 45.9 / 46.7
 //   single splits        16/2 heads, 176 short decodes beside 564 first tokens 20.1 / 24.8
+// And not where one round of halves takes longer than two of splits: the halves of a sequence of up to 2048 tokens are as long as a split may be
+// and have half of the waves, while the second round's splits are the short ones, on the units that had the shortest before.  The line is at 22 pages
+// between the longest half and the longest split of the second round.  Measured (us, one to a workgroup / two; that difference in brackets):
+//   head_dim 128   64/8 heads, 16 of lognormal 2000 (17) 32.0 / 29.9, 8/8, 22 of 446-1786 (21) 27.1 / 26.0, 40/8, 16 of lognormal 1650 (23) 24.1 / 28.3,
+//                  32/8, 23 of 275-2204 (27) 28.8 / 30.1
+//   head_dim 64    40/8 heads, 16 of 411-3288 (17) 18.8 / 15.6, 32/32, 4 of 457-3658 (23) 15.3 / 17.7, 40/8, 21 of 268-2146 (28) 15.9 / 17.0, but 8/8,
+//                  15 of lognormal 1490 (23) 18.7 / 16.5
+// In the geometric mean 241 batches on this side of the line are 8 % faster with two to a workgroup, 37 on the other 2 % slower.
+static bool halves_take_longer(const tc_plan *p, int S, int pages, int64_t at_once) {
+    int64_t count[kMaxSplitPages + 1] = {};  // splits of so many pages, one to a workgroup
+    int half = 0;
+    for (int s = 0; s < S; s++)
+        if (p->q_start[s + 1] - p->q_start[s] == 1) {
+            const int64_t kv = (int64_t)p->ctx_len[s] + 1, pg = (kv + kBlock - 1) / kBlock;
+            const int64_t n1 = num_splits(kv, kMaxSplitPages * kBlock, 1), n2 = num_splits(kv, pages * kBlock, 2);
+            count[pg / n1] += n1 - pg % n1;
+            if (pg % n1) count[pg / n1 + 1] += pg % n1;
+            half = std::max(half, (int)((pg + n2 - 1) / n2));
+        }
+    int second = kMaxSplitPages;  // the longest first: the one after `at_once`
+    for (int64_t seen = count[second] * p->Hkv; seen <= at_once && second > 1; seen += count[second] * p->Hkv) second--;
+    return half > second + 22;
+}
 static int two_split_workgroups(const tc_plan *p, int S, int split, int64_t at_once, bool decodes_only) {
     const int64_t rounds = (wide_workgroups(p, S, split, 1) + at_once - 1) / at_once;
     if (split < kMaxSplitPages * kBlock || rounds < 2 || rounds > 4) return 0;
@@ -126,7 +149,8 @@ static int two_split_workgroups(const tc_plan *p, int S, int split, int64_t at_o
         if (wide_workgroups(p, S, mid * kBlock, 2) <= most) last = mid; else pages = mid + 1;
     }
     const int64_t n = wide_workgroups(p, S, pages * kBlock, 2, &single);
-    return single * 4 > n ? 0 : pages * kBlock;
+    if (single * 4 > n || (rounds == 2 && !decodes_only && halves_take_longer(p, S, pages, at_once))) return 0;
+    return pages * kBlock;
 }
 
 // A batch of few decodes (no prefill chunk) whose single-wave splits would leave wave slots empty or keep a few waves

@@ -561,6 +561,19 @@ def test_decodes_behind_many_sweeps(tc, Hq, Hkv, D, chunk, offset, decodes, wave
     assert (info.block_threads, info.waves_per_item) == (512, waves)
 
 
+@pytest.mark.parametrize("Hq,Hkv,D,ctx,waves", [
+    (32, 32, 64, [2281, 639, 1722, 2003], 8),           # halves of up to 63 pages, eight waves on 40 of the second round
+    (40, 8, 64, [952, 623, 1571, 1056, 1556, 1411, 365, 401, 1752, 1946, 1151, 2093, 1822, 741, 430, 1267, 713, 1861, 2074, 480, 1095], 8),
+    (32, 8, 128, [2500, 5000, 4000, 9000, 7000, 8000], 4),   # long ones: halves as short as it takes
+    (32, 8, 128, [1900] * 16, 4),                       # the second round's splits are as long as the first's
+])
+def test_two_splits_to_a_workgroup_where_halves_are_not_long(tc, Hq, Hkv, D, ctx, waves):
+    sp = W.custom_spec("halves", Hq, Hkv, D, [4] + [1] * len(ctx), [2] + ctx)
+    table, mb, nb = W.make_tables(sp, np.random.default_rng(17))
+    info = check_work_list(tc, sp, table, nb)
+    assert (info.block_threads, info.waves_per_item) == (512, waves)
+
+
 def _build_ratio(tc, Hq, Hkv, first, second):
     """Host time of building one work list over that of another: the least of many, in turn, which other load does not reach."""
     pool, batches = tc.make_pool(Hq, Hkv, 128, 16), []
