@@ -70,7 +70,7 @@ struct PlanRun { int seq, h, ns, len; };
 struct PlanTeam { int seq, h, first, n, idx, wg, at; };
 struct PlanUnits { double free_us; int n; };  // n compute units that are free from then on
 struct PlanScratch {
-    std::vector<PlanRowBlock> blocks;
+    std::vector<PlanRowBlock> blocks, small_blocks;
     std::vector<PlanPiece> pieces;
     std::vector<PlanRun> runs;
     std::vector<PlanTeam> teams;

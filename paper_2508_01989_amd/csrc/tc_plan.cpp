@@ -419,6 +419,7 @@ static void make_row_blocks(const tc_plan *p, int S, int rows, std::vector<PlanR
 //                                 60.2 / 62.9 / 58.3, 2200 with 10 of 465 57.8 / 65.8 / 54.2
 struct ChunkForms {
     double whole, levelled, small;
+    double start;  // start and end of a workgroup
 };
 static ChunkForms estimate_chunk(const tc_plan *p, const std::vector<PlanRowBlock> &blocks, std::vector<PlanUnits> &units) {
     const bool d64 = p->D == 64;
@@ -427,8 +428,9 @@ static ChunkForms estimate_chunk(const tc_plan *p, const std::vector<PlanRowBloc
     double tiles = 0;
     for (const PlanRowBlock &b : blocks) tiles += b.n_tiles;
     const double load = tiles * Hkv / kNumCu, longest = blocks[0].n_tiles, fill = std::min(1.0, load / longest);
-    const double o = d64 ? 3.5 : 5.5;  // start and end of a workgroup
+    const double o = d64 ? 3.5 : 5.5;
     ChunkForms t;
+    t.start = o;
     if (items <= kNumCu) t.whole = longest * (d64 ? std::max(0.92, 0.85 + 0.2 * fill) : std::max(1.25, 1.05 + 0.65 * fill)) + o;
     else {  // heaviest first, to the unit that is free first; units that are free at the same time are one entry (the KV heads of a block take
         // the same time), so that it costs a heap operation or two per block (1000 items of 8 KV heads: a plan in 16 us, one by one 43)
@@ -458,6 +460,21 @@ static ChunkForms estimate_chunk(const tc_plan *p, const std::vector<PlanRowBloc
     const double shared_us = d64 ? (small_items > slots ? 0.62 : 0.59) : (small_items > slots ? 1.06 : 0.98);
     t.small = std::max(longest * alone_us, 2.0 * load * shared_us) + o;
     return t;
+}
+
+// KV tiles that the workgroups which begin on one compute unit sweep together, at most (small workgroups of these row blocks, as they are
+// placed, see the records).
+static int tiles_of_fullest_unit(const tc_plan *p, const std::vector<PlanRowBlock> &blocks) {
+    const int n = (int)blocks.size(), row = std::max(1, kNumCu / p->Hkv), rows = small_wg_per_cu(p->D);
+    const bool turn = (int64_t)n * p->Hkv <= (int64_t)rows * kNumCu;
+    int most = 0;
+    for (int unit = 0; unit < std::min(row, n); unit++) {
+        int tiles = 0;
+        for (int r = 0, first = 0; r < rows && first + unit < n; r++, first += row)
+            tiles += blocks[turn && (r & 1) ? first + std::min(row, n - first) - 1 - unit : first + unit].n_tiles;
+        most = std::max(most, tiles);
+    }
+    return most;
 }
 
 tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
@@ -567,7 +584,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
         } else if (items * 4 <= kNumCu) {
             choose_prefill_cuts(w.blocks, Hkv, decode_bytes, kCutTileUs);
         } else if (items <= 4 * kNumCu) {
-            const ChunkForms t = estimate_chunk(p, w.blocks, w.units);
+            ChunkForms t = estimate_chunk(p, w.blocks, w.units);
             const double t_decode = (double)decode_bytes / 5.0e6;                                 // alone on the chip
             const double unit_decode = (double)decode_bytes / (kDecodeCuGBs * 1e3) / kNumCu;  // what it takes of every unit beside sweeps
             const double t_whole = std::max(t.whole, t_decode), t_levelled = t.levelled + unit_decode;
@@ -578,7 +595,18 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
             const double level_below = items * 4 <= 3 * kNumCu ? 0.95 : decode_tokens > 0 ? 0.7 : 0.9;
             // Small workgroups: beside more decodes the queue fills the units whose sweeps end early; long sweeps run at a lower clock in either
             // form than the estimates say (6562 at 16848, 8/8 heads, 526 / 543).
-            const bool small = t.small < (w.blocks[0].n_tiles <= 64 ? 0.97 : 0.9) * t_whole && t_decode < 0.05 * t.small;
+            const double small_below = (w.blocks[0].n_tiles <= 64 ? 0.97 : 0.9) * t_whole;
+            bool small = t.small < small_below && t_decode < 0.05 * t.small;
+            // That is by a unit's share of all sweeps.  Where some units have two long ones it is theirs that count, a tile of the fullest unit 0.9 us, 0.5 at
+            // head_dim 64; for sweeps of up to 24 tiles it makes no difference.  (whole / small:) 16/2 heads, 2652 at 11274 and 2355 at 0 with 5
+            // decodes 308 / 359, 64/8, 667 at 1657 and 356 at 0 62.4 / 69.3, head_dim 64, 685 at 12873 and 830 at 0 with 2 decodes 190 / 220.  Of 440 batches
+            // that took small workgroups without this, 43 had been faster before (up to 25 %), with it 4 (9 %).
+            bool crowded = false;
+            if (small) {
+                make_row_blocks(p, S, kPrefillRows / 2, w.small_blocks);
+                crowded = w.blocks[0].n_tiles > 24 && tiles_of_fullest_unit(p, w.small_blocks) * (D == 64 ? 0.5 : 0.9) + t.start >= small_below;
+                small = !crowded;
+            }
             double tiles = 0;
             for (const PlanRowBlock &x : w.blocks) tiles += x.n_tiles;
             const double unit_prefill = tiles * Hkv * kTileUs * (D / 128.0) / kNumCu;
@@ -588,9 +616,12 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
             // Where small workgroups are estimated to be faster still, but do not serve beside so many decodes: runs all the same (whole / levelled:
             // 32/8 heads, 1408 at 0 with 3 of 579-4632 41.3 / 39.1; 64/8, 360 at 0 and 335 at 1064 with 2 of 981-7850 39.0 / 34.3; 16/2, head_dim 64,
             // 1424 at 0 with 8 of 462-3698 27.5 / 21.2), if a KV head has eight of them: with fewer, of whole units for every head, too many units have
-            // none (32/32 heads, 1136 at 174 with one of 1000 40.9 / 47.2, 776 at 1489 with 2 of 442-3540 58.5 / 63.1).
+            // none (32/32 heads, 1136 at 174 with one of 1000 40.9 / 47.2, 776 at 1489 with 2 of 442-3540 58.5 / 63.1).  Instead of crowded small ones up to
+            // three quarters of the units (40/8 heads, head_dim 64, 1204 at 4097 whole 82, runs 75); beyond whole items do as well or better (8/8, first
+            // chunks of 2837, 3049 and 3264 92 / 108, 16/2, 4014 and 1489 95 / 103).
+            const bool instead_of_small = !small && bins >= 8 && (!crowded || items * 4 <= 3 * kNumCu);
             int runs = 0;
-            if (t_levelled < level_below * t_whole && (t_levelled < t.small || (!small && bins >= 8)) && t_decode < 0.75 * t_levelled) {
+            if (t_levelled < level_below * t_whole && (t_levelled < t.small || instead_of_small) && t_decode < 0.75 * t_levelled) {
                 // (Chunks of up to three quarters of the units beside few decodes run like this whatever scratch they need.)
                 const bool any_scratch = items * 4 <= 3 * kNumCu && t_decode < 0.25 * w.blocks[0].n_tiles * kTileUs * (D / 128.0);
                 runs = level(bins, any_scratch);
@@ -601,7 +632,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
             } else if (small) {
                 p->prefill_waves = kSmallWaves;
                 p->rows_per_item = kPrefillRows / 2;
-                make_row_blocks(p, S, p->rows_per_item, w.blocks);
+                w.blocks.swap(w.small_blocks);
             } else {
                 queue = decode_tokens > 0 && items <= kNumCu;
             }

@@ -561,6 +561,24 @@ def test_decodes_behind_many_sweeps(tc, Hq, Hkv, D, chunk, offset, decodes, wave
     assert (info.block_threads, info.waves_per_item) == (512, waves)
 
 
+@pytest.mark.parametrize("Hq,Hkv,D,q_len,ctx,threads,levelled", [
+    (32, 8, 128, [1200, 1200], [3400, 0], 512, False),           # 304 long small items for 256 units: whole ones
+    (64, 8, 128, [600, 600], [3400, 0], 512, False),
+    (64, 8, 64, [685, 830, 1, 1], [12873, 0, 900, 200], 512, False),
+    (16, 2, 128, [2652, 2355] + [1] * 5, [11274, 0] + [600] * 5, 512, False),
+    (40, 8, 64, [1204], [4097], 512, True),                      # 392 long ones, from 192 items of 256 rows: runs
+    (32, 8, 128, [2048], [0], 256, False),                       # every long one with a short one beside it
+    (16, 2, 128, [4624], [0], 256, False),
+    (32, 8, 64, [1500, 900], [3400, 0], 256, False),             # three to a unit
+    (128, 8, 128, [169, 104], [0, 0], 256, False),               # short sweeps
+])
+def test_small_workgroups_where_no_unit_has_two_long_sweeps(tc, Hq, Hkv, D, q_len, ctx, threads, levelled):
+    sp = W.custom_spec("crowded", Hq, Hkv, D, q_len, ctx)
+    table, mb, nb = W.make_tables(sp, np.random.default_rng(18))
+    info = check_work_list(tc, sp, table, nb)
+    assert (info.block_threads, info.num_prefill_workgroups < info.num_prefill_pieces) == (threads, levelled)
+
+
 @pytest.mark.parametrize("Hq,Hkv,D,ctx,waves", [
     (32, 32, 64, [2281, 639, 1722, 2003], 8),           # halves of up to 63 pages, eight waves on 40 of the second round
     (40, 8, 64, [952, 623, 1571, 1056, 1556, 1411, 365, 401, 1752, 1946, 1151, 2093, 1822, 741, 430, 1267, 713, 1861, 2074, 480, 1095], 8),

@@ -458,7 +458,7 @@ SMALL_WORKGROUPS = {
     "g4_d64_ragged_chunks": (32, 8, 64, [700, 333, 45, 2], [0, 64, 100, 0], "bf16", 3),
     "g1_d64": (32, 32, 64, [900, 300], [5, 0], "fp16", 5),
     "g16_d64": (16, 1, 64, [1100], [3], "bf16", 1),
-    "window_of_page_ids": (32, 8, 128, [1200, 1200], [3400, 0], "bf16", 37),
+    "window_of_page_ids": (16, 2, 128, [4624], [0], "bf16", 37),
     "window_of_page_ids_d64": (32, 8, 64, [1500, 900], [3400, 0], "fp16", 37),
 }
 
