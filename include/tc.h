@@ -93,8 +93,9 @@ typedef struct {
     int32_t num_partials;               /* partial results of decode teams held in the workspace */
     int32_t split_tokens;               /* KV tokens a decode split holds at most, except that a sequence which one   */
                                         /* workgroup's wave slots can cover with splits of up to 1024 is cut into no  */
-                                        /* more splits than it has slots (one, where waves_per_item > 1)              */
+                                        /* more splits than it has slots (one, where a workgroup holds a single item)  */
     int32_t rows_per_prefill_item;      /* (position, head) rows per prefill workgroup: 256, or 128 for a small chunk */
+                                        /* or one of uneven sweeps                                                    */
     int32_t grid_blocks, block_threads; /* launch shape of the fused attention kernel        */
     int64_t total_pages;                /* table entries copied                              */
     int32_t num_prefill_pieces;         /* an item whose KV range is cut is several pieces, else one */
@@ -103,7 +104,8 @@ typedef struct {
     int32_t num_piece_partials;         /* partial results of pieces of cut prefill items    */
     int32_t decode_queue;               /* 1: the decode items are drawn from a queue, in units of one workgroup's   */
                                         /* worth, by grid_blocks - num_prefill_workgroups decode workgroups and by   */
-                                        /* the prefill workgroups once their pieces are done (levelled chunks)       */
+                                        /* the prefill workgroups once their pieces are done (chunks whose            */
+                                        /* workgroups of eight waves all run from the start)                          */
     int32_t waves_per_item;             /* waves that share one decode item: 1, all of a workgroup's (few, long       */
                                         /* decodes) or half of them                                                   */
     int64_t build_ns;                   /* host time of the latest work-list build ...       */
@@ -147,8 +149,8 @@ tc_status tc_plan_get_info(const tc_plan *plan, tc_plan_info *info);
  *            the whole item and writes out), pieces of the item, index of the piece in the item,
  *            arrival counter (-1), 1 if it is the last piece of its workgroup}
  * The KV range of a prefill item (a block of query rows of one KV head) may be cut into pieces: when the
- * batch has few row blocks, so that more compute units work on the chunk, and when it has about as many as
- * there are compute units, where the sweeps are levelled: the row blocks of a KV head are laid end to end
+ * batch has few row blocks, so that more compute units work on the chunk, and when whole sweeps would leave
+ * units empty or waiting for the longest, where the sweeps are levelled: the row blocks of a KV head are laid end to end
  * and cut into runs of equal cost, one workgroup each, which leaves compute units to the decode branch.
  * Piece c of a cut item leaves its partial result in piece region (first region of the item) + c.  A prefill
  * workgroup runs the pieces [first piece of the workgroup, .. the one marked last].

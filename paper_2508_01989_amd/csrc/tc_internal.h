@@ -13,9 +13,11 @@ namespace tc {
 constexpr int kBlock = 16;          // tokens per KV page
 // Launch shapes of the fused attention kernel.  A batch with a prefill chunk runs workgroups of eight
 // waves, one per compute unit (two waves per SIMD, up to 256 registers each): the eight waves sweep the
-// same K/V tiles for 256 (position, head) rows, and a decode workgroup of that launch holds eight
+// same K/V tiles for 256 (position, head) rows (128 in small items), and a decode workgroup of that launch holds eight
 // decode items (one KV split per wave; splits of one sequence and KV head that share the workgroup are
-// combined there).  A batch of decodes only runs workgroups of four waves, three per compute unit.
+// combined there), or one or two that its waves share.  Chunks of uneven sweeps run workgroups of four waves instead, for
+// 128 rows, two or three per compute unit.  A batch of decodes only runs workgroups of four waves, three per compute unit, or two
+// where a workgroup holds one or two items.
 constexpr int kMixedWaves = 8;
 constexpr int kDecodeWaves = 4;
 constexpr int kDecodeWgPerCu = 3;
@@ -46,7 +48,7 @@ constexpr int kTeamTailBit = 1 << 7;
 // slots SLOT0 .. (NPOS = 1).  A cut prefill item (these come first in the list): NPOS positions from query row QROW
 // on, NSPLIT pieces in piece regions SLOT0 ..; MG_ITEM is the index of the prefill item.
 enum { MG_SEQ, MG_KVH, MG_QROW, MG_SLOT0, MG_NSPLIT, MG_COUNTER, MG_NPOS, MG_ITEM };
-// A prefill piece is KV tiles [T0, T1) of a prefill item; a prefill workgroup runs one or more pieces
+// As tc_plan_copy_items tells them: a prefill piece is KV tiles [T0, T1) of a prefill item; a prefill workgroup runs one or more pieces
 // one after the other (LAST marks the last piece of its workgroup).  K = 1: the piece is the whole item
 // and writes the output rows (SLOT = -1).  K > 1: the item is cut into K pieces; piece C of the item
 // leaves its partial result (the accumulators of its 512 lanes, as they lie in registers) in piece
@@ -120,7 +122,7 @@ struct tc_plan {
     int items_per_wg = tc::kDecodeWaves;  // decode items a workgroup runs side by side
     int prefill_waves = tc::kMixedWaves;   // waves of a workgroup beside a prefill chunk: 8, or 4 (prefill items of 128 rows)
     int rows_per_item = tc::kPrefillRows;  // (position, head) rows of a prefill item: 256 or 128
-    int waves_per_item = 1;               // waves that share one of them: a whole workgroup's (kWideWaves, beside a chunk kMixedWaves) or 1
+    int waves_per_item = 1;               // waves that share one of them: 1, all of a workgroup's (kWideWaves, beside a chunk prefill_waves) or half of them
     int launch_threads() const { return 64 * items_per_wg * waves_per_item; }
     int grid_blocks() const { return n_prefill_wg + n_decode_wg; }
     size_t workspace_bytes() const {

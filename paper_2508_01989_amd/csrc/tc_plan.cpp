@@ -264,8 +264,8 @@ static void choose_prefill_cuts(std::vector<PlanRowBlock> &blocks, int Hkv, int6
     for (PlanRowBlock &b : blocks) b.k = prefill_cuts(b.n_tiles, items, decode_bytes, tile_us);
 }
 
-// Pieces of a batch whose row blocks would leave a good part of the chip empty (between a quarter and three
-// quarters of the compute units: a mid-sized chunk).  The row blocks of a KV head, heaviest first, are laid end to end and cut into `bins` runs of equal
+// Pieces of a batch whose row blocks would leave a good part of the chip empty or idle (more than a quarter of the compute units and up to
+// four times as many, chosen by estimate_chunk).  The row blocks of a KV head, heaviest first, are laid end to end and cut into `bins` runs of equal
 // cost; each run is one workgroup, which sweeps its pieces one after the other.  A block that straddles a cut
 // becomes pieces of two (rarely more) workgroups.  The same cuts are used for every KV head.
 static void level_prefill(std::vector<PlanRowBlock> &blocks, std::vector<PlanPiece> &pieces, int bins) {
@@ -433,7 +433,7 @@ static ChunkForms estimate_chunk(const tc_plan *p, const std::vector<PlanRowBloc
     t.start = o;
     if (items <= kNumCu) t.whole = longest * (d64 ? std::max(0.92, 0.85 + 0.2 * fill) : std::max(1.25, 1.05 + 0.65 * fill)) + o;
     else {  // heaviest first, to the unit that is free first; units that are free at the same time are one entry (the KV heads of a block take
-        // the same time), so that it costs a heap operation or two per block (1000 items of 8 KV heads: a plan in 16 us, one by one 43)
+        // the same time), so that it costs a heap operation or two per block (1.5 us of the 11 that a plan of 1000 items of 8 KV heads takes; one by one 10)
         const double tile_us = d64 ? 1.03 : 1.6;
         const auto later = [](const PlanUnits &x, const PlanUnits &y) { return x.free_us > y.free_us; };
         units.assign(1, {0.0, kNumCu});
@@ -561,7 +561,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     };
     // Regimes by the number of prefill items (row blocks x KV heads) against the compute units:
     //   at most a quarter:  cut each item's KV range so that more units work on the chunk
-    //   up to four times:   whole items, levelled runs or small workgroups, whichever is estimated to take least (estimate_chunk)
+    //   up to four times:   whole items, level runs or small workgroups, whichever of those that the batch may have is estimated to take least (estimate_chunk)
     //   more:               whole items; the hardware hands them out heaviest first
     // `queue`: the launch has no more workgroups than the chip has compute units and the decode items are drawn from a
     // queue, a workgroup's worth at a time, by whichever workgroup is free (see the kernel).
