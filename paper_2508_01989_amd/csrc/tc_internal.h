@@ -98,7 +98,7 @@ struct tc_plan {
     int n_counters = 0;    // arrival counters: one per cut prefill item, one per (sequence, KV head) with several decode teams
     int n_decode_wg = 0;   // workgroups launched for the decode branch (fewer than the decode units when those are drawn from a queue)
     int counter_stride = tc::kCounterLine;  // int32 between arrival counters; the items of the image hold a counter's index times this
-    int queue_counter = -1;  // int32 from the first arrival counter to the decode queue's two (a line each, behind them), or -1: no queue
+    int queue_counter = -1;  // int32 from the first arrival counter to the decode queue's (a line of its own, behind them), or -1: no queue
     int split_tokens = 0;
     int64_t total_pages = 0;
     std::vector<int32_t> q_start, ctx_len, page_off;  // host copies

@@ -82,7 +82,7 @@ struct AttnArgs {
     int n_prefill, n_decode; // prefill workgroups, decode wave slots
     int Hq, Hkv, G;
     int fused;               // 1: the last piece or team of a split pair to finish combines its partial results
-    int queue;               // where the decode queue's two counters (next unit, workgroups that have left; a line each) lie, or -1
+    int queue;               // where the decode queue's counter (a line of its own) lies, or -1
     float scale_log2;        // softmax scale times log2(e)
 };
 
@@ -1516,33 +1516,41 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : CHUNK ?
     t_mid = __builtin_amdgcn_s_memrealtime();
 #endif
     if constexpr (WAVES == kMixedWaves && WIDE < 2) {
-        if (A.queue >= 0) {
-        // Decode queue (the launch has no more workgroups than the chip has compute units, all resident from the
-        // start).  The decode items are handed out in units of one workgroup's worth (WAVES items, teams included)
-        // through a counter: the workgroups launched for the decode branch draw from the start, the prefill
-        // workgroups join when their pieces are done, and everybody leaves when the counter has passed the last unit,
-        // so that whichever compute unit is free carries the decode stream and no workgroup waits for another.
+        const bool late = A.n_prefill > kNumCu;  // more sweeps than the chip takes at once: the decode workgroups follow them
+        if (A.queue >= 0 && !(late && wg < A.n_prefill)) {
+        // Decode queue.  The decode items are handed out in units of one workgroup's worth (WAVES items, teams included)
+        // through a counter, so that whichever compute unit is free carries the decode stream and no workgroup waits for another.
+        // All workgroups resident from the start (at most kNumCu of them): a workgroup launched for the decode branch begins with
+        // the unit of its own index and draws the next ones, the prefill workgroups join when their pieces are done, and everybody
+        // leaves when the counter has passed the last unit.
+        // More sweeps than units: only the decode workgroups draw; those of the compute units that come to them first leave the others nothing.  Why:
+        // the hardware deals the workgroups out to the eight dies in turn, and the dies sweep and stream at rates up to 7 % apart, so that
+        // the same number of decode workgroups on each ended at 5.7 to 6.1 ms (8192 tokens at 24576 with 32 decodes: 6.19 -> 6.05 ms).
         // (Left to the hardware, decode workgroups beyond the first round were not started on the units the first
         // round had freed until the prefill workgroups ended.  Handing out single items to single waves, with the
         // splits of a pair combined by the last to arrive, measured slower than units with their teams.)
-        // The workgroup that leaves last puts both counters back to zero for the next launch.
+        // Every workgroup draws one number past the last unit; the last of those is the last draw of the launch, and puts the
+        // counter back to zero for the next one.  (With a second counter of those that have left, and a draw before the first unit,
+        // small batches took 2 us longer.)
         int *const drawn = reinterpret_cast<int *>(lds + PrefillLds<D, WAVES>::kIds);  // the slots of the page ids: free when no sweep runs
-        int32_t *const next_unit = A.counters + A.queue, *const gone = next_unit + kCounterLine;
+        int32_t *const next_unit = A.counters + A.queue;
         const int n_units = WIDE ? A.n_decode : A.n_decode / WAVES;
+        const int n_decode_wg = (int)gridDim.x - A.n_prefill, n_dealt = late ? 0 : n_decode_wg, n_drawers = late ? n_decode_wg : (int)gridDim.x;
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        int unit = late ? -1 : max(wg - A.n_prefill, -1);
         for (;;) {
             __syncthreads();  // the unit before (or the last prefill piece) is done with the LDS
-            if (threadIdx.x == 0) *drawn = __hip_atomic_fetch_add(next_unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __syncthreads();
-            const int unit = *drawn;
-            if (unit >= n_units) break;
+            if (unit < 0) {
+                if (threadIdx.x == 0) *drawn = n_dealt + __hip_atomic_fetch_add(next_unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __syncthreads();
+                unit = *drawn;
+                if (unit >= n_units) break;
+            }
             if constexpr (WIDE > 0) decode_item_wide<D, E, NS, WAVES, 1, false>(A, decode + (int64_t)unit * kItemInts, reinterpret_cast<float *>(lds));
             else decode_item<D, E, NS>(A, decode + ((int64_t)unit * WAVES + wave) * kItemInts, reinterpret_cast<float *>(lds), WAVES);
+            unit = -1;
         }
-        if (threadIdx.x == 0 && __hip_atomic_fetch_add(gone, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1) {
-            __hip_atomic_store(next_unit, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(gone, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        if (threadIdx.x == 0 && unit == n_units + n_drawers - 1) __hip_atomic_store(next_unit, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 #ifdef TC_WG_TRACE

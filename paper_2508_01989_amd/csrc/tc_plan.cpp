@@ -694,11 +694,21 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
         }
     }
     const int W = p->items_per_wg;
+    // Beside a chunk a workgroup has a unit to itself and runs eight splits: of up to 1024 tokens they take it 170 us while all units stream, and
+    // few such rounds end raggedly.  Where the sequences are long (2000 tokens on the mean) splits are shorter, down to 256 tokens (512 at head_dim 64), until
+    // there are eight rounds of them; for sequences that one workgroup covers, so that there are no more partial results.  Measured (us per step, before /
+    // with this, both with the queue below): 32/8 heads, 256 at 1234 with 256 of 512-4096 413 / 394; 424 at 2 with 162 of 826-6608 409 / 400; 32/32, 3746 at 0
+    // with 25 of 459-3676 287 / 277; 1131 at 2 with 83 of 1525-12200 411 / 399.  Of shorter sequences a wave has few pages for its start: 40/8, 1118 at 24
+    // with 389 of lognormal 656 218 / 222, 32/32, 382 at 4379 with 180 of 65-526 187 / 191.
+    const int split_long = p->split_tokens;  // of sequences that take several workgroups
+    if (!w.blocks.empty() && p->prefill_waves == kMixedWaves && p->waves_per_item == 1 && decode_tokens >= (int64_t)2000 * n_decode_seqs)
+        while (p->split_tokens * D > 256 * 128 && (int64_t)p->split_tokens * W * 4 * D * 8 * kNumCu > decode_bytes) p->split_tokens /= 2;
+    const auto splits_of = [&](int64_t kv) { return num_splits(kv, kv > (int64_t)W * kMaxSplitPages * kBlock ? split_long : p->split_tokens, W); };
     w.runs.clear();
     for (int s = 0; s < S; s++) {
         if (p->q_start[s + 1] - p->q_start[s] != 1) continue;
         const int64_t kv = (int64_t)p->ctx_len[s] + 1;
-        const int ns = num_splits(kv, p->split_tokens, W);
+        const int ns = splits_of(kv);
         w.runs.push_back({s, 0, ns, (int)std::min<int64_t>(kv, split_begin(kv, ns, 1))});
     }
     // longest split first; sequences with equal splits keep their order, and the KV heads of a sequence follow each other
@@ -751,6 +761,23 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     // With a queue the launch has a decode workgroup for every compute unit the chunk leaves free (none when its row
     // blocks fill the chip): they draw decode items from the start, the prefill workgroups when their pieces are done.
     const int64_t n_decode_units = (int64_t)w.wg_fill.size();  // workgroups' worth of decode items
+    // Chunks of few workgroups have a queue where the decode stream is long and many rounds of what the free units take at once, so that the units
+    // that stream faster take more of it: from 300 MB and 2.4 rounds on.  Measured (us per step, without / with; 32/8 heads, head_dim 128, unless stated):
+    //   3.5 rounds of 890 MB  256 at 1234 with 256 of 512-4096 428 / 413           3.6, 740 MB  40/8, 101 at 0 with 135 of 302-2422 136.7 / 132.7
+    //   5.0, 300 MB           312 at 7068 with 13 of lognormal 4371 87.0 / 84.4    2.4, 780 MB  8/8, head_dim 64, 4 at 5 with 79 of 1030-8244 135.4 / 133.9
+    //   2.3, 700 MB           32/32, 75 at 29 with 20 of lognormal 2109 124.3 / 125.8    2.1, 590 MB  40 at 24 with 15 of lognormal 9482 106.9 / 110.5
+    //   2.8, 240 MB           64/8, head_dim 64, 10 at 356 with 289 of lognormal 431 52.9 / 53.4; smaller ones lose up to 7 % (a draw takes a microsecond)
+    // Behind more sweeps than units only the decode workgroups draw (see the kernel); from 24 tiles a unit on, 41 us of sweeps: 4711 at 0, 32/32, with 272 of
+    // 31-254 334.6 / 323.9; 3797 at 2 with 80 of 77 129.4 / 126.6; 2781 at 0 with 12 of 587-4702 93.1 / 92.8; below 2343 at 0 with 5 of 758-6068 67.6 / 68.5.
+    bool late_queue = false;
+    if (!queue && n_decode_units > 0 && !w.blocks.empty() && p->prefill_waves == kMixedWaves && (p->waves_per_item == 1 || p->items_per_wg == 1)) {
+        if (n_prefill_wg <= kNumCu) queue = decode_bytes >= (int64_t)300000000 && n_decode_units * 5 >= 12 * std::max<int64_t>(kNumCu - n_prefill_wg, 1);
+        else {
+            int64_t tiles = 0;
+            for (const PlanPiece &x : w.pieces) tiles += x.t1 - x.t0;
+            late_queue = tiles * Hkv >= 24 * kNumCu;
+        }
+    }
     const int64_t n_decode_wg = !queue ? n_decode_units : std::min<int64_t>(n_decode_units, std::max<int64_t>(slots - n_prefill_wg, 0));
     const size_t off_records = 0;  // first: a record is a 128-byte line
     const size_t off_append = w.pieces.size() * kRecordInts, off_pages = off_append + (size_t)n_append * kAppendInts;
@@ -762,7 +789,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     int counter_stride = kCounterLine;
     while (counter_stride > 1 && n_counters * counter_stride > kCounterInts) counter_stride /= 2;
     const size_t off_queue = ((size_t)n_counters * counter_stride + kCounterLine - 1) / kCounterLine * kCounterLine;  // from off_counters
-    const size_t n_counter_ints = queue ? off_queue + 2 * kCounterLine : (size_t)n_counters * counter_stride;
+    const size_t n_counter_ints = queue || late_queue ? off_queue + kCounterLine : (size_t)n_counters * counter_stride;
     const size_t total = std::max<size_t>(off_counters + n_counter_ints, 1);
     if (int err = begin_plan_host(p, total)) return fail(TC_ERR_DEVICE, std::string("host buffer of the plan: ") + hip_error_text(err));
     int32_t *H = p->host;
@@ -881,7 +908,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     for (const PlanTeam &t : w.teams) {
         const int64_t kv = (int64_t)p->ctx_len[t.seq] + 1;
         const int32_t base = w.slot0[(size_t)t.seq * Hkv + t.h], merge = w.merge_of[(size_t)t.seq * Hkv + t.h];
-        const int ns = num_splits(kv, p->split_tokens, W);
+        const int ns = splits_of(kv);
         // split i begins at page i * (pages / ns) + min(i, pages % ns)
         const int64_t pg = (kv + kBlock - 1) / kBlock, each = pg / ns, odd = pg % ns;
         int32_t *dc = dc0 + ((int64_t)t.wg * W + t.at) * kItemInts;
@@ -909,7 +936,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     p->n_prefill = (int)n_prefill; p->n_pieces = (int)n_pieces; p->n_prefill_wg = (int)n_prefill_wg; p->n_decode = (int)n_decode;
     p->n_merge = (int)n_merge; p->n_partials = (int)n_partials; p->n_counters = (int)n_counters; p->n_append = (int)n_append;
     p->n_piece_partials = (int)n_piece_partials; p->n_merge_prefill = (int)n_merge_prefill;
-    p->n_decode_wg = (int)n_decode_wg; p->counter_stride = counter_stride; p->queue_counter = queue ? (int)off_queue : -1;
+    p->n_decode_wg = (int)n_decode_wg; p->counter_stride = counter_stride; p->queue_counter = queue || late_queue ? (int)off_queue : -1;
     p->off_records = off_records; p->off_append = off_append; p->off_pages = off_pages; p->off_valid = off_valid; p->off_prefill = off_prefill;
     p->off_decode = off_decode; p->off_merge = off_merge; p->off_counters = off_counters;
     p->host_n = total;
@@ -973,7 +1000,7 @@ tc_status tc_plan_get_info(const tc_plan *p, tc_plan_info *info) {
     info->num_prefill_pieces = p->n_pieces;
     info->num_prefill_workgroups = p->n_prefill_wg;
     info->num_counters = p->n_counters;
-    info->decode_queue = p->queue_counter >= 0;
+    info->decode_queue = p->queue_counter >= 0 && p->n_prefill_wg <= tc::kNumCu;
     info->build_ns = p->build_ns;
     info->upload_ns = p->upload_ns;
     return TC_OK;

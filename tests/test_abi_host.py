@@ -755,3 +755,21 @@ def test_arrival_counters_take_a_bounded_share_of_the_uploaded_image(tc, tmp_pat
     for seqs, pairs, stride, size in [(1, 8, 32, 1024), (32, 256, 32, 32768), (33, 264, 16, 16896), (512, 4096, 2, 32768), (2000, 16000, 1, 64000)]:
         out = os.popen(f"LD_LIBRARY_PATH=/opt/rocm/lib {exe} {seqs} 20000 8").read().split()
         assert [int(x) for x in out] == [pairs, stride, size], seqs
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,chunk,offset,decodes,queue,split", [
+    (32, 8, 128, 256, 1234, [2000] * 256, 1, 256),         # long sequences, eight rounds of shorter splits
+    (32, 8, 128, 256, 1234, [1998] * 256, 0, 1024),        # 1999 tokens on the mean: as long as they are, and 2.3 rounds of them
+    (32, 8, 64, 256, 1234, [2600] * 256, 1, 512),          # at head_dim 64 no shorter than the same bytes
+    (32, 8, 128, 256, 1234, [2300] * 128 + [9000], 1, 256),  # a sequence that takes two workgroups keeps its splits
+    (32, 8, 128, 256, 1234, [1023] * 74, 1, 128),          # 310 MB
+    (32, 8, 128, 256, 1234, [1023] * 71, 0, 128),          # and 298
+    (32, 8, 128, 256, 1234, [1800] * 66, 0, 256),          # 2.36 rounds of the units that the chunk leaves free
+    (32, 8, 128, 256, 1234, [1800] * 68, 1, 256),          # and 2.43
+])
+def test_long_decode_streams_beside_a_few_sweeps_are_drawn(tc, Hq, Hkv, D, chunk, offset, decodes, queue, split):
+    sp = W.custom_spec("few", Hq, Hkv, D, [chunk] + [1] * len(decodes), [offset] + decodes)
+    table, mb, nb = W.make_tables(sp, np.random.default_rng(19))
+    info = check_work_list(tc, sp, table, nb)
+    assert 0 < info.num_prefill_workgroups <= 64 and info.waves_per_item == 1, info.waves_per_item
+    assert (info.decode_queue, info.split_tokens) == (queue, split)
