@@ -683,6 +683,16 @@ struct PrefillWave {
                 pb[b][e] = (el)pv;
             }
     }
+    // The same for elements FROM .. TO - 1 of the sixteen, psum carried on.
+    template <int FROM, int TO>
+    static __device__ __forceinline__ void probs_part(const f32x16 &s, float c_log2, float m_run, x8 (&pb)[2], float &psum) {
+#pragma unroll
+        for (int i = FROM; i < TO; i++) {
+            const float pv = fast_exp2(__builtin_fmaf(s[i], c_log2, -m_run));
+            psum += pv;
+            pb[i >> 3][i & 7] = (el)pv;
+        }
+    }
     // O^T += V^T P^T over 32 tokens
     static __device__ __forceinline__ void pv(const x8 (&vf)[2][MT], const x8 (&pb)[2], f32x16 (&o)[MT]) {
 #pragma unroll
@@ -850,30 +860,54 @@ __device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ rec,
     auto phase = [&](lds_cptr v_h, int hv, lds_cptr k_after, int hk, f32x16 &cur, f32x16 &nxt, int tok_nxt, auto mask_tag,
                      auto qk_tag, auto kread_tag) {
         constexpr bool MASK = decltype(mask_tag)::value, QK = decltype(qk_tag)::value, KREAD = decltype(kread_tag)::value;
-        if (QK) W::qk(kf, qreg, nxt);
-        if (KREAD) W::load_k(k_after, hk, kf);
-        W::pv(vf, pb, o);
-        W::load_v(v_h, hv, vf);
-        W::probs(cur, c_log2, m_run, pb, psum);
-        if (MASK && QK) W::causal_mask(nxt, tok_nxt, hh, p_abs);
-        // the probabilities are used by the next phase: have them computed in this one
-        asm volatile("" : "+v"(pb[0]), "+v"(pb[1]), "+v"(psum));
-        if (!MASK && QK && KREAD) {
-            // per MFMA: the read that refills its operand; under ten of the phase's MFMAs, from the sixth on, softmax
-            // work for two elements each (measured against it on a long sweep: under the first ten 1.2 % slower,
-            // under the last ten 0.6 %, one element under every MFMA 2 %, three under the first eight 3.5 %)
-            constexpr int kMfma = KS + 2 * MT;
-            constexpr int kProb = kMfma >= 16 ? 10 : kMfma - 2, kFirst = kMfma - kProb - 1, kPer = (16 + kProb - 1) / kProb;
+        if constexpr (QK && KREAD && (!MASK || D == 128)) {
+            // The order of the instructions is given to the compiler: per MFMA the read that refills its operand, and under kProb of the phase's MFMAs, from
+            // kFirst on, softmax work for kPer elements.  Each of the two products has a scheduling region of its own, and the softmax is cut in two with
+            // them: in one region of 230 instructions the compiler lost the order whenever anything around the loop changed, and in workgroups of four waves it
+            // never had it (spills, reads in bunches): 24 chunks run by those, one region / two, 3 % faster on the mean (1439 first tokens, head_dim 64, 23.2 / 22.1 us;
+            // 2117 and 105, 52.9 / 50.8); workgroups of eight waves are where they were.
+            // Head_dim 128: two elements under nine from the sixth on (under eight or ten from the sixth, ten from the fifth or seventh 0.1-0.5 % slower; in one region under
+            // the first ten 1.2 %, the last ten 0.6 %, one element under every MFMA 2 %, three under the first eight 3.5 %).  64: three under seven from the first
+            // on (two under all eight the same, three under six from the second 0.5 % slower, four under five 1.5 %).
+            constexpr int kMfma = KS + 2 * MT, kFirst = D == 128 ? 5 : 0, kProb = D == 128 ? 9 : 7, kPer = D == 128 ? 2 : 3, kInFirst = (KS - kFirst) * kPer;
+            const auto order = [](auto from, auto to) {
 #pragma unroll
-            for (int g = 0; g < kMfma; g++) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                if (g >= kFirst && g < kFirst + kProb) {
-                    __builtin_amdgcn_sched_group_barrier(0x002, kPer, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x400, kPer, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, kPer, 0);
+                for (int g = decltype(from)::value; g < decltype(to)::value; g++) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                    if (g >= kFirst && g < kFirst + kProb) {
+                        __builtin_amdgcn_sched_group_barrier(0x002, kPer, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x400, kPer, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, kPer, 0);
+                    }
                 }
-            }
+            };
+            x8 pn[2];
+            psum = 0.f;
+            __builtin_amdgcn_sched_barrier(0);
+            W::qk(kf, qreg, nxt);
+            W::load_k(k_after, hk, kf);
+            W::template probs_part<0, kInFirst>(cur, c_log2, m_run, pn, psum);
+            order(std::integral_constant<int, 0>(), std::integral_constant<int, KS>());
+            __builtin_amdgcn_sched_barrier(0);
+            W::pv(vf, pb, o);
+            W::load_v(v_h, hv, vf);
+            W::template probs_part<kInFirst, 16>(cur, c_log2, m_run, pn, psum);
+            pb[0] = pn[0];
+            pb[1] = pn[1];
+            asm volatile("" : "+v"(pb[0]), "+v"(pb[1]), "+v"(psum));  // computed in this phase: the next one uses them
+            order(std::integral_constant<int, KS>(), std::integral_constant<int, kMfma>());
+            __builtin_amdgcn_sched_barrier(0);
+            if (MASK) W::causal_mask(nxt, tok_nxt, hh, p_abs);
+        } else {
+            if (QK) W::qk(kf, qreg, nxt);
+            if (KREAD) W::load_k(k_after, hk, kf);
+            W::pv(vf, pb, o);
+            W::load_v(v_h, hv, vf);
+            W::probs(cur, c_log2, m_run, pb, psum);
+            if (MASK && QK) W::causal_mask(nxt, tok_nxt, hh, p_abs);
+            // the probabilities are used by the next phase: have them computed in this one
+            asm volatile("" : "+v"(pb[0]), "+v"(pb[1]), "+v"(psum));
         }
         settle(cur);
     };
@@ -1460,7 +1494,7 @@ struct AttnScalars {
 // The work lists and the page table are separate const __restrict__ kernel arguments (not struct
 // members) so that the compiler knows they are never written and can fetch them with
 // scalar loads.  CHUNK: batches with a prefill chunk; WAVES = 8: one workgroup per compute unit, up to 256 registers per
-// wave; WAVES = 4: two of them (three at head_dim 64, 161 registers; at head_dim 128 all 256 and five spilled, outside the loops), chosen by estimate_chunk.  Without CHUNK: decode-only
+// wave; WAVES = 4: two of them (three at head_dim 64, 158 registers; at head_dim 128 248), chosen by estimate_chunk.  Without CHUNK: decode-only
 // batches (WAVES = 4, three workgroups per compute unit).
 // Workgroups [0, n_prefill) run the prefill pieces the plan gave them, one after the other; the rest run
 // decode items, one per wave, or (WIDE = 1 or 2; forms of their own, so that neither pays for the other's registers: both in one
