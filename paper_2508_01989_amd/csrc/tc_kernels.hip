@@ -737,7 +737,7 @@ __device__ __forceinline__ float next_reference_max(float m_run, float row_max_l
 // which set the pace, are spared them (1 % on a long sweep; copies by waves 4-7 alone measured 0.2 %
 // slower than one tensor per wave group).
 template <int D, class E, int NW>
-__device__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ rec, int kvh, char *lds) {
+__device__ __forceinline__ void prefill_item(const AttnArgs &A, const int32_t *__restrict__ rec, int kvh, char *lds) {
     using C = PrefillCfg<D>;
     using L = PrefillLds<D, NW>;
     using W = PrefillWave<D, E>;
@@ -1294,7 +1294,7 @@ struct WaveResults {
 // own and writes the output rows, or one partial result if the (sequence, KV head) has more teams (then
 // the team is the whole workgroup).
 template <int D, class E, int NS>
-__device__ void decode_item(const AttnArgs &A, const int32_t *__restrict__ it, float *team_lds, int wg_waves) {
+__device__ __forceinline__ void decode_item(const AttnArgs &A, const int32_t *__restrict__ it, float *team_lds, int wg_waves) {
     using x4 = typename E::x4;
     using el = typename E::t;
     constexpr int MT = D / 16;  // 16-row tiles of O^T
@@ -1428,7 +1428,7 @@ __device__ __forceinline__ void wide_combine(const AttnArgs &A, const WaveResult
 // W = 2: two splits (items it[0], it[1]) to a workgroup, R / 2 waves each: the two halves of up to 2048 tokens of one (sequence, KV head),
 // a team with one result, or splits of two pairs that are not cut (or one and a padding item).
 template <int D, class E, int NS, int R, int W, bool STORE>
-__device__ void decode_item_wide(const AttnArgs &A, const int32_t *__restrict__ items, float *lds) {
+__device__ __forceinline__ void decode_item_wide(const AttnArgs &A, const int32_t *__restrict__ items, float *lds) {
     constexpr int MT = D / 16, RI = R / W;  // RI: waves of a split
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));  // may be called in a loop (see prefill_item)
@@ -1487,6 +1487,7 @@ struct AttnScalars {
     int fused;
     int queue;
     int n_partials;
+    int n_dealt;     // decode units that workgroups begin with, where there is a queue; the next ones are drawn
     int n_front, n_append_rows;  // a batch of decodes whose rows this launch stores: the workgroups (the last of the grid) that do it, rows
     float scale_log2;
 };
@@ -1526,37 +1527,13 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : CHUNK ?
         }
     }
     const int wg = (int)blockIdx.x;
-    if (CHUNK && wg < A.n_prefill) {
-        if constexpr (CHUNK) {
-            const int kvh = wg % A.Hkv;
-            const int32_t *rec = records + (int64_t)(wg / A.Hkv) * kRecordInts;
-            for (;;) {
-                const int next = rec[RC_NEXT];
-                prefill_item<D, E, WAVES>(A, rec, kvh, lds);
-                if (WAVES == kSmallWaves || next < 0) break;  // (several pieces: levelled chunks)
-                rec = records + (int64_t)next * kRecordInts;
-                __syncthreads();  // the next piece's tile copies reuse the LDS
-            }
-        }
-    } else if (WAVES != kMixedWaves || WIDE == 2 || A.queue < 0) {
-        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        const int idx = (wg - A.n_prefill) * WAVES + wave;
-        // the decode items fill whole workgroups (padding items at the end of some): every wave gets one
-        if constexpr (WIDE > 0)
-            decode_item_wide<D, E, NS, WAVES, WIDE, false>(A, decode + (int64_t)(wg - A.n_prefill) * WIDE * kItemInts, reinterpret_cast<float *>(lds));
-        else if (idx < A.n_decode) decode_item<D, E, NS>(A, decode + (int64_t)idx * kItemInts, reinterpret_cast<float *>(lds), WAVES);
-    }
-#ifdef TC_WG_TRACE
-    t_mid = __builtin_amdgcn_s_memrealtime();
-#endif
     if constexpr (WAVES == kMixedWaves && WIDE < 2) {
-        const bool late = A.n_prefill > kNumCu;  // more sweeps than the chip takes at once: the decode workgroups follow them
-        if (A.queue >= 0 && !(late && wg < A.n_prefill)) {
-        // Decode queue.  The decode items are handed out in units of one workgroup's worth (WAVES items, teams included)
-        // through a counter, so that whichever compute unit is free carries the decode stream and no workgroup waits for another.
-        // All workgroups resident from the start (at most kNumCu of them): a workgroup launched for the decode branch begins with
-        // the unit of its own index and draws the next ones, the prefill workgroups join when their pieces are done, and everybody
-        // leaves when the counter has passed the last unit.
+        // Sweeps, and decode items in units of one workgroup's worth (WAVES items, teams included).  Without a queue a workgroup runs its pieces
+        // or its unit.  With one the units are handed out through a counter, so that whichever compute unit is free carries the decode stream and no workgroup
+        // waits for another:
+        // All workgroups resident from the start (at most kNumCu of them): the last workgroups of the launch begin with a unit, the n-th from the end with unit n - 1. They
+        // are those launched for the decode branch and, as many as the plan says (n_dealt), those of the lightest sweeps, which sweep after it.  The
+        // next units are drawn, by the prefill workgroups when their pieces are done, and everybody leaves when the counter has passed the last unit.
         // More sweeps than units: only the decode workgroups draw; those of the compute units that come to them first leave the others nothing.  Why:
         // the hardware deals the workgroups out to the eight dies in turn, and the dies sweep and stream at rates up to 7 % apart, so that
         // the same number of decode workgroups on each ended at 5.7 to 6.1 ms (8192 tokens at 24576 with 32 decodes: 6.19 -> 6.05 ms).
@@ -1566,26 +1543,70 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : CHUNK ?
         // Every workgroup draws one number past the last unit; the last of those is the last draw of the launch, and puts the
         // counter back to zero for the next one.  (With a second counter of those that have left, and a draw before the first unit,
         // small batches took 2 us longer.)
-        int *const drawn = reinterpret_cast<int *>(lds + PrefillLds<D, WAVES>::kIds);  // the slots of the page ids: free when no sweep runs
-        int32_t *const next_unit = A.counters + A.queue;
-        const int n_units = WIDE ? A.n_decode : A.n_decode / WAVES;
-        const int n_decode_wg = (int)gridDim.x - A.n_prefill, n_dealt = late ? 0 : n_decode_wg, n_drawers = late ? n_decode_wg : (int)gridDim.x;
-        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        int unit = late ? -1 : max(wg - A.n_prefill, -1);
-        for (;;) {
-            __syncthreads();  // the unit before (or the last prefill piece) is done with the LDS
-            if (unit < 0) {
-                if (threadIdx.x == 0) *drawn = n_dealt + __hip_atomic_fetch_add(next_unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const bool late = A.n_prefill > kNumCu, sweep = wg < A.n_prefill;
+        const auto run = [&](int unit) __attribute__((always_inline)) {
+            const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+            if constexpr (WIDE > 0) decode_item_wide<D, E, NS, WAVES, 1, false>(A, decode + (int64_t)unit * kItemInts, reinterpret_cast<float *>(lds));
+            else decode_item<D, E, NS>(A, decode + ((int64_t)unit * WAVES + wave) * kItemInts, reinterpret_cast<float *>(lds), WAVES);
+        };
+        int first = wg - A.n_prefill;
+        if (A.queue >= 0) {
+            first = (int)gridDim.x - 1 - wg;
+            if (first >= sc.n_dealt) first = -1;
+        }
+        if (first >= 0) {
+            run(first);
+            __syncthreads();  // the unit is done with the LDS
+        }
+        if (sweep) {
+            const int kvh = wg % A.Hkv;
+            const int32_t *rec = records + (int64_t)(wg / A.Hkv) * kRecordInts;
+            for (;;) {
+                const int next = rec[RC_NEXT];
+                prefill_item<D, E, WAVES>(A, rec, kvh, lds);
+                if (next < 0) break;  // (several pieces: levelled chunks)
+                rec = records + (int64_t)next * kRecordInts;
+                __syncthreads();  // the next piece's tile copies reuse the LDS
+            }
+        }
+#ifdef TC_WG_TRACE
+        t_mid = __builtin_amdgcn_s_memrealtime();
+#endif
+        if (A.queue >= 0 && !(late && sweep)) {
+            int *const drawn = reinterpret_cast<int *>(lds + PrefillLds<D, WAVES>::kIds);  // the slots of the page ids: free when no sweep runs
+            int32_t *const next_unit = A.counters + A.queue;
+            const int n_units = WIDE ? A.n_decode : A.n_decode / WAVES;
+            int unit;
+            for (;;) {
+                __syncthreads();  // the unit before (or the last prefill piece) is done with the LDS
+                if (threadIdx.x == 0) *drawn = sc.n_dealt + __hip_atomic_fetch_add(next_unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __syncthreads();
                 unit = *drawn;
                 if (unit >= n_units) break;
+                run(unit);
             }
-            if constexpr (WIDE > 0) decode_item_wide<D, E, NS, WAVES, 1, false>(A, decode + (int64_t)unit * kItemInts, reinterpret_cast<float *>(lds));
-            else decode_item<D, E, NS>(A, decode + ((int64_t)unit * WAVES + wave) * kItemInts, reinterpret_cast<float *>(lds), WAVES);
-            unit = -1;
+            const int n_drawers = late ? (int)gridDim.x - A.n_prefill : (int)gridDim.x;
+            if (threadIdx.x == 0 && unit == n_units + n_drawers - 1) __hip_atomic_store(next_unit, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        if (threadIdx.x == 0 && unit == n_units + n_drawers - 1) __hip_atomic_store(next_unit, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else if (CHUNK && wg < A.n_prefill) {
+        if constexpr (CHUNK) {
+            const int kvh = wg % A.Hkv;
+            const int32_t *rec = records + (int64_t)(wg / A.Hkv) * kRecordInts;
+            for (;;) {
+                const int next = rec[RC_NEXT];
+                prefill_item<D, E, WAVES>(A, rec, kvh, lds);
+                if (WAVES == kSmallWaves || next < 0) break;
+                rec = records + (int64_t)next * kRecordInts;
+                __syncthreads();
+            }
         }
+    } else {
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int idx = (wg - A.n_prefill) * WAVES + wave;
+        // the decode items fill whole workgroups (padding items at the end of some): every wave gets one
+        if constexpr (WIDE > 0)
+            decode_item_wide<D, E, NS, WAVES, WIDE, false>(A, decode + (int64_t)(wg - A.n_prefill) * WIDE * kItemInts, reinterpret_cast<float *>(lds));
+        else if (idx < A.n_decode) decode_item<D, E, NS>(A, decode + (int64_t)idx * kItemInts, reinterpret_cast<float *>(lds), WAVES);
     }
 #ifdef TC_WG_TRACE
     wg_trace(t_start, t_mid, (int)blockIdx.x >= sc.n_prefill);
@@ -1814,7 +1835,7 @@ static int launch_attention_d(const tc_plan *p, const AttnArgs &A, int launches,
         n_front = (int)((units + per_wg - 1) / per_wg);
         grid += n_front;
     }
-    const AttnScalars sc = {A.n_prefill, A.n_decode, A.Hq, A.Hkv, A.G, A.fused, A.queue, p->n_partials, n_front, p->n_append, A.scale_log2};
+    const AttnScalars sc = {A.n_prefill, A.n_decode, A.Hq, A.Hkv, A.G, A.fused, A.queue, p->n_partials, p->n_dealt, n_front, p->n_append, A.scale_log2};
     const int32_t *append = p->dev + p->off_append;
     if (grid > 0 && p->n_pieces > 0) {
         if (int err = allow_prefill_lds<D, E>(p->device)) return err;

@@ -773,3 +773,55 @@ def test_long_decode_streams_beside_a_few_sweeps_are_drawn(tc, Hq, Hkv, D, chunk
     info = check_work_list(tc, sp, table, nb)
     assert 0 < info.num_prefill_workgroups <= 64 and info.waves_per_item == 1, info.waves_per_item
     assert (info.decode_queue, info.split_tokens) == (queue, split)
+
+
+DEALT = """
+#include <cstdio>
+#include <algorithm>
+#include <cstdlib>
+#include <vector>
+#include "tc_internal.h"
+int main(int argc, char **argv) {  // heads, KV heads, head_dim, then q_len ctx_len of every sequence -> units dealt, prefill and decode workgroups, units
+    std::vector<int32_t> q_start(1, 0), ctx;
+    int most = 1;
+    for (int i = 4; i + 1 < argc; i += 2) {
+        q_start.push_back(q_start.back() + atoi(argv[i]));
+        ctx.push_back(atoi(argv[i + 1]));
+        most = std::max(most, (atoi(argv[i]) + atoi(argv[i + 1])) / 16 + 1);
+    }
+    std::vector<int32_t> table(ctx.size() * most, 0);
+    tc_kv_pool pool = {};
+    pool.num_q_heads = atoi(argv[1]); pool.num_kv_heads = atoi(argv[2]); pool.head_dim = atoi(argv[3]); pool.block_size = 16; pool.dtype = TC_BF16; pool.num_blocks = 1;
+    tc_batch b = {(int32_t)ctx.size(), q_start.data(), ctx.data(), table.data(), most};
+    tc_plan *p = nullptr;
+    if (tc_plan_create_host(&pool, &b, &p)) return 1;
+    printf("%d %d %d %d\\n", p->n_dealt, p->n_prefill_wg, p->n_decode_wg, p->n_decode / p->items_per_wg);
+    tc_plan_destroy(p);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def dealt_units(tc, tmp_path_factory):
+    d = tmp_path_factory.mktemp("dealt")
+    src, exe, lib_dir = d / "t.cpp", d / "t", os.path.dirname(tc.LIB_PATH)
+    src.write_text(DEALT)
+    assert os.system(f"g++ -std=c++17 -I {ROOT}/include -I {lib_dir}/csrc {src} {tc.LIB_PATH} -Wl,-rpath,{lib_dir} -Wl,-rpath-link,/opt/rocm/lib -o {exe}") == 0
+
+    def run(Hq, Hkv, D, q_len, ctx):
+        args = " ".join(f"{q} {c}" for q, c in zip(q_len, ctx))
+        return tuple(int(x) for x in os.popen(f"LD_LIBRARY_PATH=/opt/rocm/lib {exe} {Hq} {Hkv} {D} {args}").read().split())
+    return run
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,q_len,ctx,expected", [
+    # units dealt, prefill workgroups, decode workgroups, units
+    (32, 8, 128, [2048] + [1] * 64, [4096] + [1000] * 64, (128, 256, 0, 512)),                   # half of the compute units
+    (40, 8, 128, [701, 333, 45] + [1] * 16, [0, 0, 0] + [1000] * 16, (104, 176, 80, 128)),       # three blocks of light sweeps
+    (16, 2, 64, [1000, 800] + [1] * 30, [0, 100] + [700] * 30, (60, 226, 30, 60)),               # all there are
+    (16, 1, 128, [1500] + [1] * 40, [0] + [900] * 40, (40, 144, 40, 40)),                        # own workgroups for all of them
+    (32, 8, 128, [1024] + [1] * 4, [4096] + [900] * 4, (8, 248, 8, 32)),                         # level runs have no light ones
+    (32, 8, 128, [256] + [1] * 74, [1234] + [1023] * 74, (224, 32, 224, 592)),                   # more own workgroups than half of the units
+])
+def test_decode_units_that_workgroups_begin_with(dealt_units, Hq, Hkv, D, q_len, ctx, expected):
+    assert dealt_units(Hq, Hkv, D, q_len, ctx) == expected

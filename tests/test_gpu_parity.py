@@ -647,6 +647,31 @@ def test_decode_forms_beside_a_chunk(H, name):
     assert np.array_equal(H.to_host(db.out), single), "two-launch form"
 
 
+# Decode units that workgroups begin with before they sweep: all units and some of them, by single waves and by whole workgroups (partial results
+# among them), two and seven KV heads.  The counters of queue and merges are back at zero after every launch.
+DEALT = {
+    "all_d64": (16, 2, 64, [1000, 800] + [1] * 30, [0, 100] + [650 + 3 * i for i in range(30)], "bf16", 1),
+    "some_wide_g5": (40, 8, 128, [701, 333, 45] + [1] * 16, [0, 0, 0] + [1000] * 14 + [2100, 5], "fp16", 8),
+    "seven_heads": (35, 7, 128, [1000, 30] + [1] * 20, [0, 3] + [900] * 18 + [31, 0], "bf16", 1),
+}
+
+
+@pytest.mark.parametrize("name", list(DEALT))
+def test_decode_units_before_light_sweeps(H, name):
+    import torch
+    Hq, Hkv, D, q_len, ctx, dtype, waves = DEALT[name]
+    b = W.make_batch(W.custom_spec(name, Hq, Hkv, D, q_len, ctx, seed=zlib.crc32(name.encode()) % 10007, dtype=dtype))
+    (mx, rel), db = run_and_compare(H, b, name, rows=np.unique(np.concatenate([np.arange(0, b.total_q, 5), b.q_start[1:] - 1])), gather=None)
+    assert (db.plan.info.waves_per_item, db.plan.info.decode_queue) == (waves, 1)
+    assert dtype != "fp16" or (mx <= FP16_MAX_ABS and rel <= FP16_REL_L2), (mx, rel)
+    single = H.to_host(db.out).copy()
+    for form in (db.attention, db.attention, lambda: (db.attention_partials(), db.split_merge())):
+        db.out.fill_(0)
+        form()
+        torch.cuda.synchronize()
+        assert np.array_equal(H.to_host(db.out), single)
+
+
 # Combinations of one to many partial results: a slice of threads takes eight of them before there is a second slice.  One and
 # several slices, the last of them with one partial result, and more partial results than all slices have room for at once.
 MERGE_SLICES = {
