@@ -674,9 +674,8 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
             }
         }
     }
-    const int64_t n_items = (int64_t)w.blocks.size() * Hkv, slots = wg_slots(p);
-    if (n_wg_per_head <= 0) {
-        // one workgroup per piece; within a block the pieces share the tiles out evenly
+    const auto one_workgroup_per_piece = [&] {  // within a block the pieces share the tiles out evenly
+        w.pieces.clear();
         for (size_t i = 0; i < w.blocks.size(); i++) {
             const PlanRowBlock &x = w.blocks[i];
             for (int c = 0; c < x.k; c++)
@@ -685,8 +684,9 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
         // most tiles first (the hardware starts workgroups in index order)
         std::stable_sort(w.pieces.begin(), w.pieces.end(), [](const PlanPiece &x, const PlanPiece &y) { return x.t1 - x.t0 > y.t1 - y.t0; });
         for (size_t i = 0; i < w.pieces.size(); i++) w.pieces[i].wg = (int)i;
-    }
-    const int n_wg_head = w.pieces.empty() ? 0 : w.pieces.back().wg + 1;  // prefill workgroups per KV head (pieces are in workgroup order)
+    };
+    if (n_wg_per_head <= 0) one_workgroup_per_piece();
+    int n_wg_head = w.pieces.empty() ? 0 : w.pieces.back().wg + 1;  // prefill workgroups per KV head (pieces are in workgroup order)
 
     // ---- decode items.  Consecutive splits of one (sequence, KV head) that share a workgroup form a team:
     // the workgroup combines their results in LDS, and the team writes the output rows itself when it
@@ -708,7 +708,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
                 p->waves_per_item = kWideWaves / 2;
             }
         }
-    if (!w.blocks.empty() && n_decode_seqs > 0) {
+    const auto decodes_beside_chunk = [&] {
         double longest_piece = 0, tiles = 0;
         for (const PlanPiece &x : w.pieces) {
             longest_piece = std::max<double>(longest_piece, x.t1 - x.t0);
@@ -728,7 +728,32 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
                     p->waves_per_item = kMixedWaves / 2;
                 }
         }
+    };
+    if (!w.blocks.empty() && n_decode_seqs > 0) {
+        decodes_beside_chunk();
+        // Short decodes, which single waves run, beside a few uncut sweeps of at most 12 tiles: workgroups of four waves, two or three to a unit, for
+        // both, from 128 (sequence, KV head) pairs on (with fewer the two launches of a step take the host longer than the GPU, in either form).  What such a launch takes is the start and the end of its workgroups, which then lie beside each other.  Measured (us per step, eight waves / four):
+        //   32/8 heads, 20 at 0 with 17 of 140-281 15.1 / 13.1, 310 at 0 with 180 of 29-58 20.0 / 18.8, 3 at 2 with 369 of 45-90 35.1 / 32.8; 8/8, 78 at 0 with 63 of 77-623
+        //   26.9 / 22.4; 16/2, 4 at 1 with 231 of 24-198 17.3 / 13.0; 32/32, head_dim 64, 288 at 0 with 132 of 7-60 22.2 / 20.0; 40/8, 8 at 0 with 374 of 77-616 111.4 / 108.6
+        //   longer decodes: 64/8, head_dim 64, 10 at 67 with 42 of 742-5936 51.9 / 56.2; 8/8, head_dim 64, 163 at 0 with 68 of 384-3078 43.3 / 45.4
+        //   long streams: 32/32, 196 at 0 with 396 of 92-738 (2.6 GB) 472.1 / 487.6; sweeps of 15 tiles: 16/2, head_dim 64, 945 at 0 with 81 of 48-390 16.1 / 16.5
+        //   run by whole workgroups: 40/8, 157 at 0 with 9 of 745-1491 16.8 / 20.0; cut sweeps: 32/8, 11 at 2659 with 20 of lognormal 140 27.4 / 37.6
+        int64_t longest = 0;
+        bool cut = n_wg_per_head > 0 || w.blocks[0].n_tiles > 12;
+        for (int s = 0; s < S; s++)
+            if (p->q_start[s + 1] - p->q_start[s] == 1) longest = std::max(longest, (int64_t)p->ctx_len[s] + 1);
+        for (const PlanRowBlock &x : w.blocks) cut |= x.k > 1;
+        if (p->waves_per_item == 1 && p->prefill_waves == kMixedWaves && !queue && !cut && longest <= 768 && (int64_t)n_decode_seqs * Hkv * 2 >= kNumCu && decode_bytes < (int64_t)600000000 &&
+            (int64_t)w.blocks.size() * Hkv * 4 <= kNumCu) {
+            p->prefill_waves = p->items_per_wg = kSmallWaves;
+            p->rows_per_item = kPrefillRows / 2;
+            make_row_blocks(p, S, p->rows_per_item, w.blocks);
+            one_workgroup_per_piece();
+            n_wg_head = (int)w.pieces.size();
+            decodes_beside_chunk();
+        }
     }
+    const int64_t n_items = (int64_t)w.blocks.size() * Hkv, slots = wg_slots(p);
     const int W = p->items_per_wg;
     // Beside a chunk a workgroup has a unit to itself and runs eight splits: of up to 1024 tokens they take it 170 us while all units stream, and
     // few such rounds end raggedly.  Where the sequences are long (2000 tokens on the mean) splits are shorter, down to 256 tokens (512 at head_dim 64), until

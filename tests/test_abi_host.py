@@ -825,3 +825,23 @@ def dealt_units(tc, tmp_path_factory):
 ])
 def test_decode_units_that_workgroups_begin_with(dealt_units, Hq, Hkv, D, q_len, ctx, expected):
     assert dealt_units(Hq, Hkv, D, q_len, ctx) == expected
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,chunk,offset,decodes,threads", [
+    (32, 8, 128, 20, 0, [200] * 16, 256),         # 128 pairs
+    (32, 8, 128, 20, 0, [200] * 15, 512),         # and 120
+    (32, 8, 128, 300, 0, [767] * 60, 256),
+    (32, 8, 128, 300, 0, [768] + [767] * 59, 512),  # a longer decode
+    (8, 8, 64, 24, 744, [100] * 40, 256),         # 12 tiles
+    (8, 8, 64, 24, 745, [100] * 40, 512),         # and 13
+    (32, 32, 128, 100, 0, [500] * 73, 256),       # 599 MB
+    (32, 32, 128, 100, 0, [500] * 74, 512),       # and 607
+    (32, 32, 64, 256, 0, [50] * 30, 256),
+    (32, 32, 64, 512, 0, [50] * 30, 512),         # 128 items
+    (16, 2, 128, 5, 3, [100] * 64, 256),
+])
+def test_short_decodes_beside_few_sweeps_run_in_small_workgroups(tc, Hq, Hkv, D, chunk, offset, decodes, threads):
+    sp = W.custom_spec("short", Hq, Hkv, D, [chunk] + [1] * len(decodes), [offset] + decodes)
+    table, mb, nb = W.make_tables(sp, np.random.default_rng(20))
+    info = check_work_list(tc, sp, table, nb)
+    assert info.block_threads == threads

@@ -672,6 +672,24 @@ def test_decode_units_before_light_sweeps(H, name):
         assert np.array_equal(H.to_host(db.out), single)
 
 
+# Workgroups of four waves for a few short sweeps and many short decodes: padding waves, one token, the longest decode that counts as short.
+SHORT_BESIDE_FEW = {
+    "g4_whole_workgroups": (32, 8, 128, [37] + [1] * 30, [3] + [300, 0, 15, 16, 17] + [150 + i for i in range(25)], "fp16"),
+    "g4": (32, 8, 128, [60] + [1] * 60, [0] + [300] + [40 + 3 * i for i in range(59)], "bf16"),
+    "g1_d64_two_chunks": (32, 32, 64, [70, 9] + [1] * 5, [0, 200, 40, 1, 63, 300, 128], "bf16"),
+    "g8_two_heads": (16, 2, 128, [2] + [1] * 67, [5] + [3 * i for i in range(67)], "bf16"),
+}
+
+
+@pytest.mark.parametrize("name", list(SHORT_BESIDE_FEW))
+def test_short_decodes_beside_few_sweeps(H, name):
+    Hq, Hkv, D, q_len, ctx, dtype = SHORT_BESIDE_FEW[name]
+    b = W.make_batch(W.custom_spec(name, Hq, Hkv, D, q_len, ctx, seed=zlib.crc32(name.encode()) % 10007, dtype=dtype))
+    (mx, rel), db = run_and_compare(H, b, name, gather=None)
+    assert db.plan.info.block_threads == 256
+    assert dtype != "fp16" or (mx <= FP16_MAX_ABS and rel <= FP16_REL_L2), (mx, rel)
+
+
 # Combinations of one to many partial results: a slice of threads takes eight of them before there is a second slice.  One and
 # several slices, the last of them with one partial result, and more partial results than all slices have room for at once.
 MERGE_SLICES = {
