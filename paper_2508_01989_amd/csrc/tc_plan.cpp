@@ -487,7 +487,7 @@ static int tiles_of_fullest_unit(const tc_plan *p, const std::vector<PlanRowBloc
 // 701, 333 and 45 at 0 with 16 of them 37.1 / 35.4; 64/8, head_dim 64, 946 at 24 with 46 of 2490-19924 176 / 171; 808 at 0 with 8 of lognormal 2254 26.7 / 25.9.  A
 // quarter more or fewer of the units: 0.3 % slower on the mean of 40 batches, up to 8 %.
 template <class Splits>
-static int64_t deal_units(const tc_plan *p, int n_wg_head, int64_t n_decode_wg, int64_t n_units, const Splits &splits_of) {
+static int64_t deal_units(const tc_plan *p, int n_wg_head, int64_t decode_tokens, int64_t n_decode_wg, int64_t n_units, const Splits &splits_of) {
     const PlanScratch &w = p->work;
     const int Hkv = p->Hkv;
     int64_t dealt = n_decode_wg;
@@ -496,13 +496,13 @@ static int64_t deal_units(const tc_plan *p, int n_wg_head, int64_t n_decode_wg, 
         return (w.pieces[wg].t1 - w.pieces[wg].t0) * (p->D == 64 ? 1.03 : 1.65) * (p->rows_per_item == kPrefillRows ? 1.0 : 0.6) + 3.0;
     };
     const double unit_us = 4.0, us_per_token = 4.0 * p->D / 43.0e3;
-    double sum = n_units * unit_us;
+    double sum = n_units * unit_us + (double)decode_tokens * Hkv * us_per_token;
     for (int i = 0; i < n_wg_head; i++) sum += sweep_us(i) * Hkv;
     int64_t tokens[kNumCu / 2] = {};  // of the units that may be dealt
     for (const PlanTeam &x : w.teams) {
-        const int64_t kv = (int64_t)p->ctx_len[x.seq] + 1, of_team = kv * x.n / splits_of(kv);
-        sum += of_team * us_per_token;
-        if (x.wg < kNumCu / 2) tokens[x.wg] += of_team;
+        if (x.wg >= kNumCu / 2) continue;
+        const int64_t kv = (int64_t)p->ctx_len[x.seq] + 1;
+        tokens[x.wg] += kv * x.n / splits_of(kv);
     }
     const double end = 1.03 * std::max(sweep_us(0), sum / kNumCu), room = end - sweep_us(n_wg_head - 1);
     for (int i = 0; i < n_wg_head && dealt + Hkv <= std::min<int64_t>(n_units, kNumCu / 2); i++) {
@@ -840,7 +840,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
         }
     }
     const int64_t n_decode_wg = !queue ? n_decode_units : std::min<int64_t>(n_decode_units, std::max<int64_t>(slots - n_prefill_wg, 0));
-    const int64_t n_dealt = queue ? deal_units(p, n_wg_head, n_decode_wg, n_decode_units, splits_of) : 0;
+    const int64_t n_dealt = queue ? deal_units(p, n_wg_head, decode_tokens, n_decode_wg, n_decode_units, splits_of) : 0;
     const size_t off_records = 0;  // first: a record is a 128-byte line
     const size_t off_append = w.pieces.size() * kRecordInts, off_pages = off_append + (size_t)n_append * kAppendInts;
     const size_t off_valid = off_pages + (size_t)pages;
