@@ -104,8 +104,9 @@ typedef struct {
     int32_t num_piece_partials;         /* partial results of pieces of cut prefill items    */
     int32_t decode_queue;               /* 1: the decode items are drawn from a queue, in units of one workgroup's   */
                                         /* worth, by grid_blocks - num_prefill_workgroups decode workgroups and by   */
-                                        /* the prefill workgroups once their pieces are done (chunks whose            */
-                                        /* workgroups of eight waves all run from the start)                          */
+                                        /* the prefill workgroups once their pieces are done, those of light sweeps   */
+                                        /* with one unit before (chunks whose workgroups of eight waves all run from  */
+                                        /* the start)                                                                 */
     int32_t waves_per_item;             /* waves that share one decode item: 1, all of a workgroup's (few, long       */
                                         /* decodes) or half of them                                                   */
     int64_t build_ns;                   /* host time of the latest work-list build ...       */
@@ -184,8 +185,8 @@ tc_status tc_kv_append(const tc_plan *plan, const tc_kv_pool *pool, const void *
  * depend on which part that is.  No workgroup ever waits for another.  fp32 accumulation;
  * probabilities and the output are rounded to nearest even in the element type.  scale must be
  * positive and finite.  q, out, workspace: DEVICE.  Results are bitwise reproducible for a fixed
- * plan.  Two calls that use the same plan (its arrival counters) or the same workspace must not
- * overlap in time. */
+ * plan.  Two calls that use the same plan (its arrival counters and the counter of its decode queue) or the
+ * same workspace must not overlap in time. */
 tc_status tc_mixed_attention(const tc_plan *plan, const tc_kv_pool *pool, const void *q, void *out, float scale,
                              void *workspace, size_t workspace_bytes, void *stream);
 

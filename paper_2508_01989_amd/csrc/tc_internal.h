@@ -15,7 +15,7 @@ constexpr int kBlock = 16;          // tokens per KV page
 // waves, one per compute unit (two waves per SIMD, up to 256 registers each): the eight waves sweep the
 // same K/V tiles for 256 (position, head) rows (128 in small items), and a decode workgroup of that launch holds eight
 // decode items (one KV split per wave; splits of one sequence and KV head that share the workgroup are
-// combined there), or one or two that its waves share.  Chunks of uneven sweeps run workgroups of four waves instead, for
+// combined there), or one or two that its waves share.  Chunks of uneven sweeps, and short decodes beside a few short sweeps, run workgroups of four waves instead, for
 // 128 rows, two or three per compute unit.  A batch of decodes only runs workgroups of four waves, three per compute unit, or two
 // where a workgroup holds one or two items.
 constexpr int kMixedWaves = 8;

@@ -1495,7 +1495,7 @@ struct AttnScalars {
 // The work lists and the page table are separate const __restrict__ kernel arguments (not struct
 // members) so that the compiler knows they are never written and can fetch them with
 // scalar loads.  CHUNK: batches with a prefill chunk; WAVES = 8: one workgroup per compute unit, up to 256 registers per
-// wave; WAVES = 4: two of them (three at head_dim 64, 158 registers; at head_dim 128 248), chosen by estimate_chunk.  Without CHUNK: decode-only
+// wave; WAVES = 4: two of them (three at head_dim 64, 158 registers; at head_dim 128 248), chosen by estimate_chunk, or for short decodes beside few sweeps.  Without CHUNK: decode-only
 // batches (WAVES = 4, three workgroups per compute unit).
 // Workgroups [0, n_prefill) run the prefill pieces the plan gave them, one after the other; the rest run
 // decode items, one per wave, or (WIDE = 1 or 2; forms of their own, so that neither pays for the other's registers: both in one
