@@ -100,6 +100,7 @@ struct tc_plan {
     int counter_stride = tc::kCounterLine;  // int32 between arrival counters; the items of the image hold a counter's index times this
     int queue_counter = -1;  // int32 from the first arrival counter to the decode queue's (a line of its own, behind them), or -1: no queue
     int n_dealt = 0;  // decode units that the last workgroups of the launch begin with, where there is a queue; the next ones are drawn
+    int n_drawers = 0;  // workgroups that draw decode units, the last ones of the launch: all of them, those of the decode branch, or none (no queue)
     int split_tokens = 0;
     int64_t total_pages = 0;
     std::vector<int32_t> q_start, ctx_len, page_off;  // host copies

@@ -1488,6 +1488,7 @@ struct AttnScalars {
     int queue;
     int n_partials;
     int n_dealt;     // decode units that workgroups begin with, where there is a queue; the next ones are drawn
+    int n_drawers;   // the workgroups that draw, the last ones of the launch (0: no queue)
     int n_front, n_append_rows;  // a batch of decodes whose rows this launch stores: the workgroups (the last of the grid) that do it, rows
     float scale_log2;
 };
@@ -1540,17 +1541,17 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : CHUNK ?
         // (Left to the hardware, decode workgroups beyond the first round were not started on the units the first
         // round had freed until the prefill workgroups ended.  Handing out single items to single waves, with the
         // splits of a pair combined by the last to arrive, measured slower than units with their teams.)
-        // Every workgroup draws one number past the last unit; the last of those is the last draw of the launch, and puts the
+        // Who draws is the plan's decision (n_drawers).  Each of them draws one number past the last unit; the last of those is the last draw of the launch, and puts the
         // counter back to zero for the next one.  (With a second counter of those that have left, and a draw before the first unit,
         // small batches took 2 us longer.)
-        const bool late = A.n_prefill > kNumCu, sweep = wg < A.n_prefill;
+        const bool sweep = wg < A.n_prefill;
         const auto run = [&](int unit) __attribute__((always_inline)) {
             const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
             if constexpr (WIDE > 0) decode_item_wide<D, E, NS, WAVES, 1, false>(A, decode + (int64_t)unit * kItemInts, reinterpret_cast<float *>(lds));
             else decode_item<D, E, NS>(A, decode + ((int64_t)unit * WAVES + wave) * kItemInts, reinterpret_cast<float *>(lds), WAVES);
         };
         int first = wg - A.n_prefill;
-        if (A.queue >= 0) {
+        if (sc.n_drawers > 0) {
             first = (int)gridDim.x - 1 - wg;
             if (first >= sc.n_dealt) first = -1;
         }
@@ -1572,7 +1573,7 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : CHUNK ?
 #ifdef TC_WG_TRACE
         t_mid = __builtin_amdgcn_s_memrealtime();
 #endif
-        if (A.queue >= 0 && !(late && sweep)) {
+        if (wg >= (int)gridDim.x - sc.n_drawers) {
             int *const drawn = reinterpret_cast<int *>(lds + PrefillLds<D, WAVES>::kIds);  // the slots of the page ids: free when no sweep runs
             int32_t *const next_unit = A.counters + A.queue;
             const int n_units = WIDE ? A.n_decode : A.n_decode / WAVES;
@@ -1585,8 +1586,7 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : CHUNK ?
                 if (unit >= n_units) break;
                 run(unit);
             }
-            const int n_drawers = late ? (int)gridDim.x - A.n_prefill : (int)gridDim.x;
-            if (threadIdx.x == 0 && unit == n_units + n_drawers - 1) __hip_atomic_store(next_unit, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (threadIdx.x == 0 && unit == n_units + sc.n_drawers - 1) __hip_atomic_store(next_unit, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     } else if (CHUNK && wg < A.n_prefill) {
         if constexpr (CHUNK) {
@@ -1835,7 +1835,7 @@ static int launch_attention_d(const tc_plan *p, const AttnArgs &A, int launches,
         n_front = (int)((units + per_wg - 1) / per_wg);
         grid += n_front;
     }
-    const AttnScalars sc = {A.n_prefill, A.n_decode, A.Hq, A.Hkv, A.G, A.fused, A.queue, p->n_partials, p->n_dealt, n_front, p->n_append, A.scale_log2};
+    const AttnScalars sc = {A.n_prefill, A.n_decode, A.Hq, A.Hkv, A.G, A.fused, A.queue, p->n_partials, p->n_dealt, p->n_drawers, n_front, p->n_append, A.scale_log2};
     const int32_t *append = p->dev + p->off_append;
     if (grid > 0 && p->n_pieces > 0) {
         if (int err = allow_prefill_lds<D, E>(p->device)) return err;

@@ -518,7 +518,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     // an error below leaves the plan describing an empty batch
     p->S = p->T = 0;
     p->n_prefill_seqs = p->n_decode_seqs = 0;
-    p->n_prefill = p->n_decode = p->n_merge = p->n_partials = p->n_piece_partials = p->n_merge_prefill = p->n_pieces = p->n_prefill_wg = p->n_counters = p->n_append = p->n_append_prefill = p->n_decode_wg = p->n_dealt = 0;
+    p->n_prefill = p->n_decode = p->n_merge = p->n_partials = p->n_piece_partials = p->n_merge_prefill = p->n_pieces = p->n_prefill_wg = p->n_counters = p->n_append = p->n_append_prefill = p->n_decode_wg = p->n_dealt = p->n_drawers = 0;
     p->queue_counter = -1;
     p->items_per_wg = kDecodeWaves;
     p->waves_per_item = 1;
@@ -656,8 +656,11 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
             // three quarters of the units (40/8 heads, head_dim 64, 1204 at 4097 whole 82, runs 75); beyond whole items do as well or better (8/8, first
             // chunks of 2837, 3049 and 3264 92 / 108, 16/2, 4014 and 1489 95 / 103).
             const bool instead_of_small = !small && bins >= 8 && (!crowded || items * 4 <= 3 * kNumCu);
+            // Every KV head has a unit at least: with more heads than units there is one run a head, which cuts nothing, more of them than run at once, and the queue
+            // is for launches that all run from the start (us, runs / as they are: 257/257 heads, 200 at 4000 with 2 decodes 219 / 207; head_dim 64, 300/300, 69
+            // at 8000 with 3 193 / 186, 320/320, 106 at 0 and 19 at 13305 with one 301 / 211, 514/257, 138 at 21684 with 2 1095 / 789).
             int runs = 0;
-            if (t_levelled < level_below * t_whole && (t_levelled < t.small || instead_of_small) && t_decode < 0.75 * t_levelled) {
+            if (Hkv <= kNumCu && t_levelled < level_below * t_whole && (t_levelled < t.small || instead_of_small) && t_decode < 0.75 * t_levelled) {
                 // (Chunks of up to three quarters of the units beside few decodes run like this whatever scratch they need.)
                 const bool any_scratch = items * 4 <= 3 * kNumCu && t_decode < 0.25 * w.blocks[0].n_tiles * kTileUs * (D / 128.0);
                 runs = level(bins, any_scratch);
@@ -840,6 +843,8 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
         }
     }
     const int64_t n_decode_wg = !queue ? n_decode_units : std::min<int64_t>(n_decode_units, std::max<int64_t>(slots - n_prefill_wg, 0));
+    // Who draws is said here and nowhere else: a unit that no launched workgroup has of its own needs somebody to draw it.
+    const int64_t n_drawers = queue ? n_prefill_wg + n_decode_wg : late_queue ? n_decode_wg : 0;
     const int64_t n_dealt = queue ? deal_units(p, n_wg_head, decode_tokens, n_decode_wg, n_decode_units, splits_of) : 0;
     const size_t off_records = 0;  // first: a record is a 128-byte line
     const size_t off_append = w.pieces.size() * kRecordInts, off_pages = off_append + (size_t)n_append * kAppendInts;
@@ -998,7 +1003,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     p->n_prefill = (int)n_prefill; p->n_pieces = (int)n_pieces; p->n_prefill_wg = (int)n_prefill_wg; p->n_decode = (int)n_decode;
     p->n_merge = (int)n_merge; p->n_partials = (int)n_partials; p->n_counters = (int)n_counters; p->n_append = (int)n_append;
     p->n_piece_partials = (int)n_piece_partials; p->n_merge_prefill = (int)n_merge_prefill;
-    p->n_decode_wg = (int)n_decode_wg; p->n_dealt = (int)n_dealt; p->counter_stride = counter_stride; p->queue_counter = queue || late_queue ? (int)off_queue : -1;
+    p->n_decode_wg = (int)n_decode_wg; p->n_dealt = (int)n_dealt; p->n_drawers = (int)n_drawers; p->counter_stride = counter_stride; p->queue_counter = queue || late_queue ? (int)off_queue : -1;
     p->off_records = off_records; p->off_append = off_append; p->off_pages = off_pages; p->off_valid = off_valid; p->off_prefill = off_prefill;
     p->off_decode = off_decode; p->off_merge = off_merge; p->off_counters = off_counters;
     p->host_n = total;
@@ -1062,7 +1067,7 @@ tc_status tc_plan_get_info(const tc_plan *p, tc_plan_info *info) {
     info->num_prefill_pieces = p->n_pieces;
     info->num_prefill_workgroups = p->n_prefill_wg;
     info->num_counters = p->n_counters;
-    info->decode_queue = p->queue_counter >= 0 && p->n_prefill_wg <= tc::kNumCu;
+    info->decode_queue = p->n_drawers > p->n_decode_wg;  // the prefill workgroups draw too
     info->build_ns = p->build_ns;
     info->upload_ns = p->upload_ns;
     return TC_OK;

@@ -197,8 +197,9 @@ def check_work_list(tc, sp, table, nb):
         if not levelled:      # one piece per workgroup, most tiles first (uncut items, or few items whose KV ranges are cut)
             tiles_of_record = tiles_of_wg[::Hkv].copy()
             if len(pf) == len(pc) and info.block_threads == 256 and n_wg <= 256 * (2 if sp.head_dim == 128 else 3):
-                for first in range(256 // Hkv, n_wg // Hkv, 2 * (256 // Hkv)):  # workgroups of four waves that all run at once: every other row of 256 turned round
-                    tiles_of_record[first:first + 256 // Hkv] = tiles_of_record[first:first + 256 // Hkv][::-1].copy()
+                row = max(1, 256 // Hkv)
+                for first in range(row, n_wg // Hkv, 2 * row):  # workgroups of four waves that all run at once: every other row of 256 turned round
+                    tiles_of_record[first:first + row] = tiles_of_record[first:first + row][::-1].copy()
             assert n_wg == len(pc) and np.all(np.diff(tiles_of_record) <= 0)
         else:                 # every KV head has the same runs, of nearly equal cost (tiles + 3 per piece)
             assert n_wg % Hkv == 0 and n_wg <= 256
@@ -781,7 +782,7 @@ DEALT = """
 #include <cstdlib>
 #include <vector>
 #include "tc_internal.h"
-int main(int argc, char **argv) {  // heads, KV heads, head_dim, then q_len ctx_len of every sequence -> units dealt, prefill and decode workgroups, units
+int main(int argc, char **argv) {  // heads, KV heads, head_dim, then q_len ctx_len of every sequence -> units dealt, prefill and decode workgroups, units, drawers
     std::vector<int32_t> q_start(1, 0), ctx;
     int most = 1;
     for (int i = 4; i + 1 < argc; i += 2) {
@@ -795,14 +796,14 @@ int main(int argc, char **argv) {  // heads, KV heads, head_dim, then q_len ctx_
     tc_batch b = {(int32_t)ctx.size(), q_start.data(), ctx.data(), table.data(), most};
     tc_plan *p = nullptr;
     if (tc_plan_create_host(&pool, &b, &p)) return 1;
-    printf("%d %d %d %d\\n", p->n_dealt, p->n_prefill_wg, p->n_decode_wg, p->n_decode / p->items_per_wg);
+    printf("%d %d %d %d %d\\n", p->n_dealt, p->n_prefill_wg, p->n_decode_wg, p->n_decode / p->items_per_wg, p->n_drawers);
     tc_plan_destroy(p);
 }
 """
 
 
 @pytest.fixture(scope="module")
-def dealt_units(tc, tmp_path_factory):
+def launch_of(tc, tmp_path_factory):
     d = tmp_path_factory.mktemp("dealt")
     src, exe, lib_dir = d / "t.cpp", d / "t", os.path.dirname(tc.LIB_PATH)
     src.write_text(DEALT)
@@ -812,6 +813,11 @@ def dealt_units(tc, tmp_path_factory):
         args = " ".join(f"{q} {c}" for q, c in zip(q_len, ctx))
         return tuple(int(x) for x in os.popen(f"LD_LIBRARY_PATH=/opt/rocm/lib {exe} {Hq} {Hkv} {D} {args}").read().split())
     return run
+
+
+@pytest.fixture(scope="module")
+def dealt_units(launch_of):
+    return lambda *batch: launch_of(*batch)[:4]
 
 
 @pytest.mark.parametrize("Hq,Hkv,D,q_len,ctx,expected", [
@@ -845,3 +851,33 @@ def test_short_decodes_beside_few_sweeps_run_in_small_workgroups(tc, Hq, Hkv, D,
     table, mb, nb = W.make_tables(sp, np.random.default_rng(20))
     info = check_work_list(tc, sp, table, nb)
     assert info.block_threads == threads
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,q_len,ctx", [
+    (255, 255, 64, [600, 1, 1], [3000, 100, 200]),                      # a run to every unit but one
+    (256, 256, 64, [69, 20, 1, 1], [8000, 0, 101, 501]),
+    (257, 257, 64, [109, 7, 1], [3160, 0, 69]),                         # one KV head more than there are units
+    (257, 257, 128, [200, 1, 1], [4000, 100, 200]),
+    (280, 280, 64, [25, 58, 1, 1, 1], [0, 3306, 25, 129, 17]),
+    (300, 300, 64, [69, 1, 1, 1], [8000, 101, 501, 41]),
+    (300, 300, 128, [600, 1, 1], [3000, 400, 900]),
+    (600, 300, 64, [99, 86, 1], [0, 8651, 228]),
+    (514, 257, 64, [138, 1, 1], [21684, 23, 111]),                      # workgroups of four waves
+    (2080, 260, 128, [3, 12] + [1] * 6, [0, 25912, 296, 545, 18, 975, 1885, 114]),
+    (512, 512, 128, [300, 1, 1], [100, 900, 41]),
+    (1024, 1024, 64, [2, 1], [5, 3000]),
+    (1024, 1024, 128, [70, 30, 1, 1], [0, 900, 8, 64]),
+])
+def test_every_decode_unit_has_a_workgroup_that_runs_it(tc, launch_of, Hq, Hkv, D, q_len, ctx):
+    """More KV heads than compute units, and about as many: a unit has a workgroup of its own, or there are workgroups that draw."""
+    sp = W.custom_spec("many_heads", Hq, Hkv, D, q_len, ctx)
+    table, mb, nb = W.make_tables(sp, np.random.default_rng(21))
+    info = check_work_list(tc, sp, table, nb)
+    dealt, n_prefill, n_decode, units, drawers = launch_of(Hq, Hkv, D, q_len, ctx)
+    assert info.grid_blocks == n_prefill + n_decode and units > 0
+    if drawers == 0:                                     # a workgroup for every unit
+        assert n_decode == units and dealt == 0 and info.decode_queue == 0
+    elif info.decode_queue:                              # everybody draws, and runs from the start
+        assert drawers == n_prefill + n_decode <= 256 and n_decode <= dealt <= units
+    else:                                                # the decode workgroups draw, behind more sweeps than the chip takes at once
+        assert drawers == n_decode == units and dealt == 0 and n_prefill > 256

@@ -672,6 +672,32 @@ def test_decode_units_before_light_sweeps(H, name):
         assert np.array_equal(H.to_host(db.out), single)
 
 
+# More KV heads than compute units, beside sweeps of uneven length: every output row is written (`out` holds NaN before the launch).
+MORE_HEADS_THAN_UNITS = {
+    # name: (Hq, Hkv, D, q_len, ctx, dtype)
+    "g1_d64": (257, 257, 64, [109, 7, 1], [3160, 0, 69], "bf16"),
+    "g1_d64_several_decodes": (280, 280, 64, [25, 58, 1, 1, 1], [0, 3306, 25, 129, 17], "fp16"),
+    "g1_d128": (258, 258, 128, [13, 1, 1, 1], [2603, 36, 21, 52], "bf16"),
+}
+
+
+@pytest.mark.parametrize("name", list(MORE_HEADS_THAN_UNITS))
+def test_decodes_where_kv_heads_outnumber_the_units(H, name):
+    import torch
+    Hq, Hkv, D, q_len, ctx, dtype = MORE_HEADS_THAN_UNITS[name]
+    b = W.make_batch(W.custom_spec(name, Hq, Hkv, D, q_len, ctx, seed=zlib.crc32(name.encode()) % 10007, dtype=dtype))
+    rows = np.unique(np.concatenate([np.arange(0, b.total_q, 9), b.q_start[1:] - 1]))
+    (mx, rel), db = run_and_compare(H, b, name, rows=rows, gather=None)
+    assert dtype != "fp16" or (mx <= FP16_MAX_ABS and rel <= FP16_REL_L2), (mx, rel)
+    assert np.isfinite(db.out_f64()).all()
+    single = H.to_host(db.out).copy()
+    for form in (db.attention, db.attention, lambda: (db.attention_partials(), db.split_merge())):
+        db.out.fill_(-1)  # all bits set: NaN
+        form()
+        torch.cuda.synchronize()
+        assert np.array_equal(H.to_host(db.out), single)
+
+
 # Workgroups of four waves for a few short sweeps and many short decodes: padding waves, one token, the longest decode that counts as short.
 SHORT_BESIDE_FEW = {
     "g4_whole_workgroups": (32, 8, 128, [37] + [1] * 30, [3] + [300, 0, 15, 16, 17] + [150 + i for i in range(25)], "fp16"),
