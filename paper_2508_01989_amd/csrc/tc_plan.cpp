@@ -487,11 +487,13 @@ static int tiles_of_fullest_unit(const tc_plan *p, const std::vector<PlanRowBloc
 // 701, 333 and 45 at 0 with 16 of them 37.1 / 35.4; 64/8, head_dim 64, 946 at 24 with 46 of 2490-19924 176 / 171; 808 at 0 with 8 of lognormal 2254 26.7 / 25.9.  A
 // quarter more or fewer of the units: 0.3 % slower on the mean of 40 batches, up to 8 %.
 template <class Splits>
-static int64_t deal_units(const tc_plan *p, int n_wg_head, int64_t decode_tokens, int64_t n_decode_wg, int64_t n_units, const Splits &splits_of) {
+static int64_t deal_units(const tc_plan *p, int n_wg_head, bool level_runs, int64_t decode_tokens, int64_t n_decode_wg, int64_t n_units, const Splits &splits_of) {
     const PlanScratch &w = p->work;
     const int Hkv = p->Hkv;
     int64_t dealt = n_decode_wg;
-    if (n_wg_head == 0 || w.pieces.size() != (size_t)n_wg_head || dealt + Hkv > std::min<int64_t>(n_units, kNumCu / 2)) return dealt;  // (level runs are alike)
+    // Level runs are alike, also where each of them is one piece: a unit before some of them comes on top (us, none / units before a few of them: head_dim
+    // 64, 128/8 heads, 135 at 2105 with 2 of 3680 25.0 / 31.7, 64/8, 279 at 1392 with 173 of 134 26.7 / 30.5; 8/8, 1649 at 319 with 2 of 2908 36.4 / 41.9).
+    if (n_wg_head == 0 || level_runs || dealt + Hkv > std::min<int64_t>(n_units, kNumCu / 2)) return dealt;
     const auto sweep_us = [&](int wg) {  // a piece each, the longest first
         return (w.pieces[wg].t1 - w.pieces[wg].t0) * (p->D == 64 ? 1.03 : 1.65) * (p->rows_per_item == kPrefillRows ? 1.0 : 0.6) + 3.0;
     };
@@ -845,7 +847,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     const int64_t n_decode_wg = !queue ? n_decode_units : std::min<int64_t>(n_decode_units, std::max<int64_t>(slots - n_prefill_wg, 0));
     // Who draws is said here and nowhere else: a unit that no launched workgroup has of its own needs somebody to draw it.
     const int64_t n_drawers = queue ? n_prefill_wg + n_decode_wg : late_queue ? n_decode_wg : 0;
-    const int64_t n_dealt = queue ? deal_units(p, n_wg_head, decode_tokens, n_decode_wg, n_decode_units, splits_of) : 0;
+    const int64_t n_dealt = queue ? deal_units(p, n_wg_head, n_wg_per_head > 0, decode_tokens, n_decode_wg, n_decode_units, splits_of) : 0;
     const size_t off_records = 0;  // first: a record is a 128-byte line
     const size_t off_append = w.pieces.size() * kRecordInts, off_pages = off_append + (size_t)n_append * kAppendInts;
     const size_t off_valid = off_pages + (size_t)pages;

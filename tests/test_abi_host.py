@@ -827,6 +827,9 @@ def dealt_units(launch_of):
     (16, 2, 64, [1000, 800] + [1] * 30, [0, 100] + [700] * 30, (60, 226, 30, 60)),               # all there are
     (16, 1, 128, [1500] + [1] * 40, [0] + [900] * 40, (40, 144, 40, 40)),                        # own workgroups for all of them
     (32, 8, 128, [1024] + [1] * 4, [4096] + [900] * 4, (8, 248, 8, 32)),                         # level runs have no light ones
+    (128, 8, 64, [135, 1, 1], [2105, 4662, 2698], (40, 216, 40, 64)),                            # nor where each of them is a piece
+    (64, 8, 64, [279] + [1] * 173, [1392] + [133] * 173, (112, 144, 112, 346)),
+    (8, 8, 128, [30, 1649, 8, 1, 1], [3957, 319, 2863, 2877, 2940], (40, 216, 40, 64)),
     (32, 8, 128, [256] + [1] * 74, [1234] + [1023] * 74, (224, 32, 224, 592)),                   # more own workgroups than half of the units
 ])
 def test_decode_units_that_workgroups_begin_with(dealt_units, Hq, Hkv, D, q_len, ctx, expected):
