@@ -833,15 +833,21 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     //   5.0, 300 MB           312 at 7068 with 13 of lognormal 4371 87.0 / 84.4    2.4, 780 MB  8/8, head_dim 64, 4 at 5 with 79 of 1030-8244 135.4 / 133.9
     //   2.3, 700 MB           32/32, 75 at 29 with 20 of lognormal 2109 124.3 / 125.8    2.1, 590 MB  40 at 24 with 15 of lognormal 9482 106.9 / 110.5
     //   2.8, 240 MB           64/8, head_dim 64, 10 at 356 with 289 of lognormal 431 52.9 / 53.4; smaller ones lose up to 7 % (a draw takes a microsecond)
-    // Behind more sweeps than units only the decode workgroups draw (see the kernel); from 24 tiles a unit on, 41 us of sweeps: 4711 at 0, 32/32, with 272 of
-    // 31-254 334.6 / 323.9; 3797 at 2 with 80 of 77 129.4 / 126.6; 2781 at 0 with 12 of 587-4702 93.1 / 92.8; below 2343 at 0 with 5 of 758-6068 67.6 / 68.5.
+    // Behind more sweeps than units only the decode workgroups draw (see the kernel), where the sweeps are long enough for what the dies' rates differ by.  Single waves
+    // at head_dim 128 from 24 tiles a unit on, 41 us of sweeps: 4711 at 0, 32/32, with 272 of 31-254 334.6 / 323.9; 3797 at 2 with 80 of 77 129.4 / 126.6; 2781 at 0
+    // with 12 of 587-4702 93.1 / 92.8; below 2343 at 0 with 5 of 758-6068 67.6 / 68.5.  Whole workgroups, whose units are short, from 40 and from 15 for every 256 units on: 36
+    // tiles, 832 units 150.9 / 153.6, 33, 896 132.6 / 137.5, 40, 1376 169.3 / 179.2; 42, 360 124.0 / 123.0, 68, 576 206.6 / 201.0, 60, 865 214.1 / 209.2, 208, 832 419.7 / 408.3.
+    // Head_dim 64 from 140 and 60 for every 256 units on: 33 tiles, 680 units 76.3 / 79.8, 56, 660 107.1 / 110.4, 107, 504 153.5 / 156.0, 122, 720 166.3 / 169.4 (55
+    // batches below 0.7 % slower on the mean); 144, 476 222.1 / 218.9, 203, 448 245.5 / 240.0, 255, 169 318.3 / 311.3 (13 0.5 % faster, none slower by more than 0.2 %).
     bool late_queue = false;
     if (!queue && n_decode_units > 0 && !w.blocks.empty() && p->prefill_waves == kMixedWaves && (p->waves_per_item == 1 || p->items_per_wg == 1)) {
         if (n_prefill_wg <= kNumCu) queue = decode_bytes >= (int64_t)300000000 && n_decode_units * 5 >= 12 * std::max<int64_t>(kNumCu - n_prefill_wg, 1);
         else {
             int64_t tiles = 0;
             for (const PlanPiece &x : w.pieces) tiles += x.t1 - x.t0;
-            late_queue = tiles * Hkv >= 24 * kNumCu;
+            const bool waves = p->waves_per_item == 1;
+            const int64_t at_least = D == 64 ? 140 : waves ? 24 : 40, per_round = D == 64 ? 60 : waves ? 0 : 15;
+            late_queue = tiles * Hkv >= std::max(at_least * kNumCu, per_round * n_decode_units);
         }
     }
     const int64_t n_decode_wg = !queue ? n_decode_units : std::min<int64_t>(n_decode_units, std::max<int64_t>(slots - n_prefill_wg, 0));

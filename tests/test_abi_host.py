@@ -884,3 +884,28 @@ def test_every_decode_unit_has_a_workgroup_that_runs_it(tc, launch_of, Hq, Hkv, 
         assert drawers == n_prefill + n_decode <= 256 and n_decode <= dealt <= units
     else:                                                # the decode workgroups draw, behind more sweeps than the chip takes at once
         assert drawers == n_decode == units and dealt == 0 and n_prefill > 256
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,chunk,offset,decodes,waves,drawn", [
+    (64, 8, 128, 1500, 255, [3000] + [400] * 120, 1, False),   # 23.5 tiles a unit
+    (64, 8, 128, 1500, 272, [3000] + [400] * 120, 1, True),    # and 24.6
+    (64, 8, 128, 2000, 255, [2500] * 10, 8, False),            # whole workgroups: 39.8
+    (64, 8, 128, 2000, 272, [2500] * 10, 8, True),             # and 40.8
+    (128, 8, 128, 1584, 280, [600] * 100 + [5000] * 3, 8, False),  # 3.6 times as many units as compute units: 53.5
+    (128, 8, 128, 1584, 304, [600] * 100 + [5000] * 3, 8, True),   # and 54.5
+    (64, 8, 64, 2000, 3440, [3000, 100], 1, False),            # 139
+    (64, 8, 64, 2000, 3504, [3000, 100], 1, True),             # and 140.3
+    (64, 8, 64, 2000, 4980, [700] * 200, 1, False),            # 3.1 times as many units: 187
+    (64, 8, 64, 2000, 5040, [700] * 200, 1, True),             # and 187.5
+])
+def test_decodes_behind_long_sweeps_are_drawn_by_their_own_workgroups(tc, launch_of, Hq, Hkv, D, chunk, offset, decodes, waves, drawn):
+    """More sweeps than units.  tc_plan_info.decode_queue says 0 for both: no prefill workgroup draws."""
+    q_len, ctx = [chunk] + [1] * len(decodes), [offset] + decodes
+    sp = W.custom_spec("late", Hq, Hkv, D, q_len, ctx)
+    table, mb, nb = W.make_tables(sp, np.random.default_rng(22))
+    info = check_work_list(tc, sp, table, nb)
+    dealt, n_prefill, n_decode, units, drawers = launch_of(Hq, Hkv, D, q_len, ctx)
+    assert n_prefill > 256 and n_decode == units > 0 and dealt == 0
+    assert (info.block_threads, info.waves_per_item, info.decode_queue) == (512, waves, 0) and drawers == (units if drawn else 0)
+    assert drawn == (sum(-(-(offset + min(chunk, a + 256 * Hkv // Hq)) // 64) for a in range(0, chunk, 256 * Hkv // Hq)) * Hkv
+                     >= max({(128, 1): 24, (128, 8): 40, (64, 1): 140}[D, waves] * 256, {(128, 1): 0, (128, 8): 15, (64, 1): 60}[D, waves] * units))
