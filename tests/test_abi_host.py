@@ -909,3 +909,12 @@ def test_decodes_behind_long_sweeps_are_drawn_by_their_own_workgroups(tc, launch
     assert (info.block_threads, info.waves_per_item, info.decode_queue) == (512, waves, 0) and drawers == (units if drawn else 0)
     assert drawn == (sum(-(-(offset + min(chunk, a + 256 * Hkv // Hq)) // 64) for a in range(0, chunk, 256 * Hkv // Hq)) * Hkv
                      >= max({(128, 1): 24, (128, 8): 40, (64, 1): 140}[D, waves] * 256, {(128, 1): 0, (128, 8): 15, (64, 1): 60}[D, waves] * units))
+
+
+@pytest.mark.parametrize("name", ["waves", "waves_d64", "whole"])
+def test_queue_of_the_decode_workgroups_in_the_gpu_tests(launch_of, name):
+    """The batches that the GPU tests launch several times do have that queue, and draw more units than one."""
+    from test_gpu_parity import LATE_QUEUE
+    Hq, Hkv, D, q_len, ctx, dtype, waves = LATE_QUEUE[name]
+    dealt, n_prefill, n_decode, units, drawers = launch_of(Hq, Hkv, D, q_len, ctx)
+    assert n_prefill > 256 and dealt == 0 and drawers == n_decode == units > 1

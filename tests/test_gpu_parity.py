@@ -575,6 +575,35 @@ def test_decodes_behind_more_sweeps_than_units(H, name):
     assert dtype != "fp16" or (mx <= FP16_MAX_ABS and rel <= FP16_REL_L2), (mx, rel)
 
 
+# The same behind sweeps so long that the decode workgroups draw their units (the host tests check that they do): single waves and whole
+# workgroups, partial results among them.  Each plan is launched several times: its queue is back at the first unit after every launch.
+LATE_QUEUE = {
+    # name: (Hq, Hkv, D, q_len, ctx, dtype, waves per item)
+    "waves": (128, 8, 128, [570] + [1] * 6, [1203, 1700, 1700, 1600, 900, 17, 9000], "bf16", 1),
+    "waves_d64": (64, 8, 64, [2000] + [1] * 6, [3600, 3000, 700, 64, 1, 130, 9000], "fp16", 1),
+    "whole": (128, 8, 128, [530] + [1] * 4, [2400, 5000, 300, 2191, 0], "fp16", 8),
+}
+
+
+@pytest.mark.parametrize("name", list(LATE_QUEUE))
+def test_decode_workgroups_draw_behind_long_sweeps(H, name):
+    import torch
+    Hq, Hkv, D, q_len, ctx, dtype, waves = LATE_QUEUE[name]
+    b = W.make_batch(W.custom_spec(name, Hq, Hkv, D, q_len, ctx, seed=zlib.crc32(name.encode()) % 10007, dtype=dtype))
+    rows = np.unique(np.concatenate([np.arange(0, b.total_q, 37), b.q_start[1:] - 1]))
+    (mx, rel), db = run_and_compare(H, b, name, rows=rows, gather=None)
+    info = db.plan.info
+    assert info.num_prefill_workgroups > 256 and (info.block_threads, info.waves_per_item, info.decode_queue) == (512, waves, 0)
+    assert info.num_partials > 0
+    assert dtype != "fp16" or (mx <= FP16_MAX_ABS and rel <= FP16_REL_L2), (mx, rel)
+    single = H.to_host(db.out).copy()
+    for form in (db.attention, db.attention, lambda: (db.attention_partials(), db.split_merge()), db.attention):
+        db.out.fill_(-1)  # all bits set: NaN
+        form()
+        torch.cuda.synchronize()
+        assert np.array_equal(H.to_host(db.out), single)
+
+
 # Two splits to a workgroup, half of its waves each: sequences of one split beside another of theirs or a padding item, of two (one
 # result) and of up to 28 (partial results), whole pages and ragged ends, new tokens from the pool and (fused) from k_new / v_new.
 TWO_SPLITS = {
