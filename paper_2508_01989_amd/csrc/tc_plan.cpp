@@ -833,6 +833,11 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     //   5.0, 300 MB           312 at 7068 with 13 of lognormal 4371 87.0 / 84.4    2.4, 780 MB  8/8, head_dim 64, 4 at 5 with 79 of 1030-8244 135.4 / 133.9
     //   2.3, 700 MB           32/32, 75 at 29 with 20 of lognormal 2109 124.3 / 125.8    2.1, 590 MB  40 at 24 with 15 of lognormal 9482 106.9 / 110.5
     //   2.8, 240 MB           64/8, head_dim 64, 10 at 356 with 289 of lognormal 431 52.9 / 53.4; smaller ones lose up to 7 % (a draw takes a microsecond)
+    // Where sequences take several workgroups and leave partial results, from 3.2 rounds on, or from 800 MB:
+    //   2.7, 670 MB           32/32, 77 at 2 with 4 of mean 10210 109.9 / 114.4     3.1, 670 MB   64/8, head_dim 64, 3 with 72 of mean 4553 108.0 / 111.8
+    //   2.6, 790 MB           64/8, 10 with 21 of mean 9235 133.7 / 140.4           2.7, 340 MB   64/8, head_dim 64, 5 with 13 of mean 12919 63.2 / 64.6
+    //   3.3, 760 MB           40/8, head_dim 64, 23 with 38 of mean 9720 130.0 / 126.2   2.6, 880 MB   40/8, head_dim 64, 161 with 42 of mean 10215 153.0 / 148.2
+    // (43 batches between 2.4 and 3.2 rounds and under 800 MB 1.2 % slower on the mean with the queue, 38 without partial results 0.7 % faster).
     // Behind more sweeps than units only the decode workgroups draw (see the kernel), where the sweeps are long enough for what the dies' rates differ by.  Single waves
     // at head_dim 128 from 24 tiles a unit on, 41 us of sweeps: 4711 at 0, 32/32, with 272 of 31-254 334.6 / 323.9; 3797 at 2 with 80 of 77 129.4 / 126.6; 2781 at 0
     // with 12 of 587-4702 93.1 / 92.8; below 2343 at 0 with 5 of 758-6068 67.6 / 68.5.  Whole workgroups, whose units are short, from 40 and from 15 for every 256 units on: 36
@@ -841,7 +846,7 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     // batches below 0.7 % slower on the mean); 144, 476 222.1 / 218.9, 203, 448 245.5 / 240.0, 255, 169 318.3 / 311.3 (13 0.5 % faster, none slower by more than 0.2 %).
     bool late_queue = false;
     if (!queue && n_decode_units > 0 && !w.blocks.empty() && p->prefill_waves == kMixedWaves && (p->waves_per_item == 1 || p->items_per_wg == 1)) {
-        if (n_prefill_wg <= kNumCu) queue = decode_bytes >= (int64_t)300000000 && n_decode_units * 5 >= 12 * std::max<int64_t>(kNumCu - n_prefill_wg, 1);
+        if (n_prefill_wg <= kNumCu) queue = decode_bytes >= (int64_t)300000000 && n_decode_units * 5 >= (n_decode_partials > 0 && decode_bytes < (int64_t)800000000 ? 16 : 12) * std::max<int64_t>(kNumCu - n_prefill_wg, 1);
         else {
             int64_t tiles = 0;
             for (const PlanPiece &x : w.pieces) tiles += x.t1 - x.t0;

@@ -767,6 +767,10 @@ def test_arrival_counters_take_a_bounded_share_of_the_uploaded_image(tc, tmp_pat
     (32, 8, 128, 256, 1234, [1023] * 71, 0, 128),          # and 298
     (32, 8, 128, 256, 1234, [1800] * 66, 0, 256),          # 2.36 rounds of the units that the chunk leaves free
     (32, 8, 128, 256, 1234, [1800] * 68, 1, 256),          # and 2.43
+    (32, 8, 128, 256, 1234, [2000] * 84 + [9000], 0, 256),   # with partial results 3.18 rounds of 730 MB
+    (32, 8, 128, 256, 1234, [2000] * 85 + [9000], 1, 256),   # and 3.21
+    (32, 8, 128, 256, 1234, [2600] * 71 + [9000], 0, 256),   # 2.7 rounds of 794 MB
+    (32, 8, 128, 256, 1234, [2600] * 72 + [9000], 1, 256),   # and 805
 ])
 def test_long_decode_streams_beside_a_few_sweeps_are_drawn(tc, Hq, Hkv, D, chunk, offset, decodes, queue, split):
     sp = W.custom_spec("few", Hq, Hkv, D, [chunk] + [1] * len(decodes), [offset] + decodes)
