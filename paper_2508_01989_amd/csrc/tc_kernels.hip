@@ -1557,10 +1557,17 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : CHUNK ?
         }
         // Without a queue a unit is all that its workgroup does, and no barrier may follow: at head_dim 64, with three waves to a SIMD, the next workgroup begins
         // beside the waves that still combine when the others have left (us, with a barrier here / without: 32/32 heads, 4 tokens with 35 of 691
-        // 40.4 / 38.3; 40/8, 60 with 91 of 695 31.1 / 29.1; 16/2, 47 with 204 of 525 15.9 / 15.2).
+        // 40.4 / 38.3; 40/8, 60 with 91 of 695 31.1 / 29.1; 16/2, 47 with 204 of 525 15.9 / 15.2).  It returns from here: with the barrier under a condition instead, or
+        // moved to the sweep, the same instructions of the sweep's loop came to lie elsewhere and took 0.3 to 0.8 % longer (8192 at 24576 6050 / 6064 and 6097).
         if (first >= 0) {
             run(first);
-            if (sc.n_drawers > 0) __syncthreads();  // the unit is done with the LDS
+            if (sc.n_drawers == 0) {
+#ifdef TC_WG_TRACE
+                wg_trace(t_start, t_mid, true);
+#endif
+                return;
+            }
+            __syncthreads();  // the unit is done with the LDS
         }
         if (sweep) {
             const int kvh = wg % A.Hkv;
