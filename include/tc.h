@@ -91,9 +91,11 @@ typedef struct {
                                         /* padding included (whole workgroups)               */
     int32_t num_merge_items;            /* (query row, KV head) pairs that need the merge    */
     int32_t num_partials;               /* partial results of decode teams held in the workspace */
-    int32_t split_tokens;               /* KV tokens a decode split holds at most, except that a sequence which one   */
-                                        /* workgroup's wave slots can cover with splits of up to 1024 is cut into no  */
-                                        /* more splits than it has slots (one, where a workgroup holds a single item)  */
+    int32_t split_tokens;               /* KV tokens a decode split holds at most, with two exceptions: a sequence    */
+                                        /* which one workgroup's wave slots can cover with splits of up to 1024 is    */
+                                        /* cut into no more splits than it has slots (one, where a workgroup holds a  */
+                                        /* single item); and where a long decode stream beside a chunk has its        */
+                                        /* splits shortened, longer sequences keep splits of up to 1024               */
     int32_t rows_per_prefill_item;      /* (position, head) rows per prefill workgroup: 256, or 128 for a small chunk */
                                         /* or one of uneven sweeps                                                    */
     int32_t grid_blocks, block_threads; /* launch shape of the fused attention kernel        */
@@ -106,7 +108,8 @@ typedef struct {
                                         /* worth, by grid_blocks - num_prefill_workgroups decode workgroups and by   */
                                         /* the prefill workgroups once their pieces are done, those of light sweeps   */
                                         /* with one unit before (chunks whose workgroups of eight waves all run from  */
-                                        /* the start)                                                                 */
+                                        /* the start).  0: no prefill workgroup draws; behind more long sweeps than   */
+                                        /* run at once the decode workgroups may draw, which launches no fewer        */
     int32_t waves_per_item;             /* waves that share one decode item: 1, all of a workgroup's (few, long       */
                                         /* decodes) or half of them                                                   */
     int64_t build_ns;                   /* host time of the latest work-list build ...       */

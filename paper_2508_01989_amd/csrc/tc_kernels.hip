@@ -1605,7 +1605,7 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == kMixedWaves ? 1 : CHUNK ?
             for (;;) {
                 const int next = rec[RC_NEXT];
                 prefill_item<D, E, WAVES>(A, rec, kvh, lds);
-                if (WAVES == kSmallWaves || next < 0) break;
+                if (WAVES == kSmallWaves || next < 0) break;  // (the loop above; one lambda for both was laid out otherwise, 0.2 % slower on small chunks)
                 rec = records + (int64_t)next * kRecordInts;
                 __syncthreads();
             }

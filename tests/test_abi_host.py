@@ -222,6 +222,11 @@ def check_work_list(tc, sp, table, nb):
             assert it[0, 2] == 0 and np.all(it[1:, 2] == it[:-1, 3]) and it[-1, 3] == sp.kv_len[s]
             assert np.all(it[:, 2] % 16 == 0) and np.all(it[:, 3] - it[:, 2] <= 1024)
             assert np.all(it[:, 4] == qs[s])
+            # splits of at most split_tokens; beyond that a sequence that one workgroup covers has W of them, and one that takes several where the others'
+            # splits were shortened (a chunk's workgroups of eight single waves, 2000 tokens on the mean)
+            within = np.all(it[:, 3] - it[:, 2] <= info.split_tokens)
+            shortened = len(pf) > 0 and info.block_threads == 512 and info.waves_per_item == 1 and np.mean(sp.kv_len[sp.q_len == 1]) >= 2000
+            assert within or (len(it) == W_ if sp.kv_len[s] <= W_ * 1024 else shortened)
             # 1, 2, 4 .. W splits (one team), or a multiple of W when W splits of 1024 tokens cannot cover the sequence
             n_teams = int(np.sum((it[:, 7] >> 4) & 7 == 0))
             # exactly the split that ends the sequence is marked as holding the newest token
@@ -922,3 +927,15 @@ def test_queue_of_the_decode_workgroups_in_the_gpu_tests(launch_of, name):
     Hq, Hkv, D, q_len, ctx, dtype, waves = LATE_QUEUE[name]
     dealt, n_prefill, n_decode, units, drawers = launch_of(Hq, Hkv, D, q_len, ctx)
     assert n_prefill > 256 and dealt == 0 and drawers == n_decode == units > 1
+
+
+def test_split_tokens_bounds_all_but_the_long_sequences_of_a_shortened_stream(tc):
+    """128 decodes of 2300 tokens in splits of at most 256 (a workgroup covers them: eight splits, of 18 pages) and one of 9000 in longer ones."""
+    q_len, ctx = [256] + [1] * 129, [1234] + [2300] * 128 + [9000]
+    sp = W.custom_spec("splits", 32, 8, 128, q_len, ctx)
+    table, mb, nb = W.make_tables(sp, np.random.default_rng(23))
+    info = check_work_list(tc, sp, table, nb)
+    qs = np.concatenate([[0], np.cumsum(q_len)]).astype(np.int32)
+    dc = tc.Plan(tc.make_pool(32, 8, 128, nb), qs, sp.ctx_len, table, host_only=True).items(1)
+    longest = lambda seqs: int((dc[:, 3] - dc[:, 2])[np.isin(dc[:, 0], seqs)].max())
+    assert (info.split_tokens, longest(range(1, 129)), longest([129])) == (256, 288, 384)
