@@ -727,21 +727,26 @@ def test_decodes_where_kv_heads_outnumber_the_units(H, name):
         assert np.array_equal(H.to_host(db.out), single)
 
 
-# Workgroups of four waves for a few short sweeps and many short decodes: padding waves, one token, the longest decode that counts as short.
+# Workgroups of four waves for a few short sweeps and many short decodes, which those run by single waves or whole: padding waves, one token,
+# the longest decode that counts as short (768 tokens with the new one).
 SHORT_BESIDE_FEW = {
-    "g4_whole_workgroups": (32, 8, 128, [37] + [1] * 30, [3] + [300, 0, 15, 16, 17] + [150 + i for i in range(25)], "fp16"),
-    "g4": (32, 8, 128, [60] + [1] * 60, [0] + [300] + [40 + 3 * i for i in range(59)], "bf16"),
-    "g1_d64_two_chunks": (32, 32, 64, [70, 9] + [1] * 5, [0, 200, 40, 1, 63, 300, 128], "bf16"),
-    "g8_two_heads": (16, 2, 128, [2] + [1] * 67, [5] + [3 * i for i in range(67)], "bf16"),
+    # name: (Hq, Hkv, D, q_len, ctx, dtype, waves per item)
+    "g4_whole_workgroups": (32, 8, 128, [37] + [1] * 30, [3] + [300, 0, 15, 16, 17] + [150 + i for i in range(25)], "fp16", 4),
+    "g4": (32, 8, 128, [60] + [1] * 60, [0] + [300] + [40 + 3 * i for i in range(59)], "bf16", 4),
+    "g1_d64_two_chunks": (32, 32, 64, [70, 9] + [1] * 5, [0, 200, 40, 1, 63, 300, 128], "bf16", 1),
+    "g8_two_heads": (16, 2, 128, [2] + [1] * 67, [5] + [3 * i for i in range(67)], "bf16", 1),
+    "longest_g1_whole_workgroups": (8, 8, 128, [300] + [1] * 40, [0, 767, 511, 512] + [30 + 18 * i for i in range(37)], "fp16", 4),
+    "longest_g1": (32, 32, 128, [20] + [1] * 24, [0, 767, 511, 512] + [30 + 31 * i for i in range(21)], "bf16", 1),
+    "longest_g4_d64": (32, 8, 64, [77] + [1] * 70, [0, 767, 511, 512] + [30 + 10 * i for i in range(67)], "fp16", 1),
 }
 
 
 @pytest.mark.parametrize("name", list(SHORT_BESIDE_FEW))
 def test_short_decodes_beside_few_sweeps(H, name):
-    Hq, Hkv, D, q_len, ctx, dtype = SHORT_BESIDE_FEW[name]
+    Hq, Hkv, D, q_len, ctx, dtype, waves = SHORT_BESIDE_FEW[name]
     b = W.make_batch(W.custom_spec(name, Hq, Hkv, D, q_len, ctx, seed=zlib.crc32(name.encode()) % 10007, dtype=dtype))
     (mx, rel), db = run_and_compare(H, b, name, gather=None)
-    assert db.plan.info.block_threads == 256
+    assert (db.plan.info.block_threads, db.plan.info.waves_per_item) == (256, waves)
     assert dtype != "fp16" or (mx <= FP16_MAX_ABS and rel <= FP16_REL_L2), (mx, rel)
 
 
