@@ -765,7 +765,9 @@ tc_status build_plan(tc_plan *p, const tc_kv_pool *pool, const tc_batch *b) {
     // there are eight rounds of them; for sequences that one workgroup covers, so that there are no more partial results.  Measured (us per step, before /
     // with this, both with the queue below): 32/8 heads, 256 at 1234 with 256 of 512-4096 413 / 394; 424 at 2 with 162 of 826-6608 409 / 400; 32/32, 3746 at 0
     // with 25 of 459-3676 287 / 277; 1131 at 2 with 83 of 1525-12200 411 / 399.  Of shorter sequences a wave has few pages for its start: 40/8, 1118 at 24
-    // with 389 of lognormal 656 218 / 222, 32/32, 382 at 4379 with 180 of 65-526 187 / 191.
+    // with 389 of lognormal 656 218 / 222, 32/32, 382 at 4379 with 180 of 65-526 187 / 191.  The line is where none loses any more: with 800 tokens in its place 17 batches of
+    // 1400-2000 on the mean took 4 % less to 2 % more (geometric mean 1.2 % less; 32/8, 256 at 1234 with 256 of 1999 355.9 / 343.3, 2048 at 4096 with 151 of 1957 302.0 / 306.9),
+    // 38 of 640-1400 3 % less to 4 % more (0.3 % more; 40/8, 424 with 286 of 1003 222.6 / 217.7, 32/8, 512 with 467 of 1002 331.4 / 344.0, 32/32, 2048 with 60 of 1176 335.7 / 347.3).
     const int split_long = p->split_tokens;  // of sequences that take several workgroups
     if (!w.blocks.empty() && p->prefill_waves == kMixedWaves && p->waves_per_item == 1 && decode_tokens >= (int64_t)2000 * n_decode_seqs)
         while (p->split_tokens * D > 256 * 128 && (int64_t)p->split_tokens * W * 4 * D * 8 * kNumCu > decode_bytes) p->split_tokens /= 2;
